@@ -1,7 +1,8 @@
 // Device-side toolkit: PRF, per-party share arithmetic, message exchange and the
 // per-element protocol steps (Sec. II-B and Sec. V-A of the GTree paper), for gfx950.
 //
-// Execution model.  A workgroup is 3 wavefronts of 64 lanes: wavefront p IS party p
+// Execution models.  Equality grids: three parties per wavefront (WWire, at the end of this
+// file).  All other protocols: a workgroup is 3 wavefronts of 64 lanes, wavefront p IS party p
 // (threadIdx.y = p).  Lane l of each of the three wavefronts works on the same
 // element(s), each on its own party's two components.  A protocol message is a
 // store into the workgroup's message region in LDS; the receiving wavefront loads it
@@ -401,3 +402,112 @@ __device__ __forceinline__ Sh b2a(Wire &W, int p, Sh s, const Dealer &D, bool ac
 }
 
 __device__ __forceinline__ Sh not_bit(int p, Sh b) { if (p == 0) b.o ^= 1; if (p == 2) b.n ^= 1; return b; }
+
+// ---------------------------------------------------------------------------------
+// Wavefront model: the three parties of one wavefront.  Lanes 0-20 are party 0, 21-41
+// party 1, 42-62 party 2 (lane 63 repeats lane 62 and neither stores, counts nor adds), so
+// lanes t, 21 + t and 42 + t work on the same elements, each on its party's two components
+// and with its party's keys.  A message is a store into the wavefront's message region in LDS
+// that the receiving party's lane loads; LDS operations of one wavefront complete in order,
+// so no workgroup barrier is needed and the wavefronts of a compute unit run independently
+// of each other.  Every vector instruction of the protocols takes 4 cycles of its SIMD, with a
+// scalar operand or without one, so per-lane keys and party masks cost registers and no time.
+#define GT_TP 21
+
+// orders this wavefront's LDS accesses for the compiler (the hardware keeps their order)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// three-input logic, one instruction: T is the value of the expression on a = 0xf0, b = 0xcc, c = 0xaa
+template <u32 T> __device__ __forceinline__ u32 logic3(u32 a, u32 b, u32 c) { return __builtin_amdgcn_bitop3_b32(a, b, c, T); }
+// x_o y_o + x_o y_n + x_n y_o over bits (the three-term product), two instructions
+__device__ __forceinline__ u32 and3l(u32 ao, u32 an, u32 bo, u32 bn) { return logic3<0x6a>(an, bo, logic3<0x60>(ao, bo, bn)); }
+__device__ __forceinline__ u32 xor3l(u32 a, u32 b, u32 c) { return logic3<0x96>(a, b, c); }
+
+#define GT_WMSG_QUADS (4 * GT_LANES)                 // message region of a wavefront: 16 dwords per lane
+struct WWire {
+    uint4 *buf;
+    u64 *cnt;
+    int p, pn;
+    u32 m, t, nx, pv;            // this lane (63: as 62), its number in the party, the lanes of the next and the previous party
+    bool real;
+    u64 nopen, nresh;            // payload bits sent to the successor / predecessor since the last drain
+    __device__ __forceinline__ void init(uint4 *region, u64 *s_cnt)
+    {
+        const u32 l = threadIdx.x & (GT_LANES - 1);
+        real = l < 3 * GT_TP; m = real ? l : 3 * GT_TP - 1;
+        p = m >= 2 * GT_TP ? 2 : (m >= GT_TP ? 1 : 0); pn = p == 2 ? 0 : p + 1;
+        t = m - GT_TP * (u32)p;
+        nx = p == 2 ? t : m + GT_TP; pv = p == 0 ? m + 2 * GT_TP : m - GT_TP;
+        buf = region; cnt = s_cnt; nopen = 0; nresh = 0;
+        if (l < 6) cnt[l] = 0;
+        wave_sync();
+    }
+    // store ND dwords, load those that lane `from` stored
+    template <int ND>
+    __device__ __forceinline__ void pass(const u32 (&s)[ND], u32 (&r)[ND], u32 from)
+    {
+        static_assert(ND == 1 || ND == 2 || (ND % 4 == 0 && ND <= 16), "message size");
+        wave_sync();
+        // small messages use the same 16-byte slots: one address register per direction for all sizes
+        if (ND == 1) buf[m].x = s[0];
+        else if (ND == 2) *(uint2 *)&buf[m] = make_uint2(s[0], s[ND > 1 ? 1 : 0]);
+        else {
+#pragma unroll
+            for (int j = 0; j < ND / 4; j++) buf[j * GT_LANES + m] = make_uint4(s[4 * j], s[4 * j + 1], s[4 * j + 2], s[4 * j + 3]);
+        }
+        wave_sync();
+        if (ND == 1) r[0] = buf[from].x;
+        else if (ND == 2) { const uint2 v = *(const uint2 *)&buf[from]; r[0] = v.x; r[ND > 1 ? 1 : 0] = v.y; }
+        else {
+#pragma unroll
+            for (int j = 0; j < ND / 4; j++) {
+                const uint4 v = buf[j * GT_LANES + from];
+                r[4 * j] = v.x; r[4 * j + 1] = v.y; r[4 * j + 2] = v.z; r[4 * j + 3] = v.w;
+            }
+        }
+    }
+    template <int NW>
+    __device__ __forceinline__ void pass64(const u64 (&s)[NW], u64 (&r)[NW], u32 from)
+    {
+        u32 a[2 * NW], b[2 * NW];
+#pragma unroll
+        for (int j = 0; j < NW; j++) { a[2 * j] = (u32)s[j]; a[2 * j + 1] = (u32)(s[j] >> 32); }
+        pass<2 * NW>(a, b, from);
+#pragma unroll
+        for (int j = 0; j < NW; j++) r[j] = (u64)b[2 * j] | ((u64)b[2 * j + 1] << 32);
+    }
+    template <int ND> __device__ __forceinline__ void reshare(const u32 (&s)[ND], u32 (&r)[ND]) { pass<ND>(s, r, nx); }
+    template <int NW> __device__ __forceinline__ void reshare64(const u64 (&s)[NW], u64 (&r)[NW]) { pass64<NW>(s, r, nx); }
+    template <int NW> __device__ __forceinline__ void open64(const u64 (&s)[NW], u64 (&r)[NW]) { pass64<NW>(s, r, pv); }
+    __device__ __forceinline__ void drain()
+    {
+        if (real && nopen) atomicAdd((unsigned long long *)&cnt[2 * p], (unsigned long long)nopen);
+        if (real && nresh) atomicAdd((unsigned long long *)&cnt[2 * p + 1], (unsigned long long)nresh);
+        nopen = 0; nresh = 0;
+    }
+    // end of the wavefront: its sums to the context's counters (see LWire::flush)
+    __device__ __forceinline__ void flush(u64 *g)
+    {
+        drain();
+        wave_sync();
+        const u32 l = threadIdx.x & (GT_LANES - 1);
+        if (l < 6) {
+            const u64 v = cnt[l];
+            if (v) atomicAdd((unsigned long long *)&g[6 * (blockIdx.x & (GT_WIRE_SLOTS - 1)) + l], (unsigned long long)v);
+        }
+    }
+};
+
+// keys of the wavefront model: the lane's own pairwise key in vector registers (the words
+// under its next key come from the next party's lane), the dealer's key in scalar ones
+__device__ __forceinline__ Key load_lane_key(const u32 *keys, int p)
+{
+    Key k;
+#pragma unroll
+    for (int i = 0; i < 8; i++) k.k[i] = keys[p * 8 + i];
+    return k;
+}

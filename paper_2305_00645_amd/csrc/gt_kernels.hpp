@@ -395,7 +395,7 @@ struct GridArgs {
     int epi;
     LimbTri L;      // GM_STORE: limb tiles of the components, row = column k
     u32 nkc, kchunk;// column ranges per tile and their length
-    int lgs;        // GM_STORE: log2 of the lanes that share a column in one step (6 or 4)
+    u32 gpt, rps;   // groups of 8 samples per tile, adjacent columns per step (gpt * rps <= 21)
     u64 *dacc;      // [2][3][N8] partial inner products when nkc > 1
     int ndot;
 };
@@ -516,221 +516,325 @@ __device__ __forceinline__ u32 mask63_packed(const u64 (&A)[8])
     return g[0] | (g[1] << 4);
 }
 
-// Offline and pairwise-key material is produced once per workgroup and handed out
-// through LDS; a dealer block yields the components of all three parties (the dealer is a
-// role of its own, not one of the parties), each party's wavefront then reads only its
-// two components.
-//  - Per work item: the edaBits of the lane's 8 samples (one per ROW of the grid: all
-//    comparisons of a row are with public constants, so its masked index is opened once);
-//    the three wavefronts split the 8 blocks, the opening goes through LDS, afterwards
-//    every lane keeps the public c and its two Boolean components of r in registers.
-//  - Per step (one column for the lane's 8 samples): the daBits of the 8 tests come from
-//    three dealer blocks (stream 4, blocks 3g..3g+2 of the group g = e/8; test j in slot
-//    j%3 of block 3g + j/3): party p's wavefront evaluates block 3g+p, one block per
-//    lane; the mask word under key k_j is evaluated by party j's wavefront and also read
-//    by party j-1, the other holder of k_j.
+// Eight equality tests of one lane (one column, eight rows) in the wavefront model.
+//
+// The AND rounds work on packed fields from the second round on, so that one word operation
+// serves several tests; the two halves of the fields are separated before the AND, so that
+// its result is the next message as it stands: fields of 16 bits (two tests per dword), 8
+// bits (four), then nibbles, two bits in a nibble, one bit in a nibble (eight tests in one
+// dword: test s < 4 in nibble 2s, test s >= 4 in nibble 2(s-4)+1).  Mask words (own xor next
+// key): bits 0-31 round 0, 32-47 round 1, 48-55 round 2, 56-59 round 3, 60-61 round 4, 62
+// round 5, 63 an AND that follows.
+//
+// Offline and pairwise-key material is evaluated once and handed out through LDS: the daBits
+// of the eight tests come from three dealer blocks (stream 4, blocks 3g..3g+2 of the group
+// g = e/8; test j in slot j%3 of block 3g + j/3), one in the lane of each party (the dealer is a
+// role of its own: a block yields the components of all three parties, each party then loads
+// its two); the mask words under key k_j are evaluated by party j's lane and also loaded by
+// party j-1, the other holder of k_j.
 #define GT_TILE_EL (8 * GT_LANES)
+#define GT_EQ_NIB 0x11111111u
+__host__ __device__ constexpr int eq_pos(int s) { return s < 4 ? 8 * s : 8 * (s - 4) + 4; }     // bit of test s after the rounds
+#define GT_EQ_ROWS (3 * 9 * (GT_TP + 1))         // words of the daBit components: [component][test, one unused][lane]
 
-// the three daBits of one dealer block into the rows of the arithmetic components (rows
-// 6-8) and the packed bit words of lane ln: slot q serves test j = 3b + q of the group
-__device__ __forceinline__ void deal_dabits(u64 (*s_mat)[GT_TILE_EL], u32 *bitw, const u64 (&D)[8], u32 b, u32 ln)
-{
-    u32 bits = 0;
-#pragma unroll
-    for (int q = 0; q < 3; q++) {
-        const u32 j = 3 * b + q;
-        if (j < 8) {
-            const u32 el = j * GT_LANES + ln;
-            const u64 beta = (D[6] >> (3 * q)) & 1;
-            s_mat[6][el] = D[2 * q]; s_mat[7][el] = D[2 * q + 1]; s_mat[8][el] = beta - D[2 * q] - D[2 * q + 1];
-            const u32 b0 = (u32)(D[6] >> (3 * q + 1)) & 1, b1 = (u32)(D[6] >> (3 * q + 2)) & 1, b2 = ((u32)beta ^ b0 ^ b1) & 1;
-            bits |= (b0 << j) | (b1 << (8 + j)) | (b2 << (16 + j));
-        }
+struct EqWave {
+    WWire W;
+    Key own, dlr;
+    u64 *rows;                   // GT_EQ_ROWS words of the wavefront
+    u32 M0, M2;                  // all ones in the lanes of party 0 / party 2, the holders of component 0
+    u32 sh0, sh1, sh2, k2;       // positions of the three tests whose daBits this lane deals; k2: the third exists
+
+    __device__ __forceinline__ void init(const u32 *keys, uint4 *region, u64 *s_rows, u64 *s_cnt)
+    {
+        W.init(region, s_cnt);
+        own = load_lane_key(keys, W.p); dlr = load_key(keys, GT_KEY_DEALER);
+        rows = s_rows;
+        M0 = W.p == 0 ? ~0u : 0u; M2 = W.p == 2 ? ~0u : 0u;
+        sh0 = W.p == 0 ? eq_pos(0) : (W.p == 1 ? eq_pos(3) : eq_pos(6));
+        sh1 = W.p == 0 ? eq_pos(1) : (W.p == 1 ? eq_pos(4) : eq_pos(7));
+        sh2 = W.p == 0 ? eq_pos(2) : (W.p == 1 ? eq_pos(5) : 0);
+        k2 = W.p == 2 ? 0u : 7u;
     }
-    atomicOr(&bitw[ln], bits);
-}
+    // daBit component c of this lane's test s
+    __device__ __forceinline__ u64 &row(int c, int s) { return rows[(c * 9 + s) * (GT_TP + 1) + W.t]; }
 
+    // [c - base - k == 0] (and the shared bit g) for the eight rows of block index g of operation
+    // op: cd = c - base - k (public), rho the Boolean components of r.  Returns the opened
+    // f = result xor beta, test s in bit eq_pos(s); beta's arithmetic components are in row(.,s).
+    // early(): the loads of what the tests' results meet, issued after the PRF blocks (their registers
+    // are free again) and in flight during the rounds.
+    template <bool HAS_G, class F>
+    __device__ __forceinline__ u32 tests(u32 op, u64 g, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
+                                         u32 go, u32 gn, u32 nl, F early)
+    {
+        u32 bw;
+        {
+            u64 D[8];
+            chacha8(dlr, 3 * g + (u32)W.p, op, 4, D);
+            wave_sync();
+            const u32 x = (u32)D[6] & 0x1ffu;
+            u64 *r = &row(0, 3 * W.p);
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                u64 *rq = r + q * (GT_TP + 1);
+                rq[0] = D[2 * q]; rq[9 * (GT_TP + 1)] = D[2 * q + 1];
+                rq[18 * (GT_TP + 1)] = (u64)((x >> (3 * q)) & 1) - D[2 * q] - D[2 * q + 1];
+            }
+            // per test three Boolean components in a nibble: bits 1, 2 of its field and beta xor both
+            const u32 z = ((x >> 1) & 0xdbu) | ((xor3l(x, x >> 1, x >> 2) & 0x49u) << 2);
+            u32 b1[1] = { ((z & 7) << sh0) | (((z >> 3) & 7) << sh1) | (((z >> 6) & k2) << sh2) }, b2[1];
+            W.pass<1>(b1, b2, W.nx);
+            bw = b1[0] | b2[0] | W.buf[W.pv].x;
+        }
+        u32 Ah[8], xo[8], xn[8];
+        {
+            u64 A[8], An[8];
+            chacha8(own, g, op, 1, A);
+            W.pass64<8>(A, An, W.nx);
+            // round 0, width 32: the high word onto the low word
+#pragma unroll
+            for (int s = 0; s < 8; s++) {
+                const u32 dl = (u32)cd[s], dh = (u32)(cd[s] >> 32);
+                // t = rho with the complement of cd xored into component 0
+                const u32 tol = logic3<0xd2>((u32)rho_o[s], dl, M0), toh = logic3<0xd2>((u32)(rho_o[s] >> 32), dh, M0);
+                const u32 tnl = logic3<0xd2>((u32)rho_n[s], dl, M2), tnh = logic3<0xd2>((u32)(rho_n[s] >> 32), dh, M2);
+                xo[s] = xor3l(and3l(tol, tnl, toh, tnh), (u32)A[s], (u32)An[s]);
+                Ah[s] = (u32)(A[s] >> 32) ^ (u32)(An[s] >> 32);
+            }
+        }
+        early();
+        W.reshare<8>(xo, xn);
+        u32 Po[4], Pn[4], H[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {                  // round 1, width 16
+            const u32 al = __builtin_amdgcn_perm(xo[2 * j + 1], xo[2 * j], 0x05040100u), ah = __builtin_amdgcn_perm(xo[2 * j + 1], xo[2 * j], 0x07060302u);
+            const u32 bl = __builtin_amdgcn_perm(xn[2 * j + 1], xn[2 * j], 0x05040100u), bh = __builtin_amdgcn_perm(xn[2 * j + 1], xn[2 * j], 0x07060302u);
+            Po[j] = and3l(al, bl, ah, bh) ^ __builtin_amdgcn_perm(Ah[2 * j + 1], Ah[2 * j], 0x05040100u);
+            H[j] = __builtin_amdgcn_perm(Ah[2 * j + 1], Ah[2 * j], 0x07060302u);
+        }
+        W.reshare<4>(Po, Pn);
+        u32 Qo[2], Qn[2], B3[2];
+#pragma unroll
+        for (int j = 0; j < 2; j++) {                  // round 2, width 8
+            const u32 al = __builtin_amdgcn_perm(Po[2 * j + 1], Po[2 * j], 0x06040200u), ah = __builtin_amdgcn_perm(Po[2 * j + 1], Po[2 * j], 0x07050301u);
+            const u32 bl = __builtin_amdgcn_perm(Pn[2 * j + 1], Pn[2 * j], 0x06040200u), bh = __builtin_amdgcn_perm(Pn[2 * j + 1], Pn[2 * j], 0x07050301u);
+            Qo[j] = and3l(al, bl, ah, bh) ^ __builtin_amdgcn_perm(H[2 * j + 1], H[2 * j], 0x06040200u);
+            B3[j] = __builtin_amdgcn_perm(H[2 * j + 1], H[2 * j], 0x07050301u);
+        }
+        W.reshare<2>(Qo, Qn);
+        const u32 LN = 0x0f0f0f0fu;
+        // per byte the low nibble of x, the high nibble of y
+#define GT_NIBS(x, y) logic3<0xac>(LN, y, x)
+        u32 Ro[1], Rn[1];                              // round 3, width 4
+        Ro[0] = and3l(GT_NIBS(Qo[0], Qo[1] << 4), GT_NIBS(Qn[0], Qn[1] << 4), GT_NIBS(Qo[0] >> 4, Qo[1]), GT_NIBS(Qn[0] >> 4, Qn[1]))
+                ^ GT_NIBS(B3[0], B3[1] << 4);
+        W.reshare<1>(Ro, Rn);
+        const u32 Hm = GT_NIBS(B3[0] >> 4, B3[1]);     // bits 60-63 of the mask words, one nibble per test
+#undef GT_NIBS
+        u32 So[1], Sn[1];                              // round 4, width 2
+        So[0] = logic3<0x60>(0x33333333u, and3l(Ro[0], Rn[0], Ro[0] >> 2, Rn[0] >> 2), Hm);
+        W.reshare<1>(So, Sn);
+        u32 To[1], Tn[1];                              // round 5, width 1
+        To[0] = (and3l(So[0], Sn[0], So[0] >> 1, Sn[0] >> 1) ^ (Hm >> 2)) & GT_EQ_NIB;
+        W.reshare<1>(To, Tn);
+        if (HAS_G) {                                   // and with the column's shared bit (go, gn: that bit in every position)
+            To[0] = (and3l(To[0], Tn[0], go, gn) ^ (Hm >> 3)) & GT_EQ_NIB;
+            W.reshare<1>(To, Tn);
+        }
+        // bit -> arithmetic: open s xor beta
+        u32 fo[1] = { (To[0] ^ (bw >> W.p)) & GT_EQ_NIB }, fr[1];
+        W.pass<1>(fo, fr, W.pv);
+        W.nopen += nl; W.nresh += (HAS_G ? 64u : 63u) * nl;
+        return xor3l(fo[0], Tn[0] ^ (bw >> W.pn), fr[0]);
+    }
+
+    // Row part of a grid: the edaBits of the lane's eight rows (dealer blocks i0..i0+7 of stream
+    // 0, split over the lanes of the three parties), the masked values and their one opening.
+    // u: the rows' values (in: own, next).  cpub = u + r, rho: Boolean components of r.
+    __device__ __forceinline__ void open_rows(u32 op, u64 i0, const u64 (&uo)[8], const u64 (&un)[8], u64 (&cpub)[8],
+                                              u64 (&rho_o)[8], u64 (&rho_n)[8], u32 bits)
+    {
+        u64 keep[3][3], snd[8], mn[8], rcv[8];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {                  // arithmetic components, then the Boolean ones, through the same rows
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                const int s = W.p + 3 * q;             // s = 8 (party 2): the unused row
+                if (h == 0) {
+                    u64 D[8];
+                    chacha8(dlr, i0 + (u32)s, op, 0, D);
+                    wave_sync();
+                    row(0, s) = D[1]; row(1, s) = D[2]; row(2, s) = D[0] - D[1] - D[2];
+                    keep[q][0] = D[3]; keep[q][1] = D[4]; keep[q][2] = D[0] ^ D[3] ^ D[4];
+                } else { row(0, s) = keep[q][0]; row(1, s) = keep[q][1]; row(2, s) = keep[q][2]; }
+            }
+            wave_sync();
+#pragma unroll
+            for (int s = 0; s < 8; s++) {
+                if (h == 0) { snd[s] = uo[s] + row(W.p, s); mn[s] = un[s] + row(W.pn, s); }
+                else { rho_o[s] = row(W.p, s); rho_n[s] = row(W.pn, s); }
+            }
+            wave_sync();
+        }
+        W.open64<8>(snd, rcv);
+        W.nopen += bits;
+#pragma unroll
+        for (int s = 0; s < 8; s++) cpub[s] = snd[s] + mn[s] + rcv[s];
+    }
+};
+
+// the columns' part of E: f ? 1 - b : b for one component, m = all ones where f is set, k1 = that
+// party's component of the public 1, plus 1 (f ? one - b : b = (b xor m) + (m & (one + 1)))
+__device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u64)m | ((u64)m << 32))) + (u64)(m & k1); }
+
+// Equality grid (first lines of the array-access protocol, Sec. V-A; per-sample leaf flags of
+// the learning protocol, Sec. V-B): see GridArgs for the modes.
+// Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, at
+// one per 4 cycles and SIMD, and takes about 4,900 cycles.  One wavefront per workgroup, two per
+// SIMD: the rows' public values, Boolean components and sums and the values of the next column
+// fit their 256 registers, and two barrier-free wavefronts keep the vector unit as busy as three
+// did; three had to spill, and every reload waited for the loads from HBM issued before it (GM_ROWS,
+// 64 columns of 10^6 samples: 1.17 ms spilling, 0.88 ms like this).  Before, with one party per
+// wavefront and ten workgroup barriers per step: array access 200,003 x 100 0.40 ms, now 0.28;
+// 10^6 samples x (64 + 128 nodes) 3.45 -> 2.67 ms, own rows 2 x 64 columns 2.35 -> 1.77 ms, leaf
+// grid of 128 + 256 nodes 6.28 -> 5.52 ms; 48,842 samples x 294 columns 0.31 -> 0.20 ms.
 template <int MODE, bool HAS_G, int NDOT>
-__global__ __launch_bounds__(192, 3) void k_eqgrid(GridArgs a)
+__global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 {
-    // rows 0-2: the mask words under k_0..k_2; rows 3-5: the messages of the AND rounds, of
-    // the bit conversion and of the reshared inner products; rows 6-8: beta arithmetic
-    // components.  At the start of a work item rows 0-5 carry the edaBit components of the
-    // lane's samples and the opening.
-    __shared__ u64 s_mat[9][GT_TILE_EL];
-    // beta Boolean components, packed per lane: bit 8j+s = component j of the lane's test s.
-    // The dealer's lanes OR their bits in; two copies alternate between steps so that
-    // one can be cleared while the other is in use.
-    __shared__ u32 s_bitw[2][GT_LANES];
+    __shared__ uint4 s_msg[GT_WMSG_QUADS];
+    __shared__ u64 s_rows[GT_EQ_ROWS];
     __shared__ u64 s_cnt[6];
-    const int p = party_of_wave(), lane = threadIdx.x, tid = p * GT_LANES + lane, pn = p == 2 ? 0 : p + 1, pp = p == 0 ? 2 : p - 1;
-    LWire LW; LW.init(&s_mat[3][0], s_cnt);
-    static_assert(GT_LWIRE_WORDS <= 3 * GT_TILE_EL, "LDS wire does not fit the rows it uses");
-    const PartyKeys K = load_party_keys(a.c.keys, p);
+    EqWave E;
+    E.init(a.c.keys, s_msg, s_rows, s_cnt);
+    WWire &W = E.W;
+    const int p = W.p;
     const u32 op = a.c.op;
     const u64 ngrp = a.N8 / 8;
     const Sh one = pub(p, 1);
-    // work item = (tile of samples, range of columns); with more than one column
-    // range per tile the inner products are completed by atomic adds (exact in the
-    // ring) and the reshare runs in k_dot_fin.  A step covers 64 groups of 8 samples
-    // of one column, or (leaf one-hot with a column count that is a multiple of four)
-    // 16 groups of four adjacent columns each: the four 32-byte pieces that one
-    // wavefront then writes per sample block and limb make up whole 128-byte lines of
-    // the tile layout.
-    const int lgs = MODE == GM_STORE ? a.lgs : 6;      // log2 of the lanes per column
-    const u32 lgm = (1u << lgs) - 1, kstep = GT_LANES >> lgs, ro = lane >> lgs;
-    const u64 nt = (ngrp + lgm) >> lgs;
-    if (tid < 2 * GT_LANES) (&s_bitw[0][0])[tid] = 0;
-    __syncthreads();
-    u32 par = 0;
+    const u32 k1o = (u32)one.o + 1, k1n = (u32)one.n + 1;
+    // work item = (tile of gpt groups of 8 samples, range of columns); with more than one column
+    // range per tile the inner products are completed by atomic adds (exact in the ring) and
+    // the reshare runs in k_dot_fin.  A step covers rps adjacent columns of the tile.
+    const u32 gpt = a.gpt, ro = W.t / gpt, gi = W.t - ro * gpt;
+    const u64 nt = (ngrp + gpt - 1) / gpt;
     for (u64 item = blockIdx.x; item < nt * a.nkc; item += gridDim.x) {
         const u64 tile = item / a.nkc;
         const u32 kbeg = (u32)(item % a.nkc) * a.kchunk, kend = kbeg + a.kchunk < a.w ? kbeg + a.kchunk : a.w;
-        const u64 grp = (tile << lgs) + (lane & lgm), i0 = grp * 8;
-        const bool actg = grp < ngrp;
+        const u64 grp = tile * gpt + gi, i0 = grp * 8;
+        const bool actg = ro < a.rps && grp < ngrp;      // the same in lane 63 as in lane 62
         const u64 nvg = actg ? a.N : 0;
-        // ---- the row's part: edaBits of the 8 samples, masked indices, one opening
         u64 cpub[8], rho_o[8], rho_n[8];
         {
-#pragma unroll 1
-            for (int s = p; s < 8; s += 3) {            // this party's share of the 8 dealer blocks of the lane
-                u64 D[8];
-                chacha8(K.dlr, i0 + s, op, 0, D);
-                const int el = s * GT_LANES + lane;
-                s_mat[0][el] = D[1]; s_mat[1][el] = D[2]; s_mat[2][el] = D[0] - D[1] - D[2];
-                s_mat[3][el] = D[3]; s_mat[4][el] = D[4]; s_mat[5][el] = D[0] ^ D[3] ^ D[4];
-            }
-            u64 snd[8], mn[8];
-            ld8(own_of(a.u, p), i0, nvg, snd); ld8(nxt_of(a.u, p), i0, nvg, mn);
-            __syncthreads();
+            u64 uo[8], un[8];
+            ld8(own_of(a.u, p), i0, nvg, uo); ld8(nxt_of(a.u, p), i0, nvg, un);
+            // the column ranges of one tile (and the adjacent columns of a step) replay the same
+            // opening; it is counted once
+            E.open_rows(op, i0, uo, un, cpub, rho_o, rho_n, kbeg == 0 && ro == 0 ? 64u * live8(i0, nvg) : 0u);
 #pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const int el = s * GT_LANES + lane;
-                snd[s] += s_mat[p][el];                 // samples beyond N: any value serves
-                mn[s] += s_mat[pn][el];
-                rho_o[s] = s_mat[3 + p][el]; rho_n[s] = s_mat[3 + pn][el];
-            }
-            __syncthreads();
-            // the opening, 64 bits per sample: party p's message takes the place of row p.  The column
-            // ranges of one tile (and the four column lanes of the leaf grid) replay the same opening;
-            // it is counted once.
-#pragma unroll
-            for (int s = 0; s < 8; s++) s_mat[p][s * GT_LANES + lane] = snd[s];
-            if (kbeg == 0 && ro == 0) LW.nopen += 64u * live8(i0, nvg);
-            __syncthreads();
-#pragma unroll
-            for (int s = 0; s < 8; s++) cpub[s] = snd[s] + mn[s] + s_mat[pp][s * GT_LANES + lane] - a.base;
-            __syncthreads();
+            for (int s = 0; s < 8; s++) cpub[s] -= a.base;
         }
+        const u64 *w1o = nullptr, *w1n = nullptr, *xto = nullptr, *xtn = nullptr;
+        if (MODE == GM_COMMON) { w1o = own_of(a.W1, p) + a.w1off; w1n = nxt_of(a.W1, p) + a.w1off; }
+        if (MODE == GM_ROWS) { const u64 g0 = (grp < ngrp ? grp : ngrp - 1) * 8; xto = own_of(a.XT, p) + g0; xtn = nxt_of(a.XT, p) + g0; }
+        // GM_ROWS: the samples' own values of a column, fetched a whole step ahead (HBM latency)
+        u64 xo[8], xn[8];
+        const auto fetch_x = [&](u32 k) {              // whole groups: rows are padded to N8 and start at multiples of 64 bytes
+            const ulonglong2 *qo = (const ulonglong2 *)(xto + (u64)k * a.N8), *qn = (const ulonglong2 *)(xtn + (u64)k * a.N8);
+#pragma unroll
+            for (int j = 0; j < 4; j++) { const ulonglong2 v = qo[j]; xo[2 * j] = v.x; xo[2 * j + 1] = v.y; }
+#pragma unroll
+            for (int j = 0; j < 4; j++) { const ulonglong2 v = qn[j]; xn[2 * j] = v.x; xn[2 * j + 1] = v.y; }
+        };
+        if (MODE == GM_ROWS) fetch_x(kbeg);
         u64 acc[8], acc2[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) { acc[s] = 0; acc2[s] = 0; }
-        for (u32 k0 = kbeg; k0 < kend; k0 += kstep) {
+        for (u32 k0 = kbeg; k0 < kend; k0 += a.rps) {
             const bool act = MODE == GM_STORE ? actg && k0 + ro < kend : actg;
             const u32 k = MODE == GM_STORE ? (act ? k0 + ro : kbeg) : k0;   // this lane's column (an existing one when idle)
             const u64 nv = act ? a.N : 0;              // samples of this lane that exist
             const u32 nl = live8(i0, nv);              // how many of the lane's eight tests exist
-            const u64 e0 = (u64)k * a.N8 + i0;
-            u64 A[8];
-            {
-                u64 D[8];
-                chacha8(K.dlr, 3 * (e0 >> 3) + p, op, 4, D);       // daBits of the tests 3p, 3p+1, 3p+2 of the lane
-                deal_dabits(s_mat, s_bitw[par], D, (u32)p, (u32)lane);
-            }
-            chacha8(K.own, e0 >> 3, op, 1, A);         // mask words under this party's own key
+            u64 cd[8];
 #pragma unroll
-            for (int s = 0; s < 8; s++) s_mat[p][s * GT_LANES + lane] = A[s];
-            __syncthreads();
-            if (p == 0) s_bitw[par ^ 1][lane] = 0;     // the next step's bit words
-#pragma unroll
-            for (int s = 0; s < 8; s++) A[s] ^= s_mat[pn][s * GT_LANES + lane];
-            // t = rho with the complement of (c - base - k) xored into component 0, which
-            // party 0 holds as its own and party 2 as its next component
-            Sh t[8];
-#pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const u64 nx = ~(cpub[s] - k);
-                t[s].o = p == 0 ? rho_o[s] ^ nx : rho_o[s];
-                t[s].n = p == 2 ? rho_n[s] ^ nx : rho_n[s];
-            }
-            u32 To8, Tn8;
-            eq_rounds8_packed(LW, t, A, nl, To8, Tn8); // six AND rounds, 63 bits
-            if (HAS_G) {                               // and with the column's shared bit
-                const Sh gk = ld(a.g, p, k);
-                const u32 go = 0u - ((u32)gk.o & 1), gn = 0u - ((u32)gk.n & 1);
-                To8 = (and3w(To8, Tn8, go, gn) ^ mask63_packed(A)) & 0xffu;
-                u64 s1[1] = { (u64)To8 }, r1[1];
-                LW.reshare<1>(s1, r1, nl);
-                Tn8 = (u32)r1[0];
-            }
-            u32 f;
-            {                                          // bit -> arithmetic: open s xor beta
-                const u32 bw = s_bitw[par][lane];
-                const u32 fo = To8 ^ ((bw >> (8 * p)) & 0xffu), fn = Tn8 ^ ((bw >> (8 * pn)) & 0xffu);
-                f = fo ^ fn ^ (u32)LW.open1((u64)fo, nl);
-            }
+            for (int s = 0; s < 8; s++) cd[s] = cpub[s] - k;
+            u32 go = 0, gn = 0;
+            if (HAS_G) { const Sh gk = ld(a.g, p, k); go = 0u - ((u32)gk.o & 1); gn = 0u - ((u32)gk.n & 1); }
             Sh Wk = { 0, 0 }, Wk2 = { 0, 0 };
+            const u32 f = E.template tests<HAS_G>(op, (u64)k * ngrp + grp, cd, rho_o, rho_n, go, gn, nl, [&]() {
+                if (MODE == GM_COMMON) { Wk.o = w1o[k]; Wk.n = w1n[k]; }
+                if (MODE == GM_COMMON && NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
+            });
             if (MODE == GM_COMMON) {
-                Wk = ld(a.W1, p, a.w1off + k);
-                if (NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
-            }
-            u64 Eo[8], xo[8], xn[8];
-            if (MODE == GM_ROWS) { ld8(own_of(a.XT, p) + (u64)k * a.N8, i0, nv, xo); ld8(nxt_of(a.XT, p) + (u64)k * a.N8, i0, nv, xn); }
+                // E W = f ? c - z : z with z = b W, c = (the public 1) W, a constant of the column:
+                // ((z + (m & ~c)) xor m)
+                const u64 S = Wk.o + Wk.n, nc = ~(one.o * S + one.n * Wk.o);
+                const u64 S2 = Wk2.o + Wk2.n, nc2 = ~(one.o * S2 + one.n * Wk2.o);
 #pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const int el = s * GT_LANES + lane;
-                const Sh bA = { s_mat[6 + p][el], s_mat[6 + pn][el] };
-                Sh E;
-                E.o = ((f >> s) & 1) ? one.o - bA.o : bA.o;
-                E.n = ((f >> s) & 1) ? one.n - bA.n : bA.n;
-                const bool live = i0 + s < nv;
-                if (MODE == GM_STORE) Eo[s] = live ? E.o : 0;
-                if (MODE == GM_COMMON) { acc[s] += prod3(E, Wk); if (NDOT == 2) acc2[s] += prod3(E, Wk2); }
-                if (MODE == GM_ROWS) { const Sh x = { xo[s], xn[s] }; acc[s] += prod3(E, x); }
+                for (int s = 0; s < 8; s++) {
+                    const u32 m = (u32)((int)(f << (31 - eq_pos(s))) >> 31);
+                    const u64 mm = (u64)m | ((u64)m << 32), bo = E.row(p, s), bn = E.row(W.pn, s);
+                    acc[s] += ((mm & nc) + bo * S + bn * Wk.o) ^ mm;
+                    if (NDOT == 2) acc2[s] += ((mm & nc2) + bo * S2 + bn * Wk2.o) ^ mm;
+                }
+            } else {
+                u64 Eo[8];
+#pragma unroll
+                for (int s = 0; s < 8; s++) {
+                    const u32 m = (u32)((int)(f << (31 - eq_pos(s))) >> 31);
+                    const u64 eo = eq_select(E.row(p, s), m, k1o);
+                    if (MODE == GM_STORE) Eo[s] = i0 + s < nv ? eo : 0;
+                    if (MODE == GM_ROWS) {
+                        const Sh e = { eo, eq_select(E.row(W.pn, s), m, k1n) }, x = { xo[s], xn[s] };
+                        acc[s] += prod3(e, x);
+                    }
+                }
+                if (MODE == GM_ROWS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
+                if (MODE == GM_STORE && act && W.real) store_limbs8(p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]), k, i0, Eo);
             }
-            if (MODE == GM_STORE && act) {
-                store_limbs8(a.L.m[p], k, i0, Eo);
-            }
-            par ^= 1;
-            __syncthreads();                           // the material in LDS is overwritten next
         }
         if (MODE != GM_STORE && a.nkc > 1) {
+            // partial sums by atomic adds, handed round so that the lanes of a party add to consecutive
+            // words (a party's 168 sums are consecutive in memory; with the eight of a lane added one
+            // after the other every lane of an instruction touched a line of its own)
 #pragma unroll
-            for (int s = 0; s < 8; s++)
-                if (i0 + s < nvg) {
-                    atomicAdd((unsigned long long *)&a.dacc[(u64)p * a.N8 + i0 + s], (unsigned long long)acc[s]);
-                    if (NDOT == 2) atomicAdd((unsigned long long *)&a.dacc[(u64)(3 + p) * a.N8 + i0 + s], (unsigned long long)acc2[s]);
+            for (int q = 0; q < NDOT; q++) {
+                u64 *lin = (u64 *)s_msg;
+                wave_sync();
+#pragma unroll
+                for (int s = 0; s < 8; s++) lin[W.m * 8 + s] = q ? acc2[s] : acc[s];
+                wave_sync();
+                const u64 first = tile * gpt * 8;
+                u64 *d = a.dacc + (u64)(3 * q + p) * a.N8 + first;
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    const u32 w = j * GT_TP + W.t;
+                    const u64 v = lin[GT_TP * 8 * p + w];
+                    if (W.real && first + w < a.N) atomicAdd((unsigned long long *)&d[w], (unsigned long long)v);
                 }
+            }
         }
         if (MODE != GM_STORE && a.nkc == 1) {
-            u64 ao[8], an[8], snd[8], rcv[8];
-            chacha8(K.own, grp, op, 2, ao);
-            chacha8(K.nxt, grp, op, 2, an);
 #pragma unroll
-            for (int s = 0; s < 8; s++) snd[s] = acc[s] + (ao[s] - an[s]);
-            LW.reshare<8>(snd, rcv, 64u * live8(i0, nvg));
+            for (int q = 0; q < NDOT; q++) {
+                u64 ao[8], an[8], snd[8], rcv[8];
+                chacha8(E.own, grp, op, 2 + q, ao);
+                W.pass64<8>(ao, an, W.nx);             // the words under the next key, from the other holder of that key
 #pragma unroll
-            for (int s = 0; s < 8; s++) {
-                if (actg && i0 + s < a.N) {
-                    Sh z = { snd[s], rcv[s] };
-                    if (a.epi == 1) z = scale(ld(a.prev, p, i0 + s), 2) + z + one;
-                    st(a.out, p, i0 + s, z);
-                }
-            }
-            if (NDOT == 2) {
-                chacha8(K.own, grp, op, 3, ao);
-                chacha8(K.nxt, grp, op, 3, an);
-#pragma unroll
-                for (int s = 0; s < 8; s++) snd[s] = acc2[s] + (ao[s] - an[s]);
-                LW.reshare<8>(snd, rcv, 64u * live8(i0, nvg));
+                for (int s = 0; s < 8; s++) snd[s] = (q ? acc2[s] : acc[s]) + (ao[s] - an[s]);
+                W.reshare64<8>(snd, rcv);
+                W.nresh += 64u * live8(i0, nvg);
 #pragma unroll
                 for (int s = 0; s < 8; s++)
-                    if (actg && i0 + s < a.N) { Sh z = { snd[s], rcv[s] }; st(a.out2, p, i0 + s, z); }
+                    if (W.real && i0 + s < nvg) {
+                        Sh z = { snd[s], rcv[s] };
+                        if (q == 0 && a.epi == 1) z = scale(ld(a.prev, p, i0 + s), 2) + z + one;
+                        st(q ? a.out2 : a.out, p, i0 + s, z);
+                    }
             }
         }
-        LW.drain();
+        W.drain();
     }
-    LW.flush(a.c.wire);
+    W.flush(a.c.wire);
 }
 
 // Completion of split inner products: z_p = partial sum + alpha (stream 2, second

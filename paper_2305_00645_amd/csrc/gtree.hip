@@ -400,10 +400,27 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
     return T.finish(rc);
 }
 
-// work items (tile, column range) per resident workgroup slot that the column split aims at: every range
-// replays the row's edaBits and opening, so few long ranges beat many short ones (measured: 2 is best
-// for the census-shaped and the 10^6-sample workloads alike; 4 costs 6 % of the former's training time)
-#define GT_GRID_WANT 2
+// Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
+// replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
+// adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
+// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  Measured with 1, 3,
+// 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
+// 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
+static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps)
+{
+    const u64 half = c->resident, fills[] = { 1, 2, 4, 6, 8 };             // in halves of the slots
+    u64 best = 1;
+    double best_cost = 0;
+    for (u64 f : fills) {
+        u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * half / ntile));
+        const u64 len = (nsteps + n - 1) / n;
+        n = (nsteps + len - 1) / len;
+        const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
+        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5);
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
+    }
+    return best;
+}
 // the equality grid with its accounting
 static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *ext = nullptr, size_t ext_words = 0)
 {
@@ -411,13 +428,14 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
     a.ndot = ndot;
     const u64 nel = (u64)a.w * a.N;
     if (a.N && a.w) {
-        // the leaf one-hot grid takes four adjacent columns per step when it can (whole
-        // lines of the limb tiles per store); all other grids one column per step
-        a.lgs = (mode == GM_STORE && a.w % 4 == 0) ? 4 : 6;
-        const u64 kstep = GT_LANES >> a.lgs, nsteps = (a.w + kstep - 1) / kstep;
-        // enough work items (tile, column range) to keep every resident workgroup slot busy for several rounds
-        const u64 ntile = (a.N8 / 8 + (GT_LANES >> (6 - a.lgs)) - 1) >> a.lgs, want = (u64)GT_GRID_WANT * c->resident;
-        u64 nkc = std::min<u64>(nsteps, std::max<u64>(1, (want + ntile - 1) / ntile));
+        // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
+        // four groups (the 32 samples of a sample block) of five adjacent columns, or ten of two:
+        // the 32-byte pieces that it stores per limb then lie side by side.
+        a.rps = mode != GM_STORE || a.w == 1 ? 1 : (a.w <= 3 ? 2 : 5);
+        a.gpt = a.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (a.rps == 2 ? 8 : 4);
+        const u64 kstep = a.rps, nsteps = (a.w + kstep - 1) / kstep;
+        const u64 ntile = (a.N8 / 8 + a.gpt - 1) / a.gpt;
+        const u64 nkc = column_ranges(c, ntile, nsteps);
         a.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * kstep);
         a.nkc = (a.w + a.kchunk - 1) / a.kchunk;
         a.dacc = nullptr;
@@ -438,14 +456,13 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
             }
             if (!ext) a.dacc = c->dacc;
         }
-        // more workgroups than fit at once: the hardware balances them over the compute units
-        dim3 g((unsigned)std::min<u64>(ntile * a.nkc, GT_MAX_BLOCKS));
+        // more wavefronts than fit at once: the hardware balances them over the compute units
+        const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
         int rc;
-        if (mode == GM_STORE && has_g) rc = launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1>, g, GT_BLOCK, a);
-        else if (mode == GM_STORE) rc = launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, false, 1>, g, GT_BLOCK, a);
-        else if (mode == GM_COMMON && ndot == 2) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2>, g, GT_BLOCK, a);
-        else if (mode == GM_COMMON) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1>, g, GT_BLOCK, a);
-        else rc = launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1>, g, GT_BLOCK, a);
+        if (mode == GM_STORE) rc = launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1>, g, B1, a);
+        else if (mode == GM_COMMON && ndot == 2) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2>, g, B1, a);
+        else if (mode == GM_COMMON) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1>, g, B1, a);
+        else rc = launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1>, g, B1, a);
         GTCHK(rc);
         if (a.dacc) GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, dim3(tiles8(a.N8)), GT_BLOCK, a));
     }
