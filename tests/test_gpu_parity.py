@@ -57,6 +57,20 @@ def test_share_reconstruct(mods, seed, n):
     assert np.array_equal(g.rec(sg), x)
 
 
+@pytest.mark.parametrize("n", [511, 512, 513, 2047, 2049, 5 * 512 + 67])
+def test_share_and_mult_at_tile_edges(mods, seed, n):
+    """Tiles of 512 words whose PRF words change lanes: the last tile full, one short, one over."""
+    o, g = pair(mods, seed)
+    rng = np.random.default_rng(500 + n)
+    x, y = (rng.integers(0, M64, size=n, dtype=np.uint64) for _ in range(2))
+    xo, yo, xg, yg = o.share(x), o.share(y), g.share_a(x), g.share_a(y)
+    same(xg, xo, "share")
+    zg = g.mult(xg, yg)
+    same(zg, o.mult(xo, yo), "mult")
+    assert np.array_equal(g.rec(zg), x * y)
+    same_stats(o, g)
+
+
 def test_empty_vectors(mods, seed):
     o, g = pair(mods, seed)
     sg = g.share_a(np.zeros(0, dtype=np.uint64))
