@@ -243,11 +243,14 @@ __device__ __forceinline__ u64 load_limbs1(const LimbMat &m, u64 row, u64 i)
 }
 
 // The operands of the contraction z_p = x_p (y_p + y_{p+1}) + x_{p+1} y_p (the three-term
-// product of Sec. II-B with the sum moved to the factor that is written once):
-// B, the columns made at set-up, per party as (own+next, own); L, the leaf one-hot made anew at
-// every level, one matrix per COMPONENT: component j is what party j holds as its own and
-// party j-1 as its next part - the two copies are equal by construction, party j's
-// wavefront writes the one that both holders read.
+// product of Sec. II-B with the sum moved to one factor): x is stored once per COMPONENT -
+// component j is what party j holds as its own and party j-1 as its next part, the two
+// copies are equal by construction, party j's wavefront writes the one that both holders
+// read - and y per party as (own+next, own).  L, the leaf one-hot made anew at every level, has
+// 2^h rows, B, the columns made at set-up, has d*K + K.  The operand with fewer rows takes the
+// role of y (and is written twice), so that the larger one is written and read once per
+// component: for 48,842 x 294 columns and 2 classes the contraction reads 0.69 GB per level
+// instead of 1.38.  The class totals of the label level always take L as x.
 struct LimbSet { LimbMat m[3][2]; };
 struct LimbTri { LimbMat m[3]; };
 
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(192) void k_mult(MultArgs a)
 // samples of four adjacent columns (blockIdx.y = column quad): the four 32-byte pieces
 // that one wavefront writes per sample block and limb make up a whole 128-byte line
 // of the tile layout.
-struct XyArgs { KCommon c; P6 XT, YT; LimbSet B; u64 N, N8; u32 K, ncol; };
+struct XyArgs { KCommon c; P6 XT, YT; LimbSet B; LimbTri C; int comps; u64 N, N8; u32 K, ncol; };   // comps: B once per component, into C
 __global__ __launch_bounds__(192, 2) void k_xy(XyArgs a)
 {
     __shared__ u64 s_wire[GT_LWIRE_WORDS];
@@ -369,16 +372,20 @@ __global__ __launch_bounds__(192, 2) void k_xy(XyArgs a)
             if (act) {
 #pragma unroll
                 for (int s = 0; s < 8; s++) { if (i0 + s >= a.N) { snd[s] = 0; rcv[s] = 0; } rcv[s] += snd[s]; }
-                store_limbs8(a.B.m[p][0], col, i0, rcv);
-                store_limbs8(a.B.m[p][1], col, i0, snd);
+                if (a.comps) store_limbs8(p == 0 ? a.C.m[0] : (p == 1 ? a.C.m[1] : a.C.m[2]), col, i0, snd);
+                else {
+                    store_limbs8(a.B.m[p][0], col, i0, rcv);
+                    store_limbs8(a.B.m[p][1], col, i0, snd);
+                }
             }
         }
     }
     W.flush(a.c.wire);
 }
 
-// class indicator columns into limb tiles: row = rowbase + c
-__global__ __launch_bounds__(256) void k_y_limbs(P6 YT, LimbSet B, u64 N, u64 N8, u32 K, u64 rowbase)
+// class indicator columns into limb tiles: row c of Y (both forms) and, where the columns are
+// stored once per component (comps), row rowbase + c of C
+__global__ __launch_bounds__(256) void k_y_limbs(P6 YT, LimbSet Y, LimbTri C, int comps, u64 N, u64 N8, u32 K, u64 rowbase)
 {
     const u64 ngrp = N8 / 8, total = ngrp * K;
     for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (u64)gridDim.x * blockDim.x) {
@@ -390,8 +397,9 @@ __global__ __launch_bounds__(256) void k_y_limbs(P6 YT, LimbSet B, u64 N, u64 N8
                 const bool live = i0 + s < N;
                 xo[s] = live ? YT.o[p][c * N8 + i0 + s] : 0; xn[s] = live ? xo[s] + YT.n[p][c * N8 + i0 + s] : 0;
             }
-            store_limbs8(B.m[p][0], rowbase + c, i0, xn);
-            store_limbs8(B.m[p][1], rowbase + c, i0, xo);
+            store_limbs8(Y.m[p][0], c, i0, xn);
+            store_limbs8(Y.m[p][1], c, i0, xo);
+            if (comps) store_limbs8(C.m[p], rowbase + c, i0, xo);
         }
     }
 }
@@ -429,7 +437,8 @@ struct GridArgs {
     P6 g, out, out2, W1, W2, XT, prev;
     u64 w1off, w2off;
     int epi;
-    LimbTri L;      // GM_STORE: limb tiles of the components, row = column k
+    LimbTri L, S;   // GM_STORE: limb tiles of the components, row = column k; S (sums): party p's own+next
+    int sums;
     u32 nkc, kchunk;// column ranges per tile and their length
     u32 gpt, rps;   // groups of 8 samples per tile, adjacent columns per step (gpt * rps <= 21)
     u64 *dacc;      // [2][3][N8] partial inner products when nkc > 1
@@ -813,19 +822,25 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
                     if (NDOT == 2) acc2[s] += ((mm & nc2) + bo * S2 + bn * Wk2.o) ^ mm;
                 }
             } else {
-                u64 Eo[8];
+                u64 Eo[8], Es[8];
 #pragma unroll
                 for (int s = 0; s < 8; s++) {
                     const u32 m = (u32)((int)(f << (31 - eq_pos(s))) >> 31);
                     const u64 eo = eq_select(E.row(p, s), m, k1o);
-                    if (MODE == GM_STORE) Eo[s] = i0 + s < nv ? eo : 0;
+                    if (MODE == GM_STORE) {
+                        Eo[s] = i0 + s < nv ? eo : 0;
+                        if (a.sums) Es[s] = i0 + s < nv ? eo + eq_select(E.row(W.pn, s), m, k1n) : 0;
+                    }
                     if (MODE == GM_ROWS) {
                         const Sh e = { eo, eq_select(E.row(W.pn, s), m, k1n) }, x = { xo[s], xn[s] };
                         acc[s] += prod3(e, x);
                     }
                 }
                 if (MODE == GM_ROWS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
-                if (MODE == GM_STORE && act && W.real) store_limbs8(p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]), k, i0, Eo);
+                if (MODE == GM_STORE && act && W.real) {
+                    store_limbs8(p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]), k, i0, Eo);
+                    if (a.sums) store_limbs8(p == 0 ? a.S.m[0] : (p == 1 ? a.S.m[1] : a.S.m[2]), k, i0, Es);
+                }
             }
         }
         if (MODE != GM_STORE && a.nkc > 1) {
@@ -1290,7 +1305,7 @@ __global__ __launch_bounds__(192) void k_lcf_bits(LcfArgs a)
 
 // Statistics counting element by element: e = (r*PW + q)*N8 + i, q = row*2dd + 2k + v the
 // position in the (1+K) x 2dd counter array (dd = d, or 1 at the label level).
-struct LitCountArgs { KCommon c; P6 LB, XT, YT; LimbSet B; u64 N, N8; u32 nh, d, dd, K; u64 *acc; };
+struct LitCountArgs { KCommon c; P6 LB, XT, YT; LimbSet B; LimbTri C; int comps; u64 N, N8; u32 nh, d, dd, K; u64 *acc; };
 __global__ __launch_bounds__(192) void k_count_literal(LitCountArgs a)
 {
     const int p = party_of_wave();
@@ -1310,8 +1325,9 @@ __global__ __launch_bounds__(192) void k_count_literal(LitCountArgs a)
             if (row == 0) cv = v ? x : pub(p, 1) - x;
             else {
                 const u64 col = k * a.K + (row - 1);
-                const u64 xyo = load_limbs1(a.B.m[p][1], col, i);
-                const Sh xy = { xyo, load_limbs1(a.B.m[p][0], col, i) - xyo };
+                Sh xy;
+                if (a.comps) { xy.o = load_limbs1(a.C.m[p], col, i); xy.n = load_limbs1(a.C.m[p == 2 ? 0 : p + 1], col, i); }
+                else { xy.o = load_limbs1(a.B.m[p][1], col, i); xy.n = load_limbs1(a.B.m[p][0], col, i) - xy.o; }
                 cv = v ? xy : ld(a.YT, p, (row - 1) * a.N8 + i) - xy;
             }
             s = ld(a.LB, p, r * a.N8 + i);
@@ -1421,6 +1437,7 @@ __global__ __launch_bounds__(256) void k_children(P6 F, P6 src, u64 base, u64 nh
 // ---------------------------------------------------------------------------------
 // Statistics counting as a contraction in Z_2^64 (Sec. V-B):
 //   Z_p[r][col] = sum_i L_p[r][i] * (B_p + B_{p+1})[col][i] + L_{p+1}[r][i] * B_p[col][i]
+//              or sum_i (L_p + L_{p+1})[r][i] * B_p[col][i] + L_p[r][i] * B_{p+1}[col][i]
 // with L the per-sample leaf one-hot and B the sample-contiguous columns (XY products,
 // then the K class indicators).  Both operands are uniformly random 64-bit shares, so
 // this is a dense integer GEMM; it runs on the matrix cores in signed 8-bit limbs:
@@ -1435,32 +1452,34 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // sample blocks of 32 per workgroup: the int32 accumulators would allow 128; with 64 the launch
 // has twice the workgroups to balance over the compute units and takes 3 % less time
 #define CT_CHUNK_BLOCKS 64
+// A[p][q] (rows: nodes) and B[p][q] (rows: columns), q = 0, 1: party p's two products
 // bcol0: first column (row of B) of this launch, zcol0: its column in the output
 // rt: row tiles of 32 per workgroup (4, 2 or 1); the other 4/rt wavefronts take further column tiles
 // chunkblk: sample blocks of 32 per workgroup (at most CT_CHUNK_BLOCKS; the int32 accumulators bound it by 128)
 // nns: slots per chunk (0 = none) for one more column group of at most 16 columns (first column
-// nbcol0 of B, column nzcol0 of the output), handled by the same launch with 16-wide tiles
-struct CountArgs { LimbTri L; LimbSet B; u64 nblk; u32 nh, ncol; u64 bcol0; u32 zcol0; u64 *Zacc; u32 nchunk, nrowgrp, ncg, rt, chunkblk, ncoltiles;   // ncoltiles: column tiles of 32*NB in this launch
+// nbcol0 of B, column nzcol0 of the output), handled by the same launch with 16-wide tiles; X, Y: its
+// operands (x per component, y as (own+next, own) per party), xcols: x holds the columns and y the nodes
+struct CountArgs { LimbSet A, B; LimbTri X; LimbSet Y; int xcols; u64 nblk; u32 nh, ncol; u64 bcol0; u32 zcol0; u64 *Zacc; u32 nchunk, nrowgrp, ncg, rt, chunkblk, ncoltiles;   // ncoltiles: column tiles of 32*NB in this launch
                    u32 nns; u64 nbcol0; u32 nzcol0; };
 
-// A remainder of at most 16 columns (the class totals): 16 rows per wavefront with
+// A remainder of at most 16 columns (the class totals): 16 rows of x per wavefront with
 // v_mfma_i32_16x16x64_i8 (lane l holds row or column l%16 and the 16 samples
 // 16*(l/16).. of a pair of sample blocks; result C[4*(l/16)+v][l%16]), for ALL THREE
 // parties at once.  With so few columns the products are limited by the rate at which L
-// arrives, so every component L_j of L is fetched once and multiplied by one tile that
+// arrives, so every component x_j is fetched once and multiplied by one tile that
 // holds both operands it meets in the three-term products,
-//   columns 0-7:  up to 8 columns of (B_j + B_{j+1})   ->  Z_j     (L_j is party j's own part)
-//   columns 8-15: the same columns of B_{j-1}          ->  Z_{j-1} (and party j-1's next part)
-// (each party's sums still come from the two components that party holds); more than 8
-// columns take a second pass.  It runs inside the launch of the wide groups, as one more
-// column group of each sample chunk.
-__device__ __forceinline__ void count_narrow(const CountArgs &a, u64 r0, u64 ib0, u64 ib1, int lane)
+//   columns 0-7:  up to 8 rows of (y_j + y_{j+1})   ->  Z_j     (x_j is party j's own part)
+//   columns 8-15: the same rows of y_{j-1}          ->  Z_{j-1} (and party j-1's next part)
+// (each party's sums still come from the two components that party holds); rows y0 .. y1-1 of y in
+// passes of 8.  It runs inside the launch of the wide groups, as one more column group of each
+// sample chunk.  nx: rows of x that exist from x0 on.
+__device__ __forceinline__ void count_narrow(const CountArgs &a, u64 x0, u32 nx, u64 y0, u64 y1, u64 ib0, u64 ib1, int lane)
 {
-    const u32 lr = lane & 15, kq = lane >> 4, half = (kq & 1) * 16, nreal = a.ncol - a.nzcol0;
-    for (u32 c0 = 0; c0 < nreal; c0 += 8) {
-        const u32 nc = nreal - c0 < 8 ? nreal - c0 : 8;
+    const u32 lr = lane & 15, kq = lane >> 4, half = (kq & 1) * 16;
+    for (u64 yb = y0; yb < y1; yb += 8) {
+        const u32 nc = y1 - yb < 8 ? (u32)(y1 - yb) : 8;
         const bool bcol = (lr & 7) < nc;                 // this lane's column of the tile exists
-        const u64 brow = a.nbcol0 + c0 + (lr & 7);
+        const u64 brow = yb + (lr & 7);
         v4i acc[3][8];
 #pragma unroll
         for (int j = 0; j < 3; j++)
@@ -1473,17 +1492,17 @@ __device__ __forceinline__ void count_narrow(const CountArgs &a, u64 r0, u64 ib0
         {                                                                                     \
             const u64 ibl = (IB) + (kq >> 1) >= ib1 ? (IB) : (IB) + (kq >> 1);                \
             _Pragma("unroll") for (int sl = 0; sl < 8; sl++)                                  \
-                A[J][sl] = *(const v4i *)(a.L.m[J].base + limb_addr(a.L.m[J], ibl, sl, r0 + lr) + half); \
+                A[J][sl] = *(const v4i *)(a.X.m[J].base + limb_addr(a.X.m[J], ibl, sl, x0 + lr) + half); \
         }
 #define CN_LOAD_B(J, IB)                                                                      \
         {                                                                                     \
             const bool tail = (IB) + (kq >> 1) >= ib1;                                        \
             const u64 ibl = tail ? (IB) : (IB) + (kq >> 1);                                   \
-            const LimbMat &Bs_ = a.B.m[J][0], &Bo_ = a.B.m[((J) + 2) % 3][1];                 \
-            const unsigned char *bb_ = lr < 8 ? Bs_.base : Bo_.base;                          \
+            const LimbMat &Bs_ = a.Y.m[J][0], &Bo_ = a.Y.m[((J) + 2) % 3][1];                 \
+            const LimbMat bb_ = { lr < 8 ? Bs_.base : Bo_.base, lr < 8 ? Bs_.rows : Bo_.rows };\
             _Pragma("unroll") for (int sl = 0; sl < 8; sl++) {                                \
                 B[J][sl] = v4i{ 0, 0, 0, 0 };                                                 \
-                if (!tail && bcol) B[J][sl] = *(const v4i *)(bb_ + limb_addr(Bs_, ibl, sl, brow) + half); \
+                if (!tail && bcol) B[J][sl] = *(const v4i *)(bb_.base + limb_addr(bb_, ibl, sl, brow) + half); \
             }                                                                                 \
         }
 #define CN_MMA(J)                                                                             \
@@ -1522,12 +1541,12 @@ __device__ __forceinline__ void count_narrow(const CountArgs &a, u64 r0, u64 ib0
             u64 *Z = a.Zacc + (u64)pz * a.nh * a.ncol;
 #pragma unroll
             for (int v = 0; v < 4; v++) {
-                const u64 r = r0 + 4 * kq + v;
-                const u64 c = a.nzcol0 + c0 + (lr & 7);
+                const u64 xr = 4 * kq + v;               // row of x and of y of this sum: node and column, or the reverse
+                const u64 r = a.xcols ? brow : x0 + xr, c = a.nzcol0 + (a.xcols ? xr : brow - a.nbcol0);
                 u64 z = 0;
 #pragma unroll
                 for (int u = 0; u < 8; u++) z += (u64)(long long)acc[j][u][v] << (8 * u);
-                if (r < a.nh && bcol) atomicAdd((unsigned long long *)&Z[r * a.ncol + c], (unsigned long long)z);
+                if (xr < nx && bcol) atomicAdd((unsigned long long *)&Z[r * a.ncol + c], (unsigned long long)z);
             }
         }
     }
@@ -1553,10 +1572,16 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
     const u64 ib1 = ib0 + a.chunkblk < a.nblk ? ib0 + a.chunkblk : a.nblk;
     const u32 rg = blockIdx.z;
     if (sl >= 3 * a.ncg) {
-        // a narrow slot of this chunk: its workgroups of 4 wavefronts share out the row tiles
-        // of 16 (each tile for all three parties)
-        const u64 rn = ((u64)((sl - 3 * a.ncg) * a.nrowgrp + rg) * 4 + wave) * 16;
-        if (rn < a.nh) count_narrow(a, rn, ib0, ib1, lane);
+        // a narrow slot of this chunk: its workgroups of 4 wavefronts share out the nodes, 16 rows of x
+        // (each tile for all three parties) or, where x holds the columns, 8 rows of y per wavefront
+        const u64 wv = ((u64)(sl - 3 * a.ncg) * a.nrowgrp + rg) * 4 + wave;
+        const u32 nreal = a.ncol - a.nzcol0;
+        if (a.xcols) {
+            if (wv * 8 < a.nh) count_narrow(a, a.nbcol0, nreal, wv * 8, wv * 8 + 8 < a.nh ? wv * 8 + 8 : a.nh, ib0, ib1, lane);
+        } else if (wv * 16 < a.nh) {
+            const u64 left = a.nh - wv * 16;
+            count_narrow(a, wv * 16, left < 16 ? (u32)left : 16, a.nbcol0, a.nbcol0 + nreal, ib0, ib1, lane);
+        }
         return;
     }
     const int p = sl / a.ncg;
@@ -1564,9 +1589,8 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
     const u32 wr = wave % a.rt, wc = wave / a.rt, cper = 4 / a.rt;   // this wavefront's row / column tile
     const u64 r0 = ((u64)rg * a.rt + wr) * 32;
     if (r0 >= a.nh) return;                                   // whole wavefront
-    // product 0: L_p x (B_p + B_{p+1}), product 1: L_{p+1} x B_p
-    const LimbMat LA0 = p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]);
-    const LimbMat LA1 = p == 0 ? a.L.m[1] : (p == 1 ? a.L.m[2] : a.L.m[0]);
+    const LimbMat LA0 = p == 0 ? a.A.m[0][0] : (p == 1 ? a.A.m[1][0] : a.A.m[2][0]);
+    const LimbMat LA1 = p == 0 ? a.A.m[0][1] : (p == 1 ? a.A.m[1][1] : a.A.m[2][1]);
     const LimbMat LB0 = p == 0 ? a.B.m[0][0] : (p == 1 ? a.B.m[1][0] : a.B.m[2][0]);
     const LimbMat LB1 = p == 0 ? a.B.m[0][1] : (p == 1 ? a.B.m[1][1] : a.B.m[2][1]);
     const u64 ctile = (u64)cg * cper + wc;                   // column tile of 32*NB

@@ -91,8 +91,12 @@ struct gt_train {
     bool fresh_import;               // state was imported and no level has run since: nothing to export for "last"
     TreeSlot *slot;
     DSh XT, YT;                      // [k][i], [c][i]: sample-contiguous copies of the inputs
-    unsigned char *LQ, *BQ;          // limb tiles: leaf one-hot (one matrix per component), columns (own+next, own) per party
-    size_t nblk, Lrows, Brows;       // sample blocks of 32, row strides of the limb planes
+    // limb tiles: leaf one-hot (one matrix per component); columns, (own+next, own) per party or, with comps,
+    // once per component, and then the sums own+next of the leaf one-hot (levels before the last) in SQ and the
+    // class columns in both forms in YQ
+    unsigned char *LQ, *BQ, *SQ, *YQ;
+    bool comps;
+    size_t nblk, Lrows, Brows, Srows;// sample blocks of 32, row strides of the limb planes
     DSh M, T, F, C, Cn, gamma, Gn, isLeaf, SD, split;
     DSh S, Q, quo, rem, val[2], idx[2], tval, best, lab;
     DSh Clast, Glast, Slast;
@@ -527,6 +531,8 @@ static void train_free(gt_train *t)
 {
     if (t->LQ) (void)hipFree(t->LQ);
     if (t->BQ) (void)hipFree(t->BQ);
+    if (t->SQ) (void)hipFree(t->SQ);
+    if (t->YQ) (void)hipFree(t->YQ);
     DSh *all[] = { &t->XT, &t->YT, &t->M, &t->T, &t->F, &t->C, &t->Cn, &t->gamma, &t->Gn, &t->isLeaf, &t->SD,
                    &t->split, &t->S, &t->Q, &t->quo, &t->rem, &t->val[0], &t->val[1], &t->idx[0], &t->idx[1],
                    &t->tval, &t->best, &t->lab, &t->Clast, &t->Glast, &t->Slast };
@@ -550,14 +556,26 @@ static LimbSet limbs_of(unsigned char *base, size_t nblk, size_t rows)
     for (int p = 0; p < 3; p++) for (int m = 0; m < 2; m++) { L.m[p][m].base = base + (size_t)(2 * p + m) * per; L.m[p][m].rows = rows; }
     return L;
 }
-static LimbTri limbs_L(const gt_train *t)
+static LimbTri tri_of(unsigned char *base, size_t nblk, size_t rows)
 {
     LimbTri L;
-    const size_t per = t->nblk * 8 * t->Lrows * 32;
-    for (int j = 0; j < 3; j++) { L.m[j].base = t->LQ + (size_t)j * per; L.m[j].rows = t->Lrows; }
+    const size_t per = nblk * 8 * rows * 32;
+    for (int j = 0; j < 3; j++) { L.m[j].base = base + (size_t)j * per; L.m[j].rows = rows; }
     return L;
 }
+#define GT_YROWS 16              // rows of YQ: GT_MAX_K
+static LimbTri limbs_L(const gt_train *t) { return tri_of(t->LQ, t->nblk, t->Lrows); }
+static LimbTri limbs_S(const gt_train *t) { return tri_of(t->SQ, t->nblk, t->Srows); }
 static LimbSet limbs_B(const gt_train *t) { return limbs_of(t->BQ, t->nblk, t->Brows); }
+static LimbTri limbs_C(const gt_train *t) { return tri_of(t->BQ, t->nblk, t->Brows); }
+// the class columns in both forms: rows of their own, or the last rows of the columns
+static LimbSet limbs_Y(const gt_train *t)
+{
+    if (t->comps) return limbs_of(t->YQ, t->nblk, GT_YROWS);
+    LimbSet Y = limbs_B(t);
+    for (int p = 0; p < 3; p++) for (int m = 0; m < 2; m++) Y.m[p][m].base += (size_t)t->d * t->K * 32;
+    return Y;
+}
 
 extern "C" int gt_train_destroy(gt_train *t) { if (!t) return GT_EINVAL; (void)hipDeviceSynchronize(); train_free(t); return GT_OK; }
 
@@ -570,13 +588,14 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gT(N, d), B256, t->XT.v, to_p6(X), (u64)N, (u64)N8, d));
     GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gT(N, K), B256, t->YT.v, to_p6(Y), (u64)N, (u64)N8, K));
     // one-time products X[i][k] * Y[i][c] and the class columns, as limb tiles
-    XyArgs a{}; a.c = kc(c, c->op++); a.XT = t->XT.v; a.YT = t->YT.v; a.B = limbs_B(t); a.N = N; a.N8 = N8; a.K = K;
+    XyArgs a{}; a.c = kc(c, c->op++); a.XT = t->XT.v; a.YT = t->YT.v; a.comps = t->comps; a.N = N; a.N8 = N8; a.K = K;
+    if (t->comps) a.C = limbs_C(t); else a.B = limbs_B(t);
     a.ncol = d * K;
     const unsigned gy = std::min((a.ncol + 3) / 4, 4u);
     const unsigned gx = (unsigned)std::max<u64>(1, std::min<u64>((N8 / 8 + 15) / 16, GT_MAX_BLOCKS / gy));
     GTCHK(launch(c, GT_KC_MULT, k_xy, dim3(gx, gy), GT_BLOCK, a));
     acct_reshare(c, (u64)N * d * K, 1);
-    GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1((N8 / 8) * K), B256, t->YT.v, limbs_B(t), (u64)N, (u64)N8, K, (u64)d * K));
+    GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1((N8 / 8) * K), B256, t->YT.v, limbs_Y(t), t->comps ? limbs_C(t) : LimbTri{}, (int)t->comps, (u64)N, (u64)N8, K, (u64)d * K));
     // M = 0, T = 0, the root is a leaf with empty statistics, no candidate used yet
     GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(N), B256, t->M.v, (u64)0, (u64)N, (u64)0));
     GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(nodes), B256, t->T.v, (u64)0, (u64)nodes, (u64)0));
@@ -600,7 +619,7 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     const size_t N8 = pad8(N), nmax = (size_t)1 << H, nodes = ((size_t)2 << H) - 1, CW = (size_t)d * K + K;
     size_t P2 = 1; while (P2 < d) P2 *= 2;
     t->N = N; t->N8 = N8; t->d = d; t->K = K; t->H = H; t->CW = (u32)CW; t->level = 0; t->last = 0; t->P2 = (u32)P2;
-    t->finished = false; t->fresh_import = false; t->Zacc = nullptr; t->LQ = nullptr; t->BQ = nullptr; t->slot = nullptr;
+    t->finished = false; t->fresh_import = false; t->Zacc = nullptr; t->LQ = nullptr; t->BQ = nullptr; t->SQ = nullptr; t->YQ = nullptr; t->slot = nullptr;
     t->hc_open = false; t->hcp = nullptr; t->literal = false; t->lit_acc = nullptr; t->part_matmul = false; t->lt_level = ~0u; t->OHL = nullptr;
     hipStream_t s = c->stream;
     int rc = GT_OK;
@@ -626,10 +645,18 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     t->nblk = (N + 31) / 32;
     t->Lrows = std::max<size_t>(32, (nmax + 31) / 32 * 32);
     t->Brows = (CW + 63) / 64 * 64 + 64;
-    const size_t lq = 3 * t->nblk * 8 * t->Lrows * 32, bq = 6 * t->nblk * 8 * t->Brows * 32;
-    if (rc == GT_OK && hipMalloc(&t->LQ, lq) != hipSuccess) rc = GT_ENOMEM;
-    if (rc == GT_OK && hipMalloc(&t->BQ, bq) != hipSuccess) rc = GT_ENOMEM;
-    if (rc == GT_OK && (hipMemsetAsync(t->LQ, 0, lq, s) != hipSuccess || hipMemsetAsync(t->BQ, 0, bq, s) != hipSuccess)) rc = GT_EHIP;
+    // the sums go to the operand with fewer rows: whichever way needs less memory, and with it traffic
+    t->Srows = H ? std::max<size_t>(32, (nmax / 2 + 31) / 32 * 32) : 0;
+    t->comps = 3 * t->Srows + 3 * t->Brows + 6 * GT_YROWS <= 6 * t->Brows;
+    const size_t rowb = t->nblk * 8 * 32;
+    struct { unsigned char **v; size_t bytes; } tiles_of[] = {
+        { &t->LQ, 3 * t->Lrows * rowb }, { &t->BQ, (t->comps ? 3 : 6) * t->Brows * rowb },
+        { &t->SQ, t->comps ? 3 * t->Srows * rowb : 0 }, { &t->YQ, t->comps ? 6 * GT_YROWS * rowb : 0 } };
+    for (auto &q : tiles_of) {
+        if (rc != GT_OK || !q.bytes) continue;
+        if (hipMalloc(q.v, q.bytes) != hipSuccess) { *q.v = nullptr; rc = GT_ENOMEM; }
+        else if (hipMemsetAsync(*q.v, 0, q.bytes, s) != hipSuccess) rc = GT_EHIP;
+    }
     if (rc != GT_OK) { (void)hipStreamSynchronize(s); train_free(t); return T.finish(rc); }
     rc = train_start(c, t, X, Y);
     rc = T.finish(rc);
@@ -670,6 +697,8 @@ static int leaf_onehot(gt_ctx *c, gt_train *t, u32 h)
     GTCHK(do_eq(c, true, t->F.v, base, nullptr, 1, t->isLeaf.v, nh));
     GridArgs a{}; a.u = t->M.v; a.base = base; a.w = (u32)nh; a.N = t->N; a.N8 = t->N8;
     a.g = t->isLeaf.v; a.L = limbs_L(t);
+    a.sums = t->comps && h < t->H;                      // the label level's totals take the class columns' sums
+    if (a.sums) a.S = limbs_S(t);
     GTCHK(do_grid(c, GM_STORE, true, 1, a));
     t->lt_level = h;
     return GT_OK;
@@ -700,7 +729,21 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     const u32 ncol = totals_only ? t->K : t->CW;
     const u64 colbase = totals_only ? dK : 0;
     const u32 op = c->op++;
-    CountArgs a{}; a.L = limbs_L(t); a.B = limbs_B(t); a.nblk = t->nblk; a.nh = (u32)nh; a.ncol = ncol;
+    CountArgs a{}; a.nblk = t->nblk; a.nh = (u32)nh; a.ncol = ncol;
+    const LimbTri L = limbs_L(t);
+    a.xcols = t->comps && !totals_only;
+    if (a.xcols) {              // (L_p + L_{p+1}) B_p + L_p B_{p+1}
+        const LimbTri S = limbs_S(t);
+        a.X = limbs_C(t);
+        for (int p = 0; p < 3; p++) {
+            a.A.m[p][0] = S.m[p]; a.A.m[p][1] = L.m[p]; a.B.m[p][0] = a.X.m[p]; a.B.m[p][1] = a.X.m[(p + 1) % 3];
+        }
+        a.Y = a.A;
+    } else {                    // L_p (B_p + B_{p+1}) + L_{p+1} B_p
+        a.X = L; a.Y = totals_only ? limbs_Y(t) : limbs_B(t); a.B = a.Y;
+        for (int p = 0; p < 3; p++) { a.A.m[p][0] = L.m[p]; a.A.m[p][1] = L.m[(p + 1) % 3]; }
+    }
+    const u64 bcol = 0;         // the class columns' operand of the label level begins with them
     a.Zacc = t->Zacc;
     // wavefront arrangement: 4, 2 or 1 row tiles of 32 per workgroup, the rest over columns
     a.rt = nh > 64 ? 4 : (nh > 32 ? 2 : 1);
@@ -713,8 +756,9 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     // label level - runs on the 16-wide tiles alone)
     const u32 narrow = (rem && rem <= 16) ? 1 : 0;
     const u32 ncg2 = (nfull + cper - 1) / cper, ncg1 = (rem && rem <= 32 && !narrow) ? 1 : 0;
-    // narrow slots per chunk: a workgroup of the narrow group covers 64 rows (4 tiles of 16, all parties)
-    const u32 nns = narrow ? (u32)((nh + 64ull * a.nrowgrp - 1) / (64ull * a.nrowgrp)) : 0;
+    // narrow slots per chunk: a workgroup of the narrow group covers 64 nodes (4 tiles of 16, all parties), 32 where x holds the columns
+    const u64 nper = (a.xcols ? 32ull : 64ull) * a.nrowgrp;   // nodes that one narrow slot covers
+    const u32 nns = narrow ? (u32)((nh + nper - 1) / nper) : 0;
     // sample chunk per workgroup: at most CT_CHUNK_BLOCKS blocks, shorter when that is needed to
     // give every compute unit several workgroups
     const u64 wgs_per_chunk = (u64)(3 * (ncg2 + ncg1) + nns) * a.nrowgrp;
@@ -724,13 +768,13 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     a.chunkblk = (u32)cb;
     a.nchunk = (u32)((t->nblk + cb - 1) / cb);
     if (nfull || narrow) {
-        a.ncg = ncg2; a.ncoltiles = nfull; a.bcol0 = colbase; a.zcol0 = 0;
-        a.nns = nns; a.nbcol0 = colbase + (u64)nfull * 64; a.nzcol0 = nfull * 64;
+        a.ncg = ncg2; a.ncoltiles = nfull; a.bcol0 = bcol; a.zcol0 = 0;
+        a.nns = nns; a.nbcol0 = bcol + (u64)nfull * 64; a.nzcol0 = nfull * 64;
         GTCHK(launch(c, GT_KC_COUNT, k_count<2>, dim3(((a.nchunk + 7) / 8) * (3 * a.ncg + nns) * 8, 1, a.nrowgrp), B256, a));
     }
     if (ncg1) {
         a.nns = 0;
-        a.ncg = 1; a.ncoltiles = 1; a.bcol0 = colbase + (u64)nfull * 64; a.zcol0 = nfull * 64;
+        a.ncg = 1; a.ncoltiles = 1; a.bcol0 = bcol + (u64)nfull * 64; a.zcol0 = nfull * 64;
         GTCHK(launch(c, GT_KC_COUNT, k_count<1>, dim3(((a.nchunk + 7) / 8) * 3 * 8, 1, a.nrowgrp), B256, a));
     }
     CountFinArgs f{}; f.c = kc(c, op); f.Zacc = t->Zacc; f.C = t->C.v; f.n = nh * ncol; f.ncol = ncol; f.CW = t->CW; f.colbase = colbase;
@@ -868,7 +912,8 @@ static int count_literal(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     const u32 dd = totals_only ? 1 : t->d;
     const u64 PW = (u64)(1 + t->K) * 2 * dd;
     GTCHK(launch(c, GT_KC_LOCAL, k_fill_words, g1(6 * nh * PW), B256, t->lit_acc, 6 * nh * PW, (u64)0));
-    LitCountArgs a{}; a.c = kc(c, c->op++); a.LB = t->LB.v; a.XT = t->XT.v; a.YT = t->YT.v; a.B = limbs_B(t); a.N = t->N; a.N8 = t->N8;
+    LitCountArgs a{}; a.c = kc(c, c->op++); a.LB = t->LB.v; a.XT = t->XT.v; a.YT = t->YT.v; a.comps = t->comps; a.N = t->N; a.N8 = t->N8;
+    if (t->comps) a.C = limbs_C(t); else a.B = limbs_B(t);
     a.nh = (u32)nh; a.d = t->d; a.dd = dd; a.K = t->K; a.acc = t->lit_acc;
     GTCHK(launch(c, GT_KC_SMALL, k_count_literal, dim3(tiles(nh * PW * t->N8)), GT_BLOCK, a));
     GTCHK(launch(c, GT_KC_LOCAL, k_from_paper, g1(nh * t->K), B256, t->lit_acc, t->C.v, (u32)nh, t->d, dd, t->K, t->CW));

@@ -289,6 +289,32 @@ def test_train_column_group_remainders(mods, seed, N, d, K, H):
     run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=12)
 
 
+@pytest.mark.parametrize("H", [7, 8])
+@pytest.mark.parametrize("literal", [False, True])
+def test_train_operand_layouts(mods, seed, H, literal):
+    """Columns once per component with the sums on the leaf one-hot, or the sums on the columns:
+    20 columns, and the leaf one-hot's 64 (H = 7) or 128 (H = 8) rows of sums on either side of the
+    line between the two; both also read back by the learning protocol as printed."""
+    from oracle import X_M, X_C, X_SD
+    rng = np.random.default_rng(70 + H)
+    N, d, K = 75, 9, 2
+    X = (rng.random((N, d)) < 0.5).astype(np.uint64)
+    y = (X[:, 2] ^ X[:, 5]).astype(np.int64)
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    if not literal:
+        run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H))
+        return
+    o, g = pair(mods, seed, K=K)
+    o.train_create(o.share(X.reshape(-1)), o.share(Y.reshape(-1)), N, d, H)
+    g.train_create(g.share_a(X.reshape(-1)), g.share_a(Y.reshape(-1)), N, d, H)
+    o.train_set_literal(True); g.train_set_literal(True)
+    for h in range(2):
+        o.train_level(h); g.train_level(h)
+        for what in (X_M, X_C, X_SD):
+            same(g.train_export(what), o.train_export(what), "level %d" % h)
+    same_stats(o, g)
+
+
 def test_train_deep_tree_few_samples(mods, seed):
     """Far more nodes than samples: 2^11 leaves for 40 samples, most nodes empty."""
     rng = np.random.default_rng(98)
