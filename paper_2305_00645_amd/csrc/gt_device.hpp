@@ -339,7 +339,8 @@ __device__ __forceinline__ Sh and_bit(Wire &W, Sh x, Sh y, u64 alpha, bool act)
 
 // Comparison [v >= 0] (v signed, |v| < 2^63) -> Boolean bit sharing.
 // AG, AE: the lane's Boolean zero-sharing words of streams 1 and 2 (own xor next key).
-__device__ __forceinline__ Sh ge_bit_masks(Wire &W, int p, Sh v, const Dealer &D, u64 AG, u64 AE, bool act)
+template <class WireT>
+__device__ __forceinline__ Sh ge_bit_masks(WireT &W, int p, Sh v, const Dealer &D, u64 AG, u64 AE, bool act)
 {
     const u64 LOW63 = 0x7fffffffffffffffull, TOP = 0x8000000000000000ull;
     Sh m = v + D.rA;
@@ -363,7 +364,7 @@ __device__ __forceinline__ Sh ge_bit_masks(Wire &W, int p, Sh v, const Dealer &D
         if (k < 5) {
             const u64 ze = (and3(Eh, E) ^ (AE >> (s - 1))) & sm;
             u64 snd[2] = { zg, ze }, rcv[2];
-            W.reshare<2>(snd, rcv, act ? 2u * (32u >> k) : 0u);   // one bit per block start, G and E
+            W.template reshare<2>(snd, rcv, act ? 2u * (32u >> k) : 0u);   // one bit per block start, G and E
             G.o = (Gh.o & sm) ^ zg; G.n = (Gh.n & sm) ^ rcv[0];
             E.o = ze; E.n = rcv[1];
         } else {
@@ -391,7 +392,8 @@ __device__ __forceinline__ Sh ge_bit(Wire &W, const PartyKeys &K, int p, u32 op,
 // bit -> arithmetic: open f = s xor beta; s = beta if f = 0 else 1 - beta
 // (bits: what the opened value is counted as - one bit, or a ring element of 64 bits where
 // the protocol is run as the paper's cost formula prices it)
-__device__ __forceinline__ Sh b2a(Wire &W, int p, Sh s, const Dealer &D, bool act, u32 bits = 1)
+template <class WireT>
+__device__ __forceinline__ Sh b2a(WireT &W, int p, Sh s, const Dealer &D, bool act, u32 bits = 1)
 {
     const u64 fo = (s.o ^ D.bBo) & 1, fn = (s.n ^ D.bBn) & 1;
     const u64 f = (fo ^ fn ^ W.open1(fo, act ? bits : 0u)) & 1;
@@ -482,6 +484,11 @@ struct WWire {
     }
     template <int ND> __device__ __forceinline__ void reshare(const u32 (&s)[ND], u32 (&r)[ND]) { pass<ND>(s, r, nx); }
     template <int NW> __device__ __forceinline__ void reshare64(const u64 (&s)[NW], u64 (&r)[NW]) { pass64<NW>(s, r, nx); }
+    // the interface of LWire, for the per-element protocols
+    template <int NW>
+    __device__ __forceinline__ void reshare(const u64 (&s)[NW], u64 (&r)[NW], u32 bits) { nresh += bits; pass64<NW>(s, r, nx); }
+    __device__ __forceinline__ u64 reshare1(u64 v, u32 bits) { u64 s[1] = { v }, r[1]; nresh += bits; pass64<1>(s, r, nx); return r[0]; }
+    __device__ __forceinline__ u64 open1(u64 v, u32 bits) { u64 s[1] = { v }, r[1]; nopen += bits; pass64<1>(s, r, pv); return r[0]; }
     template <int NW> __device__ __forceinline__ void open64(const u64 (&s)[NW], u64 (&r)[NW]) { pass64<NW>(s, r, pv); }
     __device__ __forceinline__ void drain()
     {

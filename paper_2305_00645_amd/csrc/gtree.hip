@@ -1158,10 +1158,29 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
     return GT_OK;
 }
 
+// Groups of 8 instances per workgroup of k_infer: the 84 lanes of a party are split into noct groups
+// x 84/noct columns per step.  Few groups mean few steps per access and many workgroups; the rows'
+// part of an access (PRF blocks of its own, three barriers) costs about as much as 1.5 steps.  Two
+// workgroups fit a compute unit; one alone takes 0.65 of the time that two take together.
+static u32 infer_groups(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d)
+{
+    const u64 cus = c->resident / 4;
+    u32 best = 1;
+    double best_cost = 0;
+    for (u32 noct = 1; noct <= GT_INFER_MAX_OCT; noct++) {
+        const u64 ncol = GT_INFER_LANES / noct;
+        if (noct > 1 && GT_INFER_LANES / (noct - 1) == ncol && noct < GT_INFER_MAX_OCT && GT_INFER_LANES / (noct + 1) == ncol) continue;   // the next one has the same columns
+        double units = 0;
+        for (u32 n = 0; n <= H; n++) units += 1.5 + (double)((((u64)1 << n) + ncol - 1) / ncol) + (n < H ? 1.5 + (double)((d + ncol - 1) / ncol) : 0.0);
+        const u64 wgs = (ngrp + noct - 1) / noct * ntrees, full = wgs / (2 * cus), rest = wgs % (2 * cus);
+        const double cost = units * ((double)full + (rest == 0 ? 0.0 : rest <= cus ? 0.65 : 1.0));
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = noct; }
+    }
+    return best;
+}
+
 // One launch for the whole batch (and for every tree of a forest): a workgroup carries a
-// tile of instances through all levels of one tree.  Smaller tiles (more lanes per instance,
-// more columns per step) for batches that would otherwise leave compute units without a
-// workgroup.
+// tile of instances through all levels of one tree.
 static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u32 H, u32 ntrees,
                             const gt_shares *I, size_t NI, uint32_t d, const gt_shares *R)
 {
@@ -1170,19 +1189,14 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     a.I = to_p6(I); a.out = to_p6(R); a.NI = NI; a.N8 = N8; a.d = d; a.H = H; a.ntrees = ntrees; a.has_thr = has_thr ? 1 : 0;
     const u32 S = has_thr ? 3 : 2;
     c->op += ntrees * (H * S + 1);
-    int lgi = c->infer_lgi;
-    const u64 per64 = (NI + 63) / 64 * ntrees, per32 = (NI + 31) / 32 * ntrees;
-    if (!lgi) lgi = per64 >= 2ull * c->resident ? 6 : (per32 >= c->resident / 4 ? 5 : 4);
-    const u64 nitem = ((NI + ((u64)1 << lgi) - 1) >> lgi) * ntrees;
-    const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20));
-    const bool small = nitem <= 2ull * (c->resident / 4);      // at most two workgroups per compute unit
+    const u64 ngrp = N8 / 8;
+    a.noct = c->infer_lgi ? (1u << c->infer_lgi) / 8 : infer_groups(c, ngrp, ntrees, H, d);
+    const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
+    const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * GT_INFER_WAVES);
+    const bool alone = nitem <= c->resident / 4;               // at most one workgroup per compute unit: all registers are its own
     int rc;
-    if (small) rc = lgi == 6 ? launch(c, GT_KC_INFER, k_infer<6, 2>, g, GT_BLOCK, a)
-                  : lgi == 5 ? launch(c, GT_KC_INFER, k_infer<5, 2>, g, GT_BLOCK, a)
-                             : launch(c, GT_KC_INFER, k_infer<4, 2>, g, GT_BLOCK, a);
-    else rc = lgi == 6 ? launch(c, GT_KC_INFER, k_infer<6, 3>, g, GT_BLOCK, a)
-            : lgi == 5 ? launch(c, GT_KC_INFER, k_infer<5, 3>, g, GT_BLOCK, a)
-                       : launch(c, GT_KC_INFER, k_infer<4, 3>, g, GT_BLOCK, a);
+    if (alone) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1>, g, blk, a);
+    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2>, g, blk, a);
     for (u32 t = 0; t < ntrees; t++) {
         for (u32 n = 0; n < H; n++) {
             const u64 nel = ((u64)1 << n) * NI;

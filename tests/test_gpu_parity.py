@@ -597,6 +597,26 @@ def test_infer_paths_agree(mods, seed, how, binary, NI, H, d):
     tree.close(); g.close()
 
 
+@pytest.mark.parametrize("binary,NI,H,d", [(False, 1, 2, 90), (False, 3, 7, 84), (True, 8, 3, 85), (False, 2501, 2, 19), (True, 70001, 1, 3), (False, 40009, 2, 6)])
+def test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d):
+    """The split of a workgroup's 84 lanes per party chosen from the batch: one group of 8
+    instances with 84 columns a step (one column less, as many, one more), a few groups, and the
+    largest tile (16 groups, 5 columns) with a ragged last tile; alone on a compute unit and two."""
+    Oracle, gtree = mods
+    from paper_2305_00645_amd import workloads as wl
+    w = wl.c4_infer(NI=NI, H=H, d=d, binary=binary, seed=5000 + NI)
+    o, g = Oracle(seed), gtree.GTree(seed)
+    fo, lo, fg, lg = o.share(w["feat"]), o.share(w["leaf"]), g.share_a(w["feat"]), g.share_a(w["leaf"])
+    to = tg = None
+    if not binary:
+        to, tg = o.share(w["thr"]), g.share_a(w["thr"])
+    Io, Ig = o.share(w["I"].reshape(-1)), g.share_a(w["I"].reshape(-1))
+    tree = g.tree_import(fg, tg, lg, H)
+    same(g.infer_batch(tree, Ig, NI, d), o.infer(fo, to, lo, H, Io, NI, d), "inference")
+    same_stats(o, g)
+    tree.close(); g.close()
+
+
 @pytest.mark.parametrize("binary,ntrees,NI,H,d", [(True, 7, 150, 3, 9), (False, 3, 77, 4, 16), (True, 40, 1000, 2, 5)])
 def test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d):
     """Many shallow trees on one batch in one launch: shares, operation ids, rounds, bytes
