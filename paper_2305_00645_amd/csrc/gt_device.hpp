@@ -182,7 +182,16 @@ __device__ __forceinline__ Sh scale(Sh a, u64 c) { Sh v; v.o = a.o * c; v.n = a.
 
 // party-local part of a product: z_p = x_p y_p + x_{p+1} y_p + x_p y_{p+1}
 __device__ __forceinline__ u64 prod3(Sh x, Sh y) { return x.o * (y.o + y.n) + x.n * y.o; }
-__device__ __forceinline__ u64 and3(Sh x, Sh y) { return (x.o & (y.o ^ y.n)) ^ (x.n & y.o); }
+// three-input logic, one instruction: T is the value of the expression on a = 0xf0, b = 0xcc, c = 0xaa
+template <u32 T> __device__ __forceinline__ u32 logic3(u32 a, u32 b, u32 c) { return __builtin_amdgcn_bitop3_b32(a, b, c, T); }
+// x_o y_o + x_o y_n + x_n y_o over bits (the three-term product), two instructions
+__device__ __forceinline__ u32 and3l(u32 ao, u32 an, u32 bo, u32 bn) { return logic3<0x6a>(an, bo, logic3<0x60>(ao, bo, bn)); }
+__device__ __forceinline__ u32 xor3l(u32 a, u32 b, u32 c) { return logic3<0x96>(a, b, c); }
+__device__ __forceinline__ u64 and3(Sh x, Sh y)
+{
+    return (u64)and3l((u32)x.o, (u32)x.n, (u32)y.o, (u32)y.n)
+         | ((u64)and3l((u32)(x.o >> 32), (u32)(x.n >> 32), (u32)(y.o >> 32), (u32)(y.n >> 32)) << 32);
+}
 
 // The party of this wavefront.  All 64 lanes of a wavefront share threadIdx.y (the
 // workgroup is 64 x 3), so the value is read into a scalar register: selections and
@@ -295,7 +304,8 @@ __device__ __forceinline__ Dealer dealer_of(const PartyKeys &K, int p, u32 op, u
 // call them together (they contain barriers); inactive lanes pass zeros.
 
 // product with reshare: returns (z_p, z_{p+1})
-__device__ __forceinline__ Sh mult_sh(Wire &W, Sh x, Sh y, u64 alpha, bool act)
+template <class WireT>
+__device__ __forceinline__ Sh mult_sh(WireT &W, Sh x, Sh y, u64 alpha, bool act)
 {
     Sh z;
     z.o = prod3(x, y) + alpha;
@@ -305,14 +315,14 @@ __device__ __forceinline__ Sh mult_sh(Wire &W, Sh x, Sh y, u64 alpha, bool act)
 
 // Equality test [v == 0] -> Boolean bit sharing.  A receives the Boolean
 // zero-sharing word of stream 1 (bits 0..62 used here, bit 63 free for a following AND).
-__device__ __forceinline__ Sh eq_bit(Wire &W, const PartyKeys &K, int p, u32 op, u64 e, Sh v, const Dealer &D, u64 &A, bool act)
+template <class WireT>
+__device__ __forceinline__ Sh eq_bit_mask(WireT &W, int p, Sh v, const Dealer &D, u64 A, bool act)
 {
     Sh m = v + D.rA;
     const u64 c = m.o + m.n + W.open1(m.o, act ? 64u : 0u);
     Sh t = D.rho;
     if (p == 0) t.o ^= ~c;
     if (p == 2) t.n ^= ~c;
-    A = zero_b(K, op, 1, e);
     u32 off = 0;
 #pragma unroll
     for (int k = 0; k < 6; k++) {
@@ -327,9 +337,15 @@ __device__ __forceinline__ Sh eq_bit(Wire &W, const PartyKeys &K, int p, u32 op,
     }
     return t;
 }
+__device__ __forceinline__ Sh eq_bit(Wire &W, const PartyKeys &K, int p, u32 op, u64 e, Sh v, const Dealer &D, u64 &A, bool act)
+{
+    A = zero_b(K, op, 1, e);
+    return eq_bit_mask(W, p, v, D, A, act);
+}
 
 // one-bit AND with reshare; alpha is the mask bit
-__device__ __forceinline__ Sh and_bit(Wire &W, Sh x, Sh y, u64 alpha, bool act)
+template <class WireT>
+__device__ __forceinline__ Sh and_bit(WireT &W, Sh x, Sh y, u64 alpha, bool act)
 {
     Sh z;
     z.o = (and3(x, y) ^ alpha) & 1;
@@ -423,12 +439,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// three-input logic, one instruction: T is the value of the expression on a = 0xf0, b = 0xcc, c = 0xaa
-template <u32 T> __device__ __forceinline__ u32 logic3(u32 a, u32 b, u32 c) { return __builtin_amdgcn_bitop3_b32(a, b, c, T); }
-// x_o y_o + x_o y_n + x_n y_o over bits (the three-term product), two instructions
-__device__ __forceinline__ u32 and3l(u32 ao, u32 an, u32 bo, u32 bn) { return logic3<0x6a>(an, bo, logic3<0x60>(ao, bo, bn)); }
-__device__ __forceinline__ u32 xor3l(u32 a, u32 b, u32 c) { return logic3<0x96>(a, b, c); }
-
 #define GT_WMSG_QUADS (4 * GT_LANES)                 // message region of a wavefront: 16 dwords per lane
 struct WWire {
     uint4 *buf;
@@ -518,3 +528,67 @@ __device__ __forceinline__ Key load_lane_key(const u32 *keys, int p)
     for (int i = 0; i < 8; i++) k.k[i] = keys[p * 8 + i];
     return k;
 }
+
+// ---------------------------------------------------------------------------------
+// Per-element protocols in the wavefront model: a tile of at most 20 consecutive elements, one
+// per lane of a party.  One pass of the block function yields everything a step of the tile
+// needs: the dealer blocks of the elements (their components go to all three parties) and, for
+// NS streams, the words under the three pairwise keys of the three groups of 8 elements that
+// the tile can touch ((e0 mod 8) + elements <= 24); 20 + 9*NS <= 63 lanes.  With a party per
+// wavefront every party evaluated the same dealer blocks and a pass per one or two streams
+// kept 16 or 32 of 64 lanes busy: three passes for 21 elements instead of one.
+#define GT_EL 20
+#define GT_EL_WORDS(NS) (10 * GT_TP + (NS) * 3 * 24 + 4)      // (+ 4: idle lanes load up to four words past the last stream's)
+template <int NS>
+struct ElTile {
+    static_assert(GT_EL + 9 * NS <= 3 * GT_TP, "more blocks than lanes");
+    const u32 *keys;
+    u64 *mat;                    // GT_EL_WORDS(NS) words: [10][21] dealer components, [NS][3][24] words
+    // nel_d: elements of the tile that need the dealer's words (0: none)
+    __device__ __forceinline__ void deal(const WWire &W, u32 op, u64 e0, const u32 (&st)[NS], u32 nel_d)
+    {
+        const u32 m = W.m, r = m - GT_EL, i = r / 9, j = (r % 9) / 3, g = r % 3;
+        const bool dealer = m < GT_EL;
+        wave_sync();
+        if (dealer ? m < nel_d : r < 9 * NS) {
+            Key kv;
+            const int key = dealer ? GT_KEY_DEALER : (int)j;
+#pragma unroll
+            for (int q = 0; q < 8; q++) kv.k[q] = keys[key * 8 + q];
+            u32 stream = 0;
+#pragma unroll
+            for (int q = 0; q < NS; q++) stream = !dealer && i == (u32)q ? st[q] : stream;
+            u64 D[8];
+            chacha8(kv, dealer ? e0 + m : (e0 >> 3) + g, op, stream, D);
+            if (dealer) {
+                const u64 beta = D[5] & 1;
+                const u32 b0 = (u32)(D[5] >> 1) & 1, b1 = (u32)(D[5] >> 2) & 1;
+                mat[m] = D[1]; mat[GT_TP + m] = D[2]; mat[2 * GT_TP + m] = D[0] - D[1] - D[2];
+                mat[3 * GT_TP + m] = D[3]; mat[4 * GT_TP + m] = D[4]; mat[5 * GT_TP + m] = D[0] ^ D[3] ^ D[4];
+                mat[6 * GT_TP + m] = D[6]; mat[7 * GT_TP + m] = D[7]; mat[8 * GT_TP + m] = beta - D[6] - D[7];
+                mat[9 * GT_TP + m] = b0 | (b1 << 1) | ((((u32)beta ^ b0 ^ b1) & 1) << 2);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 8; q++) mat[10 * GT_TP + (i * 3 + j) * 24 + g * 8 + q] = D[q];
+            }
+        }
+        wave_sync();
+    }
+    // party W.p's components of the tile's element W.t
+    __device__ __forceinline__ Dealer dealer(const WWire &W) const
+    {
+        Dealer D;
+        const u64 *m = mat + W.t;
+        const u32 b = (u32)m[9 * GT_TP];
+        D.rA.o = m[W.p * GT_TP]; D.rA.n = m[W.pn * GT_TP];
+        D.rho.o = m[(3 + W.p) * GT_TP]; D.rho.n = m[(3 + W.pn) * GT_TP];
+        D.bA.o = m[(6 + W.p) * GT_TP]; D.bA.n = m[(6 + W.pn) * GT_TP];
+        D.bBo = (b >> W.p) & 1; D.bBn = (b >> W.pn) & 1;
+        return D;
+    }
+    // words of the i-th stream under the party's two keys; w: (e0 mod 8) + number of the element in the tile
+    __device__ __forceinline__ u64 za(const WWire &W, int i, u32 w) const
+    { const u64 *m = mat + 10 * GT_TP + i * 72 + w; return m[W.p * 24] - m[W.pn * 24]; }
+    __device__ __forceinline__ u64 zb(const WWire &W, int i, u32 w) const
+    { const u64 *m = mat + 10 * GT_TP + i * 72 + w; return m[W.p * 24] ^ m[W.pn * 24]; }
+};

@@ -144,36 +144,22 @@ __global__ __launch_bounds__(256) void k_fill_words(u64 *dst, u64 n, u64 c)
     for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) dst[e] = c;
 }
 
-// dst += src (local)
-__global__ __launch_bounds__(256) void k_add_inplace(P6 dst, P6 src, u64 n)
+// The local steps that end a level, in one launch (blockIdx.y): 0: this level's statistics and 1: its
+// flags kept for export, 2: T takes the split decisions, 3: children inherit the flags, rows of
+// width d: Gn[2r] = Gn[2r+1] = gamma[r] (Sec. V-B; ndup = 0 at the last level).
+struct KeepArgs { P6 C, Clast, gamma, Glast, SD, T, Gn; u64 nC, nG, nh, base, ndup; u32 d; };
+__global__ __launch_bounds__(256) void k_keep(KeepArgs a)
 {
-    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x)
-        for (int j = 0; j < 3; j++) { dst.o[j][e] += src.o[j][e]; dst.n[j][e] += src.n[j][e]; }
-}
-
-// rows of width d: dst[2r] = dst[2r+1] = src[r] (children inherit gamma, Sec. V-B)
-__global__ __launch_bounds__(256) void k_dup_rows(P6 dst, P6 src, u64 nh, u64 d)
-{
-    const u64 n = nh * d;
+    const u32 what = blockIdx.y;
+    const u64 n = what == 0 ? a.nC : (what == 1 ? a.nG : (what == 2 ? a.nh : a.ndup));
+    const P6 &src = what == 0 ? a.C : (what == 2 ? a.SD : a.gamma), &dst = what == 0 ? a.Clast : (what == 1 ? a.Glast : (what == 2 ? a.T : a.Gn));
     for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
-        const u64 r = e / d, k = e % d;
+        const u64 to = what == 2 ? a.base + e : (what == 3 ? e + e / a.d * a.d : e);
+#pragma unroll
         for (int j = 0; j < 3; j++) {
-            dst.o[j][(2 * r) * d + k] = dst.o[j][(2 * r + 1) * d + k] = src.o[j][e];
-            dst.n[j][(2 * r) * d + k] = dst.n[j][(2 * r + 1) * d + k] = src.n[j][e];
-        }
-    }
-}
-
-// idx[r*P2 + k] := k (public), val padding := 0
-__global__ __launch_bounds__(256) void k_iota(P6 idx, P6 val, u32 nh, u32 P2, u32 d)
-{
-    const u64 n = (u64)nh * P2;
-    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
-        const u64 k = e % P2;
-        for (int j = 0; j < 3; j++) {
-            idx.o[j][e] = j == 0 ? k : 0;
-            idx.n[j][e] = j == 2 ? k : 0;
-            if (k >= d) { val.o[j][e] = 0; val.n[j][e] = 0; }
+            const u64 vo = src.o[j][e], vn = src.n[j][e];
+            dst.o[j][to] = vo; dst.n[j][to] = vn;
+            if (what == 3) { dst.o[j][to + a.d] = vo; dst.n[j][to + a.d] = vn; }
         }
     }
 }
@@ -771,92 +757,96 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
     W.flush(a.c.wire);
 }
 
-// Completion of split inner products: z_p = partial sum + alpha (stream 2, second
-// output stream 3), reshare, epilogue as in k_eqgrid.  Eight rows per lane.
-__global__ __launch_bounds__(192) void k_dot_fin(GridArgs a)
-{
-    const int p = party_of_wave(), lane = threadIdx.x;
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    const PartyKeys K = load_party_keys(a.c.keys, p);
-    const u64 ngrp = a.N8 / 8;
-    const Sh one = pub(p, 1);
-    for (u64 tile = blockIdx.x, nt = (ngrp + GT_LANES - 1) / GT_LANES; tile < nt; tile += gridDim.x) {
-        const u64 grp = tile * GT_LANES + lane, i0 = grp * 8;
-        const u64 nv = grp < ngrp ? a.N : 0;
-        for (int q = 0; q < a.ndot; q++) {
-            u64 ao[8], an[8], snd[8], rcv[8];
-            chacha8(K.own, grp, a.c.op, 2 + q, ao);
-            chacha8(K.nxt, grp, a.c.op, 2 + q, an);
-#pragma unroll
-            for (int s = 0; s < 8; s++) {
-                u64 part = 0;
-                if (i0 + s < nv) {                     // take the partial sum and leave zero for the next grid
-                    u64 *d = &a.dacc[(u64)(3 * q + p) * a.N8 + i0 + s];
-                    part = *d; *d = 0;
-                }
-                snd[s] = part + (ao[s] - an[s]);
-            }
-            W.reshare<8>(snd, rcv, 64u * live8(i0, nv));
-#pragma unroll
-            for (int s = 0; s < 8; s++)
-                if (i0 + s < nv) {
-                    Sh z = { snd[s], rcv[s] };
-                    if (q == 0 && a.epi == 1) z = scale(ld(a.prev, p, i0 + s), 2) + z + one;
-                    st(q == 0 ? a.out : a.out2, p, i0 + s, z);
-                }
-        }
-    }
-    W.flush(a.c.wire);
-}
-
 // ---------------------------------------------------------------------------------
 // Small per-element protocols, one element per lane.
 
-// z = B2A([x - y_pub == 0]) or the Boolean bit (BOOL_OUT)
-struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; };
-template <bool BOOL_OUT>
-__global__ __launch_bounds__(192) void k_eq(EqArgs a)
+// a wavefront of an element kernel: tiles of GT_EL elements, grid-stride; every lane of the wavefront
+// runs the same tiles.  LDS per wavefront: messages, material, counters.
+#define GT_EL_SHARED(NS)                                                                   \
+    __shared__ uint4 s_msg[GT_LANES];                                                       \
+    __shared__ u64 s_mat[GT_EL_WORDS(NS)];                                                  \
+    __shared__ u64 s_cnt[6];                                                                \
+    WWire W; W.init(s_msg, s_cnt);                                                          \
+    const int p = W.p;                                                                      \
+    ElTile<NS> T; T.keys = a.c.keys; T.mat = s_mat;
+#define GT_FOR_EL(n) for (u64 tile_ = blockIdx.x, ntiles_ = ((u64)(n) + GT_EL - 1) / GT_EL; tile_ < ntiles_; tile_ += gridDim.x)
+__device__ __forceinline__ u32 el_live(u64 e0, u64 n) { return n - e0 < GT_EL ? (u32)(n - e0) : GT_EL; }
+
+// Completion of split inner products: z_p = partial sum + alpha (stream 2, second
+// output stream 3), reshare, epilogue as in k_eqgrid.  Rows in the lanes of the element kernels:
+// consecutive rows in consecutive lanes (eight rows per lane of 64 took 11 us for 48,842 rows).
+__global__ __launch_bounds__(64) void k_dot_fin(GridArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
+    __shared__ uint4 s_msg[GT_LANES];
+    __shared__ u64 s_mat[GT_EL_WORDS(2)];
     __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
-        Sh v = { 0, 0 };
-        if (act) v = ld(a.x, p, a.xoff + e) - pub(p, a.ysub + (a.ypub ? a.ypub[e] : 0));
-        const Dealer D = dealer_of(K, p, a.c.op, e);
-        u64 A;
-        Sh b = eq_bit(W, K, p, a.c.op, e, v, D, A, act);
-        if (!BOOL_OUT) b = b2a(W, p, b, D, act);
-        if (act) st(a.z, p, e, b);
+    WWire W; W.init(s_msg, s_cnt);
+    const int p = W.p;
+    ElTile<2> T; T.keys = a.c.keys; T.mat = s_mat;
+    const Sh one = pub(p, 1);
+    GT_FOR_EL(a.N) {
+        const u64 e0 = tile_ * GT_EL, i = e0 + W.t;
+        const bool act = W.t < GT_EL && i < a.N;
+        const u32 st2[2] = { 2, 3 }, w = (u32)(e0 & 7) + W.t;
+        u64 part[2] = { 0, 0 };
+        if (act)
+            for (int q = 0; q < a.ndot; q++) part[q] = a.dacc[(u64)(3 * q + p) * a.N8 + i];
+        T.deal(W, a.c.op, e0, st2, 0);
+        if (act)                                       // leave zero for the next grid
+            for (int q = 0; q < a.ndot; q++) a.dacc[(u64)(3 * q + p) * a.N8 + i] = 0;
+        for (int q = 0; q < a.ndot; q++) {
+            Sh z;
+            z.o = part[q] + T.za(W, q, w);
+            z.n = W.reshare1(z.o, act ? 64u : 0u);
+            if (act && W.real) {
+                if (q == 0 && a.epi == 1) z = scale(ld(a.prev, p, i), 2) + z + one;
+                st(q == 0 ? a.out : a.out2, p, i, z);
+            }
+        }
+        W.drain();
     }
     W.flush(a.c.wire);
 }
 
-// z = B2A([x >= y])
-struct GeArgs { KCommon c; P6 x, y, z; u64 n; };
-__global__ __launch_bounds__(192) void k_ge(GeArgs a)
+// z = B2A([x - y_pub == 0]) or the Boolean bit (BOOL_OUT).  300,007 elements: 51 us with a party per
+// wavefront, 23 us now.
+struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; };
+template <bool BOOL_OUT>
+__global__ __launch_bounds__(64) void k_eq(EqArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
+    GT_EL_SHARED(1)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
+        Sh v = { 0, 0 };
+        if (act) v = ld(a.x, p, a.xoff + e) - pub(p, a.ysub + (a.ypub ? a.ypub[e] : 0));
+        const u32 st1[1] = { 1 };
+        T.deal(W, a.c.op, e0, st1, el_live(e0, a.n));
+        const Dealer D = T.dealer(W);
+        Sh b = eq_bit_mask(W, p, v, D, T.zb(W, 0, (u32)(e0 & 7) + W.t), act);
+        if (!BOOL_OUT) b = b2a(W, p, b, D, act);
+        if (act && W.real) st(a.z, p, e, b);
+        W.drain();
+    }
+    W.flush(a.c.wire);
+}
+
+// z = B2A([x >= y]).  300,007 elements: 54 us with a party per wavefront, 27 us now.
+struct GeArgs { KCommon c; P6 x, y, z; u64 n; };
+__global__ __launch_bounds__(64) void k_ge(GeArgs a)
+{
+    GT_EL_SHARED(2)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
         Sh v = { 0, 0 };
         if (act) v = ld(a.x, p, e) - ld(a.y, p, e);
-        const Dealer D = dealer_of(K, p, a.c.op, e);
-        Sh b = b2a(W, p, ge_bit(W, K, p, a.c.op, e, v, D, act), D, act);
-        if (act) st(a.z, p, e, b);
+        const u32 st2[2] = { 1, 2 }, w = (u32)(e0 & 7) + W.t;
+        T.deal(W, a.c.op, e0, st2, el_live(e0, a.n));
+        const Dealer D = T.dealer(W);
+        const Sh b = b2a(W, p, ge_bit_masks(W, p, v, D, T.zb(W, 0, w), T.zb(W, 1, w), act), D, act);
+        if (act && W.real) st(a.z, p, e, b);
+        W.drain();
     }
     W.flush(a.c.wire);
 }
@@ -885,54 +875,86 @@ __global__ __launch_bounds__(192) void k_cmp_step(CmpArgs a)
 
 // Restoring division, all steps of an element in one launch (the steps of different
 // elements do not interact): step t uses operation id op + t; b = [r >= Q]; r <- r - b Q;
-// quo <- 2 quo + b; r starts as S and is doubled between steps.
-struct DivArgs { KCommon c; P6 S, Q, r, quo; u64 n; u32 nsteps; };
-__global__ __launch_bounds__(192) void k_div(DivArgs a)
+// quo <- 2 quo + b; r starts as S and is doubled between steps.  T: the step's material.
+__device__ __forceinline__ void div_step(WWire &W, const ElTile<3> &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
+    if (!first) r = scale(r, 2);
+    const Dealer D = T.dealer(W);
+    const Sh b = b2a(W, p, ge_bit_masks(W, p, r - Q, D, T.zb(W, 0, w), T.zb(W, 1, w), act), D, act);
+    const Sh bq = mult_sh(W, b, Q, T.za(W, 2, w), act);
+    r = r - bq;
+    quo = scale(quo, 2) + b;
+}
+// Material of all steps of a division by NW wavefronts side by side, then the steps by the first of
+// them: with few elements the steps' PRF blocks would otherwise lie in the chain, one per step.
+// NW = 1: a slot that is dealt anew before every step.
+template <int NW>
+__device__ __forceinline__ void div_steps_el(WWire &W, ElTile<3> &T, u64 *s_mat, int p, u32 op, u64 e0, u32 nel, u32 nsteps, Sh Q, Sh &r, Sh &quo, bool act)
+{
+    const u32 st3[3] = { 1, 2, 3 }, w = (u32)(e0 & 7) + W.t;
+    if (NW > 1) {
+        for (u32 t = threadIdx.x / GT_LANES; t < nsteps; t += NW) { T.mat = s_mat + t * GT_EL_WORDS(3); T.deal(W, op + t, e0, st3, nel); }
+        __syncthreads();
+    }
+    if (NW == 1 || threadIdx.x < GT_LANES)
+        for (u32 t = 0; t < nsteps; t++) {
+            if (NW == 1) T.deal(W, op + t, e0, st3, nel);
+            else T.mat = s_mat + t * GT_EL_WORDS(3);
+            div_step(W, T, p, w, t == 0, Q, r, quo, act);
+        }
+    if (NW > 1) __syncthreads();                       // the material is dealt anew for the next tile
+}
+#define GT_DIV_STEPS 21                                // GT_MAX_TAU + 1
+#define GT_DIV_SHARED(NW)                                                                  \
+    __shared__ uint4 s_msg[NW][GT_LANES];                                                   \
+    __shared__ u64 s_mat[(NW > 1 ? GT_DIV_STEPS : 1) * GT_EL_WORDS(3)];                      \
+    __shared__ u64 s_cnt[NW][6];                                                            \
+    const u32 wave_ = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);               \
+    WWire W; W.init(s_msg[wave_], s_cnt[wave_]);                                            \
+    const int p = W.p;                                                                      \
+    ElTile<3> T; T.keys = a.c.keys; T.mat = s_mat;
+
+// 100,003 quotients, 17 steps: 304 us with a party per wavefront, 118 us now (VALU: a PRF pass and 330
+// instructions of protocol per step and 20 elements).
+struct DivArgs { KCommon c; P6 S, Q, quo; u64 n; u32 nsteps; };
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_div(DivArgs a)
+{
+    GT_DIV_SHARED(NW)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
         Sh r = { 0, 0 }, Q = { 0, 0 }, quo = { 0, 0 };
         if (act) { Q = ld(a.Q, p, e); r = ld(a.S, p, e); }
-        for (u32 t = 0; t < a.nsteps; t++) {
-            const u32 op = a.c.op + t;
-            if (t) r = scale(r, 2);
-            const Dealer D = dealer_of(K, p, op, e);
-            const Sh b = b2a(W, p, ge_bit(W, K, p, op, e, r - Q, D, act), D, act);
-            const Sh bq = mult_sh(W, b, Q, zero_a(K, op, 3, e), act);
-            r = r - bq;
-            quo = scale(quo, 2) + b;
-        }
-        if (act) { st(a.r, p, e, r); st(a.quo, p, e, quo); }
+        div_steps_el<NW>(W, T, s_mat, p, a.c.op, e0, el_live(e0, a.n), a.nsteps, Q, r, quo, act);
+        if (act && W.real && wave_ == 0) st(a.quo, p, e, quo);
+        W.drain();
     }
     W.flush(a.c.wire);
 }
 
-// Gini numerator/denominator terms (Sec. V-B, Eq. (1)): element q = (r*d+k)*2 + j,
-// S = sum_c n_jc^2, Q = n_j * n with n_1c = C[r][k*K+c], n_0c = tot_c - n_1c.
-struct PrepArgs { KCommon c; P6 C, S, Q; u64 n; u32 d, K, CW; };
-__global__ __launch_bounds__(192) void k_score_prep(PrepArgs a)
+// Gini scores of a level in one launch (Sec. V-B, Eq. (1)).  Element q = (r*d+k)*2 + j:
+//   op:          S = sum_c n_jc^2, Q = n_j * n with n_1c = C[r][k*K+c], n_0c = tot_c - n_1c
+//   op+1:        Q <- Q + [Q == 0] (empty branch: divisor 1)
+//   op+2 ..:     restoring division, tau+1 steps
+//   op+tau+3:    score = quo(j=0) + quo(j=1), masked = score * gamma[r*d+k], written to `score`
+// Everything is local to the two elements of a candidate, so nothing but the masked score reaches memory
+// (five launches and six arrays before; 17 steps for up to 9,408 elements 29 us, 105 us before).
+struct ScoreArgs { KCommon c; P6 C, gamma, score; u64 n; u32 d, K, CW, nsteps; };
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_score(ScoreArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
+    GT_DIV_SHARED(NW)
     const u64 dK = (u64)a.d * a.K;
-    GT_FOR_TILES(a.n) {
-        const u64 q = GT_ELEM();
-        const bool act = q < a.n;
-        Sh nj = { 0, 0 }, n = { 0, 0 };
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, q = e0 + W.t, cand = q / 2;
+        const bool act = W.t < GT_EL && q < a.n;
+        const u32 nel = el_live(e0, a.n), w = (u32)(e0 & 7) + W.t;
+        const u32 cb = wave_ == 0 ? 1u : 0u;           // every wavefront runs the head of the tile (it is short), one counts
+        Sh nj = { 0, 0 }, n = { 0, 0 }, S, Q, quo = { 0, 0 };
         u64 s = 0;
         if (act) {
-            const u64 r = q / (2 * a.d), k = (q / 2) % a.d, br = q & 1;
+            const u64 r = cand / a.d, k = cand % a.d, br = q & 1;
             for (u32 cl = 0; cl < a.K; cl++) {
                 const Sh n1 = ld(a.C, p, r * a.CW + k * a.K + cl), tot = ld(a.C, p, r * a.CW + dK + cl);
                 const Sh njc = br ? n1 : tot - n1;
@@ -940,143 +962,199 @@ __global__ __launch_bounds__(192) void k_score_prep(PrepArgs a)
                 s += prod3(njc, njc);
             }
         }
-        u64 z0, z1;
-        zero_a2(K, a.c.op, 0, 1, q, z0, z1);
-        u64 snd[2] = { s + z0, prod3(nj, n) + z1 }, rcv[2];
-        W.reshare<2>(snd, rcv, act ? 128u : 0u);
-        if (act) { Sh S = { snd[0], rcv[0] }, Q = { snd[1], rcv[1] }; st(a.S, p, q, S); st(a.Q, p, q, Q); }
+        T.mat = s_mat + (NW > 1 ? wave_ : 0u) * GT_EL_WORDS(3);
+        {
+            const u32 sn[3] = { 0, 1, 1 };
+            T.deal(W, a.c.op, e0, sn, 0);
+            u64 snd[2] = { s + T.za(W, 0, w), prod3(nj, n) + T.za(W, 1, w) }, rcv[2];
+            W.template reshare<2>(snd, rcv, act ? 128u * cb : 0u);
+            S.o = snd[0]; S.n = rcv[0]; Q.o = snd[1]; Q.n = rcv[1];
+        }
+        const bool actc = act && cb;
+        {
+            const u32 sn[3] = { 1, 1, 1 };
+            T.deal(W, a.c.op + 1, e0, sn, nel);
+            const Dealer D = T.dealer(W);
+            Q = Q + b2a(W, p, eq_bit_mask(W, p, Q, D, T.zb(W, 0, w), actc), D, actc);
+        }
+        if (NW > 1) __syncthreads();                   // the head's material of all wavefronts has been read
+        div_steps_el<NW>(W, T, s_mat, p, a.c.op + 2, e0, nel, a.nsteps, Q, S, quo, actc);
+        if (wave_ == 0) {
+            // the candidate's two quotients meet in its even lane (the party's own words, no message)
+            const u64 mine[2] = { quo.o, quo.n };
+            u64 other[2];
+            W.template pass64<2>(mine, other, W.t & 1 ? W.m - 1 : (W.t < GT_EL ? W.m + 1 : W.m));
+            const bool ev = act && !(W.t & 1);
+            Sh sc = { quo.o + other[0], quo.n + other[1] }, g = { 0, 0 };
+            if (ev) g = ld(a.gamma, p, cand);
+            const u32 sn[3] = { 0, 0, 0 };
+            T.mat = s_mat;
+            T.deal(W, a.c.op + 2 + a.nsteps, e0 / 2, sn, 0);
+            const Sh z = mult_sh(W, sc, g, T.za(W, 0, (u32)((e0 / 2) & 7) + W.t / 2), ev);
+            if (ev && W.real) st(a.score, p, cand, z);
+        }
+        if (NW > 1) __syncthreads();
+        W.drain();
     }
     W.flush(a.c.wire);
 }
 
-// score = quo[2e] + quo[2e+1]; masked = score * gamma[e]; written to the export copy
-// and into the tournament array val[r*P2 + k].
-struct MaskArgs { KCommon c; P6 quo, gamma, score, val; u64 n; u32 d, P2; };
-__global__ __launch_bounds__(192) void k_mask_score(MaskArgs a)
+// Compare-and-select of a tile: b = [right > left]; val = left + b (right-left); idx likewise (material
+// of operation `op`, elements from e0).
+__device__ __forceinline__ void select_el(WWire &W, ElTile<4> &T, int p, u32 op, u64 e0, u32 nel, Sh &L, Sh R, Sh &IL, Sh IR, bool act)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
-        Sh s = { 0, 0 }, g = { 0, 0 };
-        if (act) { s = ld(a.quo, p, 2 * e) + ld(a.quo, p, 2 * e + 1); g = ld(a.gamma, p, e); }
-        const Sh z = mult_sh(W, s, g, zero_a(K, a.c.op, 0, e), act);
-        if (act) { st(a.score, p, e, z); st(a.val, p, (e / a.d) * a.P2 + e % a.d, z); }
-    }
-    W.flush(a.c.wire);
+    const u32 st4[4] = { 1, 2, 3, 4 }, w = (u32)(e0 & 7) + W.t;
+    T.deal(W, op, e0, st4, nel);
+    const Dealer D = T.dealer(W);
+    const Sh b = b2a(W, p, not_bit(p, ge_bit_masks(W, p, L - R, D, T.zb(W, 0, w), T.zb(W, 1, w), act)), D, act);
+    u64 snd[2] = { prod3(b, R - L) + T.za(W, 2, w), prod3(b, IR - IL) + T.za(W, 3, w) }, rcv[2];
+    W.template reshare<2>(snd, rcv, act ? 128u : 0u);
+    L.o += snd[0]; L.n += rcv[0]; IL.o += snd[1]; IL.n += rcv[1];
 }
 
-// Compare-and-select: b = [right > left]; val = left + b (right-left); idx likewise.
-// mode 0 (tournament level over arrays of length len per node): e = r*half + m,
-//        left = in[r*len+2m], right = in[r*len+2m+1], out[e].
-// mode 1 (label chain): left = val_in[e] / idx_in[e], right = C[e*CW + coff], index
-//        constant cidx; in place.
-struct SelArgs { KCommon c; P6 vin, iin, vout, iout, C; u64 n; u32 len, CW; u64 coff, cidx; int mode; };
-__global__ __launch_bounds__(192) void k_select_max(SelArgs a)
+// Arg-max of a level's masked scores, all rounds of the tournament in one launch: a workgroup per
+// node, tiles of 16 pairs per wavefront ((e0 mod 8) + 16 <= 24 for any e0), a barrier per round.  Round l
+// (operation op + l) compares arrays of length P2 >> l: element e = r*half + m, left 2m, right 2m+1;
+// the scores are padded with 0, the indices start as k.  The rounds' results stay in LDS for
+// P2 <= GT_ARGMAX_LDS, in the buffers val / idx otherwise.  Bound: the chain of the rounds.  512 candidates:
+// nine launches of 10.8 us, now 30 us.
+#define GT_ARGMAX_LDS 512
+#define GT_ARGMAX_WAVES 8
+struct ArgmaxArgs { KCommon c; P6 score, val[2], idx[2], SD; u32 nh, d, P2; };
+__global__ __launch_bounds__(64 * GT_ARGMAX_WAVES) void k_argmax(ArgmaxArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
-        Sh L = { 0, 0 }, R = { 0, 0 }, IL = { 0, 0 }, IR = { 0, 0 };
-        if (act) {
-            if (a.mode == 0) {
-                const u64 half = a.len / 2, r = e / half, m = e % half, l = r * a.len + 2 * m;
-                L = ld(a.vin, p, l); R = ld(a.vin, p, l + 1); IL = ld(a.iin, p, l); IR = ld(a.iin, p, l + 1);
-            } else {
-                L = ld(a.vin, p, e); IL = ld(a.iin, p, e);
-                R = ld(a.C, p, e * a.CW + a.coff); IR = pub(p, a.cidx);
+    __shared__ uint4 s_msg[GT_ARGMAX_WAVES][GT_LANES];
+    __shared__ u64 s_mat[GT_ARGMAX_WAVES][GT_EL_WORDS(4)];
+    __shared__ u64 s_cnt[GT_ARGMAX_WAVES][6];
+    __shared__ u64 s_buf[2][12][GT_ARGMAX_LDS / 2];
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
+    WWire W; W.init(s_msg[wave], s_cnt[wave]);
+    const int p = W.p;
+    ElTile<4> T; T.keys = a.c.keys; T.mat = s_mat[wave];
+    for (u64 r = blockIdx.x; r < a.nh; r += gridDim.x) {
+        u64 *vo[2], *vn[2], *io[2], *in[2];            // this party's buffers, ping-pong
+#pragma unroll
+        for (int x = 0; x < 2; x++) {
+            if (a.P2 <= GT_ARGMAX_LDS) { vo[x] = s_buf[x][4 * p]; vn[x] = s_buf[x][4 * p + 1]; io[x] = s_buf[x][4 * p + 2]; in[x] = s_buf[x][4 * p + 3]; }
+            else {
+                vo[x] = own_of(a.val[x], p) + r * a.P2; vn[x] = nxt_of(a.val[x], p) + r * a.P2;
+                io[x] = own_of(a.idx[x], p) + r * a.P2; in[x] = nxt_of(a.idx[x], p) + r * a.P2;
             }
         }
-        const Dealer D = dealer_of(K, p, a.c.op, e);
-        const Sh b = b2a(W, p, not_bit(p, ge_bit(W, K, p, a.c.op, e, L - R, D, act)), D, act);
-        u64 z3, z4;
-        zero_a2(K, a.c.op, 3, 4, e, z3, z4);
-        u64 snd[2] = { prod3(b, R - L) + z3, prod3(b, IR - IL) + z4 }, rcv[2];
-        W.reshare<2>(snd, rcv, act ? 128u : 0u);
-        if (act) {
-            Sh dv = { snd[0], rcv[0] }, di = { snd[1], rcv[1] };
-            st(a.vout, p, e, L + dv); st(a.iout, p, e, IL + di);
-        }
-    }
-    W.flush(a.c.wire);
-}
-
-// gamma[r][k] <- gamma[r][k] * (1 - [SD[r] == k])
-struct GammaArgs { KCommon c; P6 SD, gamma; u64 n; u32 d; };
-__global__ __launch_bounds__(192) void k_gamma(GammaArgs a)
-{
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
-        Sh v = { 0, 0 }, g = { 0, 0 };
-        if (act) { v = ld(a.SD, p, e / a.d) - pub(p, e % a.d); g = ld(a.gamma, p, e); }
-        const Dealer D = dealer_of(K, p, a.c.op, e);
-        u64 A;
-        const Sh oh = b2a(W, p, eq_bit(W, K, p, a.c.op, e, v, D, A, act), D, act);
-        const Sh z = mult_sh(W, g, pub(p, 1) - oh, zero_a(K, a.c.op, 2, e), act);
-        if (act) st(a.gamma, p, e, z);
-    }
-    W.flush(a.c.wire);
-}
-
-// Node r: pure = [n^2 - sum_c tot_c^2 == 0]; split = isLeaf and not pure;
-// F[base+r] <- F (1 - split); children F <- 2 - split.
-struct SplitArgs { KCommon c; P6 C, isLeaf, F, split; u64 n, base; u32 K, CW; u64 dK; };
-__global__ __launch_bounds__(192) void k_split(SplitArgs a)
-{
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 r = GT_ELEM();
-        const bool act = r < a.n;
-        Sh n = { 0, 0 }, leaf = { 0, 0 }, f = { 0, 0 };
-        u64 dv = 0;
-        if (act) {
-            for (u32 cl = 0; cl < a.K; cl++) {
-                const Sh tc = ld(a.C, p, r * a.CW + a.dK + cl);
-                n = n + tc;
-                dv -= prod3(tc, tc);
+        u32 cur = 0, round = 0;
+        for (u32 len = a.P2; len > 1; len /= 2, round++) {
+            const u32 half = len / 2;
+            for (u32 m0 = wave * 16; m0 < half; m0 += GT_ARGMAX_WAVES * 16) {
+                const u32 nel = half - m0 < 16 ? half - m0 : 16, m = m0 + W.t;
+                const bool act = W.t < nel;
+                Sh L = { 0, 0 }, R = { 0, 0 }, IL = { 0, 0 }, IR = { 0, 0 };
+                if (act) {
+                    if (round == 0) {
+                        if (2 * m < a.d) L = ld(a.score, p, r * a.d + 2 * m);
+                        if (2 * m + 1 < a.d) R = ld(a.score, p, r * a.d + 2 * m + 1);
+                        IL = pub(p, 2 * m); IR = pub(p, 2 * m + 1);
+                    } else {
+                        L.o = vo[cur][2 * m]; L.n = vn[cur][2 * m]; R.o = vo[cur][2 * m + 1]; R.n = vn[cur][2 * m + 1];
+                        IL.o = io[cur][2 * m]; IL.n = in[cur][2 * m]; IR.o = io[cur][2 * m + 1]; IR.n = in[cur][2 * m + 1];
+                    }
+                }
+                select_el(W, T, p, a.c.op + round, r * half + m0, nel, L, R, IL, IR, act);
+                if (act && W.real) {
+                    if (half == 1) st(a.SD, p, r, IL);
+                    else { vo[cur ^ 1][m] = L.o; vn[cur ^ 1][m] = L.n; io[cur ^ 1][m] = IL.o; in[cur ^ 1][m] = IL.n; }
+                }
             }
-            dv += prod3(n, n);
-            leaf = ld(a.isLeaf, p, r);
-            f = ld(a.F, p, a.base + r);
+            cur ^= 1;
+            __syncthreads();
         }
-        Sh d;
-        d.o = dv + zero_a(K, a.c.op, 2, r);
-        d.n = W.reshare1(d.o, act ? 64u : 0u);
-        const Dealer D = dealer_of(K, p, a.c.op, r);
-        u64 A;
-        const Sh npure = not_bit(p, eq_bit(W, K, p, a.c.op, r, d, D, A, act));
-        const Sh sA = b2a(W, p, and_bit(W, leaf, npure, A >> 63, act), D, act);
-        const Sh keep = pub(p, 1) - sA;
-        const Sh fz = mult_sh(W, f, keep, zero_a(K, a.c.op, 3, r), act);
-        if (act) {
-            st(a.split, p, r, sA);
-            st(a.F, p, a.base + r, fz);
-            const Sh ch = keep + pub(p, 1);
-            st(a.F, p, 2 * (a.base + r) + 1, ch);
-            st(a.F, p, 2 * (a.base + r) + 2, ch);
+        if (a.P2 == 1 && threadIdx.x < 3) { const Sh z = { 0, 0 }; st(a.SD, (int)threadIdx.x, r, z); }   // one candidate: index 0
+        W.drain();
+    }
+    W.flush(a.c.wire);
+}
+
+// Label = first maximum of the class totals, the K-1 selections of a node in one launch (operation
+// op + cl - 1): left starts as class 0, right = class cl with the index constant cl.
+struct LabelArgs { KCommon c; P6 C, lab; u64 n, dK, laboff; u32 K, CW; };
+__global__ __launch_bounds__(64) void k_labels(LabelArgs a)
+{
+    GT_EL_SHARED(4)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
+        Sh L = { 0, 0 }, IL = { 0, 0 };
+        if (act) L = ld(a.C, p, e * a.CW + a.dK);
+        for (u32 cl = 1; cl < a.K; cl++) {
+            Sh R = { 0, 0 };
+            if (act) R = ld(a.C, p, e * a.CW + a.dK + cl);
+            select_el(W, T, p, a.c.op + cl - 1, e0, el_live(e0, a.n), L, R, IL, pub(p, cl), act);
+        }
+        if (act && W.real) st(a.lab, p, a.laboff + e, IL);
+        W.drain();
+    }
+    W.flush(a.c.wire);
+}
+
+// Updates of a level in one launch, the first gblk workgroups
+//   op:   gamma[r][k] <- gamma[r][k] * (1 - [SD[r] == k])
+// the others, node r:
+//   op+1: pure = [n^2 - sum_c tot_c^2 == 0]; split = isLeaf and not pure;
+//         F[base+r] <- F (1 - split); children F <- 2 - split.
+struct UpdateArgs { KCommon c; P6 SD, gamma, C, isLeaf, F, split; u64 n, base, dK; u32 d, K, CW, gblk; };
+__global__ __launch_bounds__(64) void k_update(UpdateArgs a)
+{
+    GT_EL_SHARED(3)
+    const u32 sn[3] = { 1, 2, 3 };
+    if (blockIdx.x < a.gblk) {
+        const u64 n = a.n * a.d;
+        for (u64 tile = blockIdx.x; tile < (n + GT_EL - 1) / GT_EL; tile += a.gblk) {
+            const u64 e0 = tile * GT_EL, e = e0 + W.t;
+            const bool act = W.t < GT_EL && e < n;
+            const u32 w = (u32)(e0 & 7) + W.t;
+            Sh v = { 0, 0 }, g = { 0, 0 };
+            if (act) { v = ld(a.SD, p, e / a.d) - pub(p, e % a.d); g = ld(a.gamma, p, e); }
+            T.deal(W, a.c.op, e0, sn, el_live(e0, n));
+            const Dealer D = T.dealer(W);
+            const Sh oh = b2a(W, p, eq_bit_mask(W, p, v, D, T.zb(W, 0, w), act), D, act);
+            const Sh z = mult_sh(W, g, pub(p, 1) - oh, T.za(W, 1, w), act);
+            if (act && W.real) st(a.gamma, p, e, z);
+            W.drain();
+        }
+    } else {
+        for (u64 tile = blockIdx.x - a.gblk; tile < (a.n + GT_EL - 1) / GT_EL; tile += gridDim.x - a.gblk) {
+            const u64 e0 = tile * GT_EL, r = e0 + W.t;
+            const bool act = W.t < GT_EL && r < a.n;
+            const u32 w = (u32)(e0 & 7) + W.t;
+            Sh n = { 0, 0 }, leaf = { 0, 0 }, f = { 0, 0 };
+            u64 dv = 0;
+            if (act) {
+                for (u32 cl = 0; cl < a.K; cl++) {
+                    const Sh tc = ld(a.C, p, r * a.CW + a.dK + cl);
+                    n = n + tc;
+                    dv -= prod3(tc, tc);
+                }
+                dv += prod3(n, n);
+                leaf = ld(a.isLeaf, p, r);
+                f = ld(a.F, p, a.base + r);
+            }
+            T.deal(W, a.c.op + 1, e0, sn, el_live(e0, a.n));
+            const Dealer D = T.dealer(W);
+            Sh d;
+            d.o = dv + T.za(W, 1, w);
+            d.n = W.reshare1(d.o, act ? 64u : 0u);
+            const u64 A = T.zb(W, 0, w);
+            const Sh npure = not_bit(p, eq_bit_mask(W, p, d, D, A, act));
+            const Sh sA = b2a(W, p, and_bit(W, leaf, npure, A >> 63, act), D, act);
+            const Sh keep = pub(p, 1) - sA;
+            const Sh fz = mult_sh(W, f, keep, T.za(W, 2, w), act);
+            if (act && W.real) {
+                st(a.split, p, r, sA);
+                st(a.F, p, a.base + r, fz);
+                const Sh ch = keep + pub(p, 1);
+                st(a.F, p, 2 * (a.base + r) + 1, ch);
+                st(a.F, p, 2 * (a.base + r) + 2, ch);
+            }
+            W.drain();
         }
     }
     W.flush(a.c.wire);
@@ -1546,26 +1624,22 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
 
 // add the zero sharing, reshare, accumulate into the node statistics
 struct CountFinArgs { KCommon c; u64 *Zacc; P6 C; u64 n; u32 ncol, CW; u64 colbase; };
-__global__ __launch_bounds__(192) void k_count_fin(CountFinArgs a)
+__global__ __launch_bounds__(64) void k_count_fin(CountFinArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 o = GT_ELEM();
-        const bool act = o < a.n;
-        Sh z;
+    GT_EL_SHARED(1)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, o = e0 + W.t, idx = (o / a.ncol) * a.CW + a.colbase + o % a.ncol;
+        const bool act = W.t < GT_EL && o < a.n;
+        const u32 s0[1] = { 0 };
+        Sh z, old = { 0, 0 };
         u64 part = 0;
-        if (act) { part = a.Zacc[(u64)p * a.n + o]; a.Zacc[(u64)p * a.n + o] = 0; }   // zero again for the next contraction
-        z.o = part + zero_a(K, a.c.op, 0, o);
+        if (act) { part = a.Zacc[(u64)p * a.n + o]; old = ld(a.C, p, idx); }
+        T.deal(W, a.c.op, e0, s0, 0);
+        if (act) a.Zacc[(u64)p * a.n + o] = 0;         // zero again for the next contraction
+        z.o = part + T.za(W, 0, (u32)(e0 & 7) + W.t);
         z.n = W.reshare1(z.o, act ? 64u : 0u);
-        if (act) {
-            const u64 idx = (o / a.ncol) * a.CW + a.colbase + o % a.ncol;
-            st(a.C, p, idx, ld(a.C, p, idx) + z);
-        }
+        if (act && W.real) st(a.C, p, idx, old + z);
+        W.drain();
     }
     W.flush(a.c.wire);
 }

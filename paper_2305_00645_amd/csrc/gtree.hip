@@ -50,7 +50,6 @@ struct gt_ctx {
     std::vector<int> ev_cls;
     gt_prof prof;
     DSh ws[5];                // inference workspace, grown on demand, kept between calls
-    DSh divrem;               // remainders of gt_div, grown on demand, kept between calls
     u64 *dacc;                // partial inner products of split equality grids
     size_t dacc_words;
     u64 *scratch_d;           // this device's copy of the static scratch array
@@ -98,7 +97,7 @@ struct gt_train {
     bool comps;
     size_t nblk, Lrows, Brows, Srows;// sample blocks of 32, row strides of the limb planes
     DSh M, T, F, C, Cn, gamma, Gn, isLeaf, SD, split;
-    DSh S, Q, quo, rem, val[2], idx[2], tval, best, lab;
+    DSh val[2], idx[2], tval, best;
     DSh Clast, Glast, Slast;
     u64 *Zacc;
 };
@@ -228,6 +227,8 @@ plain:
 }
 static dim3 g1(u64 n) { return dim3(blocks_for(n, 256)); }   // plain elementwise kernels
 static const dim3 B256(256);
+static dim3 gE(u64 n) { return dim3((unsigned)std::min<u64>((n + GT_EL - 1) / GT_EL, 1u << 16)); }   // element kernels: a wavefront per GT_EL elements
+static const dim3 B64(GT_LANES);
 static dim3 gT(u64 N, u64 w) { return dim3((unsigned)std::min<u64>(((N + 31) / 32) * ((w + 31) / 32), 65535), 1, 6); }  // k_transpose
 
 // ---------------------------------------------------------------------------------
@@ -286,7 +287,6 @@ extern "C" int gt_ctx_destroy(gt_ctx *c)
     (void)hipStreamSynchronize(c->stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     for (DSh &w : c->ws) dsh_free(w);
-    dsh_free(c->divrem);
     if (c->dacc) (void)hipFree(c->dacc);
     (void)hipFree(c->wire_d);
     (void)hipFree(c->keys_d);
@@ -379,8 +379,8 @@ extern "C" int gt_mult(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
 static int do_eq(gt_ctx *c, bool bool_out, P6 x, u64 xoff, const u64 *ypub, u64 ysub, P6 z, u64 n)
 {
     EqArgs a{}; a.c = kc(c, c->op++); a.x = x; a.xoff = xoff; a.ypub = ypub; a.ysub = ysub; a.z = z; a.n = n;
-    if (n) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, dim3(tiles(n)), GT_BLOCK, a)
-                          : launch(c, GT_KC_SMALL, k_eq<false>, dim3(tiles(n)), GT_BLOCK, a));
+    if (n) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, gE(n), B64, a)
+                          : launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a));
     acct_eq(c, n);
     if (!bool_out) acct_b2a(c, n);
     return GT_OK;
@@ -399,7 +399,7 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
     Timed T(c);
     GeArgs a{}; a.c = kc(c, c->op++); a.x = to_p6(x); a.y = to_p6(y); a.z = to_p6(z); a.n = n;
     int rc = GT_OK;
-    if (n) rc = launch(c, GT_KC_SMALL, k_ge, dim3(tiles(n)), GT_BLOCK, a);
+    if (n) rc = launch(c, GT_KC_SMALL, k_ge, gE(n), B64, a);
     acct_ge(c, n); acct_b2a(c, n);
     return T.finish(rc);
 }
@@ -468,7 +468,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         else if (mode == GM_COMMON) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1>, g, B1, a);
         else rc = launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1>, g, B1, a);
         GTCHK(rc);
-        if (a.dacc) GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, dim3(tiles8(a.N8)), GT_BLOCK, a));
+        if (a.dacc) GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, gE(a.N), B64, a));
     }
     acct_eq_grid(c, a.N, nel);
     if (has_g) acct_and1(c, nel);
@@ -502,27 +502,24 @@ extern "C" int gt_oaa_static(gt_ctx *c, const gt_shares *W, size_t w, const gt_s
     return T.finish(rc);
 }
 
-static int div_steps(gt_ctx *c, P6 S, P6 Q, P6 rem, P6 quo, u64 n)
-{
-    // tau+1 protocol steps, one operation id each, in one launch
-    DivArgs a{}; a.c = kc(c, c->op); a.S = S; a.Q = Q; a.r = rem; a.quo = quo; a.n = n; a.nsteps = c->tau + 1;
-    c->op += c->tau + 1;
-    if (n) GTCHK(launch(c, GT_KC_SMALL, k_div, dim3(tiles(n)), GT_BLOCK, a));
-    for (u32 t = 0; t <= c->tau; t++) { acct_ge(c, n); acct_b2a(c, n); acct_reshare(c, n, 1); }
-    return GT_OK;
-}
+// Divisions of up to this many elements run with four wavefronts per 20 elements, which deal the steps'
+// material side by side; above, the tiles alone fill the wavefront slots.
+// Scores of a level, 17 steps: up to 9,408 candidates' halves 29 us with four and about 65 with one; 18,816 (940 tiles,
+// the line) 68 us either way; 37,632 64 us with one.
+static bool few_elements(const gt_ctx *c, u64 n) { return (n + GT_EL - 1) / GT_EL <= c->resident; }
+
+static void acct_div(gt_ctx *c, u64 n) { for (u32 t = 0; t <= c->tau; t++) { acct_ge(c, n); acct_b2a(c, n); acct_reshare(c, n, 1); } }
 
 extern "C" int gt_div(gt_ctx *c, const gt_shares *S, const gt_shares *Q, size_t n, const gt_shares *q)
 {
     if (!c || !shares_ok(S, n) || !shares_ok(Q, n) || !shares_ok(q, n)) return GT_EINVAL;
     Timed T(c);
+    // tau+1 protocol steps, one operation id each, in one launch
+    DivArgs a{}; a.c = kc(c, c->op); a.S = to_p6(S); a.Q = to_p6(Q); a.quo = to_p6(q); a.n = n; a.nsteps = c->tau + 1;
+    c->op += c->tau + 1;
     int rc = GT_OK;
-    if (c->divrem.n < n) {                      // first use or a larger batch: grow the kept scratch
-        (void)hipStreamSynchronize(c->stream);
-        dsh_free(c->divrem);
-        rc = dsh_alloc(c->divrem, n, c->stream);
-    }
-    if (rc == GT_OK) rc = div_steps(c, to_p6(S), to_p6(Q), c->divrem.v, to_p6(q), n);
+    if (n) rc = few_elements(c, n) ? launch(c, GT_KC_SMALL, k_div<4>, gE(n), dim3(4 * GT_LANES), a) : launch(c, GT_KC_SMALL, k_div<1>, gE(n), B64, a);
+    acct_div(c, n);
     return T.finish(rc);
 }
 
@@ -534,8 +531,8 @@ static void train_free(gt_train *t)
     if (t->SQ) (void)hipFree(t->SQ);
     if (t->YQ) (void)hipFree(t->YQ);
     DSh *all[] = { &t->XT, &t->YT, &t->M, &t->T, &t->F, &t->C, &t->Cn, &t->gamma, &t->Gn, &t->isLeaf, &t->SD,
-                   &t->split, &t->S, &t->Q, &t->quo, &t->rem, &t->val[0], &t->val[1], &t->idx[0], &t->idx[1],
-                   &t->tval, &t->best, &t->lab, &t->Clast, &t->Glast, &t->Slast };
+                   &t->split, &t->val[0], &t->val[1], &t->idx[0], &t->idx[1],
+                   &t->tval, &t->best, &t->Clast, &t->Glast, &t->Slast };
     for (DSh *s : all) dsh_free(*s);
     if (t->Zacc) (void)hipFree(t->Zacc);
     if (t->hcp) (void)hipFree(t->hcp);
@@ -623,12 +620,12 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     t->hc_open = false; t->hcp = nullptr; t->literal = false; t->lit_acc = nullptr; t->part_matmul = false; t->lt_level = ~0u; t->OHL = nullptr;
     hipStream_t s = c->stream;
     int rc = GT_OK;
+    const size_t wide = P2 > GT_ARGMAX_LDS ? nmax : 0;          // the arg-max of fewer candidates stays in LDS
     struct { DSh *v; size_t n; } plan[] = {
         { &t->XT, d * N8 }, { &t->YT, K * N8 }, { &t->M, N }, { &t->T, nodes }, { &t->F, nodes },
         { &t->C, nmax * CW }, { &t->Cn, nmax * CW }, { &t->gamma, nmax * d }, { &t->Gn, nmax * d }, { &t->isLeaf, nmax },
-        { &t->SD, nmax }, { &t->split, nmax }, { &t->S, nmax * d * 2 }, { &t->Q, nmax * d * 2 },
-        { &t->quo, nmax * d * 2 }, { &t->rem, nmax * d * 2 }, { &t->val[0], nmax * P2 }, { &t->val[1], nmax * P2 },
-        { &t->idx[0], nmax * P2 }, { &t->idx[1], nmax * P2 }, { &t->tval, N }, { &t->best, nmax }, { &t->lab, nmax },
+        { &t->SD, nmax }, { &t->split, nmax }, { &t->val[0], wide * P2 }, { &t->val[1], wide * P2 },
+        { &t->idx[0], wide * P2 }, { &t->idx[1], wide * P2 }, { &t->tval, N }, { &t->best, nmax },
         { &t->Clast, nmax * CW }, { &t->Glast, nmax * d }, { &t->Slast, nmax * d },
     };
     for (auto &pl : plan) { rc = dsh_alloc(*pl.v, pl.n, s); if (rc != GT_OK) break; }
@@ -764,7 +761,9 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     const u64 wgs_per_chunk = (u64)(3 * (ncg2 + ncg1) + nns) * a.nrowgrp;
     u64 want_chunks = ((u64)c->resident + wgs_per_chunk - 1) / wgs_per_chunk;
     u64 cb = (t->nblk + want_chunks - 1) / want_chunks;
-    cb = std::max<u64>(8, std::min<u64>(CT_CHUNK_BLOCKS, cb));
+    // at least 8 blocks: the 64-bit atomic adds of a chunk's sums cost as much as a few (19,997 samples: 57 us a
+    // level with 8, 71 with 2); 2 where few samples leave the chain of a chunk's blocks (267: 9 us, 20 with 8)
+    cb = std::max<u64>(t->nblk <= 64 ? 2 : 8, std::min<u64>(CT_CHUNK_BLOCKS, cb));
     a.chunkblk = (u32)cb;
     a.nchunk = (u32)((t->nblk + cb - 1) / cb);
     if (nfull || narrow) {
@@ -778,53 +777,39 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
         GTCHK(launch(c, GT_KC_COUNT, k_count<1>, dim3(((a.nchunk + 7) / 8) * 3 * 8, 1, a.nrowgrp), B256, a));
     }
     CountFinArgs f{}; f.c = kc(c, op); f.Zacc = t->Zacc; f.C = t->C.v; f.n = nh * ncol; f.ncol = ncol; f.CW = t->CW; f.colbase = colbase;
-    GTCHK(launch(c, GT_KC_SMALL, k_count_fin, dim3(tiles(f.n)), GT_BLOCK, f));
+    GTCHK(launch(c, GT_KC_SMALL, k_count_fin, gE(f.n), B64, f));
     acct_reshare(c, nh * ncol, 1);
     return GT_OK;
 }
 
-static int select_max(gt_ctx *c, SelArgs a)
-{
-    a.c = kc(c, c->op++);
-    if (a.n) GTCHK(launch(c, GT_KC_SMALL, k_select_max, dim3(tiles(a.n)), GT_BLOCK, a));
-    acct_ge(c, a.n); acct_b2a(c, a.n); acct_reshare(c, a.n, 2);
-    return GT_OK;
-}
+static void acct_select(gt_ctx *c, u64 n) { acct_ge(c, n); acct_b2a(c, n); acct_reshare(c, n, 2); }
 
 static int heuristic(gt_ctx *c, gt_train *t, u32 h)
 {
     const u64 nh = (u64)1 << h, d = t->d, nq = nh * d * 2, ns = nh * d;
-    PrepArgs pa{}; pa.c = kc(c, c->op++); pa.C = t->C.v; pa.S = t->S.v; pa.Q = t->Q.v; pa.n = nq; pa.d = t->d; pa.K = t->K; pa.CW = t->CW;
-    GTCHK(launch(c, GT_KC_SMALL, k_score_prep, dim3(tiles(nq)), GT_BLOCK, pa));
+    ScoreArgs a{}; a.c = kc(c, c->op); a.C = t->C.v; a.gamma = t->gamma.v; a.score = t->Slast.v; a.n = nq; a.d = t->d; a.K = t->K; a.CW = t->CW; a.nsteps = c->tau + 1;
+    c->op += c->tau + 4;
+    GTCHK(few_elements(c, nq) ? launch(c, GT_KC_SMALL, k_score<4>, gE(nq), dim3(4 * GT_LANES), a) : launch(c, GT_KC_SMALL, k_score<1>, gE(nq), B64, a));
     acct_reshare(c, nq, 2);
-    // empty branch: make the divisor 1
-    DSh &z = t->rem;    // scratch for the 0/1 sharing of [Q == 0]
-    GTCHK(do_eq(c, false, t->Q.v, 0, nullptr, 0, z.v, nq));
-    GTCHK(launch(c, GT_KC_LOCAL, k_add_inplace, g1(nq), B256, t->Q.v, z.v, nq));
-    GTCHK(div_steps(c, t->S.v, t->Q.v, t->rem.v, t->quo.v, nq));
-    GTCHK(launch(c, GT_KC_LOCAL, k_iota, g1(nh * t->P2), B256, t->idx[0].v, t->val[0].v, (u32)nh, t->P2, t->d));
-    MaskArgs ma{}; ma.c = kc(c, c->op++); ma.quo = t->quo.v; ma.gamma = t->gamma.v; ma.score = t->Slast.v; ma.val = t->val[0].v; ma.n = ns; ma.d = t->d; ma.P2 = t->P2;
-    GTCHK(launch(c, GT_KC_SMALL, k_mask_score, dim3(tiles(ns)), GT_BLOCK, ma));
+    acct_eq(c, nq); acct_b2a(c, nq);
+    acct_div(c, nq);
     acct_reshare(c, ns, 1);
-    int cur = 0;
-    for (u64 len = t->P2; len > 1; len /= 2) {
-        SelArgs sa{}; sa.vin = t->val[cur].v; sa.iin = t->idx[cur].v; sa.vout = t->val[cur ^ 1].v; sa.iout = t->idx[cur ^ 1].v;
-        sa.n = nh * (len / 2); sa.len = (u32)len; sa.mode = 0;
-        GTCHK(select_max(c, sa));
-        cur ^= 1;
-    }
-    return copy6(c, t->SD.v, 0, t->idx[cur].v, 0, 1, nh);
+    ArgmaxArgs m{}; m.c = kc(c, c->op); m.score = t->Slast.v; m.SD = t->SD.v; m.nh = (u32)nh; m.d = t->d; m.P2 = t->P2;
+    for (int x = 0; x < 2; x++) { m.val[x] = t->val[x].v; m.idx[x] = t->idx[x].v; }
+    GTCHK(launch(c, GT_KC_SMALL, k_argmax, dim3((unsigned)std::min<u64>(nh, 4096)), dim3(GT_LANES * GT_ARGMAX_WAVES), m));
+    for (u64 len = t->P2; len > 1; len /= 2) { c->op++; acct_select(c, nh * (len / 2)); }
+    return GT_OK;
 }
 
 static int update_flags(gt_ctx *c, gt_train *t, u32 h)
 {
     const u64 nh = (u64)1 << h, base = nh - 1, d = t->d;
-    GammaArgs ga{}; ga.c = kc(c, c->op++); ga.SD = t->SD.v; ga.gamma = t->gamma.v; ga.n = nh * d; ga.d = t->d;
-    GTCHK(launch(c, GT_KC_SMALL, k_gamma, dim3(tiles(ga.n)), GT_BLOCK, ga));
+    UpdateArgs a{}; a.c = kc(c, c->op); c->op += 2;
+    a.SD = t->SD.v; a.gamma = t->gamma.v; a.C = t->C.v; a.isLeaf = t->isLeaf.v; a.F = t->F.v; a.split = t->split.v;
+    a.n = nh; a.base = base; a.d = t->d; a.K = t->K; a.CW = t->CW; a.dK = (u64)t->d * t->K;
+    a.gblk = gE(nh * d).x;
+    GTCHK(launch(c, GT_KC_SMALL, k_update, dim3(a.gblk + gE(nh).x), B64, a));
     acct_eq(c, nh * d); acct_b2a(c, nh * d); acct_reshare(c, nh * d, 1);
-    SplitArgs sa{}; sa.c = kc(c, c->op++); sa.C = t->C.v; sa.isLeaf = t->isLeaf.v; sa.F = t->F.v; sa.split = t->split.v;
-    sa.n = nh; sa.base = base; sa.K = t->K; sa.CW = t->CW; sa.dK = (u64)t->d * t->K;
-    GTCHK(launch(c, GT_KC_SMALL, k_split, dim3(tiles(nh)), GT_BLOCK, sa));
     acct_reshare(c, nh, 1); acct_eq(c, nh); acct_and1(c, nh); acct_b2a(c, nh); acct_reshare(c, nh, 1);
     return GT_OK;
 }
@@ -858,20 +843,18 @@ static int heuristic_open(gt_ctx *c, gt_train *t, u32 h)
 static int node_split(gt_ctx *c, gt_train *t, u32 h)
 {
     const u64 nh = (u64)1 << h, base = nh - 1, d = t->d, CW = t->CW;
-    // keep this level's statistics and flags for export; T takes the split decisions
-    GTCHK(copy6(c, t->Clast.v, 0, t->C.v, 0, 1, nh * CW));
-    GTCHK(copy6(c, t->Glast.v, 0, t->gamma.v, 0, 1, nh * d));
-    GTCHK(copy6(c, t->T.v, base, t->SD.v, 0, 1, nh));
+    // keep this level's statistics and flags for export; T takes the split decisions; gamma is always inherited
+    const bool dup = h + 1 <= t->H && 2 * nh <= ((u64)1 << t->H);
+    KeepArgs k{}; k.C = t->C.v; k.Clast = t->Clast.v; k.gamma = t->gamma.v; k.Glast = t->Glast.v; k.SD = t->SD.v; k.T = t->T.v; k.Gn = t->Gn.v;
+    k.nC = nh * CW; k.nG = nh * d; k.nh = nh; k.base = base; k.ndup = dup ? nh * d : 0; k.d = t->d;
+    GTCHK(launch(c, GT_KC_LOCAL, k_keep, dim3(g1(nh * CW).x, 4), B256, k));
     t->last = h;
-    // children: statistics inherited unless the node was split; gamma always inherited
+    // children: statistics inherited unless the node was split
     MultArgs m{}; m.x = t->C.v; m.y = t->split.v; m.z = t->Cn.v; m.n = nh * CW; m.CW = t->CW;
     GTCHK(do_mult(c, 2, m));
     acct_reshare(c, nh * CW, 1);
     std::swap(t->C, t->Cn);
-    if (h + 1 <= t->H && 2 * nh <= ((u64)1 << t->H)) {
-        GTCHK(launch(c, GT_KC_LOCAL, k_dup_rows, g1(nh * d), B256, t->Gn.v, t->gamma.v, nh, d));
-        std::swap(t->gamma, t->Gn);
-    }
+    if (dup) std::swap(t->gamma, t->Gn);
     return GT_OK;
 }
 
@@ -1019,15 +1002,13 @@ extern "C" int gt_train_finish(gt_ctx *c, gt_train *t, gt_tree **out)
         if (rc == GT_OK) rc = leaf_onehot(c, t, H);
         if (rc == GT_OK) rc = count(c, t, H, true);
     }
-    // label = first maximum of the class totals
-    if (rc == GT_OK) rc = copy6(c, t->best.v, 0, t->C.v, dK, t->CW, nh);
-    if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_fill_const, g1(nh), B256, t->lab.v, (u64)0, nh, (u64)0);
-    for (u32 cl = 1; cl < t->K && rc == GT_OK; cl++) {
-        SelArgs sa{}; sa.vin = t->best.v; sa.iin = t->lab.v; sa.vout = t->best.v; sa.iout = t->lab.v; sa.C = t->C.v;
-        sa.n = nh; sa.CW = t->CW; sa.coff = dK + cl; sa.cidx = cl; sa.mode = 1;
-        rc = select_max(c, sa);
+    // label = first maximum of the class totals, into the last level of T
+    if (rc == GT_OK) {
+        LabelArgs la{}; la.c = kc(c, c->op); la.C = t->C.v; la.lab = t->T.v; la.n = nh; la.dK = dK; la.laboff = base; la.K = t->K; la.CW = t->CW;
+        c->op += t->K - 1;
+        rc = launch(c, GT_KC_SMALL, k_labels, gE(nh), B64, la);
+        for (u32 cl = 1; cl < t->K; cl++) acct_select(c, nh);
     }
-    if (rc == GT_OK) rc = copy6(c, t->T.v, base, t->lab.v, 0, 1, nh);
     if (rc == GT_OK) rc = copy6(c, t->Clast.v, 0, t->C.v, 0, 1, nh * t->CW);
     gt_tree *tr = nullptr;
     if (rc == GT_OK) {

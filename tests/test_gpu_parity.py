@@ -172,6 +172,34 @@ def test_div(mods, seed, tau):
     same_stats(o, g)
 
 
+@pytest.mark.parametrize("w,n", [(1, 167), (3, 168), (7, 169), (300, 8), (41, 168 * 13 + 1)])
+def test_oaa_at_tile_edges(mods, seed, w, n):
+    """Tiles of 21 groups of 8 rows: one row short, full, one over; one group and many columns
+    (every column range a wavefront of its own); many tiles with split columns."""
+    o, g = pair(mods, seed)
+    rng = np.random.default_rng(w + n)
+    Wp = rng.integers(0, M64, size=w, dtype=np.uint64)
+    u = rng.integers(0, w + 2, size=n).astype(np.uint64)
+    same(g.oaa(g.share_a(Wp), g.share_a(u)), o.oaa(o.share(Wp), o.share(u)), "oaa")
+    same_stats(o, g)
+
+
+@pytest.mark.parametrize("n", [1, 19, 20, 21, 41, 20480, 20501])
+def test_element_kernels_at_tile_edges(mods, seed, n):
+    """Tiles of 20 elements whose mask words come from three blocks: short, full and over; for the
+    division also the line between four wavefronts per tile and one."""
+    o, g = pair(mods, seed, tau=4)
+    rng = np.random.default_rng(n)
+    x = rng.integers(0, 1 << 39, size=n).astype(np.uint64)
+    y = np.where(rng.random(n) < 0.4, x, rng.integers(0, 1 << 39, size=n).astype(np.uint64))
+    S, Q = np.minimum(x, y), np.maximum(x, y) + np.uint64(1)
+    xo, yo, xg, yg = o.share(x), o.share(y), g.share_a(x), g.share_a(y)
+    same(g.eq_a(xg, y), o.eq_a(xo, y), "eq")
+    same(g.ge_a(xg, yg), o.ge_a(xo, yo), "ge")
+    same(g.div(g.share_a(S), g.share_a(Q)), o.div(o.share(S), o.share(Q)), "div")
+    same_stats(o, g)
+
+
 # ------------------------------------------------------------------ training
 def run_train_pair(mods, seed, w, tau=16, H=None, every_level=True):
     from oracle import X_T, X_F, X_M, X_C, X_GAMMA, X_SD, X_L, X_SCORE, X_C_PAPER
@@ -313,6 +341,18 @@ def test_train_operand_layouts(mods, seed, H, literal):
         for what in (X_M, X_C, X_SD):
             same(g.train_export(what), o.train_export(what), "level %d" % h)
     same_stats(o, g)
+
+
+@pytest.mark.parametrize("N,d,K,H", [(30, 1, 2, 2), (25, 2, 3, 2), (21, 512, 2, 1), (21, 513, 2, 2), (20, 1300, 2, 4)])
+def test_train_argmax_widths(mods, seed, N, d, K, H):
+    """The tournament of a node: one candidate (no round), one pair, the widest that stays in LDS, the
+    narrowest that does not, and levels whose scores are on either side of the line between four
+    wavefronts per tile and one."""
+    rng = np.random.default_rng(d)
+    X = (rng.random((N, d)) < 0.5).astype(np.uint64)
+    y = (X[:, 0].astype(np.int64) + X[:, d // 2].astype(np.int64)) % K
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=6)
 
 
 def test_train_deep_tree_few_samples(mods, seed):
