@@ -1420,7 +1420,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // nns: slots per chunk (0 = none) for one more column group of at most 16 columns (first column
 // nbcol0 of B, column nzcol0 of the output), handled by the same launch with 16-wide tiles; X, Y: its
 // operands (x per component, y as (own+next, own) per party), xcols: x holds the columns and y the nodes
-struct CountArgs { LimbSet A, B; LimbTri X; LimbSet Y; int xcols; u64 nblk; u32 nh, ncol; u64 bcol0; u32 zcol0; u64 *Zacc; u32 nchunk, nrowgrp, ncg, rt, chunkblk, ncoltiles;   // ncoltiles: column tiles of 32*NB in this launch
+struct CountArgs { LimbSet A, B; LimbTri X; LimbSet Y; int xcols; u64 nblk; u32 nh, ncol; u64 bcol0; u32 zcol0; u64 *Zacc; u32 nchunk, nrowgrp, nwide, rt, chunkblk, ncoltiles;   // ncoltiles: column tiles of 32*NB in this launch; nwide: slots per chunk that they take
                    u32 nns; u64 nbcol0; u32 nzcol0; };
 
 // A remainder of at most 16 columns (the class totals): 16 rows of x per wavefront with
@@ -1521,21 +1521,26 @@ __device__ __forceinline__ void count_narrow(const CountArgs &a, u64 x0, u32 nx,
 template <int NB>
 __global__ __launch_bounds__(256) void k_count(CountArgs a)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // Workgroups go round-robin to the 8 XCDs, each with its own L2.  The column groups of
     // one sample chunk, of all three parties, read the same rows of the three components of
     // L, so they are given consecutive slots of the same XCD: id = slot*8 + xcd; per chunk
-    // 3*ncg wide slots (party-major) and nns narrow ones.
-    const u32 per = 3 * a.ncg + a.nns, id = blockIdx.x, xcd = id & 7, slot = id >> 3;
+    // nwide wide slots and nns narrow ones.  The column tiles of the three parties are dealt out to the
+    // wavefronts of the wide slots one after the other (with a slot per party and group of tiles, nine
+    // tiles of 64 columns left a quarter of the wavefronts without work), the three parties of a tile
+    // side by side where x holds the columns (each component of a tile is read by two of them), party
+    // by party otherwise.
+    const u32 per = a.nwide + a.nns, id = blockIdx.x, xcd = id & 7, slot = id >> 3;
     const u32 sl = slot % per, chunk = (slot / per) * 8 + xcd;
     if (chunk >= a.nchunk) return;                            // whole workgroup, no barrier in this kernel
     const u64 ib0 = (u64)chunk * a.chunkblk;
     const u64 ib1 = ib0 + a.chunkblk < a.nblk ? ib0 + a.chunkblk : a.nblk;
     const u32 rg = blockIdx.z;
-    if (sl >= 3 * a.ncg) {
+    if (sl >= a.nwide) {
         // a narrow slot of this chunk: its workgroups of 4 wavefronts share out the nodes, 16 rows of x
         // (each tile for all three parties) or, where x holds the columns, 8 rows of y per wavefront
-        const u64 wv = ((u64)(sl - 3 * a.ncg) * a.nrowgrp + rg) * 4 + wave;
+        const u64 wv = ((u64)(sl - a.nwide) * a.nrowgrp + rg) * 4 + wave;
         const u32 nreal = a.ncol - a.nzcol0;
         if (a.xcols) {
             if (wv * 8 < a.nh) count_narrow(a, a.nbcol0, nreal, wv * 8, wv * 8 + 8 < a.nh ? wv * 8 + 8 : a.nh, ib0, ib1, lane);
@@ -1545,17 +1550,16 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
         }
         return;
     }
-    const int p = sl / a.ncg;
-    const u32 cg = sl % a.ncg;
-    const u32 wr = wave % a.rt, wc = wave / a.rt, cper = 4 / a.rt;   // this wavefront's row / column tile
+    const u32 wr = wave % a.rt, task = sl * (4 / a.rt) + wave / a.rt;   // this wavefront's row tile, party and column tile
+    if (task >= 3 * a.ncoltiles) return;                      // whole wavefront
+    const int p = a.xcols ? task % 3 : task / a.ncoltiles;
     const u64 r0 = ((u64)rg * a.rt + wr) * 32;
     if (r0 >= a.nh) return;                                   // whole wavefront
     const LimbMat LA0 = p == 0 ? a.A.m[0][0] : (p == 1 ? a.A.m[1][0] : a.A.m[2][0]);
     const LimbMat LA1 = p == 0 ? a.A.m[0][1] : (p == 1 ? a.A.m[1][1] : a.A.m[2][1]);
     const LimbMat LB0 = p == 0 ? a.B.m[0][0] : (p == 1 ? a.B.m[1][0] : a.B.m[2][0]);
     const LimbMat LB1 = p == 0 ? a.B.m[0][1] : (p == 1 ? a.B.m[1][1] : a.B.m[2][1]);
-    const u64 ctile = (u64)cg * cper + wc;                   // column tile of 32*NB
-    if (ctile >= a.ncoltiles) return;                         // whole wavefront
+    const u64 ctile = a.xcols ? task / 3 : task % a.ncoltiles;   // column tile of 32*NB
     const u64 c0 = a.bcol0 + ctile * (32 * NB);
     const u32 lr = lane & 31;
     v16i acc[8][NB];

@@ -752,29 +752,32 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     // (a remainder of at most 16 columns with no full group beside it - the class totals of the
     // label level - runs on the 16-wide tiles alone)
     const u32 narrow = (rem && rem <= 16) ? 1 : 0;
-    const u32 ncg2 = (nfull + cper - 1) / cper, ncg1 = (rem && rem <= 32 && !narrow) ? 1 : 0;
+    const u32 nw2 = (3 * nfull + cper - 1) / cper, nw1 = (rem && rem <= 32 && !narrow) ? (3 + cper - 1) / cper : 0;
     // narrow slots per chunk: a workgroup of the narrow group covers 64 nodes (4 tiles of 16, all parties), 32 where x holds the columns
     const u64 nper = (a.xcols ? 32ull : 64ull) * a.nrowgrp;   // nodes that one narrow slot covers
     const u32 nns = narrow ? (u32)((nh + nper - 1) / nper) : 0;
-    // sample chunk per workgroup: at most CT_CHUNK_BLOCKS blocks, shorter when that is needed to
-    // give every compute unit several workgroups
-    const u64 wgs_per_chunk = (u64)(3 * (ncg2 + ncg1) + nns) * a.nrowgrp;
-    u64 want_chunks = ((u64)c->resident + wgs_per_chunk - 1) / wgs_per_chunk;
-    u64 cb = (t->nblk + want_chunks - 1) / want_chunks;
-    // at least 8 blocks: the 64-bit atomic adds of a chunk's sums cost as much as a few (19,997 samples: 57 us a
-    // level with 8, 71 with 2); 2 where few samples leave the chain of a chunk's blocks (267: 9 us, 20 with 8)
-    cb = std::max<u64>(t->nblk <= 64 ? 2 : 8, std::min<u64>(CT_CHUNK_BLOCKS, cb));
+    // Sample chunk per workgroup, at most CT_CHUNK_BLOCKS blocks.  A workgroup (of 512 registers per lane) has a
+    // compute unit to itself and chunks go round-robin to the 8 XCDs: the length that minimises the fillings of
+    // an XCD's compute units times (length + 4), where 4 blocks stand for the first fetch and the atomic adds of
+    // a chunk's sums.  At least 8 blocks (19,997 samples: 57 us a level with 8, 71 with 2), 2 where few samples
+    // leave the chain of a chunk's blocks (267: 9 us, 20 with 8).
+    const u64 wgs_per_chunk = (u64)(nw2 + nw1 + nns) * a.nrowgrp, per_xcd = c->resident / 32;
+    u64 cb = CT_CHUNK_BLOCKS, best = ~(u64)0;
+    for (u64 q = t->nblk <= 64 ? 2 : 8; q <= CT_CHUNK_BLOCKS; q++) {
+        const u64 per = ((t->nblk + q - 1) / q + 7) / 8 * wgs_per_chunk, cost = (per + per_xcd - 1) / per_xcd * (q + 4);
+        if (cost < best) { best = cost; cb = q; }
+    }
     a.chunkblk = (u32)cb;
     a.nchunk = (u32)((t->nblk + cb - 1) / cb);
     if (nfull || narrow) {
-        a.ncg = ncg2; a.ncoltiles = nfull; a.bcol0 = bcol; a.zcol0 = 0;
+        a.nwide = nw2; a.ncoltiles = nfull; a.bcol0 = bcol; a.zcol0 = 0;
         a.nns = nns; a.nbcol0 = bcol + (u64)nfull * 64; a.nzcol0 = nfull * 64;
-        GTCHK(launch(c, GT_KC_COUNT, k_count<2>, dim3(((a.nchunk + 7) / 8) * (3 * a.ncg + nns) * 8, 1, a.nrowgrp), B256, a));
+        GTCHK(launch(c, GT_KC_COUNT, k_count<2>, dim3(((a.nchunk + 7) / 8) * (nw2 + nns) * 8, 1, a.nrowgrp), B256, a));
     }
-    if (ncg1) {
+    if (nw1) {
         a.nns = 0;
-        a.ncg = 1; a.ncoltiles = 1; a.bcol0 = bcol + (u64)nfull * 64; a.zcol0 = nfull * 64;
-        GTCHK(launch(c, GT_KC_COUNT, k_count<1>, dim3(((a.nchunk + 7) / 8) * 3 * 8, 1, a.nrowgrp), B256, a));
+        a.nwide = nw1; a.ncoltiles = 1; a.bcol0 = bcol + (u64)nfull * 64; a.zcol0 = nfull * 64;
+        GTCHK(launch(c, GT_KC_COUNT, k_count<1>, dim3(((a.nchunk + 7) / 8) * nw1 * 8, 1, a.nrowgrp), B256, a));
     }
     CountFinArgs f{}; f.c = kc(c, op); f.Zacc = t->Zacc; f.C = t->C.v; f.n = nh * ncol; f.ncol = ncol; f.CW = t->CW; f.colbase = colbase;
     GTCHK(launch(c, GT_KC_SMALL, k_count_fin, gE(f.n), B64, f));
