@@ -38,18 +38,15 @@ __device__ __forceinline__ void tr_put(u64 *tr, u32 lane, const u64 (&w)[8])
 __device__ __forceinline__ u64 tr_get(const u64 *tr, u32 lane, int j) { return tr[(lane & 7) * 72 + 8 * j + (lane >> 3)]; }
 
 // Share^A (Sec. II-B): x1, x2 from the owner's key (streams 0 and 1), x3 = x - x1 - x2.
-// key: whose randomness shares the values (the data owner / query user, or the scorer of the
-// heuristic by reconstruction, who uses the dealer's key); off: first element of `out`.
 // Bound: memory (one word read, six written).  2^24 words: 1.30 ms when every lane stored its own
 // 8 consecutive words (a line per lane and instruction), 0.19 ms now (5.0 TB/s).
-__global__ __launch_bounds__(256) void k_share(const u32 *keys, int key, u32 op, const u64 *plain, u64 n, P6 out, u64 off)
+// put(e, a, b, x3) stores the three components of element e.
+template <class F>
+__device__ __forceinline__ void share_tiles(const u32 *keys, int key, u32 op, const u64 *plain, u64 n, u64 *ta, u64 *tb, F put)
 {
-    __shared__ u64 s_tr[4][2][GT_TR_WORDS];
     const Key ko = load_key(keys, key);
     const u32 lane = threadIdx.x & (GT_LANES - 1), wave = threadIdx.x / GT_LANES;
-    u64 *ta = s_tr[wave][0], *tb = s_tr[wave][1];
-    const u64 ntile = (n + 511) / 512;
-    for (u64 t = (u64)blockIdx.x * 4 + wave; t < ntile; t += (u64)gridDim.x * 4) {
+    for (u64 t = (u64)blockIdx.x * 4 + wave; t < (n + 511) / 512; t += (u64)gridDim.x * 4) {
         u64 w[8];
         wave_sync();
         chacha8(ko, t * GT_LANES + lane, op, 0, w);
@@ -60,14 +57,39 @@ __global__ __launch_bounds__(256) void k_share(const u32 *keys, int key, u32 op,
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             const u64 e = t * 512 + j * GT_LANES + lane, a = tr_get(ta, lane, j), b = tr_get(tb, lane, j);
-            if (e < n) {
-                const u64 x3 = plain[e] - a - b;
-                out.o[0][off + e] = a;  out.n[0][off + e] = b;
-                out.o[1][off + e] = b;  out.n[1][off + e] = x3;
-                out.o[2][off + e] = x3; out.n[2][off + e] = a;
-            }
+            if (e < n) put(e, a, b, plain[e] - a - b);
         }
     }
+}
+__device__ __forceinline__ void put_share(const P6 &out, u64 e, u64 a, u64 b, u64 x3)
+{
+    out.o[0][e] = a;  out.n[0][e] = b;
+    out.o[1][e] = b;  out.n[1][e] = x3;
+    out.o[2][e] = x3; out.n[2][e] = a;
+}
+// the data owner's / query user's role
+__global__ __launch_bounds__(256) void k_share(const u32 *keys, u32 op, const u64 *plain, u64 n, P6 out)
+{
+    __shared__ u64 s_tr[4][2][GT_TR_WORDS];
+    const u32 wave = threadIdx.x / GT_LANES;
+    share_tiles(keys, GT_KEY_OWNER, op, plain, n, s_tr[wave][0], s_tr[wave][1], [&](u64 e, u64 a, u64 b, u64 x3) { put_share(out, e, a, b, x3); });
+}
+
+// The six sharings that the scorer of the heuristic by reconstruction hands back, one launch:
+// blockIdx.y = which (operation op + which), under the dealer's key; `off` the first element of
+// `out`.  The fourth, the children's node type, goes to both children of a node.  (Six launches and a
+// copy before: 34 us a level.)
+struct ShareBackArgs { const u32 *keys; u32 op; const u64 *plain[6]; u64 n[6], off[6]; P6 out[6]; };
+__global__ __launch_bounds__(256) void k_share_back(ShareBackArgs a)
+{
+    __shared__ u64 s_tr[4][2][GT_TR_WORDS];
+    const u32 wave = threadIdx.x / GT_LANES, q = blockIdx.y;
+    const P6 &out = a.out[q];
+    const u64 off = a.off[q];
+    share_tiles(a.keys, GT_KEY_DEALER, a.op + q, a.plain[q], a.n[q], s_tr[wave][0], s_tr[wave][1], [&](u64 e, u64 x, u64 y, u64 z) {
+        if (q == 3) { put_share(out, 2 * (off + e) + 1, x, y, z); put_share(out, 2 * (off + e) + 2, x, y, z); }
+        else put_share(out, off + e, x, y, z);
+    });
 }
 
 // Rec^A: party 0 adds its two components and the one it receives from party 2.
@@ -136,6 +158,21 @@ __global__ __launch_bounds__(256) void k_fill_const(P6 dst, u64 off, u64 n, u64 
             dst.o[j][off + e] = j == 0 ? c : 0;
             dst.n[j][off + e] = j == 2 ? c : 0;
         }
+}
+
+// the state a training starts from, one launch (blockIdx.y): M, T, C := 0; F := 0, the root a leaf (1);
+// gamma of the root := 1
+struct StartArgs { P6 M, T, F, C, gamma; u64 N, nodes, nC, d; };
+__global__ __launch_bounds__(256) void k_start(StartArgs a)
+{
+    const u32 what = blockIdx.y;
+    const u64 n = what == 0 ? a.N : (what == 3 ? a.nC : (what == 4 ? a.d : a.nodes));
+    const P6 &dst = what == 0 ? a.M : (what == 1 ? a.T : (what == 2 ? a.F : (what == 3 ? a.C : a.gamma)));
+    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
+        const u64 c = what == 4 || (what == 2 && e == 0) ? 1 : 0;
+#pragma unroll
+        for (int j = 0; j < 3; j++) { dst.o[j][e] = j == 0 ? c : 0; dst.n[j][e] = j == 2 ? c : 0; }
+    }
 }
 
 // plain words := c
@@ -1383,16 +1420,6 @@ __global__ __launch_bounds__(256) void k_hc_open(HcOpenArgs a)
         }
         __syncthreads();
     }
-}
-
-// F of both children of node r := the sharing of node r in src
-__global__ __launch_bounds__(256) void k_children(P6 F, P6 src, u64 base, u64 nh)
-{
-    for (u64 r = (u64)blockIdx.x * blockDim.x + threadIdx.x; r < nh; r += (u64)gridDim.x * blockDim.x)
-        for (int j = 0; j < 3; j++) {
-            F.o[j][2 * (base + r) + 1] = F.o[j][2 * (base + r) + 2] = src.o[j][r];
-            F.n[j][2 * (base + r) + 1] = F.n[j][2 * (base + r) + 2] = src.n[j][r];
-        }
 }
 
 // ---------------------------------------------------------------------------------

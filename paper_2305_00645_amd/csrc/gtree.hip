@@ -92,12 +92,12 @@ struct gt_train {
     DSh XT, YT;                      // [k][i], [c][i]: sample-contiguous copies of the inputs
     // limb tiles: leaf one-hot (one matrix per component); columns, (own+next, own) per party or, with comps,
     // once per component, and then the sums own+next of the leaf one-hot (levels before the last) in SQ and the
-    // class columns in both forms in YQ
+    // class columns in both forms in YQ; all in the allocation that LQ begins
     unsigned char *LQ, *BQ, *SQ, *YQ;
     bool comps;
     size_t nblk, Lrows, Brows, Srows;// sample blocks of 32, row strides of the limb planes
     DSh M, T, F, C, Cn, gamma, Gn, isLeaf, SD, split;
-    DSh val[2], idx[2], tval, best;
+    DSh val[2], idx[2], tval;
     DSh Clast, Glast, Slast;
     u64 *Zacc;
 };
@@ -335,7 +335,7 @@ extern "C" int gt_share_a(gt_ctx *c, const uint64_t *plain, size_t n, const gt_s
     Timed T(c);
     u32 op = c->op++;
     int rc = GT_OK;
-    if (n) rc = launch(c, GT_KC_SHARE, k_share, g1((n + 7) / 8), B256, (const u32 *)c->keys_d, (int)GT_KEY_OWNER, op, plain, (u64)n, to_p6(out), (u64)0);
+    if (n) rc = launch(c, GT_KC_SHARE, k_share, g1((n + 7) / 8), B256, (const u32 *)c->keys_d, op, plain, (u64)n, to_p6(out));
     return T.finish(rc);
 }
 
@@ -527,12 +527,9 @@ extern "C" int gt_div(gt_ctx *c, const gt_shares *S, const gt_shares *Q, size_t 
 static void train_free(gt_train *t)
 {
     if (t->LQ) (void)hipFree(t->LQ);
-    if (t->BQ) (void)hipFree(t->BQ);
-    if (t->SQ) (void)hipFree(t->SQ);
-    if (t->YQ) (void)hipFree(t->YQ);
     DSh *all[] = { &t->XT, &t->YT, &t->M, &t->T, &t->F, &t->C, &t->Cn, &t->gamma, &t->Gn, &t->isLeaf, &t->SD,
                    &t->split, &t->val[0], &t->val[1], &t->idx[0], &t->idx[1],
-                   &t->tval, &t->best, &t->Clast, &t->Glast, &t->Slast };
+                   &t->tval, &t->Clast, &t->Glast, &t->Slast };
     for (DSh *s : all) dsh_free(*s);
     if (t->Zacc) (void)hipFree(t->Zacc);
     if (t->hcp) (void)hipFree(t->hcp);
@@ -594,12 +591,9 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     acct_reshare(c, (u64)N * d * K, 1);
     GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1((N8 / 8) * K), B256, t->YT.v, limbs_Y(t), t->comps ? limbs_C(t) : LimbTri{}, (int)t->comps, (u64)N, (u64)N8, K, (u64)d * K));
     // M = 0, T = 0, the root is a leaf with empty statistics, no candidate used yet
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(N), B256, t->M.v, (u64)0, (u64)N, (u64)0));
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(nodes), B256, t->T.v, (u64)0, (u64)nodes, (u64)0));
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(nodes), B256, t->F.v, (u64)0, (u64)nodes, (u64)0));
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(nmax * t->CW), B256, t->C.v, (u64)0, (u64)(nmax * t->CW), (u64)0));
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, dim3(1), B256, t->F.v, (u64)0, (u64)1, (u64)1));
-    GTCHK(launch(c, GT_KC_LOCAL, k_fill_const, g1(d), B256, t->gamma.v, (u64)0, (u64)d, (u64)1));
+    StartArgs st{}; st.M = t->M.v; st.T = t->T.v; st.F = t->F.v; st.C = t->C.v; st.gamma = t->gamma.v;
+    st.N = N; st.nodes = nodes; st.nC = nmax * t->CW; st.d = d;
+    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>(N, nmax * t->CW)).x, 5), B256, st));
     t->level = 0; t->last = 0; t->finished = false; t->fresh_import = false; t->lt_level = ~0u;
     return GT_OK;
 }
@@ -625,10 +619,10 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         { &t->XT, d * N8 }, { &t->YT, K * N8 }, { &t->M, N }, { &t->T, nodes }, { &t->F, nodes },
         { &t->C, nmax * CW }, { &t->Cn, nmax * CW }, { &t->gamma, nmax * d }, { &t->Gn, nmax * d }, { &t->isLeaf, nmax },
         { &t->SD, nmax }, { &t->split, nmax }, { &t->val[0], wide * P2 }, { &t->val[1], wide * P2 },
-        { &t->idx[0], wide * P2 }, { &t->idx[1], wide * P2 }, { &t->tval, N }, { &t->best, nmax },
+        { &t->idx[0], wide * P2 }, { &t->idx[1], wide * P2 }, { &t->tval, N },
         { &t->Clast, nmax * CW }, { &t->Glast, nmax * d }, { &t->Slast, nmax * d },
     };
-    for (auto &pl : plan) { rc = dsh_alloc(*pl.v, pl.n, s); if (rc != GT_OK) break; }
+    for (auto &pl : plan) { rc = pl.n ? dsh_alloc(*pl.v, pl.n, s) : GT_OK; if (rc != GT_OK) break; }
     if (rc == GT_OK) {
         t->slot = new (std::nothrow) TreeSlot();
         if (!t->slot) rc = GT_ENOMEM;
@@ -646,13 +640,12 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     t->Srows = H ? std::max<size_t>(32, (nmax / 2 + 31) / 32 * 32) : 0;
     t->comps = 3 * t->Srows + 3 * t->Brows + 6 * GT_YROWS <= 6 * t->Brows;
     const size_t rowb = t->nblk * 8 * 32;
-    struct { unsigned char **v; size_t bytes; } tiles_of[] = {
-        { &t->LQ, 3 * t->Lrows * rowb }, { &t->BQ, (t->comps ? 3 : 6) * t->Brows * rowb },
-        { &t->SQ, t->comps ? 3 * t->Srows * rowb : 0 }, { &t->YQ, t->comps ? 6 * GT_YROWS * rowb : 0 } };
-    for (auto &q : tiles_of) {
-        if (rc != GT_OK || !q.bytes) continue;
-        if (hipMalloc(q.v, q.bytes) != hipSuccess) { *q.v = nullptr; rc = GT_ENOMEM; }
-        else if (hipMemsetAsync(*q.v, 0, q.bytes, s) != hipSuccess) rc = GT_EHIP;
+    // one allocation; planes are multiples of 256 bytes
+    const size_t lq = 3 * t->Lrows * rowb, bq = (t->comps ? 3 : 6) * t->Brows * rowb, sq = t->comps ? 3 * t->Srows * rowb : 0, yq = t->comps ? 6 * GT_YROWS * rowb : 0;
+    if (rc == GT_OK && hipMalloc(&t->LQ, lq + bq + sq + yq) != hipSuccess) { t->LQ = nullptr; rc = GT_ENOMEM; }
+    if (rc == GT_OK) {
+        t->BQ = t->LQ + lq; t->SQ = t->BQ + bq; t->YQ = t->SQ + sq;
+        if (hipMemsetAsync(t->LQ, 0, lq + bq + sq + yq, s) != hipSuccess) rc = GT_EHIP;
     }
     if (rc != GT_OK) { (void)hipStreamSynchronize(s); train_free(t); return T.finish(rc); }
     rc = train_start(c, t, X, Y);
@@ -830,14 +823,14 @@ static int heuristic_open(gt_ctx *c, gt_train *t, u32 h)
     c->acc.scorer_bytes[0] += 3 * 8 * nh * (t->CW + d + 1);
     c->acc.rounds += 1;
     struct { const u64 *plain; u64 n; P6 out; u64 off; } sh[6] = {
-        { SDp, nh, t->SD.v, 0 }, { Gp, nh * d, t->gamma.v, 0 }, { Fn, nh, t->F.v, base }, { Fc, nh, t->best.v, 0 },
+        { SDp, nh, t->SD.v, 0 }, { Gp, nh * d, t->gamma.v, 0 }, { Fn, nh, t->F.v, base }, { Fc, nh, t->F.v, base },
         { Sp, nh, t->split.v, 0 }, { SCp, nh * d, t->Slast.v, 0 } };
+    ShareBackArgs b{}; b.keys = c->keys_d; b.op = c->op; c->op += 6;
     for (int i = 0; i < 6; i++) {
-        GTCHK(launch(c, GT_KC_SHARE, k_share, g1((sh[i].n + 7) / 8), B256, (const u32 *)c->keys_d, (int)GT_KEY_DEALER, c->op++,
-                     sh[i].plain, sh[i].n, sh[i].out, sh[i].off));
+        b.plain[i] = sh[i].plain; b.n[i] = sh[i].n; b.out[i] = sh[i].out; b.off[i] = sh[i].off;
         c->acc.scorer_bytes[1] += 3 * 2 * 8 * sh[i].n;
-        if (i == 3) GTCHK(launch(c, GT_KC_LOCAL, k_children, g1(nh), B256, t->F.v, t->best.v, base, nh));
     }
+    GTCHK(launch(c, GT_KC_SHARE, k_share_back, dim3(g1((nh * d + 7) / 8).x, 6), B256, b));
     c->acc.rounds += 1;
     return GT_OK;
 }
