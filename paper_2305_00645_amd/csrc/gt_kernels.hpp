@@ -1205,23 +1205,20 @@ __global__ __launch_bounds__(64) void k_update(UpdateArgs a)
 //               M[i] <- 2 M[i] + sum_k sel[k][i] * X[k][i] + 1, zero sharing of stream 0, word i
 //               (gt_partmm.hpp, on the matrix cores)
 struct OnehotArgs { KCommon c; P6 T, OH; u64 base, n; u32 d; };
-__global__ __launch_bounds__(192) void k_onehot(OnehotArgs a)
+__global__ __launch_bounds__(64) void k_onehot(OnehotArgs a)
 {
-    const int p = party_of_wave();
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    __shared__ u64 s_cnt[6];
-    Wire W; W.init(s_wire, s_cnt);
-    __shared__ u64 s_prf[3][GT_PRF_SCRATCH_WORDS];
-    const PartyKeys K = load_party_keys(a.c.keys, p, s_prf[p]);
-    GT_FOR_TILES(a.n) {
-        const u64 e = GT_ELEM();
-        const bool act = e < a.n;
+    GT_EL_SHARED(1)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
         Sh v = { 0, 0 };
         if (act) v = ld(a.T, p, a.base + e / a.d) - pub(p, e % a.d);
-        const Dealer D = dealer_of(K, p, a.c.op, e);
-        u64 A;
-        const Sh oh = b2a(W, p, eq_bit(W, K, p, a.c.op, e, v, D, A, act), D, act);
-        if (act) st(a.OH, p, e, oh);
+        const u32 s1[1] = { 1 };
+        T.deal(W, a.c.op, e0, s1, el_live(e0, a.n));
+        const Dealer D = T.dealer(W);
+        const Sh oh = b2a(W, p, eq_bit_mask(W, p, v, D, T.zb(W, 0, (u32)(e0 & 7) + W.t), act), D, act);
+        if (act && W.real) st(a.OH, p, e, oh);
+        W.drain();
     }
     W.flush(a.c.wire);
 }

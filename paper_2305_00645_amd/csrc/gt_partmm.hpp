@@ -45,35 +45,33 @@ struct PartMmArgs {
     u32 d, dpad, rpad;         // columns, padded to 64; node rows padded to 32
 };
 
-// Zero-sharing words of one pass of the epilogue: the pass (t, vq) covers the 8 rows
-// m = t*32 + 8*vq + ri, ri < 8, of the 64 x 32 tile; lane l < 32 evaluates the own-key block
-// of row ri = l/4, sample group l%4, lanes 32.. the next-key blocks; words to
-// scr[((pass*2 + key)*8 + ri)*32 + sample].
-__device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const PartyKeys &K, u64 *scr, u32 pass, u32 kg, u64 ib, u32 n, u32 hi)
+// Zero-sharing words under the party's own key for one pass of the epilogue: pass covers the 16 rows
+// m = pass*16 + ri, ri < 16, of the 64 x 32 tile; lane l evaluates the block of row ri = l/4, sample
+// group l%4; words to scr[m*32 + sample].  The words under the next key are the next party's, in its
+// scratch (evaluating both keys per party took twice the passes: 154 us a level
+// for 19,997 x 101, 129 us now).
+__device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const Key &own, u64 *scr, u32 pass, u32 kg, u64 ib, u32 lane)
 {
-    const u32 ri = n >> 2, g = n & 3;
-    const u64 kcol = (u64)kg * 64 + (pass >> 2) * 32 + 8 * (pass & 3) + ri;
-    const u32 mk = 0u - hi;
-    Key kv;
-#pragma unroll
-    for (int q = 0; q < 8; q++) kv.k[q] = K.own.k[q] ^ ((K.own.k[q] ^ K.nxt.k[q]) & mk);
+    const u32 m = pass * 16 + (lane >> 2), g = lane & 3;
+    const u64 kcol = (u64)kg * 64 + m;
     u64 blk[8];
-    chacha8(kv, ((kcol * a.N8 + ib * 32) >> 3) + g, a.c.op, 0, blk);
+    chacha8(own, ((kcol * a.N8 + ib * 32) >> 3) + g, a.c.op, 0, blk);
 #pragma unroll
-    for (int q = 0; q < 8; q++) scr[((pass * 2 + hi) * 8 + ri) * 32 + g * 8 + q] = blk[q];
+    for (int q = 0; q < 8; q++) scr[m * 32 + g * 8 + q] = blk[q];
 }
 
 __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 {
     __shared__ u64 s_wire[GT_LWIRE_WORDS];
     __shared__ u64 s_cnt[6];
-    __shared__ u64 s_prf[3][8 * 2 * 8 * 32];     // per party: the zero-sharing words of a 64 x 32 tile under two keys
+    __shared__ u64 s_prf[3][64 * 32];            // per party: the zero-sharing words of a 64 x 32 tile under its own key
     __shared__ u64 s_x[3][16 * GT_LANES];        // the reshared components, 16 per lane and exchange
     __shared__ u32 s_tp[3][2 * PM_TP_WORDS];     // two transpose areas per wavefront, used alternately
     const int p = party_of_wave(), lane = threadIdx.x, pn = p == 2 ? 0 : p + 1;
     LWire W; W.init(s_wire, s_cnt);
     const PartyKeys K = load_party_keys(a.c.keys, p);
     u64 *scr = s_prf[p];
+    const u64 *scrn = s_prf[pn];
     u32 *tp = s_tp[p];
     const u32 n = lane & 31, hi = (u32)lane >> 5;
     const Sh one = pub(p, 1);
@@ -94,8 +92,8 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
             // chunks of 32 node rows: first those of L_p x (OH own+next), then those of L_{p+1} x OH own.
             // The eight limb tiles of the next chunk are in flight while this one is transposed and
             // multiplied (the last iteration loads its own chunk again, unused, so that the number of
-            // loads in flight at every wait is the same).  Two passes of the epilogue's zero-sharing
-            // words are evaluated per chunk, in the shadow of the matrix-core instructions.
+            // loads in flight at every wait is the same).  One pass of the epilogue's zero-sharing
+            // words is evaluated per chunk, in the shadow of the matrix-core instructions.
             v4i xn[8];
 #define PM_LOAD(X, CH)                                                                               \
             {                                                                                        \
@@ -143,8 +141,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
                     }
                     Bt[s] = o;
                 }
-                pm_prf_pass(a, K, scr, (2 * ch) & 7, kg, ib, n, hi);
-                pm_prf_pass(a, K, scr, (2 * ch + 1) & 7, kg, ib, n, hi);
+                pm_prf_pass(a, K.own, scr, ch & 3, kg, ib, (u32)lane);
 #pragma unroll
                 for (int t = 0; t < 2; t++)
 #pragma unroll
@@ -152,46 +149,48 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 #pragma unroll
                         for (int u = 0; u < 8 - s; u++)
                             acc[s + u][t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[t][s], Bt[u], acc[s + u][t], 0, 0, 0);
-                // one matrix-core instruction, then a dozen vector instructions of the PRF, and so on
+                // one matrix-core instruction, then half a dozen vector instructions of the PRF, and so on
 #pragma unroll
                 for (int q = 0; q < 72; q++) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
                 }
             }
 #undef PM_LOAD
-            for (u32 pass = 2 * nch; pass < 8; pass++) pm_prf_pass(a, K, scr, pass, kg, ib, n, hi);   // fewer than four chunks
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            // epilogue, one half of the tile (32 columns, 16 per lane) at a time: recombine the limb
-            // levels, add the zero sharing, send the component to the predecessor, inner product with X
+            // the samples' own values for the epilogue, on their way while the remaining words are evaluated
+            Sh xv[2][16];
+            u32 nl = 0;
 #pragma unroll
-            for (int t = 0; t < 2; t++) {
-                Sh xv[16];
-                u32 nl = 0;
+            for (int t = 0; t < 2; t++)
 #pragma unroll
                 for (int v = 0; v < 16; v++) {
                     const u64 kcol = (u64)kg * 64 + t * 32 + 8 * (v >> 2) + hi * 4 + (v & 3);
                     const bool live = ilive && kcol < a.d;
                     nl += live ? 1u : 0u;
-                    xv[v] = live ? ld(a.XT, p, kcol * a.N8 + i) : Sh{ 0, 0 };
+                    xv[t][v] = live ? ld(a.XT, p, kcol * a.N8 + i) : Sh{ 0, 0 };
                 }
+            for (u32 pass = nch; pass < 4; pass++) pm_prf_pass(a, K.own, scr, pass, kg, ib, (u32)lane);   // fewer than four chunks
+            W.nresh += 64u * nl;
+            __syncthreads();                             // every party's words are there
+            // epilogue, one half of the tile (32 columns, 16 per lane) at a time: recombine the limb
+            // levels, add the zero sharing, send the component to the predecessor, inner product with X
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
                 u64 snd[16];
 #pragma unroll
                 for (int v = 0; v < 16; v++) {
                     u64 z = 0;
 #pragma unroll
                     for (int u = 0; u < 8; u++) z += (u64)(long long)acc[u][t][v] << (8 * u);
-                    const u32 pass = t * 4 + (v >> 2), ri = hi * 4 + (v & 3);
-                    snd[v] = z + (scr[((pass * 2) * 8 + ri) * 32 + n] - scr[((pass * 2 + 1) * 8 + ri) * 32 + n]);
+                    const u32 m = t * 32 + 8 * (v >> 2) + hi * 4 + (v & 3);
+                    snd[v] = z + (scr[m * 32 + n] - scrn[m * 32 + n]);
                     s_x[p][v * GT_LANES + lane] = snd[v];
                 }
-                W.nresh += 64u * nl;
                 __syncthreads();
 #pragma unroll
                 for (int v = 0; v < 16; v++) {
                     const Sh sel = { snd[v], s_x[pn][v * GT_LANES + lane] };
-                    dacc += prod3(sel, xv[v]);                       // X is zero where the element does not exist
+                    dacc += prod3(sel, xv[t][v]);                       // X is zero where the element does not exist
                 }
                 __syncthreads();
             }
@@ -199,22 +198,17 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
         // the two halves of the wavefront hold the sums over different rows of the same sample
         dacc += (u64)__shfl_xor((unsigned long long)dacc, 32, GT_LANES);
         {
-            // zero sharing of the inner product: words ib*32 .. +31 of stream 0 under op+1, four blocks per key
-            if (lane < 8) {
-                const u32 mk = 0u - ((u32)lane >> 2);
-                Key kv;
-#pragma unroll
-                for (int q = 0; q < 8; q++) kv.k[q] = K.own.k[q] ^ ((K.own.k[q] ^ K.nxt.k[q]) & mk);
+            // zero sharing of the inner product: words ib*32 .. +31 of stream 0 under op+1, four blocks
+            if (lane < 4) {
                 u64 blk[8];
-                chacha8(kv, ib * 4 + (lane & 3), a.c.op + 1, 0, blk);
+                chacha8(K.own, ib * 4 + lane, a.c.op + 1, 0, blk);
 #pragma unroll
-                for (int q = 0; q < 8; q++) scr[(lane >> 2) * 32 + (lane & 3) * 8 + q] = blk[q];
+                for (int q = 0; q < 8; q++) scr[lane * 8 + q] = blk[q];
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            __syncthreads();
         }
         Sh z;
-        z.o = dacc + (scr[n] - scr[32 + n]);
+        z.o = dacc + (scr[n] - scrn[n]);
         z.n = W.reshare1(z.o, (ilive && hi == 0) ? 64u : 0u);
         if (ilive && hi == 0) st(a.M, p, i, scale(ld(a.M, p, i), 2) + z + one);
         __syncthreads();                         // the message slots and the scratch are rewritten by the next block

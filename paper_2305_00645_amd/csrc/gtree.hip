@@ -700,7 +700,7 @@ static int partition_matmul(gt_ctx *c, gt_train *t, u32 h)
     if (t->lt_level != h - 1) return GT_ESTATE;         // needs the one-hot of the level just processed
     const u64 np = (u64)1 << (h - 1), base = np - 1, d = t->d, N = t->N;
     OnehotArgs oa{}; oa.c = kc(c, c->op++); oa.T = t->T.v; oa.OH = t->OH.v; oa.base = base; oa.n = np * d; oa.d = t->d;
-    GTCHK(launch(c, GT_KC_SMALL, k_onehot, dim3(tiles(np * d)), GT_BLOCK, oa));
+    GTCHK(launch(c, GT_KC_SMALL, k_onehot, gE(np * d), B64, oa));
     acct_eq(c, np * d); acct_b2a(c, np * d);
     const u32 rpad = (u32)((np + 31) / 32 * 32), dpad = (t->d + 63) / 64 * 64;
     GTCHK(launch(c, GT_KC_LOCAL, k_oh_limbs, g1(6ull * dpad * rpad), B256, t->OH.v, t->OHL, (u32)np, t->d, rpad, dpad));
