@@ -57,14 +57,6 @@ __device__ __forceinline__ void chacha8(const Key &key, u64 blk, u32 op, u32 str
     out[6] = (u64)x12 | ((u64)x13 << 32); out[7] = (u64)x14 | ((u64)x15 << 32);
 }
 
-__device__ __forceinline__ u64 sel8(const u64 (&w)[8], u32 i)
-{
-    u64 a = (i & 1) ? w[1] : w[0], b = (i & 1) ? w[3] : w[2];
-    u64 c = (i & 1) ? w[5] : w[4], d = (i & 1) ? w[7] : w[6];
-    u64 ab = (i & 2) ? b : a, cd = (i & 2) ? d : c;
-    return (i & 4) ? cd : ab;
-}
-
 __device__ __forceinline__ Key load_key(const u32 *keys, int idx)
 {
     Key k;
@@ -88,14 +80,6 @@ __device__ __forceinline__ PartyKeys load_party_keys(const u32 *keys, int p, u64
     K.dlr = load_key(keys, GT_KEY_DEALER);
     K.scr = scr;
     return K;
-}
-
-// word j of stream (op, stream) under one key
-__device__ __forceinline__ u64 prf_word(const Key &k, u32 op, u32 stream, u64 j)
-{
-    u64 w[8];
-    chacha8(k, j >> 3, op, stream, w);
-    return sel8(w, (u32)j & 7);
 }
 
 // Words of NS streams under the own and the next key for a tile of 64 consecutive
@@ -148,12 +132,6 @@ __device__ __forceinline__ u64 zero_b(const PartyKeys &K, u32 op, u32 stream, u6
     return wo[0] ^ wn[0];
 }
 // two streams in one pass
-__device__ __forceinline__ void zero_a2(const PartyKeys &K, u32 op, u32 s0, u32 s1, u64 e, u64 &z0, u64 &z1)
-{
-    const u32 st[2] = { s0, s1 }; u64 wo[2], wn[2];
-    prf_tile<2>(K, op, st, e, wo, wn);
-    z0 = wo[0] - wn[0]; z1 = wo[1] - wn[1];
-}
 __device__ __forceinline__ void zero_b2(const PartyKeys &K, u32 op, u32 s0, u32 s1, u64 e, u64 &z0, u64 &z1)
 {
     const u32 st[2] = { s0, s1 }; u64 wo[2], wn[2];

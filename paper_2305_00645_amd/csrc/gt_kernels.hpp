@@ -18,12 +18,6 @@ struct KCommon { const u32 *keys; u32 op; u64 *wire; };
 // number of the lane's 8 consecutive elements (first one i0) that exist below n
 __device__ __forceinline__ u32 live8(u64 i0, u64 n) { return i0 >= n ? 0u : (n - i0 >= 8 ? 8u : (u32)(n - i0)); }
 
-__device__ __forceinline__ P6 p6_off(P6 a, size_t off)
-{
-    for (int j = 0; j < 3; j++) { a.o[j] += off; a.n[j] += off; }
-    return a;
-}
-
 // ---------------------------------------------------------------------------------
 // A PRF block holds the words of 8 consecutive elements, one block per lane; memory wants
 // consecutive elements in consecutive lanes.  The 512 words of a wavefront change hands through

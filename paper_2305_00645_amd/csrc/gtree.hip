@@ -116,8 +116,6 @@ static int dsh_alloc(DSh &s, size_t n, hipStream_t st)
 }
 static void dsh_free(DSh &s) { if (s.base) (void)hipFree(s.base); s.base = nullptr; s.n = 0; }
 
-static P6 off6(P6 a, size_t off) { for (int j = 0; j < 3; j++) { a.o[j] += off; a.n[j] += off; } return a; }
-
 static bool shares_ok(const gt_shares *s, size_t n)
 {
     if (!s) return false;
