@@ -1570,14 +1570,15 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
     }
     const u32 wr = wave % a.rt, task = sl * (4 / a.rt) + wave / a.rt;   // this wavefront's row tile, party and column tile
     if (task >= 3 * a.ncoltiles) return;                      // whole wavefront
-    const int p = a.xcols ? task % 3 : task / a.ncoltiles;
+    const bool beside = a.xcols && a.rt < 4;                  // four row tiles: the nodes' operands are the larger part
+    const int p = beside ? task % 3 : task / a.ncoltiles;
     const u64 r0 = ((u64)rg * a.rt + wr) * 32;
     if (r0 >= a.nh) return;                                   // whole wavefront
     const LimbMat LA0 = p == 0 ? a.A.m[0][0] : (p == 1 ? a.A.m[1][0] : a.A.m[2][0]);
     const LimbMat LA1 = p == 0 ? a.A.m[0][1] : (p == 1 ? a.A.m[1][1] : a.A.m[2][1]);
     const LimbMat LB0 = p == 0 ? a.B.m[0][0] : (p == 1 ? a.B.m[1][0] : a.B.m[2][0]);
     const LimbMat LB1 = p == 0 ? a.B.m[0][1] : (p == 1 ? a.B.m[1][1] : a.B.m[2][1]);
-    const u64 ctile = a.xcols ? task / 3 : task % a.ncoltiles;   // column tile of 32*NB
+    const u64 ctile = beside ? task / 3 : task % a.ncoltiles;    // column tile of 32*NB
     const u64 c0 = a.bcol0 + ctile * (32 * NB);
     const u32 lr = lane & 31;
     v16i acc[8][NB];
