@@ -23,15 +23,16 @@ LANE_OPS_PEAK = 256 * 4 * 16 * 2.4e9 / 1e12   # 32-bit vector ALU lane-ops, Tops
 # is 400 ops.  Dealer: 3 blocks per 8 tests (150: the daBits of the tests, offline material that the
 # paper's timings exclude but that this simulation derives inside the kernel; the edaBit is one
 # block per ROW of the grid, 400/w per test, left out) + 3 mask blocks per 8 tests (150: the zero
-# sharings of the AND rounds, online) + protocol steps 3 x 50 on packed fields (online)
-EQ_ALU_OPS_DEALER, EQ_ALU_OPS_ONLINE = 150, 300
+# sharings of the AND rounds, online) + protocol steps 3 x 33 on packed fields with three-input logic
+# counted as one (online); the kernels execute 420 to 430
+EQ_ALU_OPS_DEALER, EQ_ALU_OPS_ONLINE = 150, 250
 EQ_ALU_OPS = EQ_ALU_OPS_DEALER + EQ_ALU_OPS_ONLINE
 # HBM bytes per equality test of the three grid variants, from rocprofv3 FETCH_SIZE / WRITE_SIZE
 # (table in profiles/pmc_traffic_micro.md): inner product against a shared array, against the
 # sample's own row, leaf one-hot written as limb tiles
-# (the one-launch inference reads every feature of an instance once per level: 10 levels x 48 B x 64
-# features over 2687 tests per instance at C5)
-EQ_HBM_BYTES = {"eqgrid": 7.4, "eqgrid_rows": 55.4, "eqgrid_store": 24.4, "infer": 15.1}
+# (56 for the level, whose tiles hold the sums too, and 25 for the label level, by their tests); the
+# one-launch inference reads every feature of an instance at least once per level
+EQ_HBM_BYTES = {"eqgrid": 1.6, "eqgrid_rows": 53.5, "eqgrid_store": 35.7, "infer": 25.0}
 SHADER_CLOCK_MEASURED_GHZ = 2.1  # under the equality grid's load (profiles/pmc_sq_micro.md); the peak below uses the nominal 2.4
 
 
@@ -333,12 +334,12 @@ def main():
                        "note": "the equality-test kernels together (three grid variants of training and the one-launch inference: most of the step); %d 32-bit ALU ops per "
                                "test for the three parties, of which %d are the dealer's PRF blocks (the daBits, offline material of the test: "
                                "the paper's timings exclude its generation, this simulation derives it in the kernel) and %d are "
-                               "online work (mask words 150, protocol 150): counting online ops only the figure is %.2f of the "
+                               "online work (mask words 150, protocol 100): counting online ops only the figure is %.2f of the "
                                "peak; peak = 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz nominal (the shader clock under this load "
                                "reads %.1f GHz); traffic = HBM bytes per launch = per-variant counter bytes per test "
                                "(profiles/pmc_traffic_micro.md) x this run's tests per variant; the >=50%% HBM target of the "
                                "workload description is not met and cannot be by this kernel: its messages stay in LDS and it "
-                               "is bound by the PRF (VALU issue share 0.77-0.83, profiles/pmc_sq_micro.md), see eqgrid_hbm_view"
+                               "is bound by the vector ALU (issue share 0.84-0.92, profiles/pmc_sq_micro.md), see eqgrid_hbm_view"
                                % (EQ_ALU_OPS, EQ_ALU_OPS_DEALER, EQ_ALU_OPS_ONLINE,
                                   EQ_ALU_OPS_ONLINE * n_eq * k / (eq_ms / 1e3) / 1e12 / LANE_OPS_PEAK, SHADER_CLOCK_MEASURED_GHZ),
                        "avg_launch_ms": eq_ms / max(eq_l, 1), "launches_per_step": eq_l // k,
@@ -350,12 +351,12 @@ def main():
             # the two launches of the contraction have different bounds: the level's (128 nodes x 260 columns)
             # is matrix-core work, the label level's (256 nodes x 4 class columns) streams L once
             "count": {"bound": "mfma", "achieved": 72.0 * macs_level / (lvl_cnt_ms / 1e3) / 1e12, "peak": 5000.0,
-                      "unit": "TOP/s", "traffic": 19.0e9,
+                      "unit": "TOP/s", "traffic": 28.3e9,
                       "note": "the contraction of the split-scoring level: ring MAC = 36 int8 limb products on the matrix "
                               "cores = 72 int8 ops; int8 dense peak 5.0 POP/s; %d ring MACs (every party's two products "
-                              "are computed; the leaf one-hot is stored once per component, the copy that both of its "
+                              "are computed; the columns are stored once per component, the copy that both of its "
                               "holders read); traffic: FETCH_SIZE + WRITE_SIZE of this launch in profiles/pmc_traffic_micro.md "
-                              "(compulsory 15.6 GB)" % macs_level,
+                              "(compulsory 12.4 GB)" % macs_level,
                       "avg_launch_ms": lvl_cnt_ms, "launches_per_step": 1},
             "count_label_level": {"bound": "hbm", "achieved": lbl_bytes / (lbl_cnt_ms / 1e3) / 1e9, "peak": HBM_PEAK_GBS,
                                   "unit": "GB/s", "traffic": lbl_bytes,

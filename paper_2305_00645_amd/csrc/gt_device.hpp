@@ -1,13 +1,14 @@
 // Device-side toolkit: PRF, per-party share arithmetic, message exchange and the
 // per-element protocol steps (Sec. II-B and Sec. V-A of the GTree paper), for gfx950.
 //
-// Execution models.  Equality grids: three parties per wavefront (WWire, at the end of this
-// file).  All other protocols: a workgroup is 3 wavefronts of 64 lanes, wavefront p IS party p
-// (threadIdx.y = p).  Lane l of each of the three wavefronts works on the same
-// element(s), each on its own party's two components.  A protocol message is a
-// store into the workgroup's message region in LDS; the receiving wavefront loads it
-// after a workgroup barrier.  A party's lanes never
-// read another party's shares or keys, only the words sent to it.
+// Execution models.  Wavefront model (WWire, ElTile, further down): the three parties of an
+// element sit in three lanes of one wavefront; equality grids, inference and the per-node
+// protocols run like this.  Workgroup model (products, one-time products, partition by
+// products, the protocols as printed): a workgroup is 3 wavefronts of 64 lanes, wavefront p IS
+// party p (threadIdx.y = p), lane l of each works on the same element(s).  Either way a
+// party's lane holds its own two components, a protocol message is a store into a message
+// region in LDS that the receiving party's lane loads (after a workgroup barrier in the second
+// model), and a party's lanes never read another party's shares, only the words sent to it.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -1,5 +1,5 @@
 // Kernels of the GTree hot path for gfx950.  See gt_device.hpp for the execution
-// model (workgroup = 3 wavefronts = 3 parties; messages through LDS).
+// models (three parties per wavefront, or per workgroup; messages through LDS).
 #pragma once
 #include "gt_device.hpp"
 
