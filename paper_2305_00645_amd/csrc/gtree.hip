@@ -92,7 +92,7 @@ struct gt_train {
     DSh XT, YT;                      // [k][i], [c][i]: sample-contiguous copies of the inputs
     // limb tiles: leaf one-hot (one matrix per component); columns, (own+next, own) per party or, with comps,
     // once per component, and then the sums own+next of the leaf one-hot (levels before the last) in SQ and the
-    // class columns in both forms in YQ; all in the allocation that LQ begins
+    // class columns in both forms in YQ; SQ is part of LQ's allocation, YQ of BQ's
     unsigned char *LQ, *BQ, *SQ, *YQ;
     bool comps;
     size_t nblk, Lrows, Brows, Srows;// sample blocks of 32, row strides of the limb planes
@@ -525,6 +525,7 @@ extern "C" int gt_div(gt_ctx *c, const gt_shares *S, const gt_shares *Q, size_t 
 static void train_free(gt_train *t)
 {
     if (t->LQ) (void)hipFree(t->LQ);
+    if (t->BQ) (void)hipFree(t->BQ);
     DSh *all[] = { &t->XT, &t->YT, &t->M, &t->T, &t->F, &t->C, &t->Cn, &t->gamma, &t->Gn, &t->isLeaf, &t->SD,
                    &t->split, &t->val[0], &t->val[1], &t->idx[0], &t->idx[1],
                    &t->tval, &t->Clast, &t->Glast, &t->Slast };
@@ -638,12 +639,13 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     t->Srows = H ? std::max<size_t>(32, (nmax / 2 + 31) / 32 * 32) : 0;
     t->comps = 3 * t->Srows + 3 * t->Brows + 6 * GT_YROWS <= 6 * t->Brows;
     const size_t rowb = t->nblk * 8 * 32;
-    // one allocation; planes are multiples of 256 bytes
+    // two allocations, the nodes' tiles and the columns'; planes are multiples of 256 bytes
     const size_t lq = 3 * t->Lrows * rowb, bq = (t->comps ? 3 : 6) * t->Brows * rowb, sq = t->comps ? 3 * t->Srows * rowb : 0, yq = t->comps ? 6 * GT_YROWS * rowb : 0;
-    if (rc == GT_OK && hipMalloc(&t->LQ, lq + bq + sq + yq) != hipSuccess) { t->LQ = nullptr; rc = GT_ENOMEM; }
+    if (rc == GT_OK && hipMalloc(&t->LQ, lq + sq) != hipSuccess) { t->LQ = nullptr; rc = GT_ENOMEM; }
+    if (rc == GT_OK && hipMalloc(&t->BQ, bq + yq) != hipSuccess) { t->BQ = nullptr; rc = GT_ENOMEM; }
     if (rc == GT_OK) {
-        t->BQ = t->LQ + lq; t->SQ = t->BQ + bq; t->YQ = t->SQ + sq;
-        if (hipMemsetAsync(t->LQ, 0, lq + bq + sq + yq, s) != hipSuccess) rc = GT_EHIP;
+        t->SQ = t->LQ + lq; t->YQ = t->BQ + bq;
+        if (hipMemsetAsync(t->LQ, 0, lq + sq, s) != hipSuccess || hipMemsetAsync(t->BQ, 0, bq + yq, s) != hipSuccess) rc = GT_EHIP;
     }
     if (rc != GT_OK) { (void)hipStreamSynchronize(s); train_free(t); return T.finish(rc); }
     rc = train_start(c, t, X, Y);
