@@ -1043,62 +1043,92 @@ __device__ __forceinline__ void select_el(WWire &W, ElTile<4> &T, int p, u32 op,
     L.o += snd[0]; L.n += rcv[0]; IL.o += snd[1]; IL.n += rcv[1];
 }
 
-// Arg-max of a level's masked scores, all rounds of the tournament in one launch: a workgroup per
-// node, tiles of 16 pairs per wavefront ((e0 mod 8) + 16 <= 24 for any e0), a barrier per round.  Round l
-// (operation op + l) compares arrays of length P2 >> l: element e = r*half + m, left 2m, right 2m+1;
-// the scores are padded with 0, the indices start as k.  The rounds' results stay in LDS for
-// P2 <= GT_ARGMAX_LDS, in the buffers val / idx otherwise.  Bound: the chain of the rounds.  512 candidates:
-// nine launches of 10.8 us, now 30 us.
-#define GT_ARGMAX_LDS 512
-#define GT_ARGMAX_WAVES 8
-struct ArgmaxArgs { KCommon c; P6 score, val[2], idx[2], SD; u32 nh, d, P2; };
-__global__ __launch_bounds__(64 * GT_ARGMAX_WAVES) void k_argmax(ArgmaxArgs a)
+// The tournament of a level's masked scores.  Round l (operation op + l) compares arrays of length
+// P2 >> l, node after node: element e = r*half + m, left 2e, right 2e + 1 of the round before; the scores
+// are padded with 0, the indices start as k.
+struct SelectPair { Sh L, R, IL, IR; };
+// element e of the first round (half = 1 << lgh)
+__device__ __forceinline__ SelectPair first_pair(const P6 &score, int p, u64 e, u32 lgh, u32 d)
 {
-    __shared__ uint4 s_msg[GT_ARGMAX_WAVES][GT_LANES];
-    __shared__ u64 s_mat[GT_ARGMAX_WAVES][GT_EL_WORDS(4)];
-    __shared__ u64 s_cnt[GT_ARGMAX_WAVES][6];
-    __shared__ u64 s_buf[2][12][GT_ARGMAX_LDS / 2];
+    const u64 r = e >> lgh;
+    const u32 k = 2 * (u32)(e - (r << lgh));
+    SelectPair q = { { 0, 0 }, { 0, 0 }, pub(p, k), pub(p, k + 1) };
+    if (k < d) q.L = ld(score, p, r * d + k);
+    if (k + 1 < d) q.R = ld(score, p, r * d + k + 1);
+    return q;
+}
+__device__ __forceinline__ SelectPair next_pair(const P6 &val, const P6 &idx, int p, u64 e)
+{
+    SelectPair q = { ld(val, p, 2 * e), ld(val, p, 2 * e + 1), ld(idx, p, 2 * e), ld(idx, p, 2 * e + 1) };
+    return q;
+}
+
+// One round of all nodes, tiles of GT_EL elements over the whole chip, for rounds that fill it.
+struct SelectArgs { KCommon c; P6 score, vin, iin, vout, iout; u64 n; u32 d, lgh; int first; };
+__global__ __launch_bounds__(64) void k_select_round(SelectArgs a)
+{
+    GT_EL_SHARED(4)
+    GT_FOR_EL(a.n) {
+        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
+        const bool act = W.t < GT_EL && e < a.n;
+        SelectPair q = { { 0, 0 }, { 0, 0 }, { 0, 0 }, { 0, 0 } };
+        if (act) q = a.first ? first_pair(a.score, p, e, a.lgh, a.d) : next_pair(a.vin, a.iin, p, e);
+        select_el(W, T, p, a.c.op, e0, el_live(e0, a.n), q.L, q.R, q.IL, q.IR, act);
+        if (act && W.real) { st(a.vout, p, e, q.L); st(a.iout, p, e, q.IL); }
+        W.drain();
+    }
+    W.flush(a.c.wire);
+}
+
+// All rounds from arrays of `len` on in one launch: NW wavefronts per node, tiles of 16 elements
+// ((e0 mod 8) + 16 <= 24 for any e0), the rounds' results in LDS.  One wavefront holds the 32/len nodes
+// whose first rounds make up a tile and needs no barrier; with two, four or eight a node's first round is a
+// tile per wavefront (two for len = 512) and a barrier ends a round.  LDS per wavefront 7 KB (10 with eight).
+// Bound: the chain of the rounds (about 3 us each) and, from thousands of nodes on, the vector ALU.  One node of 512
+// candidates 27 us; 4,096 nodes of 8 candidates 11 us, where a workgroup of eight wavefronts and 90 KB for every node
+// took 126 and a launch per round 40; 32,768 nodes 40 us (884; 82).
+#define GT_ARGMAX_LDS 512
+struct ArgmaxArgs { KCommon c; P6 score, vin, iin, SD; u64 nh; u32 d, len, lgh; int first; };   // lgh: log2(len / 2); first: from the scores, else from vin, iin
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_argmax(ArgmaxArgs a)
+{
+    constexpr u32 RES = NW == 8 ? GT_ARGMAX_LDS / 2 : 16 * NW;          // elements of the first round
+    __shared__ uint4 s_msg[NW][GT_LANES];
+    __shared__ u64 s_mat[NW][GT_EL_WORDS(4)];
+    __shared__ u64 s_cnt[NW][6];
+    __shared__ u64 s_buf[12][RES + RES / 2];                            // results of the even rounds, of the odd ones
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     WWire W; W.init(s_msg[wave], s_cnt[wave]);
     const int p = W.p;
     ElTile<4> T; T.keys = a.c.keys; T.mat = s_mat[wave];
-    for (u64 r = blockIdx.x; r < a.nh; r += gridDim.x) {
-        u64 *vo[2], *vn[2], *io[2], *in[2];            // this party's buffers, ping-pong
-#pragma unroll
-        for (int x = 0; x < 2; x++) {
-            if (a.P2 <= GT_ARGMAX_LDS) { vo[x] = s_buf[x][4 * p]; vn[x] = s_buf[x][4 * p + 1]; io[x] = s_buf[x][4 * p + 2]; in[x] = s_buf[x][4 * p + 3]; }
-            else {
-                vo[x] = own_of(a.val[x], p) + r * a.P2; vn[x] = nxt_of(a.val[x], p) + r * a.P2;
-                io[x] = own_of(a.idx[x], p) + r * a.P2; in[x] = nxt_of(a.idx[x], p) + r * a.P2;
-            }
-        }
-        u32 cur = 0, round = 0;
-        for (u32 len = a.P2; len > 1; len /= 2, round++) {
-            const u32 half = len / 2;
-            for (u32 m0 = wave * 16; m0 < half; m0 += GT_ARGMAX_WAVES * 16) {
-                const u32 nel = half - m0 < 16 ? half - m0 : 16, m = m0 + W.t;
+    u64 *vo = s_buf[4 * p], *vn = s_buf[4 * p + 1], *io = s_buf[4 * p + 2], *in = s_buf[4 * p + 3];
+    const u32 per = NW == 1 ? 32 / a.len : 1;                           // nodes of a workgroup
+    for (u64 r0 = (u64)blockIdx.x * per; r0 < a.nh; r0 += (u64)gridDim.x * per) {
+        const u32 nn = a.nh - r0 < per ? (u32)(a.nh - r0) : per;
+        u32 round = 0, from = RES, to = 0;
+        for (u32 half = a.len / 2; half > 0; half /= 2, round++) {
+            const u32 n = nn * half;
+            for (u32 m0 = wave * 16; m0 < n; m0 += NW * 16) {
+                const u32 nel = n - m0 < 16 ? n - m0 : 16, m = m0 + W.t;
                 const bool act = W.t < nel;
-                Sh L = { 0, 0 }, R = { 0, 0 }, IL = { 0, 0 }, IR = { 0, 0 };
+                SelectPair q = { { 0, 0 }, { 0, 0 }, { 0, 0 }, { 0, 0 } };
                 if (act) {
-                    if (round == 0) {
-                        if (2 * m < a.d) L = ld(a.score, p, r * a.d + 2 * m);
-                        if (2 * m + 1 < a.d) R = ld(a.score, p, r * a.d + 2 * m + 1);
-                        IL = pub(p, 2 * m); IR = pub(p, 2 * m + 1);
-                    } else {
-                        L.o = vo[cur][2 * m]; L.n = vn[cur][2 * m]; R.o = vo[cur][2 * m + 1]; R.n = vn[cur][2 * m + 1];
-                        IL.o = io[cur][2 * m]; IL.n = in[cur][2 * m]; IR.o = io[cur][2 * m + 1]; IR.n = in[cur][2 * m + 1];
-                    }
+                    if (round > 0) {
+                        const u32 j = from + 2 * m;
+                        q = { { vo[j], vn[j] }, { vo[j + 1], vn[j + 1] }, { io[j], in[j] }, { io[j + 1], in[j + 1] } };
+                    } else q = a.first ? first_pair(a.score, p, (r0 << a.lgh) + m, a.lgh, a.d) : next_pair(a.vin, a.iin, p, (r0 << a.lgh) + m);
                 }
-                select_el(W, T, p, a.c.op + round, r * half + m0, nel, L, R, IL, IR, act);
+                select_el(W, T, p, a.c.op + round, r0 * half + m0, nel, q.L, q.R, q.IL, q.IR, act);
                 if (act && W.real) {
-                    if (half == 1) st(a.SD, p, r, IL);
-                    else { vo[cur ^ 1][m] = L.o; vn[cur ^ 1][m] = L.n; io[cur ^ 1][m] = IL.o; in[cur ^ 1][m] = IL.n; }
+                    if (half == 1) st(a.SD, p, r0 + m, q.IL);
+                    else { vo[to + m] = q.L.o; vn[to + m] = q.L.n; io[to + m] = q.IL.o; in[to + m] = q.IL.n; }
                 }
             }
-            cur ^= 1;
-            __syncthreads();
+            from = to; to = RES - to;
+            if (NW > 1) __syncthreads(); else wave_sync();
         }
-        if (a.P2 == 1 && threadIdx.x < 3) { const Sh z = { 0, 0 }; st(a.SD, (int)threadIdx.x, r, z); }   // one candidate: index 0
+        if (a.len == 1)                                                 // one candidate: index 0
+            for (u32 j = W.t; j < nn; j += GT_TP) if (W.real && wave == 0) st(a.SD, p, r0 + j, Sh{ 0, 0 });
         W.drain();
     }
     W.flush(a.c.wire);

@@ -102,6 +102,7 @@ struct gt_train {
     u64 *Zacc;
 };
 
+static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len);
 static size_t pad8(size_t n) { return (n + 7) & ~(size_t)7; }
 
 static int dsh_alloc(DSh &s, size_t n, hipStream_t st)
@@ -613,12 +614,13 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     t->hc_open = false; t->hcp = nullptr; t->literal = false; t->lit_acc = nullptr; t->part_matmul = false; t->lt_level = ~0u; t->OHL = nullptr;
     hipStream_t s = c->stream;
     int rc = GT_OK;
-    const size_t wide = P2 > GT_ARGMAX_LDS ? nmax : 0;          // the arg-max of fewer candidates stays in LDS
+    // results of the tournament's rounds that run in launches of their own, at the widest level that counts columns
+    const size_t sel = H && select_by_rounds(c, nmax / 2, P2) ? nmax / 2 * (P2 / 2) : 0;
     struct { DSh *v; size_t n; } plan[] = {
         { &t->XT, d * N8 }, { &t->YT, K * N8 }, { &t->M, N }, { &t->T, nodes }, { &t->F, nodes },
         { &t->C, nmax * CW }, { &t->Cn, nmax * CW }, { &t->gamma, nmax * d }, { &t->Gn, nmax * d }, { &t->isLeaf, nmax },
-        { &t->SD, nmax }, { &t->split, nmax }, { &t->val[0], wide * P2 }, { &t->val[1], wide * P2 },
-        { &t->idx[0], wide * P2 }, { &t->idx[1], wide * P2 }, { &t->tval, N },
+        { &t->SD, nmax }, { &t->split, nmax }, { &t->val[0], sel }, { &t->val[1], sel / 2 },
+        { &t->idx[0], sel }, { &t->idx[1], sel / 2 }, { &t->tval, N },
         { &t->Clast, nmax * CW }, { &t->Glast, nmax * d }, { &t->Slast, nmax * d },
     };
     for (auto &pl : plan) { rc = pl.n ? dsh_alloc(*pl.v, pl.n, s) : GT_OK; if (rc != GT_OK) break; }
@@ -780,6 +782,36 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
 
 static void acct_select(gt_ctx *c, u64 n) { acct_ge(c, n); acct_b2a(c, n); acct_reshare(c, n, 2); }
 
+// A round of the tournament gets a launch of its own (about 6 us) where its pairs fill the chip by themselves, or the
+// arrays are too long for one workgroup's LDS, whose eight wavefronts would also run tile after tile (65,536
+// candidates of one node: 1,770 us in one workgroup, 74 like this).  Where the second line lies: 256 nodes of 512
+// candidates (65,536 pairs) 30 us in one launch, 39 with two rounds before it; 1,024 nodes (262,144 pairs) 117 us
+// with all rounds in a workgroup per node, 79 with two rounds before.
+static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len) { return len > GT_ARGMAX_LDS || (len > 32 && nh * (len / 2) >= 128 * (u64)c->resident); }
+static int argmax(gt_ctx *c, gt_train *t, u64 nh)
+{
+    u32 len = t->P2;
+    int in = -1;                                       // buffer that the last round wrote, -1: none, the scores
+    ArgmaxArgs m{}; m.score = t->Slast.v; m.SD = t->SD.v; m.nh = nh; m.d = t->d; m.first = 1;
+    for (; select_by_rounds(c, nh, len); len /= 2) {
+        const int out = in == 0 ? 1 : 0;
+        SelectArgs a{}; a.c = kc(c, c->op++); a.score = m.score; a.vin = m.vin; a.iin = m.iin; a.vout = t->val[out].v; a.iout = t->idx[out].v;
+        a.n = nh * (len / 2); a.d = t->d; a.first = m.first;
+        while (2u << a.lgh < len) a.lgh++;
+        GTCHK(launch(c, GT_KC_SMALL, k_select_round, gE(a.n), B64, a));
+        acct_select(c, a.n);
+        in = out; m.vin = a.vout; m.iin = a.iout; m.first = 0;
+    }
+    m.c = kc(c, c->op); m.len = len;
+    while (2u << m.lgh < len) m.lgh++;
+    const u64 per = len < 32 ? 32 / len : 1;
+    const dim3 g((unsigned)std::min<u64>((nh + per - 1) / per, 1u << 16));
+    GTCHK(len <= 32 ? launch(c, GT_KC_SMALL, k_argmax<1>, g, B64, m) : len <= 64 ? launch(c, GT_KC_SMALL, k_argmax<2>, g, dim3(2 * GT_LANES), m)
+          : len <= 128 ? launch(c, GT_KC_SMALL, k_argmax<4>, g, dim3(4 * GT_LANES), m) : launch(c, GT_KC_SMALL, k_argmax<8>, g, dim3(8 * GT_LANES), m));
+    for (; len > 1; len /= 2) { c->op++; acct_select(c, nh * (len / 2)); }
+    return GT_OK;
+}
+
 static int heuristic(gt_ctx *c, gt_train *t, u32 h)
 {
     const u64 nh = (u64)1 << h, d = t->d, nq = nh * d * 2, ns = nh * d;
@@ -790,11 +822,7 @@ static int heuristic(gt_ctx *c, gt_train *t, u32 h)
     acct_eq(c, nq); acct_b2a(c, nq);
     acct_div(c, nq);
     acct_reshare(c, ns, 1);
-    ArgmaxArgs m{}; m.c = kc(c, c->op); m.score = t->Slast.v; m.SD = t->SD.v; m.nh = (u32)nh; m.d = t->d; m.P2 = t->P2;
-    for (int x = 0; x < 2; x++) { m.val[x] = t->val[x].v; m.idx[x] = t->idx[x].v; }
-    GTCHK(launch(c, GT_KC_SMALL, k_argmax, dim3((unsigned)std::min<u64>(nh, 4096)), dim3(GT_LANES * GT_ARGMAX_WAVES), m));
-    for (u64 len = t->P2; len > 1; len /= 2) { c->op++; acct_select(c, nh * (len / 2)); }
-    return GT_OK;
+    return argmax(c, t, nh);
 }
 
 static int update_flags(gt_ctx *c, gt_train *t, u32 h)

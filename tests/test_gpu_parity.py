@@ -355,6 +355,59 @@ def test_train_argmax_widths(mods, seed, N, d, K, H):
     run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=6)
 
 
+# 8, 4 and 2 nodes per wavefront (4, 8 and 16 candidates after padding), fewer nodes than one wavefront
+# holds, a wavefront per node at its widest, two, four and eight, and a level whose first round runs in a
+# launch of its own because its 4096 x 32 pairs fill the chip
+@pytest.mark.parametrize("N,d,K,h", [(20, 3, 2, 5), (20, 5, 2, 1), (24, 12, 3, 4), (20, 32, 2, 2), (20, 33, 2, 3), (20, 128, 2, 2),
+                                     (20, 129, 2, 2), (30, 33, 2, 12)])
+def test_train_argmax_nodes_per_wavefront(mods, seed, N, d, K, h):
+    from oracle import X_C, X_SD, X_SCORE, X_F, X_T
+    from paper_2305_00645_amd import workloads as wl
+    w = wl.c5_level(N=N, d=d, K=K, h=h)
+    o, g = pair(mods, seed, tau=3, K=K)
+    o.train_create(o.share(w["X"].reshape(-1)), o.share(w["Y"].reshape(-1)), N, d, h + 1)
+    g.train_create(g.share_a(w["X"].reshape(-1)), g.share_a(w["Y"].reshape(-1)), N, d, h + 1)
+    # random statistics: every node has scores of its own
+    rng = np.random.default_rng(h * 1000 + d)
+    n1 = rng.integers(0, 9, size=(1 << h, d, K))
+    C = np.concatenate([n1.reshape(1 << h, d * K), n1.max(axis=1)], axis=1).astype(np.uint64)
+    st = [w["M"], w["Tprev"], w["F"], C.reshape(-1), w["gamma"].reshape(-1)]
+    o.train_import(h, *[o.share(a) for a in st])
+    g.train_import(h, *[g.share_a(a) for a in st])
+    o.train_level(h); g.train_level(h)
+    for what in (X_C, X_SCORE, X_SD, X_F, X_T):
+        same(g.train_export(what), o.train_export(what), "export %d" % what)
+    same_stats(o, g)
+    g.close()
+
+
+def test_train_argmax_time_follows_the_candidates(mods, seed):
+    """65,536 candidates cost about the same as one node's, as 128 nodes' or as 8192 nodes': the per-node
+    protocols of a level (score to update) may differ by a factor of 2.2 between the three.  Measured 1.4; with a
+    workgroup of eight wavefronts per node, whatever its number of candidates, 14 (one node) and 2.6 (8192)."""
+    _, gtree = mods
+    best = {}
+    for h, d in ((0, 65536), (7, 512), (13, 8)):
+        g = gtree.GTree(seed, tau=1, K=2, profile=True)
+        N, nh = 8, 1 << h
+        rng = np.random.default_rng(d)
+        X, y = (rng.random((N, d)) < 0.5).astype(np.uint64), np.arange(N) % 2
+        Y = np.zeros((N, 2), dtype=np.uint64); Y[np.arange(N), y] = 1
+        Xs, Ys = g.share_a(X.reshape(-1)), g.share_a(Y.reshape(-1))
+        g.train_create(Xs, Ys, N, d, h + 1)
+        st = [g.share_a(np.full(n, v, dtype=np.uint64)) for n, v in
+              ((N, nh // 2 - 1 if h else 0), (max(nh // 2, 1), 0), (nh, 1), (nh * 2 * (d + 1), 0), (nh * d, 1))]
+        ms = []
+        for _ in range(6):
+            g.train_import(h, *st)
+            g.stats_reset()
+            g.train_level(h)
+            ms.append(g.prof()["small"][0])
+        best[(h, d)] = min(ms)
+        g.close()
+    assert max(best.values()) < 2.2 * min(best.values()), best
+
+
 def test_train_deep_tree_few_samples(mods, seed):
     """Far more nodes than samples: 2^11 leaves for 40 samples, most nodes empty."""
     rng = np.random.default_rng(98)
