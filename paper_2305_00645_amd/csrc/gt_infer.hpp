@@ -10,24 +10,23 @@
 
 struct InferArgs {
     KCommon c;                 // c.op: first operation id of the batch
-    P6 feat, thr, leaf;        // per tree 2^H-1 ids, 2^H-1 thresholds (has_thr), 2^H labels, tree after tree
+    P6 feat, thr, leaf;        // per tree 2^H-1 ids, 2^H-1 thresholds (THR), 2^H labels, tree after tree
     P6 I, out;                 // NI x d row-major instances; results out[t*NI + i]
     u64 NI, N8;
     u32 d, H, ntrees;          // ntrees > 1: a forest; tree t takes the operation ids that the t-th of
-    int has_thr;               // ntrees single-tree batches in a row would take
-    u32 noct;                  // groups of 8 instances per tile, at most GT_INFER_MAX_OCT
+                               // ntrees single-tree batches in a row would take
+    u32 noct;                  // groups of 8 instances per tile, at most GT_INFER_OCT(NW)
 };
 
-// A workgroup is GT_INFER_WAVES wavefronts, each with the three parties in 21 lanes (WWire).  Its
-// 84 lanes per party split into noct groups of 8 instances x ncol columns: lane (o, cl) tests the
-// 8 instances of group o against columns cl, cl + ncol, ... of the current access and adds up its
+// A workgroup is NW wavefronts (4; 1 or 2 where a tile would leave most of the lanes of four idle), each
+// with the three parties in 21 lanes (WWire).  Its 21 NW lanes per party split into noct groups of 8
+// instances x ncol columns: lane (o, cl) tests the 8 instances of group o against columns cl, cl + ncol, ... of the current access and adds up its
 // share of the inner products in registers; the ncol partial sums meet in LDS.  The messages of
 // the tests stay inside a wavefront; the workgroup synchronises three times per access, where the
 // offline and zero-sharing words of the rows, evaluated by all lanes side by side, and the sums
 // change hands.
-#define GT_INFER_WAVES 4
-#define GT_INFER_LANES (GT_INFER_WAVES * GT_TP)
-#define GT_INFER_MAX_OCT 16
+#define GT_INFER_LANES(NW) ((NW) * GT_TP)
+#define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup at most: 19 KB of LDS per wavefront, two per SIMD
 // words per group of 8 instances.  Material of an access: r's arithmetic and Boolean components
 // [6][8], zero-sharing words [2 streams][3 keys][8]; of a comparison: [9][8] components (r, r's bits,
 // beta), beta's bits [8], mask words [2][3][8].  Values: index, id, threshold as [party][own, next][8].
@@ -227,21 +226,21 @@ struct InferWg {
 // wavefront, a barrier per message) and now: 10^6 instances x 64 features, depth 10, 46.6 -> 34.5 ms
 // (7.8e10 tests/s); 16 trees of depth 5 on 5,003 x 30 with thresholds 0.74 -> 0.58 ms; 10^4 x 16, depth
 // 7, thresholds 0.26 -> 0.16 ms (0.19 with the registers cut for two); one instance 153 -> 127 us (144).
-template <bool THR, int OCC>
-__global__ __launch_bounds__(64 * GT_INFER_WAVES, OCC) void k_infer(InferArgs a)
+template <bool THR, int OCC, int NW>
+__global__ __launch_bounds__(64 * NW, OCC) void k_infer(InferArgs a)
 {
-    __shared__ uint4 s_msg[GT_INFER_WAVES][GT_WMSG_QUADS];
-    __shared__ u64 s_rows[GT_INFER_WAVES][GT_EQ_ROWS];
-    __shared__ u64 s_cnt[GT_INFER_WAVES][6];
-    __shared__ u64 s_mat[GT_INFER_MAX_OCT][GT_INFER_MAT];
-    __shared__ u64 s_val[GT_INFER_MAX_OCT][3 * GT_INFER_VAL];
-    __shared__ u64 s_sum[GT_INFER_MAX_OCT][48];
+    __shared__ uint4 s_msg[NW][GT_WMSG_QUADS];
+    __shared__ u64 s_rows[NW][GT_EQ_ROWS];
+    __shared__ u64 s_cnt[NW][6];
+    __shared__ u64 s_mat[GT_INFER_OCT(NW)][GT_INFER_MAT];
+    __shared__ u64 s_val[GT_INFER_OCT(NW)][3 * GT_INFER_VAL];
+    __shared__ u64 s_sum[GT_INFER_OCT(NW)][48];
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     InferWg X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
     WWire &W = X.E.W;
     X.p = W.p; X.pn = W.pn; X.keys = a.c.keys;
-    X.ncol = GT_INFER_LANES / a.noct;
+    X.ncol = GT_INFER_LANES(NW) / a.noct;
     const u32 q = wave * GT_TP + W.t, o = q % a.noct;
     X.cl = q / a.noct; X.active = X.cl < X.ncol; X.one = X.cl == 0 && W.real;
     X.mat = s_mat[o]; X.val = s_val[o]; X.sum = s_sum[o];

@@ -1163,23 +1163,35 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
     return GT_OK;
 }
 
-// Groups of 8 instances per workgroup of k_infer: the 84 lanes of a party are split into noct groups
-// x 84/noct columns per step.  Few groups mean few steps per access and many workgroups; the rows'
-// part of an access (PRF blocks of its own, three barriers) costs about as much as 1.5 steps.  Two
-// workgroups fit a compute unit; one alone takes 0.65 of the time that two take together.
-static u32 infer_groups(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d)
+// Wavefronts per workgroup of k_infer and groups of 8 instances per workgroup: the 21 lanes of a party per
+// wavefront are split into noct groups x ncol columns per step.  Few groups mean few steps per access and many
+// workgroups; the rows' part of an access (PRF blocks of its own, three barriers) costs about as much as 1.5
+// steps.  Two wavefronts fit a SIMD; one alone takes 0.65 of the time that two take together.
+// Fewer than four wavefronts only where a tile cannot use them: where they take 22 % off this cost (many trees
+// on few instances, small tiles asked for by the caller), and where a step's few columns do not fetch the rows'
+// 128-byte lines more than twice (unless the rows stay in the L2s).  1,000 trees of depth 3 on one instance of 16
+// features: 199 us with four, 71 with one; 40 of them 60 and 60.  Without that margin, 300 trees of depth 6 on 30
+// instances of 50 features: 255 us with four, 280 with the two that the cost alone would choose; without the
+// lines, 3 * 10^5 instances of 150 features in tiles of 64, depth 4: 3.9 ms with four, 5.8 with two.
+struct InferShape { u32 nw, noct; };
+static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d)
 {
-    const u64 cus = c->resident / 4;
-    u32 best = 1;
+    const u64 simds = c->resident;
+    const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
+    InferShape best = { 4, 1 };
     double best_cost = 0;
-    for (u32 noct = 1; noct <= GT_INFER_MAX_OCT; noct++) {
-        const u64 ncol = GT_INFER_LANES / noct;
-        if (noct > 1 && GT_INFER_LANES / (noct - 1) == ncol && noct < GT_INFER_MAX_OCT && GT_INFER_LANES / (noct + 1) == ncol) continue;   // the next one has the same columns
-        double units = 0;
-        for (u32 n = 0; n <= H; n++) units += 1.5 + (double)((((u64)1 << n) + ncol - 1) / ncol) + (n < H ? 1.5 + (double)((d + ncol - 1) / ncol) : 0.0);
-        const u64 wgs = (ngrp + noct - 1) / noct * ntrees, full = wgs / (2 * cus), rest = wgs % (2 * cus);
-        const double cost = units * ((double)full + (rest == 0 ? 0.0 : rest <= cus ? 0.65 : 1.0));
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = noct; }
+    for (u32 nw = 4; nw >= 1; nw /= 2) {
+        const double four = best_cost;                         // nw < 4: the cost to beat
+        for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
+            if (c->infer_lgi && noct != (1u << c->infer_lgi) / 8) continue;
+            const u64 ncol = GT_INFER_LANES(nw) / noct, xsteps = (d + ncol - 1) / ncol;
+            if (nw < 4 && !in_l2 && xsteps > 2 * (((u64)d + 15) / 16)) continue;
+            double units = 0;
+            for (u32 n = 0; n <= H; n++) units += 1.5 + (double)((((u64)1 << n) + ncol - 1) / ncol) + (n < H ? 1.5 + (double)xsteps : 0.0);
+            const u64 waves = (ngrp + noct - 1) / noct * ntrees * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
+            const double cost = units * ((double)full + (rest == 0 ? 0.0 : rest <= simds ? 0.65 : 1.0));
+            if (best_cost == 0 || cost < best_cost && (nw == 4 || best.nw < 4 || cost < 0.78 * four)) { best_cost = cost; best = { nw, noct }; }
+        }
     }
     return best;
 }
@@ -1191,17 +1203,20 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
 {
     const size_t N8 = pad8(NI);
     InferArgs a{}; a.c = kc(c, c->op); a.feat = feat; a.thr = thr; a.leaf = leaf;
-    a.I = to_p6(I); a.out = to_p6(R); a.NI = NI; a.N8 = N8; a.d = d; a.H = H; a.ntrees = ntrees; a.has_thr = has_thr ? 1 : 0;
+    a.I = to_p6(I); a.out = to_p6(R); a.NI = NI; a.N8 = N8; a.d = d; a.H = H; a.ntrees = ntrees;
     const u32 S = has_thr ? 3 : 2;
     c->op += ntrees * (H * S + 1);
     const u64 ngrp = N8 / 8;
-    a.noct = c->infer_lgi ? (1u << c->infer_lgi) / 8 : infer_groups(c, ngrp, ntrees, H, d);
+    const InferShape sh = infer_shape(c, ngrp, ntrees, H, d);
+    a.noct = sh.noct;
     const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
-    const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * GT_INFER_WAVES);
+    const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * sh.nw);
     const bool alone = nitem <= c->resident / 4;               // at most one workgroup per compute unit: all registers are its own
     int rc;
-    if (alone) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1>, g, blk, a);
-    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2>, g, blk, a);
+    if (sh.nw == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 1>, g, blk, a);
+    else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 2>, g, blk, a);
+    else if (alone) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, 4>, g, blk, a);
+    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 4>, g, blk, a);
     for (u32 t = 0; t < ntrees; t++) {
         for (u32 n = 0; n < H; n++) {
             const u64 nel = ((u64)1 << n) * NI;

@@ -744,6 +744,46 @@ def test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d):
     forest.close(); g.close()
 
 
+# two and one wavefronts per workgroup: 1 group of 8 instances with 42 and with 21 columns a step (more and
+# fewer features), ragged tiles of 2, 3 and 4 groups
+@pytest.mark.parametrize("binary,ntrees,NI,H,d", [(False, 300, 1, 3, 16), (False, 700, 5, 2, 9), (True, 600, 9, 2, 23), (True, 300, 30, 2, 16),
+                                                  (False, 500, 20, 3, 5), (True, 900, 30, 1, 3)])
+def test_forest_on_few_instances(mods, seed, binary, ntrees, NI, H, d):
+    test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d)
+
+
+# forced tiles that take one wavefront (2 and 4 groups) or two (8 groups)
+@pytest.mark.parametrize("how,binary,NI,H,d", [(16, True, 9001, 2, 5), (32, False, 20003, 2, 5), (64, True, 40007, 2, 5)])
+def test_infer_small_forced_tiles(mods, seed, how, binary, NI, H, d):
+    test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
+
+
+def test_forest_time_on_one_instance(mods, seed):
+    """1,000 trees on one instance fit the wavefront slots at once: less than twice the time of 40 trees, which
+    leave most of the chip idle.  Measured 1.2; with four wavefronts per tree 3.3, from two fillings of the slots."""
+    _, gtree = mods
+    from paper_2305_00645_amd import workloads as wl
+    rng, H, d, ms = np.random.default_rng(9), 3, 16, {}
+    for ntrees in (40, 1000):
+        g = gtree.GTree(seed, profile=True)
+        trees = []
+        for _ in range(ntrees):
+            f, t, l = wl.random_tree(H, d, rng, thresholds=True)
+            trees.append(g.tree_import(g.share_a(f), g.share_a(t), g.share_a(l), H))
+        forest = g.forest_create(trees)
+        for tr in trees:
+            tr.close()
+        I = g.share_a(rng.integers(0, 1 << 16, size=d).astype(np.uint64))
+        times = []
+        for _ in range(6):
+            g.stats_reset()
+            g.infer_forest(forest, I, 1, d)
+            times.append(g.prof()["infer"][0])
+        ms[ntrees] = min(times)
+        forest.close(); g.close()
+    assert ms[1000] < 2 * ms[40], ms
+
+
 def test_infer_depth0(mods, seed):
     o, g = pair(mods, seed)
     lo, lg = o.share(u64([3])), g.share_a(u64([3]))
