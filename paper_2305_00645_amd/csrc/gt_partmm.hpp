@@ -49,7 +49,7 @@ struct PartMmArgs {
 // m = pass*16 + ri, ri < 16, of the 64 x 32 tile; lane l evaluates the block of row ri = l/4, sample
 // group l%4; words to scr[m*32 + sample].  The words under the next key are the next party's, in its
 // scratch (evaluating both keys per party took twice the passes: 154 us a level
-// for 19,997 x 101, 129 us now).
+// for 19,997 x 101, 131 us now).
 __device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const Key &own, u64 *scr, u32 pass, u32 kg, u64 ib, u32 lane)
 {
     const u32 m = pass * 16 + (lane >> 2), g = lane & 3;
@@ -60,6 +60,8 @@ __device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const Key &own,
     for (int q = 0; q < 8; q++) scr[m * 32 + g * 8 + q] = blk[q];
 }
 
+// Bound: vector work (the PRF, recombination, byte permutes) beside matrix-core time, one wavefront per SIMD on three of a
+// compute unit's four: 256 accumulators leave room for no second workgroup, and 47 registers spill (192 B a lane).
 __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 {
     __shared__ u64 s_wire[GT_LWIRE_WORDS];
@@ -69,7 +71,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
     __shared__ u32 s_tp[3][2 * PM_TP_WORDS];     // two transpose areas per wavefront, used alternately
     const int p = party_of_wave(), lane = threadIdx.x, pn = p == 2 ? 0 : p + 1;
     LWire W; W.init(s_wire, s_cnt);
-    const PartyKeys K = load_party_keys(a.c.keys, p);
+    const Key own = load_key(a.c.keys, p);
     u64 *scr = s_prf[p];
     const u64 *scrn = s_prf[pn];
     u32 *tp = s_tp[p];
@@ -92,8 +94,13 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
             // chunks of 32 node rows: first those of L_p x (OH own+next), then those of L_{p+1} x OH own.
             // The eight limb tiles of the next chunk are in flight while this one is transposed and
             // multiplied (the last iteration loads its own chunk again, unused, so that the number of
-            // loads in flight at every wait is the same).  One pass of the epilogue's zero-sharing
-            // words is evaluated per chunk, in the shadow of the matrix-core instructions.
+            // loads in flight at every wait is the same).  The four passes of the epilogue's zero-sharing
+            // words go one with each chunk, in the shadow of its matrix-core instructions; with the two
+            // chunks of at most 32 nodes two passes are left for after the loop, from the fifth chunk on
+            // words already there are evaluated again, because a branch or a second loop takes the passes out
+            // of the schedule of the first four chunks (19,997 x 101 with up to 32, 64, 256 nodes in the
+            // level before: 131, 155, 346 us like this; with a branch 165, 211, 520; with a second loop 205,
+            // 228, 410).
             v4i xn[8];
 #define PM_LOAD(X, CH)                                                                               \
             {                                                                                        \
@@ -141,7 +148,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
                     }
                     Bt[s] = o;
                 }
-                pm_prf_pass(a, K.own, scr, ch & 3, kg, ib, (u32)lane);
+                pm_prf_pass(a, own, scr, ch & 3, kg, ib, (u32)lane);
 #pragma unroll
                 for (int t = 0; t < 2; t++)
 #pragma unroll
@@ -169,7 +176,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
                     nl += live ? 1u : 0u;
                     xv[t][v] = live ? ld(a.XT, p, kcol * a.N8 + i) : Sh{ 0, 0 };
                 }
-            for (u32 pass = nch; pass < 4; pass++) pm_prf_pass(a, K.own, scr, pass, kg, ib, (u32)lane);   // fewer than four chunks
+            for (u32 pass = nch; pass < 4; pass++) pm_prf_pass(a, own, scr, pass, kg, ib, (u32)lane);   // fewer than four chunks
             W.nresh += 64u * nl;
             __syncthreads();                             // every party's words are there
             // epilogue, one half of the tile (32 columns, 16 per lane) at a time: recombine the limb
@@ -201,7 +208,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
             // zero sharing of the inner product: words ib*32 .. +31 of stream 0 under op+1, four blocks
             if (lane < 4) {
                 u64 blk[8];
-                chacha8(K.own, ib * 4 + lane, a.c.op + 1, 0, blk);
+                chacha8(own, ib * 4 + lane, a.c.op + 1, 0, blk);
 #pragma unroll
                 for (int q = 0; q < 8; q++) scr[lane * 8 + q] = blk[q];
             }

@@ -620,6 +620,32 @@ def test_partition_by_products(mods, seed, case):
     tree.close(); g.close()
 
 
+@pytest.mark.parametrize("N,d,H", [(75, 67, 7), (41, 130, 8), (33, 3, 9)])
+def test_partition_by_products_deep(mods, seed, N, d, H):
+    """More than one chunk of 32 nodes in the level before (64, 128 and 256 of them), columns just above one
+    and two groups of 64 or far below, a ragged last block of samples: both products' chunks and the passes of
+    zero-sharing words that are spread over them."""
+    from oracle import X_M, X_L, X_C, X_SD
+    rng = np.random.default_rng(10 * N + H)
+    K = 2
+    X = (rng.random((N, d)) < 0.5).astype(np.uint64)
+    y = rng.integers(0, K, N)
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    o, g = pair(mods, seed, tau=4, K=K)
+    o.train_create(o.share(X.reshape(-1)), o.share(Y.reshape(-1)), N, d, H)
+    g.train_create(g.share_a(X.reshape(-1)), g.share_a(Y.reshape(-1)), N, d, H)
+    o.train_set_partition(True); g.train_set_partition(True)
+    for h in range(H):
+        o.train_level(h); g.train_level(h)
+        for what in (X_M, X_L, X_C, X_SD):
+            same(g.train_export(what), o.train_export(what), "level %d, export %d" % (h, what))
+    o.train_finish()
+    g.train_finish().close()
+    same(g.train_export(X_M), o.train_export(X_M), "M at the label level")
+    same_stats(o, g)
+    g.close()
+
+
 def test_train_errors(mods, seed):
     Oracle, gtree = mods
     from paper_2305_00645_amd import workloads as wl
