@@ -824,7 +824,8 @@ def test_infer_depth0(mods, seed):
 # the shapes reach the variants of the statistics contraction: few nodes; 128 nodes with a
 # remainder of 4 columns beside a full group of 64; 256 nodes with a remainder of 18 columns;
 # exactly 64 columns; 64 nodes (two row tiles per workgroup) with a remainder above 32
-# columns; 32 nodes (one row tile per workgroup) with exactly 64 columns
+# columns; 32 nodes (one row tile per workgroup) with exactly 64 columns.  The fourth shape (exactly
+# 64 columns, 128 nodes) and the third keep the sums on the columns, the others on the leaf one-hot.
 @pytest.mark.parametrize("N,d,K,h", [(5000, 12, 4, 3), (1500, 16, 4, 7), (700, 40, 2, 8),
                                      (900, 15, 4, 7), (900, 24, 4, 6), (600, 31, 2, 5)])
 def test_single_level_from_imported_state(mods, seed, N, d, K, h):
@@ -859,6 +860,25 @@ def test_single_level_from_imported_state(mods, seed, N, d, K, h):
             assert C[r, d * K + c] == (sel & (y == c)).sum()
             assert np.array_equal(C[r, :d * K].reshape(d, K)[:, c], X[sel & (y == c)].sum(axis=0))
     same_stats(o, g)
+
+
+# columns stored once per component: two groups of 128 nodes with a remainder of 10 columns (narrow tiles) and of
+# 30 (a launch of its own); four row tiles with remainders of 18 and 38.  Sums on the columns: a remainder of 8
+# columns beside a full group, with two groups of 128 nodes
+@pytest.mark.parametrize("N,d,K,h", [(700, 100, 2, 8), (500, 110, 2, 8), (600, 40, 2, 7), (600, 50, 2, 7), (500, 17, 4, 8)])
+def test_single_level_operand_layouts(mods, seed, N, d, K, h):
+    test_single_level_from_imported_state(mods, seed, N, d, K, h)
+
+
+def test_train_sums_on_columns_with_narrow_remainder(mods, seed):
+    """72 columns and depth 9: the leaf one-hot has more rows than the columns, so the columns carry the sums at
+    every level, and their remainder of 8 beside a full group meets one, two and four row tiles per workgroup."""
+    rng = np.random.default_rng(179)
+    N, d, K = 60, 17, 4
+    X = (rng.random((N, d)) < 0.5).astype(np.uint64)
+    y = (X[:, 0].astype(np.int64) * 2 + X[:, 16].astype(np.int64) + rng.integers(0, 2, N)) % K
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=9), tau=3, every_level=False)
 
 
 def test_launch_and_message_pattern_is_data_independent(mods, seed):
