@@ -279,7 +279,7 @@ struct LimbTri { LimbMat m[3]; };
 // The zero-sharing words under key k_j are evaluated by party j's wavefront and also loaded by
 // party j-1, the other holder of that key.  Bound: memory (12 words read, 6 written).  2^24 products:
 // 0.92 ms with lanes on 8 consecutive elements each and both keys' blocks per party, 0.50 ms now (4.8 TB/s).
-struct MultArgs { KCommon c; P6 x, y, z; u64 n, N, N8; u32 K, CW; };
+struct MultArgs { KCommon c; P6 x, y, z; u64 n; u32 CW; };   // CW: MODE 2
 
 template <int MODE>
 __global__ __launch_bounds__(192) void k_mult(MultArgs a)

@@ -40,7 +40,7 @@ struct gt_ctx {
     hipStream_t stream;
     u32 *keys_d;
     u64 *wire_d;              // GT_WIRE_SLOTS x six counters filled by the kernels: payload bits party p sent to p+1 [2p], to p-1 [2p+1]
-    unsigned resident;        // workgroups of 192 lanes that fit on the device at once
+    unsigned simds;           // SIMDs of the device: four per compute unit
     gt_stats acc;
     bool profile;
     bool levelwise_infer;     // GT_FLAG_LEVELWISE_INFER
@@ -250,7 +250,7 @@ extern "C" int gt_ctx_create(gt_ctx **out, const gt_params *prm)
     gt_ctx *c = new (std::nothrow) gt_ctx();
     if (!c) return GT_ENOMEM;
     c->noalloc = false; c->scratch_d = nullptr;
-    c->op = 0; c->ev_used = 0; c->keys_d = nullptr; c->wire_d = nullptr; c->dacc = nullptr; c->dacc_words = 0; c->resident = 1024;
+    c->op = 0; c->ev_used = 0; c->keys_d = nullptr; c->wire_d = nullptr; c->dacc = nullptr; c->dacc_words = 0; c->simds = 1024;
     memset(&c->acc, 0, sizeof c->acc); memset(&c->prof, 0, sizeof c->prof);
     c->profile = (prm->flags & GT_FLAG_PROFILE) != 0;
     c->levelwise_infer = (prm->flags & GT_FLAG_LEVELWISE_INFER) != 0;
@@ -269,7 +269,7 @@ extern "C" int gt_ctx_create(gt_ctx **out, const gt_params *prm)
     }
     c->scratch_d = g_scratch_ptr[dev];
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-        c->resident = std::min<unsigned>(GT_MAX_BLOCKS, 4u * (unsigned)cus);
+        c->simds = std::min<unsigned>(GT_MAX_BLOCKS, 4u * (unsigned)cus);
     if (hipMalloc(&c->keys_d, sizeof keys) != hipSuccess) { delete c; return GT_ENOMEM; }
     if (hipMalloc(&c->wire_d, 6 * GT_WIRE_SLOTS * sizeof(u64)) != hipSuccess) { (void)hipFree(c->keys_d); delete c; return GT_ENOMEM; }
     if (hipMemcpy(c->keys_d, keys, sizeof keys, hipMemcpyHostToDevice) != hipSuccess ||
@@ -411,7 +411,7 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
 // 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
 static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps)
 {
-    const u64 half = c->resident, fills[] = { 1, 2, 4, 6, 8 };             // in halves of the slots
+    const u64 half = c->simds, fills[] = { 1, 2, 4, 6, 8 };             // in halves of the wavefront slots
     u64 best = 1;
     double best_cost = 0;
     for (u64 f : fills) {
@@ -432,8 +432,8 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
     const u64 nel = (u64)a.w * a.N;
     if (a.N && a.w) {
         // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
-        // four groups (the 32 samples of a sample block) of five adjacent columns, or ten of two:
-        // the 32-byte pieces that it stores per limb then lie side by side.
+        // four groups (the 32 samples of a sample block) of five adjacent columns, eight of two (at most three
+        // columns) or twenty of one: the 32-byte pieces that it stores per limb then lie side by side.
         a.rps = mode != GM_STORE || a.w == 1 ? 1 : (a.w <= 3 ? 2 : 5);
         a.gpt = a.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (a.rps == 2 ? 8 : 4);
         const u64 kstep = a.rps, nsteps = (a.w + kstep - 1) / kstep;
@@ -505,7 +505,7 @@ extern "C" int gt_oaa_static(gt_ctx *c, const gt_shares *W, size_t w, const gt_s
 // material side by side; above, the tiles alone fill the wavefront slots.
 // Scores of a level, 17 steps: up to 9,408 candidates' halves 29 us with four and about 65 with one; 18,816 (940 tiles,
 // the line) 68 us either way; 37,632 64 us with one.
-static bool few_elements(const gt_ctx *c, u64 n) { return (n + GT_EL - 1) / GT_EL <= c->resident; }
+static bool few_elements(const gt_ctx *c, u64 n) { return (n + GT_EL - 1) / GT_EL <= c->simds; }
 
 static void acct_div(gt_ctx *c, u64 n) { for (u32 t = 0; t <= c->tau; t++) { acct_ge(c, n); acct_b2a(c, n); acct_reshare(c, n, 1); } }
 
@@ -709,7 +709,7 @@ static int partition_matmul(gt_ctx *c, gt_train *t, u32 h)
     PartMmArgs pa{}; pa.c = kc(c, c->op); c->op += 2;
     pa.L = limbs_L(t); pa.OHL = t->OHL; pa.XT = t->XT.v; pa.M = t->M.v; pa.N = N; pa.N8 = t->N8; pa.nblk = t->nblk;
     pa.d = t->d; pa.dpad = dpad; pa.rpad = rpad;
-    GTCHK(launch(c, GT_KC_PARTMM, k_part_mm, dim3((unsigned)std::min<u64>(t->nblk, 16 * (u64)c->resident)), GT_BLOCK, pa));
+    GTCHK(launch(c, GT_KC_PARTMM, k_part_mm, dim3((unsigned)std::min<u64>(t->nblk, 16 * (u64)c->simds)), GT_BLOCK, pa));
     acct_reshare(c, N * d, 1);
     acct_reshare(c, N, 1);
     return GT_OK;
@@ -735,7 +735,6 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
         a.X = L; a.Y = totals_only ? limbs_Y(t) : limbs_B(t); a.B = a.Y;
         for (int p = 0; p < 3; p++) { a.A.m[p][0] = L.m[p]; a.A.m[p][1] = L.m[(p + 1) % 3]; }
     }
-    const u64 bcol = 0;         // the class columns' operand of the label level begins with them
     a.Zacc = t->Zacc;
     // wavefront arrangement: 4, 2 or 1 row tiles of 32 per workgroup, the rest over columns
     a.rt = nh > 64 ? 4 : (nh > 32 ? 2 : 1);
@@ -756,7 +755,7 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     // an XCD's compute units times (length + 4), where 4 blocks stand for the first fetch and the atomic adds of
     // a chunk's sums.  At least 8 blocks (19,997 samples: 57 us a level with 8, 71 with 2), 2 where few samples
     // leave the chain of a chunk's blocks (267: 9 us, 20 with 8).
-    const u64 wgs_per_chunk = (u64)(nw2 + nw1 + nns) * a.nrowgrp, per_xcd = c->resident / 32;
+    const u64 wgs_per_chunk = (u64)(nw2 + nw1 + nns) * a.nrowgrp, per_xcd = std::max(1u, c->simds / 4 / 8);
     u64 cb = CT_CHUNK_BLOCKS, best = ~(u64)0;
     for (u64 q = t->nblk <= 64 ? 2 : 8; q <= CT_CHUNK_BLOCKS; q++) {
         const u64 per = ((t->nblk + q - 1) / q + 7) / 8 * wgs_per_chunk, cost = (per + per_xcd - 1) / per_xcd * (q + 4);
@@ -765,13 +764,13 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     a.chunkblk = (u32)cb;
     a.nchunk = (u32)((t->nblk + cb - 1) / cb);
     if (nfull || narrow) {
-        a.nwide = nw2; a.ncoltiles = nfull; a.bcol0 = bcol; a.zcol0 = 0;
-        a.nns = nns; a.nbcol0 = bcol + (u64)nfull * 64; a.nzcol0 = nfull * 64;
+        a.nwide = nw2; a.ncoltiles = nfull; a.bcol0 = 0; a.zcol0 = 0;
+        a.nns = nns; a.nbcol0 = (u64)nfull * 64; a.nzcol0 = nfull * 64;
         GTCHK(launch(c, GT_KC_COUNT, k_count<2>, dim3(((a.nchunk + 7) / 8) * (nw2 + nns) * 8, 1, a.nrowgrp), B256, a));
     }
     if (nw1) {
         a.nns = 0;
-        a.nwide = nw1; a.ncoltiles = 1; a.bcol0 = bcol + (u64)nfull * 64; a.zcol0 = nfull * 64;
+        a.nwide = nw1; a.ncoltiles = 1; a.bcol0 = (u64)nfull * 64; a.zcol0 = nfull * 64;
         GTCHK(launch(c, GT_KC_COUNT, k_count<1>, dim3(((a.nchunk + 7) / 8) * nw1 * 8, 1, a.nrowgrp), B256, a));
     }
     CountFinArgs f{}; f.c = kc(c, op); f.Zacc = t->Zacc; f.C = t->C.v; f.n = nh * ncol; f.ncol = ncol; f.CW = t->CW; f.colbase = colbase;
@@ -787,7 +786,7 @@ static void acct_select(gt_ctx *c, u64 n) { acct_ge(c, n); acct_b2a(c, n); acct_
 // candidates of one node: 1,770 us in one workgroup, 74 like this).  Where the second line lies: 256 nodes of 512
 // candidates (65,536 pairs) 30 us in one launch, 39 with two rounds before it; 1,024 nodes (262,144 pairs) 117 us
 // with all rounds in a workgroup per node, 79 with two rounds before.
-static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len) { return len > GT_ARGMAX_LDS || (len > 32 && nh * (len / 2) >= 128 * (u64)c->resident); }
+static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len) { return len > GT_ARGMAX_LDS || (len > 32 && nh * (len / 2) >= 128 * (u64)c->simds); }
 static int argmax(gt_ctx *c, gt_train *t, u64 nh)
 {
     u32 len = t->P2;
@@ -1176,7 +1175,7 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
 struct InferShape { u32 nw, noct; };
 static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d)
 {
-    const u64 simds = c->resident;
+    const u64 simds = c->simds;
     const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
     InferShape best = { 4, 1 };
     double best_cost = 0;
@@ -1211,7 +1210,7 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     a.noct = sh.noct;
     const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
     const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * sh.nw);
-    const bool alone = nitem <= c->resident / 4;               // at most one workgroup per compute unit: all registers are its own
+    const bool alone = nitem <= c->simds / 4;               // at most one workgroup per compute unit: all registers are its own
     int rc;
     if (sh.nw == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 1>, g, blk, a);
     else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 2>, g, blk, a);
