@@ -20,9 +20,10 @@
  *    context must not overlap.  Device memory is allocated by the create/import calls;
  *    gt_train_level, gt_train_finish and gt_train_reset allocate nothing (the tree that
  *    gt_train_finish returns uses buffers made by gt_train_create, unless the tree of an
- *    earlier finish of the same object is still alive); gt_infer_batch, gt_oaa and
- *    gt_div keep a workspace in the context that grows on first use or for a larger
- *    batch (then they wait for the stream and allocate).
+ *    earlier finish of the same object is still alive); gt_oaa, gt_oaa_literal
+ *    and, level by level only, gt_infer_batch keep a workspace in the context that grows
+ *    on first use or for more rows (then they wait for the stream and allocate);
+ *    gt_train_create makes it large enough for the levels of its job.
  *  - Return value 0 = success, negative = error; nothing is thrown or aborted.
  *    After an error the output buffers are unspecified; the context stays usable
  *    unless the error is GT_EHIP.

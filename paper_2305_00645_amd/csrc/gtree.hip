@@ -424,6 +424,19 @@ static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps)
     }
     return best;
 }
+// The context's workspace of partial inner products.  Zero once: its users (k_dot_fin, k_lit_fin) leave every
+// word that they have read at zero again.
+static int grow_dacc(gt_ctx *c, size_t need)
+{
+    if (c->dacc_words >= need) return GT_OK;
+    (void)hipStreamSynchronize(c->stream);
+    if (c->dacc) (void)hipFree(c->dacc);
+    c->dacc = nullptr; c->dacc_words = 0;
+    if (hipMalloc(&c->dacc, need * 8) != hipSuccess) { c->dacc = nullptr; return GT_ENOMEM; }
+    c->dacc_words = need;
+    HIPCHK(hipMemsetAsync(c->dacc, 0, need * 8, c->stream));
+    return GT_OK;
+}
 // the equality grid with its accounting
 static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *ext = nullptr, size_t ext_words = 0)
 {
@@ -448,15 +461,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
                 if (need > ext_words) return GT_EINVAL;
                 GTCHK(launch(c, GT_KC_LOCAL, k_fill_words, g1(need), B256, ext, (u64)need, (u64)0));
                 a.dacc = ext;
-            } else if (c->dacc_words < need) {
-                (void)hipStreamSynchronize(c->stream);
-                if (c->dacc) (void)hipFree(c->dacc);
-                c->dacc = nullptr; c->dacc_words = 0;
-                if (hipMalloc(&c->dacc, need * 8) != hipSuccess) return GT_ENOMEM;
-                c->dacc_words = need;
-                // zero once: k_dot_fin leaves every word it has read at zero again
-                HIPCHK(hipMemsetAsync(c->dacc, 0, need * 8, c->stream));
-            }
+            } else GTCHK(grow_dacc(c, need));
             if (!ext) a.dacc = c->dacc;
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
@@ -649,6 +654,7 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         t->SQ = t->LQ + lq; t->YQ = t->BQ + bq;
         if (hipMemsetAsync(t->LQ, 0, lq + sq, s) != hipSuccess || hipMemsetAsync(t->BQ, 0, bq + yq, s) != hipSuccess) rc = GT_EHIP;
     }
+    if (rc == GT_OK) rc = grow_dacc(c, 6 * N8);                  // the levels' partitions allocate nothing
     if (rc != GT_OK) { (void)hipStreamSynchronize(s); train_free(t); return T.finish(rc); }
     rc = train_start(c, t, X, Y);
     rc = T.finish(rc);
@@ -960,14 +966,7 @@ extern "C" int gt_oaa_literal(gt_ctx *c, const gt_shares *W, size_t w, const gt_
     if (!c || !shares_ok(W, w) || !shares_ok(u, n) || !shares_ok(z, n) || w == 0 || w > 0xffffffffu) return GT_EINVAL;
     Timed T(c);
     const size_t N8 = pad8(n), need = 6 * N8;
-    if (c->dacc_words < need) {
-        (void)hipStreamSynchronize(c->stream);
-        if (c->dacc) (void)hipFree(c->dacc);
-        c->dacc = nullptr; c->dacc_words = 0;
-        if (hipMalloc(&c->dacc, need * 8) != hipSuccess) return T.finish(GT_ENOMEM);
-        c->dacc_words = need;
-        HIPCHK(hipMemsetAsync(c->dacc, 0, need * 8, c->stream));     // both users leave it at zero
-    }
+    GTCHK(grow_dacc(c, need));
     return T.finish(oaa_literal(c, false, to_p6(u), 0, w, n, N8, to_p6(W), 0, to_p6(W), c->dacc, to_p6(z), to_p6(z), 0));
 }
 

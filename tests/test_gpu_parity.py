@@ -464,6 +464,31 @@ def test_train_reset_starts_an_equal_job(mods, seed):
     t2.close(); t3.close()
 
 
+def test_levels_and_finish_allocate_nothing(mods, seed):
+    """The partial sums of a level's partition (6 x 100,000 words) are there when the first level begins."""
+    import torch
+    _, gtree = mods
+    N, d, H = 100000, 8, 3
+    rng = np.random.default_rng(31)
+    X, y = (rng.random((N, d)) < 0.5).astype(np.uint64), rng.integers(0, 2, N)
+    Y = np.zeros((N, 2), dtype=np.uint64); Y[np.arange(N), y] = 1
+    for job in range(2):                                  # the first one loads the kernels
+        g = gtree.GTree(seed, K=2)
+        Xs, Ys = g.share_a(X.reshape(-1)), g.share_a(Y.reshape(-1))
+        g.train_create(Xs, Ys, N, d, H)
+        torch.cuda.synchronize()
+        free = [torch.cuda.mem_get_info()[0]]
+        for h in range(H):
+            g.train_level(h)
+            torch.cuda.synchronize()
+            free.append(torch.cuda.mem_get_info()[0])
+        tree = g.train_finish()
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+        tree.close(); g.close()
+    assert len(set(free)) == 1, free
+
+
 def test_export_after_import_needs_a_level(mods, seed):
     Oracle, gtree = mods
     from oracle import X_C, X_M
