@@ -32,7 +32,7 @@ EQ_ALU_OPS = EQ_ALU_OPS_DEALER + EQ_ALU_OPS_ONLINE
 # sample's own row, leaf one-hot written as limb tiles
 # (56 for the level, whose tiles hold the sums too, and 25 for the label level, by their tests); the
 # one-launch inference reads every feature of an instance at least once per level
-EQ_HBM_BYTES = {"eqgrid": 1.6, "eqgrid_rows": 53.5, "eqgrid_store": 35.7, "infer": 25.0}
+EQ_HBM_BYTES = {"eqgrid": 1.6, "eqgrid_rows": 53.5, "eqgrid_store": 35.7, "infer": 25.7}
 SHADER_CLOCK_MEASURED_GHZ = 2.1  # under the equality grid's load (profiles/pmc_sq_micro.md); the peak below uses the nominal 2.4
 
 
@@ -351,7 +351,7 @@ def main():
             # the two launches of the contraction have different bounds: the level's (128 nodes x 260 columns)
             # is matrix-core work, the label level's (256 nodes x 4 class columns) streams L once
             "count": {"bound": "mfma", "achieved": 72.0 * macs_level / (lvl_cnt_ms / 1e3) / 1e12, "peak": 5000.0,
-                      "unit": "TOP/s", "traffic": 28.3e9,
+                      "unit": "TOP/s", "traffic": 28.7e9,
                       "note": "the contraction of the split-scoring level: ring MAC = 36 int8 limb products on the matrix "
                               "cores = 72 int8 ops; int8 dense peak 5.0 POP/s; %d ring MACs (every party's two products "
                               "are computed; the columns are stored once per component, the copy that both of its "

@@ -23,7 +23,8 @@ typedef uint32_t u32;
 // ---------------------------------------------------------------------------------
 // ChaCha block function, 8 rounds, as a counter-based PRF.  State words 12..15 are
 // (block lo, block hi, op, stream); output word w (64 bit) is the little-endian pair
-// (2w, 2w+1).  The key is wave-uniform and lives in scalar registers.
+// (2w, 2w+1).  A key is wave-uniform and in scalar registers (load_key) where a wavefront is a party, per lane and
+// in vector registers where its lanes take different roles (load_lane_key, ElTile, k_infer).
 struct Key { u32 k[8]; };
 
 __device__ __forceinline__ u32 rotl32(u32 x, int r) { return __builtin_rotateleft32(x, r); }

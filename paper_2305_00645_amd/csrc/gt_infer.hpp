@@ -219,13 +219,15 @@ struct InferWg {
     }
 };
 
-// OCC: workgroups per compute unit the registers are cut for; 1 for batches of at most one workgroup
-// per compute unit (nothing spills, and more could not be resident anyway).
+// OCC: wavefronts per SIMD the registers are cut for; 1 for batches of at most one workgroup of four
+// wavefronts per compute unit (nothing spills, and more could not be resident anyway).  With 256 registers for two
+// wavefronts 69 spill, 108 with thresholds (280 and 436 bytes a lane); 10^6 instances write 3.3 GB of scratch.
 // Bound: a large batch by the vector ALU (see k_eqgrid), a small one by the chain of an access: three
 // PRF blocks one after the other, nine rounds, three barriers.  Measured, before (one party per
 // wavefront, a barrier per message) and now: 10^6 instances x 64 features, depth 10, 46.6 -> 34.5 ms
 // (7.8e10 tests/s); 16 trees of depth 5 on 5,003 x 30 with thresholds 0.74 -> 0.58 ms; 10^4 x 16, depth
-// 7, thresholds 0.26 -> 0.16 ms (0.19 with the registers cut for two); one instance 153 -> 127 us (144).
+// 7, thresholds 0.26 -> 0.16 ms (0.19 with the registers cut for two); one instance 153 -> 127 us (144).  For NW
+// see infer_shape.
 template <bool THR, int OCC, int NW>
 __global__ __launch_bounds__(64 * NW, OCC) void k_infer(InferArgs a)
 {

@@ -637,9 +637,9 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 // Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, at
 // one per 4 cycles and SIMD, and takes about 4,900 cycles.  One wavefront per workgroup, two per
 // SIMD: the rows' public values, Boolean components and sums and the values of the next column
-// fit their 256 registers, and two barrier-free wavefronts keep the vector unit as busy as three
-// did; three had to spill, and every reload waited for the loads from HBM issued before it (GM_ROWS,
-// 64 columns of 10^6 samples: 1.17 ms spilling, 0.88 ms like this).  Before, with one party per
+// fit their 256 registers but for 8 in GM_ROWS and 4 with two sums, and two barrier-free wavefronts keep the
+// vector unit as busy as three did; three had to spill far more, and every reload waited for the loads from
+// HBM issued before it (GM_ROWS, 64 columns of 10^6 samples: 1.17 ms with three, 0.88 ms with two).  Before, with one party per
 // wavefront and ten workgroup barriers per step: array access 200,003 x 100 0.40 ms, now 0.28;
 // 10^6 samples x (64 + 128 nodes) 3.45 -> 2.67 ms, own rows 2 x 64 columns 2.35 -> 1.77 ms, leaf
 // grid of 128 + 256 nodes 6.28 -> 5.52 ms; 48,842 samples x 294 columns 0.31 -> 0.20 ms.
@@ -945,7 +945,7 @@ __device__ __forceinline__ void div_steps_el(WWire &W, ElTile<3> &T, u64 *s_mat,
     const int p = W.p;                                                                      \
     ElTile<3> T; T.keys = a.c.keys; T.mat = s_mat;
 
-// 100,003 quotients, 17 steps: 304 us with a party per wavefront, 118 us now (VALU: a PRF pass and 330
+// 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us now (VALU: a PRF pass and 330
 // instructions of protocol per step and 20 elements).
 struct DivArgs { KCommon c; P6 S, Q, quo; u64 n; u32 nsteps; };
 template <int NW>
@@ -1561,11 +1561,12 @@ __device__ __forceinline__ void count_narrow(const CountArgs &a, u64 x0, u32 nx,
     }
 }
 
-// Workgroup = 4 wavefronts = 128 rows x (32*NB) columns; NB = 2 for full groups of 64
-// columns, NB = 1 for a remainder of at most 32.  The kernel is limited by the rate at
-// which the L1 cache can fetch the two operands (about 24 KB per wavefront and
-// product), not by the matrix cores; the operands of the next product are in flight
-// while the current one is multiplied.
+// Workgroup = 4 wavefronts, each 32 rows x (32*NB) columns of one party: rt row tiles (4, 2 or 1, by the nodes)
+// x 4/rt tiles of columns and parties; NB = 2 for full groups of 64 columns, NB = 1 for a remainder of at
+// most 32.  Bound: with 128 rows and more the matrix cores (busy 0.73 at the 1.4 GHz that their power leaves:
+// 2.1 POP/s for 128 x 260 columns of 10^6 samples, a large int8 product of the vendor library reaches 2.0); with
+// few rows the rate at which the operands arrive (about 24 KB per wavefront and product, rows below 32 are
+// padding).  The operands of the next product are in flight while the current one is multiplied.
 template <int NB>
 __global__ __launch_bounds__(256) void k_count(CountArgs a)
 {
