@@ -715,7 +715,7 @@ def test_infer(mods, seed, binary, NI, H):
 @pytest.mark.parametrize("binary,NI,H,d", [(False, 333, 5, 16), (True, 1000, 7, 16), (True, 70, 9, 3), (False, 129, 3, 37), (True, 17, 0, 5)])
 def test_infer_paths_agree(mods, seed, how, binary, NI, H, d):
     """The level-by-level path and the one-launch path with each of its three tile shapes
-    (16, 32, 64 instances per workgroup; 32, 16, 8 columns per step, so column counts that
+    (16, 32, 64 instances per workgroup; 42, 21, 10 columns per step, so column counts that
     are not a multiple of the step and instance counts that leave a ragged tile) all give the
     oracle's shares, rounds, bytes and bits."""
     import plain_cart
