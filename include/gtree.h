@@ -22,8 +22,7 @@
  *    gt_train_finish returns uses buffers made by gt_train_create, unless the tree of an
  *    earlier finish of the same object is still alive); gt_oaa, gt_oaa_literal
  *    and, level by level only, gt_infer_batch keep a workspace in the context that grows
- *    on first use or for more rows (then they wait for the stream and allocate);
- *    gt_train_create makes it large enough for the levels of its job.
+ *    on first use or for more rows (then they wait for the stream and allocate).
  *  - Return value 0 = success, negative = error; nothing is thrown or aborted.
  *    After an error the output buffers are unspecified; the context stays usable
  *    unless the error is GT_EHIP.

@@ -99,7 +99,7 @@ struct gt_train {
     DSh M, T, F, C, Cn, gamma, Gn, isLeaf, SD, split;
     DSh val[2], idx[2], tval;
     DSh Clast, Glast, Slast;
-    u64 *Zacc;
+    u64 *Zacc, *dacc;                // sums of the contraction; behind them the partial inner products of the partition's grids
 };
 
 static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len);
@@ -454,6 +454,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         const u64 nkc = column_ranges(c, ntile, nsteps);
         a.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * kstep);
         a.nkc = (a.w + a.kchunk - 1) / a.kchunk;
+        u64 *const own = a.dacc;               // a training object's: zero, like the context's
         a.dacc = nullptr;
         if (mode != GM_STORE && a.nkc > 1) {
             const size_t need = (size_t)6 * a.N8;
@@ -461,8 +462,8 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
                 if (need > ext_words) return GT_EINVAL;
                 GTCHK(launch(c, GT_KC_LOCAL, k_fill_words, g1(need), B256, ext, (u64)need, (u64)0));
                 a.dacc = ext;
-            } else GTCHK(grow_dacc(c, need));
-            if (!ext) a.dacc = c->dacc;
+            } else if (own) a.dacc = own;
+            else { GTCHK(grow_dacc(c, need)); a.dacc = c->dacc; }
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
         const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
@@ -615,7 +616,7 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     const size_t N8 = pad8(N), nmax = (size_t)1 << H, nodes = ((size_t)2 << H) - 1, CW = (size_t)d * K + K;
     size_t P2 = 1; while (P2 < d) P2 *= 2;
     t->N = N; t->N8 = N8; t->d = d; t->K = K; t->H = H; t->CW = (u32)CW; t->level = 0; t->last = 0; t->P2 = (u32)P2;
-    t->finished = false; t->fresh_import = false; t->Zacc = nullptr; t->LQ = nullptr; t->BQ = nullptr; t->SQ = nullptr; t->YQ = nullptr; t->slot = nullptr;
+    t->finished = false; t->fresh_import = false; t->Zacc = nullptr; t->dacc = nullptr; t->LQ = nullptr; t->BQ = nullptr; t->SQ = nullptr; t->YQ = nullptr; t->slot = nullptr;
     t->hc_open = false; t->hcp = nullptr; t->literal = false; t->lit_acc = nullptr; t->part_matmul = false; t->lt_level = ~0u; t->OHL = nullptr;
     hipStream_t s = c->stream;
     int rc = GT_OK;
@@ -628,17 +629,19 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         { &t->idx[0], sel }, { &t->idx[1], sel / 2 }, { &t->tval, N },
         { &t->Clast, nmax * CW }, { &t->Glast, nmax * d }, { &t->Slast, nmax * d },
     };
-    for (auto &pl : plan) { rc = pl.n ? dsh_alloc(*pl.v, pl.n, s) : GT_OK; if (rc != GT_OK) break; }
+    for (auto &pl : plan) { if (rc != GT_OK) break; rc = pl.n ? dsh_alloc(*pl.v, pl.n, s) : GT_OK; }
     if (rc == GT_OK) {
         t->slot = new (std::nothrow) TreeSlot();
         if (!t->slot) rc = GT_ENOMEM;
         if (rc == GT_OK) rc = dsh_alloc(t->slot->feat, nmax - 1, s);
         if (rc == GT_OK) rc = dsh_alloc(t->slot->leaf, nmax, s);
     }
-    if (rc == GT_OK && hipMalloc(&t->Zacc, 3 * nmax * CW * 8) != hipSuccess) rc = GT_ENOMEM;
+    const size_t zacc = 3 * nmax * CW;
+    if (rc == GT_OK && hipMalloc(&t->Zacc, (zacc + 6 * N8) * 8) != hipSuccess) { t->Zacc = nullptr; rc = GT_ENOMEM; }
     if (rc == GT_OK && hipMalloc(&t->hcp, nmax * (2 * (size_t)d + 4) * 8) != hipSuccess) rc = GT_ENOMEM;
-    // zero once: k_count_fin leaves every word it has read at zero again
-    if (rc == GT_OK && hipMemsetAsync(t->Zacc, 0, 3 * nmax * CW * 8, s) != hipSuccess) rc = GT_EHIP;
+    // zero once: k_count_fin and k_dot_fin leave every word they have read at zero again
+    if (rc == GT_OK) t->dacc = t->Zacc + zacc;
+    if (rc == GT_OK && hipMemsetAsync(t->Zacc, 0, (zacc + 6 * N8) * 8, s) != hipSuccess) rc = GT_EHIP;
     t->nblk = (N + 31) / 32;
     t->Lrows = std::max<size_t>(32, (nmax + 31) / 32 * 32);
     t->Brows = (CW + 63) / 64 * 64 + 64;
@@ -654,7 +657,6 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         t->SQ = t->LQ + lq; t->YQ = t->BQ + bq;
         if (hipMemsetAsync(t->LQ, 0, lq + sq, s) != hipSuccess || hipMemsetAsync(t->BQ, 0, bq + yq, s) != hipSuccess) rc = GT_EHIP;
     }
-    if (rc == GT_OK) rc = grow_dacc(c, 6 * N8);                  // the levels' partitions allocate nothing
     if (rc != GT_OK) { (void)hipStreamSynchronize(s); train_free(t); return T.finish(rc); }
     rc = train_start(c, t, X, Y);
     rc = T.finish(rc);
@@ -682,10 +684,10 @@ static int partition(gt_ctx *c, gt_train *t, u32 h)
 {
     const u64 wprev = (u64)1 << (h - 1), base = wprev - 1;
     GridArgs a{}; a.u = t->M.v; a.base = base; a.w = (u32)wprev; a.N = t->N; a.N8 = t->N8;
-    a.W1 = t->T.v; a.w1off = base; a.out = t->tval.v; a.epi = 0;
+    a.W1 = t->T.v; a.w1off = base; a.out = t->tval.v; a.epi = 0; a.dacc = t->dacc;
     GTCHK(do_grid(c, GM_COMMON, false, 1, a));
     GridArgs b{}; b.u = t->tval.v; b.base = 0; b.w = t->d; b.N = t->N; b.N8 = t->N8;
-    b.XT = t->XT.v; b.out = t->M.v; b.prev = t->M.v; b.epi = 1;
+    b.XT = t->XT.v; b.out = t->M.v; b.prev = t->M.v; b.epi = 1; b.dacc = t->dacc;
     return do_grid(c, GM_ROWS, false, 1, b);
 }
 
