@@ -636,7 +636,7 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         if (rc == GT_OK) rc = dsh_alloc(t->slot->feat, nmax - 1, s);
         if (rc == GT_OK) rc = dsh_alloc(t->slot->leaf, nmax, s);
     }
-    const size_t zacc = 3 * nmax * CW;
+    const size_t zacc = (3 * nmax * CW + 31) / 32 * 32;         // what follows starts a line of its own
     if (rc == GT_OK && hipMalloc(&t->Zacc, (zacc + 6 * N8) * 8) != hipSuccess) { t->Zacc = nullptr; rc = GT_ENOMEM; }
     if (rc == GT_OK && hipMalloc(&t->hcp, nmax * (2 * (size_t)d + 4) * 8) != hipSuccess) rc = GT_ENOMEM;
     // zero once: k_count_fin and k_dot_fin leave every word they have read at zero again
