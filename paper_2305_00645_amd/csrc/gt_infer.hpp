@@ -33,6 +33,7 @@ struct InferArgs {
 #define GT_INFER_MAT 128
 #define GT_INFER_VAL 48
 
+template <int ISSUE>
 struct InferWg {
     EqWave E;
     u64 *mat, *val, *sum;        // of this lane's group: GT_INFER_MAT, 3 * GT_INFER_VAL, [2][3][8] words
@@ -51,7 +52,7 @@ struct InferWg {
         Key kv;
 #pragma unroll
         for (int i = 0; i < 8; i++) kv.k[i] = keys[key * 8 + i];
-        chacha8(kv, blk, op, stream, D);
+        chacha8<ISSUE>(kv, blk, op, stream, D);
     }
 
     // One array access: E[k] = [u - base == k] for k < w, converted to arithmetic, and
@@ -127,7 +128,7 @@ struct InferWg {
             u64 cd[8];
 #pragma unroll
             for (int s = 0; s < 8; s++) cd[s] = cpub[s] - col;
-            const u32 f = E.template tests<false>(op, (u64)col * ngrp + grp, cd, rho_o, rho_n, 0, 0, act ? live() : 0u, [&]() {
+            const u32 f = E.template tests<false, ISSUE>(op, (u64)col * ngrp + grp, cd, rho_o, rho_n, 0, 0, act ? live() : 0u, [&]() {
                 if (!ROWS && act) { Wk.o = w1o[col]; Wk.n = w1n[col]; }
                 if (!ROWS && NDOT == 2 && act && nd2) { Wk2.o = w2o[col]; Wk2.n = w2n[col]; }
             });
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_infer(InferArgs a)
     __shared__ u64 s_val[GT_INFER_OCT(NW)][3 * GT_INFER_VAL];
     __shared__ u64 s_sum[GT_INFER_OCT(NW)][48];
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
-    InferWg X;
+    InferWg<(OCC > 1 ? PRF_PAIR_LOOP : PRF_ALONE)> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
     WWire &W = X.E.W;
     X.p = W.p; X.pn = W.pn; X.keys = a.c.keys;

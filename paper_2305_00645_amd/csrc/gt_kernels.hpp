@@ -508,14 +508,14 @@ struct EqWave {
     // f = result xor beta, test s in bit eq_pos(s); beta's arithmetic components are in row(.,s).
     // early(): the loads of what the tests' results meet, issued after the PRF blocks (their registers
     // are free again) and in flight during the rounds.
-    template <bool HAS_G, class F>
+    template <bool HAS_G, int ISSUE, class F>
     __device__ __forceinline__ u32 tests(u32 op, u64 g, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
                                          u32 go, u32 gn, u32 nl, F early)
     {
         u32 bw;
         {
             u64 D[8];
-            chacha8(dlr, 3 * g + (u32)W.p, op, 4, D);
+            chacha8<ISSUE>(dlr, 3 * g + (u32)W.p, op, 4, D);
             wave_sync();
             const u32 x = (u32)D[6] & 0x1ffu;
             u64 *r = &row(0, 3 * W.p);
@@ -534,7 +534,7 @@ struct EqWave {
         u32 Ah[8], xo[8], xn[8];
         {
             u64 A[8], An[8];
-            chacha8(own, g, op, 1, A);
+            chacha8<ISSUE>(own, g, op, 1, A);
             W.pass64<8>(A, An, W.nx);
             // round 0, width 32: the high word onto the low word
 #pragma unroll
@@ -596,6 +596,7 @@ struct EqWave {
     // Row part of a grid: the edaBits of the lane's eight rows (dealer blocks i0..i0+7 of stream
     // 0, split over the lanes of the three parties), the masked values and their one opening.
     // u: the rows' values (in: own, next).  cpub = u + r, rho: Boolean components of r.
+    template <int ISSUE>
     __device__ __forceinline__ void open_rows(u32 op, u64 i0, const u64 (&uo)[8], const u64 (&un)[8], u64 (&cpub)[8],
                                               u64 (&rho_o)[8], u64 (&rho_n)[8], u32 bits)
     {
@@ -607,7 +608,7 @@ struct EqWave {
                 const int s = W.p + 3 * q;             // s = 8 (party 2): the unused row
                 if (h == 0) {
                     u64 D[8];
-                    chacha8(dlr, i0 + (u32)s, op, 0, D);
+                    chacha8<ISSUE>(dlr, i0 + (u32)s, op, 0, D);
                     wave_sync();
                     row(0, s) = D[1]; row(1, s) = D[2]; row(2, s) = D[0] - D[1] - D[2];
                     keep[q][0] = D[3]; keep[q][1] = D[4]; keep[q][2] = D[0] ^ D[3] ^ D[4];
@@ -644,7 +645,7 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 // array access 200,003 x 100 0.40 ms, now 0.27; 10^6 samples x (64 + 128 nodes) 3.45 -> 2.67 ms, own
 // rows 2 x 64 columns 2.35 -> 1.77 ms, leaf grid of 128 + 256 nodes 6.28 -> 6.2 ms (5.52 before it also
 // wrote the sums of the level); 48,842 samples x 294 columns 0.31 -> 0.20 ms.
-template <int MODE, bool HAS_G, int NDOT>
+template <int MODE, bool HAS_G, int NDOT, int ISSUE>
 __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 {
     __shared__ uint4 s_msg[GT_WMSG_QUADS];
@@ -675,7 +676,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
             ld8(own_of(a.u, p), i0, nvg, uo); ld8(nxt_of(a.u, p), i0, nvg, un);
             // the column ranges of one tile (and the adjacent columns of a step) replay the same
             // opening; it is counted once
-            E.open_rows(op, i0, uo, un, cpub, rho_o, rho_n, kbeg == 0 && ro == 0 ? 64u * live8(i0, nvg) : 0u);
+            E.template open_rows<ISSUE>(op, i0, uo, un, cpub, rho_o, rho_n, kbeg == 0 && ro == 0 ? 64u * live8(i0, nvg) : 0u);
 #pragma unroll
             for (int s = 0; s < 8; s++) cpub[s] -= a.base;
         }
@@ -706,7 +707,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
             u32 go = 0, gn = 0;
             if (HAS_G) { const Sh gk = ld(a.g, p, k); go = 0u - ((u32)gk.o & 1); gn = 0u - ((u32)gk.n & 1); }
             Sh Wk = { 0, 0 }, Wk2 = { 0, 0 };
-            const u32 f = E.template tests<HAS_G>(op, (u64)k * ngrp + grp, cd, rho_o, rho_n, go, gn, nl, [&]() {
+            const u32 f = E.template tests<HAS_G, ISSUE>(op, (u64)k * ngrp + grp, cd, rho_o, rho_n, go, gn, nl, [&]() {
                 if (MODE == GM_COMMON) { Wk.o = w1o[k]; Wk.n = w1n[k]; }
                 if (MODE == GM_COMMON && NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
             });
@@ -794,13 +795,13 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 
 // a wavefront of an element kernel: tiles of GT_EL elements, grid-stride; every lane of the wavefront
 // runs the same tiles.  LDS per wavefront: messages, material, counters.
-#define GT_EL_SHARED(NS)                                                                   \
+#define GT_EL_SHARED(NS, ISSUE)                                                                \
     __shared__ uint4 s_msg[GT_LANES];                                                       \
     __shared__ u64 s_mat[GT_EL_WORDS(NS)];                                                  \
     __shared__ u64 s_cnt[6];                                                                \
     WWire W; W.init(s_msg, s_cnt);                                                          \
     const int p = W.p;                                                                      \
-    ElTile<NS> T; T.keys = a.c.keys; T.mat = s_mat;
+    ElTile<NS, ISSUE> T; T.keys = a.c.keys; T.mat = s_mat;
 #define GT_FOR_EL(n) for (u64 tile_ = blockIdx.x, ntiles_ = ((u64)(n) + GT_EL - 1) / GT_EL; tile_ < ntiles_; tile_ += gridDim.x)
 __device__ __forceinline__ u32 el_live(u64 e0, u64 n) { return n - e0 < GT_EL ? (u32)(n - e0) : GT_EL; }
 
@@ -846,7 +847,7 @@ struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; }
 template <bool BOOL_OUT>
 __global__ __launch_bounds__(64) void k_eq(EqArgs a)
 {
-    GT_EL_SHARED(1)
+    GT_EL_SHARED(1, BOOL_OUT ? PRF_ALONE : PRF_PAIR)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
         const bool act = W.t < GT_EL && e < a.n;
@@ -867,7 +868,7 @@ __global__ __launch_bounds__(64) void k_eq(EqArgs a)
 struct GeArgs { KCommon c; P6 x, y, z; u64 n; };
 __global__ __launch_bounds__(64) void k_ge(GeArgs a)
 {
-    GT_EL_SHARED(2)
+    GT_EL_SHARED(2, PRF_PAIR)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
         const bool act = W.t < GT_EL && e < a.n;
@@ -908,7 +909,8 @@ __global__ __launch_bounds__(192) void k_cmp_step(CmpArgs a)
 // Restoring division, all steps of an element in one launch (the steps of different
 // elements do not interact): step t uses operation id op + t; b = [r >= Q]; r <- r - b Q;
 // quo <- 2 quo + b; r starts as S and is doubled between steps.  T: the step's material.
-__device__ __forceinline__ void div_step(WWire &W, const ElTile<3> &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
+template <class TileT>
+__device__ __forceinline__ void div_step(WWire &W, const TileT &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
 {
     if (!first) r = scale(r, 2);
     const Dealer D = T.dealer(W);
@@ -920,8 +922,8 @@ __device__ __forceinline__ void div_step(WWire &W, const ElTile<3> &T, int p, u3
 // Material of all steps of a division by NW wavefronts side by side, then the steps by the first of
 // them: with few elements the steps' PRF blocks would otherwise lie in the chain, one per step.
 // NW = 1: a slot that is dealt anew before every step.
-template <int NW>
-__device__ __forceinline__ void div_steps_el(WWire &W, ElTile<3> &T, u64 *s_mat, int p, u32 op, u64 e0, u32 nel, u32 nsteps, Sh Q, Sh &r, Sh &quo, bool act)
+template <int NW, class TileT>
+__device__ __forceinline__ void div_steps_el(WWire &W, TileT &T, u64 *s_mat, int p, u32 op, u64 e0, u32 nel, u32 nsteps, Sh Q, Sh &r, Sh &quo, bool act)
 {
     const u32 st3[3] = { 1, 2, 3 }, w = (u32)(e0 & 7) + W.t;
     if (NW > 1) {
@@ -944,7 +946,7 @@ __device__ __forceinline__ void div_steps_el(WWire &W, ElTile<3> &T, u64 *s_mat,
     const u32 wave_ = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);               \
     WWire W; W.init(s_msg[wave_], s_cnt[wave_]);                                            \
     const int p = W.p;                                                                      \
-    ElTile<3> T; T.keys = a.c.keys; T.mat = s_mat;
+    ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.keys = a.c.keys; T.mat = s_mat;
 
 // 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us now (VALU: a PRF pass and 330
 // instructions of protocol per step and 20 elements).
@@ -1033,7 +1035,8 @@ __global__ __launch_bounds__(64 * NW) void k_score(ScoreArgs a)
 
 // Compare-and-select of a tile: b = [right > left]; val = left + b (right-left); idx likewise (material
 // of operation `op`, elements from e0).
-__device__ __forceinline__ void select_el(WWire &W, ElTile<4> &T, int p, u32 op, u64 e0, u32 nel, Sh &L, Sh R, Sh &IL, Sh IR, bool act)
+template <class TileT>
+__device__ __forceinline__ void select_el(WWire &W, TileT &T, int p, u32 op, u64 e0, u32 nel, Sh &L, Sh R, Sh &IL, Sh IR, bool act)
 {
     const u32 st4[4] = { 1, 2, 3, 4 }, w = (u32)(e0 & 7) + W.t;
     T.deal(W, op, e0, st4, nel);
@@ -1068,7 +1071,7 @@ __device__ __forceinline__ SelectPair next_pair(const P6 &val, const P6 &idx, in
 struct SelectArgs { KCommon c; P6 score, vin, iin, vout, iout; u64 n; u32 d, lgh; int first; };
 __global__ __launch_bounds__(64) void k_select_round(SelectArgs a)
 {
-    GT_EL_SHARED(4)
+    GT_EL_SHARED(4, PRF_PAIR)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
         const bool act = W.t < GT_EL && e < a.n;
@@ -1140,7 +1143,7 @@ __global__ __launch_bounds__(64 * NW) void k_argmax(ArgmaxArgs a)
 struct LabelArgs { KCommon c; P6 C, lab; u64 n, dK, laboff; u32 K, CW; };
 __global__ __launch_bounds__(64) void k_labels(LabelArgs a)
 {
-    GT_EL_SHARED(4)
+    GT_EL_SHARED(4, PRF_ALONE)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
         const bool act = W.t < GT_EL && e < a.n;
@@ -1165,7 +1168,7 @@ __global__ __launch_bounds__(64) void k_labels(LabelArgs a)
 struct UpdateArgs { KCommon c; P6 SD, gamma, C, isLeaf, F, split; u64 n, base, dK; u32 d, K, CW, gblk; };
 __global__ __launch_bounds__(64) void k_update(UpdateArgs a)
 {
-    GT_EL_SHARED(3)
+    GT_EL_SHARED(3, PRF_ALONE)
     const u32 sn[3] = { 1, 2, 3 };
     if (blockIdx.x < a.gblk) {
         const u64 n = a.n * a.d;
@@ -1232,7 +1235,7 @@ __global__ __launch_bounds__(64) void k_update(UpdateArgs a)
 struct OnehotArgs { KCommon c; P6 T, OH; u64 base, n; u32 d; };
 __global__ __launch_bounds__(64) void k_onehot(OnehotArgs a)
 {
-    GT_EL_SHARED(1)
+    GT_EL_SHARED(1, PRF_ALONE)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
         const bool act = W.t < GT_EL && e < a.n;
@@ -1681,7 +1684,7 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
 struct CountFinArgs { KCommon c; u64 *Zacc; P6 C; u64 n; u32 ncol, CW; u64 colbase; };
 __global__ __launch_bounds__(64) void k_count_fin(CountFinArgs a)
 {
-    GT_EL_SHARED(1)
+    GT_EL_SHARED(1, PRF_ALONE)
     GT_FOR_EL(a.n) {
         const u64 e0 = tile_ * GT_EL, o = e0 + W.t, idx = (o / a.ncol) * a.CW + a.colbase + o % a.ncol;
         const bool act = W.t < GT_EL && o < a.n;

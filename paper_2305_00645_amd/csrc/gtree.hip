@@ -437,6 +437,14 @@ static int grow_dacc(gt_ctx *c, size_t need)
     HIPCHK(hipMemsetAsync(c->dacc, 0, need * 8, c->stream));
     return GT_OK;
 }
+template <int ISSUE>
+static int launch_grid(gt_ctx *c, int mode, int ndot, dim3 g, dim3 b, const GridArgs &a)
+{
+    if (mode == GM_STORE) return launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, ISSUE>, g, b, a);
+    if (mode == GM_ROWS) return launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1, ISSUE>, g, b, a);
+    if (ndot == 2) return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2, ISSUE>, g, b, a);
+    return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1, ISSUE>, g, b, a);
+}
 // the equality grid with its accounting
 static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *ext = nullptr, size_t ext_words = 0)
 {
@@ -467,12 +475,8 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
         const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
-        int rc;
-        if (mode == GM_STORE) rc = launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1>, g, B1, a);
-        else if (mode == GM_COMMON && ndot == 2) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2>, g, B1, a);
-        else if (mode == GM_COMMON) rc = launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1>, g, B1, a);
-        else rc = launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1>, g, B1, a);
-        GTCHK(rc);
+        // a wavefront that has its SIMD to itself runs the variant without issue priorities (see chacha8)
+        GTCHK(ntile * a.nkc <= c->simds ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
         if (a.dacc) GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, gE(a.N), B64, a));
     }
     acct_eq_grid(c, a.N, nel);
