@@ -18,8 +18,7 @@ struct InferArgs {
     u32 noct;                  // groups of 8 instances per tile, at most GT_INFER_OCT(NW)
 };
 
-// A workgroup is NW wavefronts (4; 1 or 2 where a tile would leave most of the lanes of four idle), each
-// with the three parties in 21 lanes (WWire).  Its 21 NW lanes per party split into noct groups of 8
+// A workgroup is NW wavefronts (1, 2 or 4), each with the three parties in 21 lanes (WWire).  Its 21 NW lanes per party split into noct groups of 8
 // instances x ncol columns: lane (o, cl) tests the 8 instances of group o against columns cl, cl + ncol, ... of the current access and adds up its
 // share of the inner products in registers; the ncol partial sums meet in LDS.  The messages of
 // the tests stay inside a wavefront; the workgroup synchronises three times per access, where the
@@ -220,17 +219,15 @@ struct InferWg {
     }
 };
 
-// OCC: wavefronts per SIMD the registers are cut for; 1 for batches of at most one workgroup of four
-// wavefronts per compute unit (nothing spills, and more could not be resident anyway).  With 256 registers for two
-// wavefronts 69 spill, 108 with thresholds (280 and 436 bytes a lane); 10^6 instances write 3.3 GB of scratch.
+// Four wavefronts per workgroup: at most one workgroup per compute unit, a wavefront has all registers of its SIMD; with one or
+// two the registers are cut for two wavefronts per SIMD (70 spill, 107 with thresholds).
 // Bound: a large batch by the vector ALU (see k_eqgrid), a small one by the chain of an access: three
-// PRF blocks one after the other, nine rounds, three barriers.  Measured, before (one party per
-// wavefront, a barrier per message) and now: 10^6 instances x 64 features, depth 10, 46.6 -> 34.5 ms
-// (7.8e10 tests/s); 16 trees of depth 5 on 5,003 x 30 with thresholds 0.74 -> 0.58 ms; 10^4 x 16, depth
-// 7, thresholds 0.26 -> 0.16 ms (0.19 with the registers cut for two); one instance 153 -> 127 us (144).  For NW
-// see infer_shape.
-template <bool THR, int OCC, int NW>
-__global__ __launch_bounds__(64 * NW, OCC) void k_infer(InferArgs a)
+// PRF blocks one after the other, nine rounds, three barriers.  Measured, with one party per wavefront and a barrier per
+// message, in workgroups of four, now: 10^6 instances x 64 features, depth 10, 46.6, 34.5, 27 ms;
+// 16 trees of depth 5 on 5,003 x 30 with thresholds 0.74, 0.58, 0.46 ms; 10^4 x 16, depth
+// 7, thresholds 0.26 -> 0.16 ms; one instance 153 -> 127 us.  For NW see infer_shape.
+template <bool THR, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 1 : 2) void k_infer(InferArgs a)
 {
     __shared__ uint4 s_msg[NW][GT_WMSG_QUADS];
     __shared__ u64 s_rows[NW][GT_EQ_ROWS];
@@ -239,7 +236,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_infer(InferArgs a)
     __shared__ u64 s_val[GT_INFER_OCT(NW)][3 * GT_INFER_VAL];
     __shared__ u64 s_sum[GT_INFER_OCT(NW)][48];
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
-    InferWg<(OCC > 1 ? PRF_PAIR_LOOP : PRF_ALONE)> X;
+    InferWg<NW == 4 ? PRF_ALONE : PRF_PAIR_LOOP> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
     WWire &W = X.E.W;
     X.p = W.p; X.pn = W.pn; X.keys = a.c.keys;

@@ -1168,35 +1168,46 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
 }
 
 // Wavefronts per workgroup of k_infer and groups of 8 instances per workgroup: the 21 lanes of a party per
-// wavefront are split into noct groups x ncol columns per step.  Few groups mean few steps per access and many
-// workgroups; the rows' part of an access (PRF blocks of its own, three barriers) costs about as much as 1.5
-// steps.  Two wavefronts fit a SIMD; one alone takes 0.65 of the time that two take together.
-// Fewer than four wavefronts only where a tile cannot use them: where they take 22 % off this cost (many trees
-// on few instances, small tiles asked for by the caller), and where a step's few columns do not fetch the rows'
-// 128-byte lines more than twice (unless the rows stay in the L2s).  1,000 trees of depth 3 on one instance of 16
-// features: 199 us with four, 71 with one; 40 of them 60 and 60.  Without that margin, 300 trees of depth 6 on 30
-// instances of 50 features: 255 us with four, 280 with the two that the cost alone would choose; without the
-// lines, 3 * 10^5 instances of 150 features in tiles of 64, depth 4: 3.9 ms with four, 5.8 with two.
+// wavefront are split into noct groups x ncol columns per step.  Four wavefronts while no compute unit gets more than one
+// workgroup: they share out a tile's columns and nothing else is there to fill the chip with.  Otherwise one wavefront with at
+// most four groups: it waits for no other one, and its loads touch the lines of at most 32 rows of instances at a
+// time (50,000 instances of 20 features, depth 6, thresholds: 405 us in workgroups of four, 308 in single ones;
+// 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of depth 5 on 5,003 x 30: 570 and 457 us).  Two where the caller
+// asks for tiles of 64 instances and there are more of these than compute units.
+// The cost, in steps of one wavefront on a full SIMD: an access costs 2.1 beside its steps (PRF blocks of its own,
+// the opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its SIMD
+// takes 0.85 to 0.9 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns
+// waits for lines that it had before.  Over 53 batches and forests of 1 to 700,000 instances this
+// picks within 2 % of the best of all 20 shapes on average, 9 % at worst.
 struct InferShape { u32 nw, noct; };
-static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d)
+static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d, bool has_thr)
 {
     const u64 simds = c->simds;
-    const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
-    InferShape best = { 4, 1 };
+    InferShape best = { 1, 1 };
     double best_cost = 0;
-    for (u32 nw = 4; nw >= 1; nw /= 2) {
-        const double four = best_cost;                         // nw < 4: the cost to beat
+    for (u32 nw = 4; nw >= 1; nw /= 2)
         for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
             if (c->infer_lgi && noct != (1u << c->infer_lgi) / 8) continue;
+            const u64 items = (ngrp + noct - 1) / noct * ntrees;
+            if (nw == 4 && items > simds / 4) continue;
+            if (nw == 2 && noct <= GT_INFER_OCT(1)) continue;
+            if (nw == 2 && !c->infer_lgi) continue;
             const u64 ncol = GT_INFER_LANES(nw) / noct, xsteps = (d + ncol - 1) / ncol;
-            if (nw < 4 && !in_l2 && xsteps > 2 * (((u64)d + 15) / 16)) continue;
             double units = 0;
-            for (u32 n = 0; n <= H; n++) units += 1.5 + (double)((((u64)1 << n) + ncol - 1) / ncol) + (n < H ? 1.5 + (double)xsteps : 0.0);
-            const u64 waves = (ngrp + noct - 1) / noct * ntrees * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
-            const double cost = units * ((double)full + (rest == 0 ? 0.0 : rest <= simds ? 0.65 : 1.0));
-            if (best_cost == 0 || cost < best_cost && (nw == 4 || best.nw < 4 || cost < 0.78 * four)) { best_cost = cost; best = { nw, noct }; }
+            for (u32 n = 0; n <= H; n++) {
+                units += 2.1 + (double)((((u64)1 << n) + ncol - 1) / ncol);
+                if (n < H) units += 2.1 + (double)xsteps + (has_thr ? 0.4 + 0.4 * (double)((8 + ncol - 1) / ncol) : 0.0);
+            }
+            double cost = 0.85 * units;
+            if (nw < 4) {
+                const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
+                const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
+                if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.26 * H * (double)xsteps;
+                const double last = rest == 0 ? 0.0 : rest <= simds ? 0.9 : full ? 0.9 + 0.1 * (double)(rest - simds) / (double)simds : 1.0;
+                cost = units * ((double)full + last);
+            }
+            if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { nw, noct }; }
         }
-    }
     return best;
 }
 
@@ -1211,16 +1222,14 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     const u32 S = has_thr ? 3 : 2;
     c->op += ntrees * (H * S + 1);
     const u64 ngrp = N8 / 8;
-    const InferShape sh = infer_shape(c, ngrp, ntrees, H, d);
+    const InferShape sh = infer_shape(c, ngrp, ntrees, H, d, has_thr);
     a.noct = sh.noct;
     const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
     const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * sh.nw);
-    const bool alone = nitem <= c->simds / 4;               // at most one workgroup per compute unit: all registers are its own
     int rc;
-    if (sh.nw == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 1>, g, blk, a);
-    else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 2>, g, blk, a);
-    else if (alone) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, 4>, g, blk, a);
-    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, 4>, g, blk, a);
+    if (sh.nw == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1>, g, blk, a);
+    else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2>, g, blk, a);
+    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 4>, g, blk, a);
     for (u32 t = 0; t < ntrees; t++) {
         for (u32 n = 0; n < H; n++) {
             const u64 nel = ((u64)1 << n) * NI;

@@ -761,6 +761,13 @@ def test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d):
     tree.close(); g.close()
 
 
+@pytest.mark.parametrize("binary,NI,H,d", [(False, 13001, 4, 9), (True, 20011, 1, 70), (False, 16391, 2, 33), (True, 33003, 2, 22), (False, 52005, 1, 12)])
+def test_infer_single_wavefront_tiles(mods, seed, binary, NI, H, d):
+    """Batches of more tiles than compute units: workgroups of one wavefront with one to four groups of 8 instances
+    (21, 10, 7, 5 columns a step, the last lanes idle where these do not divide 21), with a ragged last tile."""
+    test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d)
+
+
 @pytest.mark.parametrize("binary,ntrees,NI,H,d", [(True, 7, 150, 3, 9), (False, 3, 77, 4, 16), (True, 40, 1000, 2, 5)])
 def test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d):
     """Many shallow trees on one batch in one launch: shares, operation ids, rounds, bytes
