@@ -480,7 +480,7 @@ struct WWire {
         t = m - GT_TP * (u32)p;
         nx = p == 2 ? t : m + GT_TP; pv = p == 0 ? m + 2 * GT_TP : m - GT_TP;
         buf = region; cnt = s_cnt; nopen = 0; nresh = 0;
-        if (l < 6) cnt[l] = 0;
+        if (cnt && l < 6) cnt[l] = 0;
         wave_sync();
     }
     // store ND dwords, load those that lane `from` stored

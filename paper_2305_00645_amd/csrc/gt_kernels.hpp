@@ -503,6 +503,27 @@ struct EqWave {
     // daBit component c of this lane's test s
     __device__ __forceinline__ u64 &row(int c, int s) { return rows[(c * 9 + s) * (GT_TP + 1) + W.t]; }
 
+    // The daBits of the eight tests of block index g of operation op: this lane's block, components to the rows of `r` (row(0, 0)
+    // of a row area); returns the Boolean components of its three tests, in their positions.
+    template <int ISSUE>
+    __device__ __forceinline__ u32 deal_bits(u32 op, u64 g, u64 *r)
+    {
+        u64 D[8];
+        chacha8<ISSUE>(dlr, 3 * g + (u32)W.p, op, 4, D);
+        wave_sync();
+        const u32 x = (u32)D[6] & 0x1ffu;
+        r += 3 * W.p * (GT_TP + 1);
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            u64 *rq = r + q * (GT_TP + 1);
+            rq[0] = D[2 * q]; rq[9 * (GT_TP + 1)] = D[2 * q + 1];
+            rq[18 * (GT_TP + 1)] = (u64)((x >> (3 * q)) & 1) - D[2 * q] - D[2 * q + 1];
+        }
+        // per test three Boolean components in a nibble: bits 1, 2 of its field and beta xor both
+        const u32 z = ((x >> 1) & 0xdbu) | ((xor3l(x, x >> 1, x >> 2) & 0x49u) << 2);
+        return ((z & 7) << sh0) | (((z >> 3) & 7) << sh1) | (((z >> 6) & k2) << sh2);
+    }
+
     // [c - base - k == 0] (and the shared bit g) for the eight rows of block index g of operation
     // op: cd = c - base - k (public), rho the Boolean components of r.  Returns the opened
     // f = result xor beta, test s in bit eq_pos(s); beta's arithmetic components are in row(.,s).
@@ -512,40 +533,30 @@ struct EqWave {
     __device__ __forceinline__ u32 tests(u32 op, u64 g, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
                                          u32 go, u32 gn, u32 nl, F early)
     {
-        u32 bw;
-        {
-            u64 D[8];
-            chacha8<ISSUE>(dlr, 3 * g + (u32)W.p, op, 4, D);
-            wave_sync();
-            const u32 x = (u32)D[6] & 0x1ffu;
-            u64 *r = &row(0, 3 * W.p);
-#pragma unroll
-            for (int q = 0; q < 3; q++) {
-                u64 *rq = r + q * (GT_TP + 1);
-                rq[0] = D[2 * q]; rq[9 * (GT_TP + 1)] = D[2 * q + 1];
-                rq[18 * (GT_TP + 1)] = (u64)((x >> (3 * q)) & 1) - D[2 * q] - D[2 * q + 1];
-            }
-            // per test three Boolean components in a nibble: bits 1, 2 of its field and beta xor both
-            const u32 z = ((x >> 1) & 0xdbu) | ((xor3l(x, x >> 1, x >> 2) & 0x49u) << 2);
-            u32 b1[1] = { ((z & 7) << sh0) | (((z >> 3) & 7) << sh1) | (((z >> 6) & k2) << sh2) }, b2[1];
-            W.pass<1>(b1, b2, W.nx);
-            bw = b1[0] | b2[0] | W.buf[W.pv].x;
-        }
+        u32 b1[1] = { deal_bits<ISSUE>(op, g, &row(0, 0)) }, b2[1];
+        W.pass<1>(b1, b2, W.nx);
+        const u32 bw = b1[0] | b2[0] | W.buf[W.pv].x;
+        u64 A[8], An[8];
+        chacha8<ISSUE>(own, g, op, 1, A);
+        W.pass64<8>(A, An, W.nx);
+        return rounds<HAS_G>(A, An, bw, cd, rho_o, rho_n, go, gn, nl, early);
+    }
+
+    // The rounds of the eight tests: A, An the mask words under the party's two keys, bw the Boolean components of the daBits.
+    template <bool HAS_G, class F>
+    __device__ __forceinline__ u32 rounds(const u64 (&A)[8], const u64 (&An)[8], u32 bw, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
+                                          u32 go, u32 gn, u32 nl, F early)
+    {
         u32 Ah[8], xo[8], xn[8];
-        {
-            u64 A[8], An[8];
-            chacha8<ISSUE>(own, g, op, 1, A);
-            W.pass64<8>(A, An, W.nx);
-            // round 0, width 32: the high word onto the low word
+        // round 0, width 32: the high word onto the low word
 #pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const u32 dl = (u32)cd[s], dh = (u32)(cd[s] >> 32);
-                // t = rho with the complement of cd xored into component 0
-                const u32 tol = logic3<0xd2>((u32)rho_o[s], dl, M0), toh = logic3<0xd2>((u32)(rho_o[s] >> 32), dh, M0);
-                const u32 tnl = logic3<0xd2>((u32)rho_n[s], dl, M2), tnh = logic3<0xd2>((u32)(rho_n[s] >> 32), dh, M2);
-                xo[s] = xor3l(and3l(tol, tnl, toh, tnh), (u32)A[s], (u32)An[s]);
-                Ah[s] = (u32)(A[s] >> 32) ^ (u32)(An[s] >> 32);
-            }
+        for (int s = 0; s < 8; s++) {
+            const u32 dl = (u32)cd[s], dh = (u32)(cd[s] >> 32);
+            // t = rho with the complement of cd xored into component 0
+            const u32 tol = logic3<0xd2>((u32)rho_o[s], dl, M0), toh = logic3<0xd2>((u32)(rho_o[s] >> 32), dh, M0);
+            const u32 tnl = logic3<0xd2>((u32)rho_n[s], dl, M2), tnh = logic3<0xd2>((u32)(rho_n[s] >> 32), dh, M2);
+            xo[s] = xor3l(and3l(tol, tnl, toh, tnh), (u32)A[s], (u32)An[s]);
+            Ah[s] = (u32)(A[s] >> 32) ^ (u32)(An[s] >> 32);
         }
         early();
         W.reshare<8>(xo, xn);

@@ -1167,46 +1167,49 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
     return GT_OK;
 }
 
-// Wavefronts per workgroup of k_infer and groups of 8 instances per workgroup: the 21 lanes of a party per
-// wavefront are split into noct groups x ncol columns per step.  Four wavefronts while no compute unit gets more than one
-// workgroup: they share out a tile's columns and nothing else is there to fill the chip with.  Otherwise one wavefront with at
-// most four groups: it waits for no other one, and its loads touch the lines of at most 32 rows of instances at a
-// time (50,000 instances of 20 features, depth 6, thresholds: 405 us in workgroups of four, 308 in single ones;
-// 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of depth 5 on 5,003 x 30: 570 and 457 us).  Two where the caller
-// asks for tiles of 64 instances and there are more of these than compute units.
-// The cost, in steps of one wavefront on a full SIMD: an access costs 2.1 beside its steps (PRF blocks of its own,
-// the opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its SIMD
-// takes 0.85 to 0.9 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns
-// waits for lines that it had before.  Over 53 batches and forests of 1 to 700,000 instances this
-// picks within 2 % of the best of all 20 shapes on average, 9 % at worst.
-struct InferShape { u32 nw, noct; };
+// Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
+// groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
+// 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
+// other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
+// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of
+// depth 5 on 5,003 x 30: 570 and 436 us); of two wavefronts where the caller asks for tiles of 64 instances.
+// The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
+// opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its
+// SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
+// lines that it had before.  k_infer_ahead: 3.6 for a launch, 0.1 and 0.1 more for every 21 lanes an access (barriers), 0.32 a
+// step, 0.41 with thresholds, 0.27 for every instance of a half group that a lane compares; all but the launch times
+// 2.2 where the chip is full.  Over 53 batches and forests of 1 to 700,000 instances this picks within 2 % of the
+// best of all shapes on average, 16 % at worst.
+struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
 static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d, bool has_thr)
 {
     const u64 simds = c->simds;
-    InferShape best = { 1, 1 };
+    InferShape best = { 0, 1, 1 };
     double best_cost = 0;
-    for (u32 nw = 4; nw >= 1; nw /= 2)
-        for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
-            if (c->infer_lgi && noct != (1u << c->infer_lgi) / 8) continue;
-            const u64 items = (ngrp + noct - 1) / noct * ntrees;
-            if (nw == 4 && items > simds / 4) continue;
-            if (nw == 2 && noct <= GT_INFER_OCT(1)) continue;
-            if (nw == 2 && !c->infer_lgi) continue;
-            const u64 ncol = GT_INFER_LANES(nw) / noct, xsteps = (d + ncol - 1) / ncol;
-            double units = 0;
-            for (u32 n = 0; n <= H; n++) {
-                units += 2.1 + (double)((((u64)1 << n) + ncol - 1) / ncol);
-                if (n < H) units += 2.1 + (double)xsteps + (has_thr ? 0.4 + 0.4 * (double)((8 + ncol - 1) / ncol) : 0.0);
-            }
-            double cost = 0.85 * units;
-            if (nw < 4) {
-                const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
-                const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
-                if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.26 * H * (double)xsteps;
-                const double last = rest == 0 ? 0.0 : rest <= simds ? 0.9 : full ? 0.9 + 0.1 * (double)(rest - simds) / (double)simds : 1.0;
-                cost = units * ((double)full + last);
-            }
-            if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { nw, noct }; }
+    const auto steps = [&](u64 ncol) {
+        u64 n = H * ((d + ncol - 1) / ncol);
+        for (u32 h = 0; h <= H; h++) n += (((u64)1 << h) + ncol - 1) / ncol;
+        return (double)n;
+    };
+    const auto forced = [&](u32 noct) { return !c->infer_lgi || noct == (1u << c->infer_lgi) / 8; };
+    const auto take = [&](u32 nq, u32 nw, u32 noct, double cost) { if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { nq, nw, noct }; } };
+    for (u32 nq = 4; nq >= 1; nq /= 2)
+        for (u32 noct = 1; noct <= GT_AHEAD_OCT(nq); noct++) {
+            const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nq) / noct;
+            if (!forced(noct) || items > simds / nq) continue;
+            const double chain = (0.11 + 0.093 * nq) * (2 * H + 1) + (has_thr ? 0.41 : 0.32) * steps(ncol) + (has_thr ? 0.27 * (double)(H * ((4 + ncol - 1) / ncol)) : 0.0);
+            take(nq, 0, noct, 3.6 + chain * (1.0 + 1.17 * (double)(items * nq) / (double)simds));
+        }
+    for (u32 nw = 2; nw >= 1; nw /= 2)
+        for (u32 noct = nw == 1 ? 1 : GT_INFER_OCT(1) + 1; noct <= GT_INFER_OCT(nw); noct++) {
+            if (!forced(noct) || (nw == 2 && !c->infer_lgi)) continue;
+            const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nw) / noct;
+            double units = 2.4 * (2 * H + 1) + steps(ncol) + (has_thr ? H * (0.4 + 0.4 * (double)((8 + ncol - 1) / ncol)) : 0.0);
+            const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
+            if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.27 * H * (double)((d + ncol - 1) / ncol);
+            const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
+            const double last = rest == 0 ? 0.0 : rest <= simds ? 0.84 : full ? 0.84 + 0.16 * (double)(rest - simds) / (double)simds : 1.0;
+            take(0, nw, noct, units * ((double)full + last));
         }
     return best;
 }
@@ -1223,13 +1226,17 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     c->op += ntrees * (H * S + 1);
     const u64 ngrp = N8 / 8;
     const InferShape sh = infer_shape(c, ngrp, ntrees, H, d, has_thr);
-    a.noct = sh.noct;
+    a.noct = sh.noct; a.cus = std::max(1u, c->simds / 4);
     const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
     const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * sh.nw);
     int rc;
-    if (sh.nw == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1>, g, blk, a);
-    else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2>, g, blk, a);
-    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 4>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 4>, g, blk, a);
+    const dim3 aq(256 * sh.nq);
+    if (sh.nq == 4) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 4>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 4>, g, aq, a);
+    else if (sh.nq == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 2>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 2>, g, aq, a);
+    else if (sh.nq == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 1>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 1>, g, aq, a);
+    else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, false>, g, blk, a);
+    else if (a.noct <= 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, true>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, true>, g, blk, a);
+    else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, false>, g, blk, a);
     for (u32 t = 0; t < ntrees; t++) {
         for (u32 n = 0; n < H; n++) {
             const u64 nel = ((u64)1 << n) * NI;

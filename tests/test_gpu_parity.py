@@ -768,6 +768,15 @@ def test_infer_single_wavefront_tiles(mods, seed, binary, NI, H, d):
     test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d)
 
 
+@pytest.mark.parametrize("binary,NI,H,d", [(False, 1, 1, 1), (True, 4, 1, 64), (False, 5, 4, 22), (True, 2044, 8, 13), (False, 4101, 3, 43), (True, 8190, 4, 30),
+                                           (False, 10004, 2, 200)])
+def test_infer_ahead_tiles(mods, seed, binary, NI, H, d):
+    """Batches whose tiles are all on the chip at once: one column and more than a step has, one step and several (an odd and
+    an even number, so that either buffer of the material comes first), only the first half of a group's instances
+    and one of the second, 84, 42 and 21 lanes per party, several workgroups on a compute unit."""
+    test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d)
+
+
 @pytest.mark.parametrize("binary,ntrees,NI,H,d", [(True, 7, 150, 3, 9), (False, 3, 77, 4, 16), (True, 40, 1000, 2, 5)])
 def test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d):
     """Many shallow trees on one batch in one launch: shares, operation ids, rounds, bytes
