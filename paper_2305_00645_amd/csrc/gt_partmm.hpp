@@ -60,7 +60,7 @@ __device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const Key &own,
     for (int q = 0; q < 8; q++) scr[m * 32 + g * 8 + q] = blk[q];
 }
 
-// Bound: vector work (the PRF, recombination, byte permutes) beside matrix-core time, one wavefront per SIMD on three of a
+// More than GT_PM16_NODES nodes in the level before.  Bound: vector work (the PRF, recombination, byte permutes) beside matrix-core time, one wavefront per SIMD on three of a
 // compute unit's four: 256 accumulators leave room for no second workgroup, and 47 registers spill (192 B a lane).
 __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 {
@@ -221,5 +221,120 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
         __syncthreads();                         // the message slots and the scratch are rewritten by the next block
         W.drain();
     }
+    W.flush(a.c.wire);
+}
+
+// ---------------------------------------------------------------------------------
+// The same for at most GT_PM16_NODES nodes in the level before: both terms' nodes, 2 x 32, are the contraction of one
+// v_mfma_i32_16x16x64_i8, so a party's wavefront keeps the limbs of its 16 samples in 32 registers for all columns and a
+// tile of 16 columns needs 32 accumulators instead of the 256 that leave a SIMD of k_part_mm to one wavefront.  A step covers
+// 32 columns x 16 samples: one PRF pass, 72 matrix-core instructions, two barriers.
+// Bound: the vector ALU (PRF, recombination, three-term products) and the reads of X, with three wavefronts per SIMD.
+// 19,997 samples x 101 columns, 1 to 32 nodes in the level before: 131 us a level with k_part_mm, 51 now (with two wavefronts
+// per SIMD 56, with four, which spill 100 registers, 90).
+#define GT_PM16_NODES 32
+#define PM16_STRIDE 80                       // bytes between the samples of a limb in the staging area (64 and a pad)
+__global__ __launch_bounds__(192, 3) void k_part_mm16(PartMmArgs a)
+{
+    union Stage { unsigned char limb[8 * 16 * PM16_STRIDE]; struct { u64 prf[8 * GT_LANES], x[8 * GT_LANES]; }; };
+    __shared__ Stage s_w[3];                     // first the samples' limbs, then zero-sharing words under the party's own key and messages
+    __shared__ u64 s_cnt[6];
+    const int p = party_of_wave(), pn = p == 2 ? 0 : p + 1;
+    const u32 lane = threadIdx.x, n = lane & 15, kq = lane >> 4;
+    LWire W; W.init(nullptr, s_cnt);
+    const Key own = load_key(a.c.keys, p);
+    const u64 i0 = (u64)blockIdx.x * 16, i = i0 + n;
+    const bool ilive = i < a.N;
+    const u64 *xpo = own_of(a.XT, p), *xpn = nxt_of(a.XT, p), ic = ilive ? i : a.N - 1;
+    // L: lane = (term, node), 16 samples of a limb per load; afterwards lane = (sample, 16 of the 64 nodes of both terms)
+    v4i B[8];
+    {
+        const int j = lane < 32 ? p : pn;
+        const LimbMat m = j == 0 ? a.L.m[0] : (j == 1 ? a.L.m[1] : a.L.m[2]);
+        v4i x[8];
+#pragma unroll
+        for (int s = 0; s < 8; s++) x[s] = *(const v4i *)(m.base + limb_addr(m, i0 >> 5, s, lane & 31) + (i0 & 31));
+        unsigned char *st = s_w[p].limb + lane;
+#pragma unroll
+        for (int s = 0; s < 8; s++)
+#pragma unroll
+            for (int q = 0; q < 16; q++) st[(s * 16 + q) * PM16_STRIDE] = (unsigned char)((u32)x[s][q >> 2] >> (8 * (q & 3)));
+        wave_sync();
+#pragma unroll
+        for (int s = 0; s < 8; s++) B[s] = *(const v4i *)(s_w[p].limb + (s * 16 + n) * PM16_STRIDE + kq * 16);
+        wave_sync();
+    }
+    // the columns' limbs: row = column, own + next part with the first term's nodes, own part with the second's
+    const unsigned char *A0 = a.OHL + ((u64)(p * 2 + (kq >> 1)) * 8 * a.dpad + n) * a.rpad + (kq & 1) * 16;
+    u64 dacc = 0;
+    for (u32 k0 = 0; k0 < a.d; k0 += 32) {
+        {
+            u64 blk[8];
+            chacha8<PRF_PAIR>(own, (((u64)(k0 + (lane >> 1)) * a.N8 + i0) >> 3) + (lane & 1), a.c.op, 0, blk);
+#pragma unroll
+            for (int s = 0; s < 8; s++) s_w[p].prf[lane * 8 + s] = blk[s];
+        }
+        u64 z[8];
+        Sh x[8];
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            v4i A[8], acc[8];
+#pragma unroll
+            for (int s = 0; s < 8; s++) A[s] = *(const v4i *)(A0 + ((u64)s * a.dpad + k0 + t * 16) * a.rpad);
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                // (an existing element where this one does not exist: a load without a branch, cleared below)
+                const u32 k = k0 + t * 16 + kq * 4 + v;
+                const u64 e = (u64)(k < a.d ? k : a.d - 1) * a.N8 + ic;
+                x[t * 4 + v].o = xpo[e]; x[t * 4 + v].n = xpn[e];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; u++) acc[u] = v4i{ 0, 0, 0, 0 };
+#pragma unroll
+            for (int s = 0; s < 8; s++)
+#pragma unroll
+                for (int u = 0; u < 8 - s; u++) acc[s + u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[s], B[u], acc[s + u], 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                u64 r = 0;
+#pragma unroll
+                for (int u = 0; u < 8; u++) r += (u64)(long long)acc[u][v] << (8 * u);
+                z[t * 4 + v] = r;
+            }
+        }
+        __syncthreads();                             // every party's words are there
+#pragma unroll
+        for (int v = 0; v < 8; v++) {
+            const u32 w = ((v >> 2) * 16 + kq * 4 + (v & 3)) * 16 + n;
+            z[v] += s_w[p].prf[w] - s_w[pn].prf[w];
+            s_w[p].x[v * GT_LANES + lane] = z[v];
+        }
+#pragma unroll
+        for (int v = 0; v < 8; v++) {
+            const bool live = ilive && k0 + (v >> 2) * 16 + kq * 4 + (v & 3) < a.d;
+            W.nresh += live ? 64u : 0u;
+            x[v].o = live ? x[v].o : 0; x[v].n = live ? x[v].n : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 8; v++) dacc += prod3(Sh{ z[v], s_w[pn].x[v * GT_LANES + lane] }, x[v]);
+    }
+    // the lanes of a sample hold the sums over different columns
+    dacc += (u64)__shfl_xor((unsigned long long)dacc, 16, GT_LANES);
+    dacc += (u64)__shfl_xor((unsigned long long)dacc, 32, GT_LANES);
+    __syncthreads();                                 // the last messages have been read
+    if (lane < 2) {                                  // zero sharing of the inner product: words i0 .. i0 + 15 of stream 0 under op + 1
+        u64 blk[8];
+        chacha8(own, (i0 >> 3) + lane, a.c.op + 1, 0, blk);
+#pragma unroll
+        for (int q = 0; q < 8; q++) s_w[p].prf[lane * 8 + q] = blk[q];
+    }
+    __syncthreads();
+    Sh z = { dacc + (s_w[p].prf[n] - s_w[pn].prf[n]), 0 };
+    s_w[p].x[lane] = z.o;
+    W.nresh += ilive && kq == 0 ? 64u : 0u;
+    __syncthreads();
+    z.n = s_w[pn].x[lane];
+    if (ilive && kq == 0) st(a.M, p, i, scale(ld(a.M, p, i), 2) + z + pub(p, 1));
     W.flush(a.c.wire);
 }

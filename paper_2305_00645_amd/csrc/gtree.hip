@@ -721,7 +721,8 @@ static int partition_matmul(gt_ctx *c, gt_train *t, u32 h)
     PartMmArgs pa{}; pa.c = kc(c, c->op); c->op += 2;
     pa.L = limbs_L(t); pa.OHL = t->OHL; pa.XT = t->XT.v; pa.M = t->M.v; pa.N = N; pa.N8 = t->N8; pa.nblk = t->nblk;
     pa.d = t->d; pa.dpad = dpad; pa.rpad = rpad;
-    GTCHK(launch(c, GT_KC_PARTMM, k_part_mm, dim3((unsigned)std::min<u64>(t->nblk, 16 * (u64)c->simds)), GT_BLOCK, pa));
+    if (np <= GT_PM16_NODES) GTCHK(launch(c, GT_KC_PARTMM, k_part_mm16, dim3((unsigned)((N + 15) / 16)), GT_BLOCK, pa));
+    else GTCHK(launch(c, GT_KC_PARTMM, k_part_mm, dim3((unsigned)std::min<u64>(t->nblk, 16 * (u64)c->simds)), GT_BLOCK, pa));
     acct_reshare(c, N * d, 1);
     acct_reshare(c, N, 1);
     return GT_OK;

@@ -671,6 +671,13 @@ def test_partition_by_products_deep(mods, seed, N, d, H):
     g.close()
 
 
+@pytest.mark.parametrize("N,d,H", [(15, 31, 2), (17, 32, 3), (31, 33, 6), (32, 64, 2), (2049, 65, 3)])
+def test_partition_by_products_few_nodes(mods, seed, N, d, H):
+    """At most 32 nodes in the level before (16 samples x 32 columns per step): a last tile with one sample, without
+    its second half and full, column counts around a step and around the limbs' padding to 64."""
+    test_partition_by_products_deep(mods, seed, N, d, H)
+
+
 def test_train_errors(mods, seed):
     Oracle, gtree = mods
     from paper_2305_00645_amd import workloads as wl
