@@ -599,6 +599,14 @@ struct ElTile {
         }
         wave_sync();
     }
+    // a single stream, the first (the words of further ones, where the tile has room for them, are not used)
+    __device__ __forceinline__ void deal_mask(const WWire &W, u32 op, u64 e0, u32 stream, u32 nel_d)
+    {
+        u32 st[NS];
+#pragma unroll
+        for (int q = 0; q < NS; q++) st[q] = stream;
+        deal(W, op, e0, st, nel_d);
+    }
     // party W.p's components of the tile's element W.t
     __device__ __forceinline__ Dealer dealer(const WWire &W) const
     {

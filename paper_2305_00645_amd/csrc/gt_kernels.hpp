@@ -93,23 +93,29 @@ __global__ __launch_bounds__(256) void k_reconstruct(P6 in, u64 n, u64 *plain)
         plain[e] = in.o[0][e] + in.n[0][e] + in.o[2][e];
 }
 
-// local copy / strided gather of shares: dst[doff + e] = src[soff + e*sstride]
-__global__ __launch_bounds__(256) void k_copy(P6 dst, u64 doff, P6 src, u64 soff, u64 sstride, u64 n)
+// local copies of shares, up to three in a launch (blockIdx.y): dst[doff + e] = src[soff + e]
+struct CopyArgs { P6 dst[3], src[3]; u64 doff[3], soff[3], n[3]; };
+__global__ __launch_bounds__(256) void k_copy(CopyArgs a)
 {
-    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x)
+    const u32 q = blockIdx.y;
+    const P6 &dst = a.dst[q], &src = a.src[q];
+    const u64 doff = a.doff[q], soff = a.soff[q];
+    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < a.n[q]; e += (u64)gridDim.x * blockDim.x)
         for (int j = 0; j < 3; j++) {
-            dst.o[j][doff + e] = src.o[j][soff + e * sstride];
-            dst.n[j][doff + e] = src.n[j][soff + e * sstride];
+            dst.o[j][doff + e] = src.o[j][soff + e];
+            dst.n[j][doff + e] = src.n[j][soff + e];
         }
 }
 
 // dst[k][i] (row stride N8) = src[i][k] (row stride w): sample-contiguous layout.
 // 32 x 32 tiles through LDS so that both the reads and the writes are contiguous;
-// blockIdx.z selects one of the six planes.
-__global__ __launch_bounds__(256) void k_transpose(P6 dst, P6 src, u64 N, u64 N8, u32 w)
+// blockIdx.z selects one of the six planes, of the second pair of matrices from 6 on (a training's Y beside its X).
+__global__ __launch_bounds__(256) void k_transpose(P6 dst0, P6 src0, u32 w0, P6 dst1, P6 src1, u32 w1, u64 N, u64 N8)
 {
     __shared__ u64 tile[32][33];
-    const int pl = blockIdx.z, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
+    const P6 &dst = blockIdx.z < 6 ? dst0 : dst1, &src = blockIdx.z < 6 ? src0 : src1;
+    const u32 w = blockIdx.z < 6 ? w0 : w1;
+    const int pl = blockIdx.z % 6, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
     const u64 *in = pl < 3 ? src.o[pl] : src.n[pl - 3];
     u64 *out = pl < 3 ? dst.o[pl] : dst.n[pl - 3];
     const u64 ntx = (w + 31) / 32, nty = (N + 31) / 32;
@@ -154,37 +160,21 @@ __global__ __launch_bounds__(256) void k_fill_const(P6 dst, u64 off, u64 n, u64 
         }
 }
 
-// the state a training starts from, one launch (blockIdx.y): M, T, C := 0; F := 0, the root a leaf (1);
-// gamma of the root := 1
-struct StartArgs { P6 M, T, F, C, gamma; u64 N, nodes, nC, d; };
-__global__ __launch_bounds__(256) void k_start(StartArgs a)
-{
-    const u32 what = blockIdx.y;
-    const u64 n = what == 0 ? a.N : (what == 3 ? a.nC : (what == 4 ? a.d : a.nodes));
-    const P6 &dst = what == 0 ? a.M : (what == 1 ? a.T : (what == 2 ? a.F : (what == 3 ? a.C : a.gamma)));
-    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
-        const u64 c = what == 4 || (what == 2 && e == 0) ? 1 : 0;
-#pragma unroll
-        for (int j = 0; j < 3; j++) { dst.o[j][e] = j == 0 ? c : 0; dst.n[j][e] = j == 2 ? c : 0; }
-    }
-}
-
 // plain words := c
 __global__ __launch_bounds__(256) void k_fill_words(u64 *dst, u64 n, u64 c)
 {
     for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) dst[e] = c;
 }
 
-// The local steps that end a level, in one launch (blockIdx.y): 0: this level's statistics and 1: its
+// The local steps that end a level (k_split runs them beside the node split): 0: this level's statistics and 1: its
 // flags kept for export, 2: T takes the split decisions, 3: children inherit the flags, rows of
 // width d: Gn[2r] = Gn[2r+1] = gamma[r] (Sec. V-B; ndup = 0 at the last level).
 struct KeepArgs { P6 C, Clast, gamma, Glast, SD, T, Gn; u64 nC, nG, nh, base, ndup; u32 d; };
-__global__ __launch_bounds__(256) void k_keep(KeepArgs a)
+__device__ __forceinline__ void keep_part(const KeepArgs &a, u32 what, u64 first, u64 step)
 {
-    const u32 what = blockIdx.y;
     const u64 n = what == 0 ? a.nC : (what == 1 ? a.nG : (what == 2 ? a.nh : a.ndup));
     const P6 &src = what == 0 ? a.C : (what == 2 ? a.SD : a.gamma), &dst = what == 0 ? a.Clast : (what == 1 ? a.Glast : (what == 2 ? a.T : a.Gn));
-    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
+    for (u64 e = first; e < n; e += step) {
         const u64 to = what == 2 ? a.base + e : (what == 3 ? e + e / a.d * a.d : e);
 #pragma unroll
         for (int j = 0; j < 3; j++) {
@@ -282,7 +272,7 @@ struct LimbTri { LimbMat m[3]; };
 struct MultArgs { KCommon c; P6 x, y, z; u64 n; u32 CW; };   // CW: MODE 2
 
 template <int MODE>
-__global__ __launch_bounds__(192) void k_mult(MultArgs a)
+__device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blocks)
 {
     const int p = party_of_wave(), lane = threadIdx.x, pn = p == 2 ? 0 : p + 1;
     __shared__ u64 s_wire[GT_LWIRE_WORDS];
@@ -294,7 +284,7 @@ __global__ __launch_bounds__(192) void k_mult(MultArgs a)
     u64 *zo = own_of(a.z, p), *zn = nxt_of(a.z, p);
     const Sh one = pub(p, 1);
     const bool narrow = a.n <= 0xffffffffu;            // 32-bit division: a tenth of the instructions of the 64-bit one
-    for (u64 tile = blockIdx.x, nt = (a.n + 511) / 512; tile < nt; tile += gridDim.x) {
+    for (u64 tile = block, nt = (a.n + 511) / 512; tile < nt; tile += blocks) {
         u64 w[8];
         chacha8(own, tile * GT_LANES + lane, a.c.op, 0, w);
         tr_put(s_tr[p], lane, w);
@@ -334,6 +324,17 @@ __global__ __launch_bounds__(192) void k_mult(MultArgs a)
         __syncthreads();                               // the words in LDS are overwritten next
     }
     W.flush(a.c.wire);
+}
+__global__ __launch_bounds__(192) void k_mult(MultArgs a) { mult_tiles<0>(a, blockIdx.x, gridDim.x); }
+// End of a level in one launch: the first mblk workgroups the children's statistics, the others (in fours) the local copies.
+// (Two launches, each a few microseconds at small levels: training of 267 x 22, depth 4.)
+__global__ __launch_bounds__(192) void k_split(MultArgs m, KeepArgs k, u32 mblk)
+{
+    if (blockIdx.x < mblk) mult_tiles<2>(m, blockIdx.x, mblk);
+    else {
+        const u32 b = blockIdx.x - mblk, nb = (gridDim.x - mblk) / 4;
+        keep_part(k, b & 3, (u64)(b >> 2) * 192 + threadIdx.y * GT_LANES + threadIdx.x, (u64)nb * 192);
+    }
 }
 
 // One-time products of the learning protocol (Sec. V-B): column col = k*K + c,
@@ -402,9 +403,12 @@ __global__ __launch_bounds__(192, 2) void k_xy(XyArgs a)
 
 // class indicator columns into limb tiles: row c of Y (both forms) and, where the columns are
 // stored once per component (comps), row rowbase + c of C
-__global__ __launch_bounds__(256) void k_y_limbs(P6 YT, LimbSet Y, LimbTri C, int comps, u64 N, u64 N8, u32 K, u64 rowbase)
+struct YLimbsArgs { P6 YT; LimbSet Y; LimbTri C; int comps; u64 N, N8, rowbase; u32 K; };
+__device__ __forceinline__ void y_limbs(const YLimbsArgs &a)
 {
-    const u64 ngrp = N8 / 8, total = ngrp * K;
+    const P6 &YT = a.YT;
+    const u64 N = a.N, N8 = a.N8;
+    const u64 ngrp = N8 / 8, total = ngrp * a.K;
     for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (u64)gridDim.x * blockDim.x) {
         const u64 c = t / ngrp, i0 = (t % ngrp) * 8;
         for (int p = 0; p < 3; p++) {
@@ -414,10 +418,26 @@ __global__ __launch_bounds__(256) void k_y_limbs(P6 YT, LimbSet Y, LimbTri C, in
                 const bool live = i0 + s < N;
                 xo[s] = live ? YT.o[p][c * N8 + i0 + s] : 0; xn[s] = live ? xo[s] + YT.n[p][c * N8 + i0 + s] : 0;
             }
-            store_limbs8(Y.m[p][0], c, i0, xn);
-            store_limbs8(Y.m[p][1], c, i0, xo);
-            if (comps) store_limbs8(C.m[p], rowbase + c, i0, xo);
+            store_limbs8(a.Y.m[p][0], c, i0, xn);
+            store_limbs8(a.Y.m[p][1], c, i0, xo);
+            if (a.comps) store_limbs8(a.C.m[p], a.rowbase + c, i0, xo);
         }
+    }
+}
+
+// what a training starts from, one launch (blockIdx.y): M, T, C := 0; F := 0, the root a leaf (1); gamma of the
+// root := 1; 5: the class columns' limb tiles
+struct StartArgs { P6 M, T, F, C, gamma; u64 N, nodes, nC, d; };
+__global__ __launch_bounds__(256) void k_start(StartArgs a, YLimbsArgs yl)
+{
+    if (blockIdx.y == 5) { y_limbs(yl); return; }
+    const u32 what = blockIdx.y;
+    const u64 n = what == 0 ? a.N : (what == 3 ? a.nC : (what == 4 ? a.d : a.nodes));
+    const P6 &dst = what == 0 ? a.M : (what == 1 ? a.T : (what == 2 ? a.F : (what == 3 ? a.C : a.gamma)));
+    for (u64 e = (u64)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (u64)gridDim.x * blockDim.x) {
+        const u64 c = what == 4 || (what == 2 && e == 0) ? 1 : 0;
+#pragma unroll
+        for (int j = 0; j < 3; j++) { dst.o[j][e] = j == 0 ? c : 0; dst.n[j][e] = j == 2 ? c : 0; }
     }
 }
 
@@ -816,10 +836,37 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 #define GT_FOR_EL(n) for (u64 tile_ = blockIdx.x, ntiles_ = ((u64)(n) + GT_EL - 1) / GT_EL; tile_ < ntiles_; tile_ += gridDim.x)
 __device__ __forceinline__ u32 el_live(u64 e0, u64 n) { return n - e0 < GT_EL ? (u32)(n - e0) : GT_EL; }
 
+// z = B2A([x - y_pub == 0]) or the Boolean bit (BOOL_OUT).  300,007 elements: 51 us with a party per
+// wavefront, 23 us in the wavefront model, 20 with the issue priorities of PRF_PAIR.
+struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; };
+template <bool BOOL_OUT, class TileT>
+__device__ __forceinline__ void eq_tile(const EqArgs &a, WWire &W, TileT &T, u64 tile)
+{
+    const int p = W.p;
+    const u64 e0 = tile * GT_EL, e = e0 + W.t;
+    const bool act = W.t < GT_EL && e < a.n;
+    Sh v = { 0, 0 };
+    if (act) v = ld(a.x, p, a.xoff + e) - pub(p, a.ysub + (a.ypub ? a.ypub[e] : 0));
+    T.deal_mask(W, a.c.op, e0, 1, el_live(e0, a.n));
+    const Dealer D = T.dealer(W);
+    Sh b = eq_bit_mask(W, p, v, D, T.zb(W, 0, (u32)(e0 & 7) + W.t), act);
+    if (!BOOL_OUT) b = b2a(W, p, b, D, act);
+    if (act && W.real) st(a.z, p, e, b);
+    W.drain();
+}
+template <bool BOOL_OUT>
+__global__ __launch_bounds__(64) void k_eq(EqArgs a)
+{
+    GT_EL_SHARED(1, BOOL_OUT ? PRF_ALONE : PRF_PAIR)
+    GT_FOR_EL(a.n) eq_tile<BOOL_OUT>(a, W, T, tile_);
+    W.flush(a.c.wire);
+}
+
 // Completion of split inner products: z_p = partial sum + alpha (stream 2, second
 // output stream 3), reshare, epilogue as in k_eqgrid.  Rows in the lanes of the element kernels:
-// consecutive rows in consecutive lanes (eight rows per lane of 64 took 11 us for 48,842 rows).
-__global__ __launch_bounds__(64) void k_dot_fin(GridArgs a)
+// consecutive rows in consecutive lanes (eight rows per lane of 64 took 11 us for 48,842 rows).  The workgroups from finblk on
+// run equality tests that do not depend on it (a level's leaf flags; a launch of 5 us before).
+__global__ __launch_bounds__(64) void k_dot_fin(GridArgs a, u32 finblk, EqArgs eq)
 {
     __shared__ uint4 s_msg[GT_LANES];
     __shared__ u64 s_mat[GT_EL_WORDS(2)];
@@ -828,7 +875,12 @@ __global__ __launch_bounds__(64) void k_dot_fin(GridArgs a)
     const int p = W.p;
     ElTile<2> T; T.keys = a.c.keys; T.mat = s_mat;
     const Sh one = pub(p, 1);
-    GT_FOR_EL(a.N) {
+    if (blockIdx.x >= finblk) {
+        for (u64 tile = blockIdx.x - finblk; tile < (eq.n + GT_EL - 1) / GT_EL; tile += gridDim.x - finblk) eq_tile<true>(eq, W, T, tile);
+        W.flush(eq.c.wire);
+        return;
+    }
+    for (u64 tile_ = blockIdx.x; tile_ < (a.N + GT_EL - 1) / GT_EL; tile_ += finblk) {
         const u64 e0 = tile_ * GT_EL, i = e0 + W.t;
         const bool act = W.t < GT_EL && i < a.N;
         const u32 st2[2] = { 2, 3 }, w = (u32)(e0 & 7) + W.t;
@@ -847,29 +899,6 @@ __global__ __launch_bounds__(64) void k_dot_fin(GridArgs a)
                 st(q == 0 ? a.out : a.out2, p, i, z);
             }
         }
-        W.drain();
-    }
-    W.flush(a.c.wire);
-}
-
-// z = B2A([x - y_pub == 0]) or the Boolean bit (BOOL_OUT).  300,007 elements: 51 us with a party per
-// wavefront, 23 us now.
-struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; };
-template <bool BOOL_OUT>
-__global__ __launch_bounds__(64) void k_eq(EqArgs a)
-{
-    GT_EL_SHARED(1, BOOL_OUT ? PRF_ALONE : PRF_PAIR)
-    GT_FOR_EL(a.n) {
-        const u64 e0 = tile_ * GT_EL, e = e0 + W.t;
-        const bool act = W.t < GT_EL && e < a.n;
-        Sh v = { 0, 0 };
-        if (act) v = ld(a.x, p, a.xoff + e) - pub(p, a.ysub + (a.ypub ? a.ypub[e] : 0));
-        const u32 st1[1] = { 1 };
-        T.deal(W, a.c.op, e0, st1, el_live(e0, a.n));
-        const Dealer D = T.dealer(W);
-        Sh b = eq_bit_mask(W, p, v, D, T.zb(W, 0, (u32)(e0 & 7) + W.t), act);
-        if (!BOOL_OUT) b = b2a(W, p, b, D, act);
-        if (act && W.real) st(a.z, p, e, b);
         W.drain();
     }
     W.flush(a.c.wire);

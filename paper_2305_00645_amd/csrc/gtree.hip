@@ -347,38 +347,42 @@ extern "C" int gt_reconstruct_a(gt_ctx *c, const gt_shares *in, uint64_t *plain,
     return T.finish(rc);
 }
 
-static int copy6(gt_ctx *c, P6 dst, u64 doff, P6 src, u64 soff, u64 sstride, u64 n)
+// local copies, up to three in one launch
+struct Copies {
+    CopyArgs a{};
+    unsigned count = 0;
+    u64 most = 0;
+    void add(P6 dst, u64 doff, P6 src, u64 soff, u64 n)
+    {
+        if (!n) return;
+        a.dst[count] = dst; a.src[count] = src; a.doff[count] = doff; a.soff[count] = soff; a.n[count] = n;
+        count++; most = std::max(most, n);
+    }
+    int run(gt_ctx *c) const { return count ? launch(c, GT_KC_LOCAL, k_copy, dim3(g1(most).x, count), B256, a) : GT_OK; }
+};
+static int copy6(gt_ctx *c, P6 dst, u64 doff, P6 src, u64 soff, u64 n)
 {
-    if (!n) return GT_OK;
-    return launch(c, GT_KC_LOCAL, k_copy, g1(n), B256, dst, doff, src, soff, sstride, n);
+    Copies cp;
+    cp.add(dst, doff, src, soff, n);
+    return cp.run(c);
 }
 
 // ---- building blocks ---------------------------------------------------------------
-static int do_mult(gt_ctx *c, int mode, MultArgs a)
-{
-    a.c = kc(c, c->op++);
-    if (a.n) {
-        dim3 g(tiles8(a.n));
-        if (mode == 0) return launch(c, GT_KC_MULT, k_mult<0>, g, GT_BLOCK, a);
-        return launch(c, GT_KC_MULT, k_mult<2>, g, GT_BLOCK, a);
-    }
-    return GT_OK;
-}
-
 extern "C" int gt_mult(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t n, const gt_shares *z)
 {
     if (!c || !shares_ok(x, n) || !shares_ok(y, n) || !shares_ok(z, n)) return GT_EINVAL;
     Timed T(c);
     MultArgs a{}; a.x = to_p6(x); a.y = to_p6(y); a.z = to_p6(z); a.n = n;
-    int rc = do_mult(c, 0, a);
+    a.c = kc(c, c->op++);
+    int rc = n ? launch(c, GT_KC_MULT, k_mult, dim3(tiles8(n)), GT_BLOCK, a) : GT_OK;
     acct_reshare(c, n, 1);
     return T.finish(rc);
 }
 
-static int do_eq(gt_ctx *c, bool bool_out, P6 x, u64 xoff, const u64 *ypub, u64 ysub, P6 z, u64 n)
+static int do_eq(gt_ctx *c, bool bool_out, P6 x, u64 xoff, const u64 *ypub, u64 ysub, P6 z, u64 n, bool launched = false)
 {
     EqArgs a{}; a.c = kc(c, c->op++); a.x = x; a.xoff = xoff; a.ypub = ypub; a.ysub = ysub; a.z = z; a.n = n;
-    if (n) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, gE(n), B64, a)
+    if (n && !launched) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, gE(n), B64, a)
                           : launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a));
     acct_eq(c, n);
     if (!bool_out) acct_b2a(c, n);
@@ -406,12 +410,14 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
 // Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
 // replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
 // adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
-// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  Measured with 1, 3,
+// last wave; a SIMD with one wavefront takes 0.7 of the time of one with two.  `sums`: more than one range costs the
+// launch that completes the sums (5 us and more with the rows, in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
+// in one range 11 us, in two 10 and 5.  Measured with 1, 3,
 // 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
 // 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
-static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps)
+static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps, bool sums)
 {
-    const u64 half = c->simds, fills[] = { 1, 2, 4, 6, 8 };             // in halves of the wavefront slots
+    const u64 half = c->simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
     u64 best = 1;
     double best_cost = 0;
     for (u64 f : fills) {
@@ -419,7 +425,8 @@ static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps)
         const u64 len = (nsteps + n - 1) / n;
         n = (nsteps + len - 1) / len;
         const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
-        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5);
+        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.7 : 1.0)) * ((double)len + 2.5)
+                            + (sums && n > 1 ? 1.6 + 0.0035 * (double)ntile : 0.0);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
     }
     return best;
@@ -446,7 +453,8 @@ static int launch_grid(gt_ctx *c, int mode, int ndot, dim3 g, dim3 b, const Grid
     return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1, ISSUE>, g, b, a);
 }
 // the equality grid with its accounting
-static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *ext = nullptr, size_t ext_words = 0)
+// rider: equality tests that may run beside the sums' completion, as the operation after this one; n = 0 afterwards: they do
+static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *ext = nullptr, size_t ext_words = 0, EqArgs *rider = nullptr)
 {
     a.c = kc(c, c->op++);
     a.ndot = ndot;
@@ -459,7 +467,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         a.gpt = a.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (a.rps == 2 ? 8 : 4);
         const u64 kstep = a.rps, nsteps = (a.w + kstep - 1) / kstep;
         const u64 ntile = (a.N8 / 8 + a.gpt - 1) / a.gpt;
-        const u64 nkc = column_ranges(c, ntile, nsteps);
+        const u64 nkc = column_ranges(c, ntile, nsteps, mode != GM_STORE);
         a.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * kstep);
         a.nkc = (a.w + a.kchunk - 1) / a.kchunk;
         u64 *const own = a.dacc;               // a training object's: zero, like the context's
@@ -477,7 +485,12 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
         // a wavefront that has its SIMD to itself runs the variant without issue priorities (see chacha8)
         GTCHK(ntile * a.nkc <= c->simds ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
-        if (a.dacc) GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, gE(a.N), B64, a));
+        if (a.dacc) {
+            EqArgs eq{};
+            if (rider) { eq = *rider; eq.c = kc(c, c->op); rider->n = 0; }
+            const unsigned finblk = gE(a.N).x;
+            GTCHK(launch(c, GT_KC_SMALL, k_dot_fin, dim3(finblk + (eq.n ? gE(eq.n).x : 0)), B64, a, (u32)finblk, eq));
+        }
     }
     acct_eq_grid(c, a.N, nel);
     if (has_g) acct_and1(c, nel);
@@ -589,8 +602,8 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     const u32 d = t->d, K = t->K;
     const size_t N = t->N, N8 = t->N8, nmax = (size_t)1 << t->H, nodes = ((size_t)2 << t->H) - 1;
     // sample-contiguous copies of X and Y (Y goes behind the d*K product columns)
-    GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gT(N, d), B256, t->XT.v, to_p6(X), (u64)N, (u64)N8, d));
-    GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gT(N, K), B256, t->YT.v, to_p6(Y), (u64)N, (u64)N8, K));
+    dim3 gXY = gT(N, d); gXY.x = std::max(gXY.x, gT(N, K).x); gXY.z = 12;
+    GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gXY, B256, t->XT.v, to_p6(X), d, t->YT.v, to_p6(Y), K, (u64)N, (u64)N8));
     // one-time products X[i][k] * Y[i][c] and the class columns, as limb tiles
     XyArgs a{}; a.c = kc(c, c->op++); a.XT = t->XT.v; a.YT = t->YT.v; a.comps = t->comps; a.N = N; a.N8 = N8; a.K = K;
     if (t->comps) a.C = limbs_C(t); else a.B = limbs_B(t);
@@ -599,11 +612,11 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     const unsigned gx = (unsigned)std::max<u64>(1, std::min<u64>((N8 / 8 + 15) / 16, GT_MAX_BLOCKS / gy));
     GTCHK(launch(c, GT_KC_MULT, k_xy, dim3(gx, gy), GT_BLOCK, a));
     acct_reshare(c, (u64)N * d * K, 1);
-    GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1((N8 / 8) * K), B256, t->YT.v, limbs_Y(t), t->comps ? limbs_C(t) : LimbTri{}, (int)t->comps, (u64)N, (u64)N8, K, (u64)d * K));
+    YLimbsArgs yl{}; yl.YT = t->YT.v; yl.Y = limbs_Y(t); if (t->comps) yl.C = limbs_C(t); yl.comps = t->comps; yl.N = N; yl.N8 = N8; yl.K = K; yl.rowbase = (u64)d * K;
     // M = 0, T = 0, the root is a leaf with empty statistics, no candidate used yet
     StartArgs st{}; st.M = t->M.v; st.T = t->T.v; st.F = t->F.v; st.C = t->C.v; st.gamma = t->gamma.v;
     st.N = N; st.nodes = nodes; st.nC = nmax * t->CW; st.d = d;
-    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>(N, nmax * t->CW)).x, 5), B256, st));
+    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>({ N, nmax * t->CW, N8 / 8 * K })).x, 6), B256, st, yl));
     t->level = 0; t->last = 0; t->finished = false; t->fresh_import = false; t->lt_level = ~0u;
     return GT_OK;
 }
@@ -684,7 +697,7 @@ extern "C" int gt_train_reset(gt_ctx *c, gt_train *t, const gt_shares *X, const 
 }
 
 // data partition: Tval = T_level(h-1)[M - base], Dval = X[i][Tval], M <- 2M + Dval + 1
-static int partition(gt_ctx *c, gt_train *t, u32 h)
+static int partition(gt_ctx *c, gt_train *t, u32 h, bool &leaves)
 {
     const u64 wprev = (u64)1 << (h - 1), base = wprev - 1;
     GridArgs a{}; a.u = t->M.v; a.base = base; a.w = (u32)wprev; a.N = t->N; a.N8 = t->N8;
@@ -692,13 +705,17 @@ static int partition(gt_ctx *c, gt_train *t, u32 h)
     GTCHK(do_grid(c, GM_COMMON, false, 1, a));
     GridArgs b{}; b.u = t->tval.v; b.base = 0; b.w = t->d; b.N = t->N; b.N8 = t->N8;
     b.XT = t->XT.v; b.out = t->M.v; b.prev = t->M.v; b.epi = 1; b.dacc = t->dacc;
-    return do_grid(c, GM_ROWS, false, 1, b);
+    EqArgs eq{}; eq.x = t->F.v; eq.xoff = 2 * wprev - 1; eq.ysub = 1; eq.z = t->isLeaf.v; eq.n = 2 * wprev;   // the leaf flags of this level's nodes
+    GTCHK(do_grid(c, GM_ROWS, false, 1, b, nullptr, 0, &eq));
+    leaves = eq.n == 0;
+    return GT_OK;
 }
 
-static int leaf_onehot(gt_ctx *c, gt_train *t, u32 h)
+// leaves: the level's leaf flags are already on their way
+static int leaf_onehot(gt_ctx *c, gt_train *t, u32 h, bool leaves)
 {
     const u64 nh = (u64)1 << h, base = nh - 1;
-    GTCHK(do_eq(c, true, t->F.v, base, nullptr, 1, t->isLeaf.v, nh));
+    GTCHK(do_eq(c, true, t->F.v, base, nullptr, 1, t->isLeaf.v, nh, leaves));
     GridArgs a{}; a.u = t->M.v; a.base = base; a.w = (u32)nh; a.N = t->N; a.N8 = t->N8;
     a.g = t->isLeaf.v; a.L = limbs_L(t);
     a.sums = t->comps && h < t->H;                      // the label level's totals take the class columns' sums
@@ -883,11 +900,12 @@ static int node_split(gt_ctx *c, gt_train *t, u32 h)
     const bool dup = h + 1 <= t->H && 2 * nh <= ((u64)1 << t->H);
     KeepArgs k{}; k.C = t->C.v; k.Clast = t->Clast.v; k.gamma = t->gamma.v; k.Glast = t->Glast.v; k.SD = t->SD.v; k.T = t->T.v; k.Gn = t->Gn.v;
     k.nC = nh * CW; k.nG = nh * d; k.nh = nh; k.base = base; k.ndup = dup ? nh * d : 0; k.d = t->d;
-    GTCHK(launch(c, GT_KC_LOCAL, k_keep, dim3(g1(nh * CW).x, 4), B256, k));
     t->last = h;
     // children: statistics inherited unless the node was split
     MultArgs m{}; m.x = t->C.v; m.y = t->split.v; m.z = t->Cn.v; m.n = nh * CW; m.CW = t->CW;
-    GTCHK(do_mult(c, 2, m));
+    m.c = kc(c, c->op++);
+    const unsigned mblk = tiles8(m.n), kblk = 4 * blocks_for(nh * CW, 192);
+    GTCHK(launch(c, GT_KC_MULT, k_split, dim3(mblk + kblk), GT_BLOCK, m, k, mblk));
     acct_reshare(c, nh * CW, 1);
     std::swap(t->C, t->Cn);
     if (dup) std::swap(t->gamma, t->Gn);
@@ -988,8 +1006,9 @@ extern "C" int gt_train_level(gt_ctx *c, gt_train *t, uint32_t h)
         if (rc == GT_OK) rc = leaf_bits_literal(c, t, h);
         if (rc == GT_OK) rc = count_literal(c, t, h, false);
     } else {
-        if (h > 0) rc = t->part_matmul ? partition_matmul(c, t, h) : partition(c, t, h);
-        if (rc == GT_OK) rc = leaf_onehot(c, t, h);
+        bool leaves = false;
+        if (h > 0) rc = t->part_matmul ? partition_matmul(c, t, h) : partition(c, t, h, leaves);
+        if (rc == GT_OK) rc = leaf_onehot(c, t, h, leaves);
         if (rc == GT_OK) rc = count(c, t, h, false);
     }
     if (rc == GT_OK && t->hc_open) rc = heuristic_open(c, t, h);
@@ -1027,8 +1046,9 @@ extern "C" int gt_train_finish(gt_ctx *c, gt_train *t, gt_tree **out)
         if (rc == GT_OK) rc = leaf_bits_literal(c, t, H);
         if (rc == GT_OK) rc = count_literal(c, t, H, true);
     } else {
-        if (H > 0) rc = t->part_matmul ? partition_matmul(c, t, H) : partition(c, t, H);
-        if (rc == GT_OK) rc = leaf_onehot(c, t, H);
+        bool leaves = false;
+        if (H > 0) rc = t->part_matmul ? partition_matmul(c, t, H) : partition(c, t, H, leaves);
+        if (rc == GT_OK) rc = leaf_onehot(c, t, H, leaves);
         if (rc == GT_OK) rc = count(c, t, H, true);
     }
     // label = first maximum of the class totals, into the last level of T
@@ -1038,7 +1058,6 @@ extern "C" int gt_train_finish(gt_ctx *c, gt_train *t, gt_tree **out)
         rc = launch(c, GT_KC_SMALL, k_labels, gE(nh), B64, la);
         for (u32 cl = 1; cl < t->K; cl++) acct_select(c, nh);
     }
-    if (rc == GT_OK) rc = copy6(c, t->Clast.v, 0, t->C.v, 0, 1, nh * t->CW);
     gt_tree *tr = nullptr;
     if (rc == GT_OK) {
         if (t->slot && !t->slot->in_use) {       // the buffers allocated with the training object
@@ -1047,8 +1066,11 @@ extern "C" int gt_train_finish(gt_ctx *c, gt_train *t, gt_tree **out)
             else { tr->H = H; tr->has_thr = false; tr->feat = t->slot->feat; tr->leaf = t->slot->leaf; tr->slot = t->slot; t->slot->in_use = true; }
         } else rc = tree_alloc(c, H, false, &tr);  // the previous tree of this object is still alive
     }
-    if (rc == GT_OK) rc = copy6(c, tr->feat.v, 0, t->T.v, 0, 1, base);
-    if (rc == GT_OK) rc = copy6(c, tr->leaf.v, 0, t->T.v, base, 1, nh);
+    if (rc == GT_OK) {
+        Copies cp;
+        cp.add(t->Clast.v, 0, t->C.v, 0, nh * t->CW); cp.add(tr->feat.v, 0, t->T.v, 0, base); cp.add(tr->leaf.v, 0, t->T.v, base, nh);
+        rc = cp.run(c);
+    }
     if (rc == GT_OK) { t->last = H; t->level = H + 1; t->finished = true; t->fresh_import = false; }
     rc = T.finish(rc);
     if (rc != GT_OK) { if (tr) gt_tree_destroy(tr); return rc; }
@@ -1097,7 +1119,7 @@ extern "C" int gt_train_export(gt_ctx *c, const gt_train *t, int what, const gt_
     default: break;
     }
     int rc = GT_OK;
-    if (src) rc = copy6(c, to_p6(out), 0, src->v, 0, 1, n);
+    if (src) rc = copy6(c, to_p6(out), 0, src->v, 0, n);
     else if (what == GT_X_L) rc = launch(c, GT_KC_LOCAL, k_l_export, g1(n), B256, limbs_L(t), to_p6(out), (u64)1 << t->last, (u64)t->N, (u64)t->N8);
     else {
         const u32 nh = 1u << t->last;
@@ -1114,11 +1136,11 @@ extern "C" int gt_train_import(gt_ctx *c, gt_train *t, uint32_t h, const gt_shar
     if (!shares_ok(M, t->N) || !shares_ok(Fl, nh) || !shares_ok(Cc, nh * t->CW) || !shares_ok(gm, nh * t->d)) return GT_EINVAL;
     if (h > 0 && !shares_ok(Tprev, nh / 2)) return GT_EINVAL;
     Timed T(c);
-    int rc = copy6(c, t->M.v, 0, to_p6(M), 0, 1, t->N);
-    if (rc == GT_OK && h > 0) rc = copy6(c, t->T.v, base - nh / 2, to_p6(Tprev), 0, 1, nh / 2);
-    if (rc == GT_OK) rc = copy6(c, t->F.v, base, to_p6(Fl), 0, 1, nh);
-    if (rc == GT_OK) rc = copy6(c, t->C.v, 0, to_p6(Cc), 0, 1, nh * t->CW);
-    if (rc == GT_OK) rc = copy6(c, t->gamma.v, 0, to_p6(gm), 0, 1, nh * t->d);
+    int rc = copy6(c, t->M.v, 0, to_p6(M), 0, t->N);
+    if (rc == GT_OK && h > 0) rc = copy6(c, t->T.v, base - nh / 2, to_p6(Tprev), 0, nh / 2);
+    if (rc == GT_OK) rc = copy6(c, t->F.v, base, to_p6(Fl), 0, nh);
+    if (rc == GT_OK) rc = copy6(c, t->C.v, 0, to_p6(Cc), 0, nh * t->CW);
+    if (rc == GT_OK) rc = copy6(c, t->gamma.v, 0, to_p6(gm), 0, nh * t->d);
     if (rc == GT_OK) { t->level = h; t->finished = false; t->fresh_import = true; t->lt_level = ~0u; }
     return T.finish(rc);
 }
@@ -1133,9 +1155,9 @@ extern "C" int gt_tree_import(gt_ctx *c, const gt_shares *feat, const gt_shares 
     Timed T(c);
     gt_tree *tr = nullptr;
     int rc = tree_alloc(c, H, thr != nullptr, &tr);
-    if (rc == GT_OK) rc = copy6(c, tr->feat.v, 0, to_p6(feat), 0, 1, nint);
-    if (rc == GT_OK) rc = copy6(c, tr->leaf.v, 0, to_p6(leaf), 0, 1, nleaf);
-    if (rc == GT_OK && thr) rc = copy6(c, tr->thr.v, 0, to_p6(thr), 0, 1, nint);
+    if (rc == GT_OK) rc = copy6(c, tr->feat.v, 0, to_p6(feat), 0, nint);
+    if (rc == GT_OK) rc = copy6(c, tr->leaf.v, 0, to_p6(leaf), 0, nleaf);
+    if (rc == GT_OK && thr) rc = copy6(c, tr->thr.v, 0, to_p6(thr), 0, nint);
     rc = T.finish(rc);
     if (rc != GT_OK) { if (tr) gt_tree_destroy(tr); return rc; }
     *out = tr;
@@ -1148,9 +1170,9 @@ extern "C" int gt_tree_export(gt_ctx *c, const gt_tree *tr, const gt_shares *fea
     const size_t nint = ((size_t)1 << tr->H) - 1, nleaf = (size_t)1 << tr->H;
     if (!shares_ok(feat, nint) || !shares_ok(leaf, nleaf)) return GT_EINVAL;
     Timed T(c);
-    int rc = copy6(c, to_p6(feat), 0, tr->feat.v, 0, 1, nint);
-    if (rc == GT_OK) rc = copy6(c, to_p6(leaf), 0, tr->leaf.v, 0, 1, nleaf);
-    return T.finish(rc);
+    Copies cp;
+    cp.add(to_p6(feat), 0, tr->feat.v, 0, nint); cp.add(to_p6(leaf), 0, tr->leaf.v, 0, nleaf);
+    return T.finish(cp.run(c));
 }
 
 extern "C" int gt_tree_destroy(gt_tree *tr)
@@ -1266,7 +1288,7 @@ extern "C" int gt_infer_batch(gt_ctx *c, const gt_tree *tr, const gt_shares *I, 
         if (c->ws[i].n < need[i]) { (void)hipStreamSynchronize(c->stream); dsh_free(c->ws[i]); rc = dsh_alloc(c->ws[i], need[i], c->stream); }
     DSh &IT = c->ws[0], &tidx = c->ws[1], &f = c->ws[2], &th = c->ws[3], &x = c->ws[4];
     if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_fill_const, g1(NI), B256, tidx.v, (u64)0, (u64)NI, (u64)0);
-    if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_transpose, gT(NI, d), B256, IT.v, to_p6(I), (u64)NI, (u64)N8, d);
+    if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_transpose, gT(NI, d), B256, IT.v, to_p6(I), d, IT.v, to_p6(I), d, (u64)NI, (u64)N8);
     for (u32 n = 0; n < H && rc == GT_OK; n++) {
         const u64 w = (u64)1 << n, base = w - 1;
         GridArgs a{}; a.u = tidx.v; a.base = base; a.w = (u32)w; a.N = NI; a.N8 = N8;
@@ -1308,9 +1330,9 @@ extern "C" int gt_forest_create(gt_ctx *c, const gt_tree *const *trees, size_t n
     if (rc == GT_OK) rc = dsh_alloc(f->leaf, ntrees * nleaf, c->stream);
     if (rc == GT_OK && f->has_thr) rc = dsh_alloc(f->thr, ntrees * nint, c->stream);
     for (size_t t = 0; t < ntrees && rc == GT_OK; t++) {
-        rc = copy6(c, f->feat.v, t * nint, trees[t]->feat.v, 0, 1, nint);
-        if (rc == GT_OK) rc = copy6(c, f->leaf.v, t * nleaf, trees[t]->leaf.v, 0, 1, nleaf);
-        if (rc == GT_OK && f->has_thr) rc = copy6(c, f->thr.v, t * nint, trees[t]->thr.v, 0, 1, nint);
+        rc = copy6(c, f->feat.v, t * nint, trees[t]->feat.v, 0, nint);
+        if (rc == GT_OK) rc = copy6(c, f->leaf.v, t * nleaf, trees[t]->leaf.v, 0, nleaf);
+        if (rc == GT_OK && f->has_thr) rc = copy6(c, f->thr.v, t * nint, trees[t]->thr.v, 0, nint);
     }
     rc = T.finish(rc);
     if (rc != GT_OK) { (void)hipStreamSynchronize(c->stream); dsh_free(f->feat); dsh_free(f->leaf); dsh_free(f->thr); delete f; return rc; }
