@@ -483,6 +483,7 @@ struct WWire {
         if (cnt && l < 6) cnt[l] = 0;
         wave_sync();
     }
+    __device__ __forceinline__ u32 lane_of(u32 e) const { return GT_TP * (u32)p + e; }     // the party's lane number e
     // store ND dwords, load those that lane `from` stored
     template <int ND>
     __device__ __forceinline__ void pass(const u32 (&s)[ND], u32 (&r)[ND], u32 from)
@@ -543,6 +544,49 @@ struct WWire {
         }
     }
 };
+
+// The wavefront model for the per-element protocols where their chain counts and not the vector unit: a row of 16 lanes is 5
+// elements x 3 parties (lane 16 r + 5 p + j: party p of element 5 r + j; the row's last lane repeats its first and
+// neither stores nor counts), so that a message is a copy from lane to lane inside a row, two DPP moves a dword and no LDS
+// latency: about 30 cycles instead of 150.  Not where SIMDs are full: the moves take the vector unit's time.
+// Training of 267 x 22, depth 4, 473 -> 463 us; of 1,200 x 60, depth 6, 738 -> 720 us.
+struct DWire : WWire {
+    __device__ __forceinline__ void init(uint4 *region, u64 *s_cnt)
+    {
+        const u32 l = threadIdx.x & (GT_LANES - 1), x = l & 15;
+        real = x < 15; m = l;
+        p = x == 15 ? 0 : (int)(x / 5); pn = p == 2 ? 0 : p + 1;
+        t = (l >> 4) * 5 + (x == 15 ? 0 : x - 5 * (u32)p);
+        nx = 0; pv = 0;
+        buf = region; cnt = s_cnt; nopen = 0; nresh = 0;
+        if (l < 6) cnt[l] = 0;
+        wave_sync();
+    }
+    __device__ __forceinline__ u32 lane_of(u32 e) const { return e / 5 * 16 + 5 * (u32)p + e % 5; }
+    // from the next party's lane, 5 on in the row's 15; from the previous one's, 10 on
+    static __device__ __forceinline__ u32 from_next(u32 v)
+    {
+        const u32 w = (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x110 + 10, 0xf, 0xf, false);          // lanes 10-14: lane - 10
+        return (u32)__builtin_amdgcn_update_dpp((int)w, (int)v, 0x100 + 5, 0xf, 0xf, false);                  // lanes 0-10: lane + 5 (15 is as 0)
+    }
+    static __device__ __forceinline__ u32 from_prev(u32 v)
+    {
+        const u32 w = (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x100 + 10, 0xf, 0xf, false);          // lanes 0-5: lane + 10 (15 is as 0)
+        return (u32)__builtin_amdgcn_update_dpp((int)w, (int)v, 0x110 + 5, 0xf, 0xf, false);                  // lanes 5-15: lane - 5
+    }
+    static __device__ __forceinline__ u64 join(u32 lo, u32 hi) { return (u64)lo | ((u64)hi << 32); }
+    template <int NW>
+    __device__ __forceinline__ void reshare(const u64 (&s)[NW], u64 (&r)[NW], u32 bits)
+    {
+        nresh += bits;
+#pragma unroll
+        for (int j = 0; j < NW; j++) r[j] = join(from_next((u32)s[j]), from_next((u32)(s[j] >> 32)));
+    }
+    __device__ __forceinline__ u64 reshare1(u64 v, u32 bits) { u64 s[1] = { v }, r[1]; reshare<1>(s, r, bits); return r[0]; }
+    __device__ __forceinline__ u64 open1(u64 v, u32 bits) { nopen += bits; return join(from_prev((u32)v), from_prev((u32)(v >> 32))); }
+};
+template <int ISSUE> struct ElWire { typedef WWire T; };
+template <> struct ElWire<PRF_ALONE> { typedef DWire T; };
 
 // keys of the wavefront model: the lane's own pairwise key in vector registers (the words
 // under its next key come from the next party's lane), the dealer's key in scalar ones

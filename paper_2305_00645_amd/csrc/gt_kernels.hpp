@@ -830,7 +830,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
     __shared__ uint4 s_msg[GT_LANES];                                                       \
     __shared__ u64 s_mat[GT_EL_WORDS(NS)];                                                  \
     __shared__ u64 s_cnt[6];                                                                \
-    WWire W; W.init(s_msg, s_cnt);                                                          \
+    typename ElWire<ISSUE>::T W; W.init(s_msg, s_cnt);                                      \
     const int p = W.p;                                                                      \
     ElTile<NS, ISSUE> T; T.keys = a.c.keys; T.mat = s_mat;
 #define GT_FOR_EL(n) for (u64 tile_ = blockIdx.x, ntiles_ = ((u64)(n) + GT_EL - 1) / GT_EL; tile_ < ntiles_; tile_ += gridDim.x)
@@ -839,8 +839,8 @@ __device__ __forceinline__ u32 el_live(u64 e0, u64 n) { return n - e0 < GT_EL ? 
 // z = B2A([x - y_pub == 0]) or the Boolean bit (BOOL_OUT).  300,007 elements: 51 us with a party per
 // wavefront, 23 us in the wavefront model, 20 with the issue priorities of PRF_PAIR.
 struct EqArgs { KCommon c; P6 x; const u64 *ypub; u64 ysub; P6 z; u64 n, xoff; };
-template <bool BOOL_OUT, class TileT>
-__device__ __forceinline__ void eq_tile(const EqArgs &a, WWire &W, TileT &T, u64 tile)
+template <bool BOOL_OUT, class WireT, class TileT>
+__device__ __forceinline__ void eq_tile(const EqArgs &a, WireT &W, TileT &T, u64 tile)
 {
     const int p = W.p;
     const u64 e0 = tile * GT_EL, e = e0 + W.t;
@@ -871,7 +871,7 @@ __global__ __launch_bounds__(64) void k_dot_fin(GridArgs a, u32 finblk, EqArgs e
     __shared__ uint4 s_msg[GT_LANES];
     __shared__ u64 s_mat[GT_EL_WORDS(2)];
     __shared__ u64 s_cnt[6];
-    WWire W; W.init(s_msg, s_cnt);
+    ElWire<PRF_ALONE>::T W; W.init(s_msg, s_cnt);
     const int p = W.p;
     ElTile<2> T; T.keys = a.c.keys; T.mat = s_mat;
     const Sh one = pub(p, 1);
@@ -949,8 +949,8 @@ __global__ __launch_bounds__(192) void k_cmp_step(CmpArgs a)
 // Restoring division, all steps of an element in one launch (the steps of different
 // elements do not interact): step t uses operation id op + t; b = [r >= Q]; r <- r - b Q;
 // quo <- 2 quo + b; r starts as S and is doubled between steps.  T: the step's material.
-template <class TileT>
-__device__ __forceinline__ void div_step(WWire &W, const TileT &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
+template <class WireT, class TileT>
+__device__ __forceinline__ void div_step(WireT &W, const TileT &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
 {
     if (!first) r = scale(r, 2);
     const Dealer D = T.dealer(W);
@@ -962,8 +962,8 @@ __device__ __forceinline__ void div_step(WWire &W, const TileT &T, int p, u32 w,
 // Material of all steps of a division by NW wavefronts side by side, then the steps by the first of
 // them: with few elements the steps' PRF blocks would otherwise lie in the chain, one per step.
 // NW = 1: a slot that is dealt anew before every step.
-template <int NW, class TileT>
-__device__ __forceinline__ void div_steps_el(WWire &W, TileT &T, u64 *s_mat, int p, u32 op, u64 e0, u32 nel, u32 nsteps, Sh Q, Sh &r, Sh &quo, bool act)
+template <int NW, class WireT, class TileT>
+__device__ __forceinline__ void div_steps_el(WireT &W, TileT &T, u64 *s_mat, int p, u32 op, u64 e0, u32 nel, u32 nsteps, Sh Q, Sh &r, Sh &quo, bool act)
 {
     const u32 st3[3] = { 1, 2, 3 }, w = (u32)(e0 & 7) + W.t;
     if (NW > 1) {
@@ -984,7 +984,7 @@ __device__ __forceinline__ void div_steps_el(WWire &W, TileT &T, u64 *s_mat, int
     __shared__ u64 s_mat[(NW > 1 ? GT_DIV_STEPS : 1) * GT_EL_WORDS(3)];                      \
     __shared__ u64 s_cnt[NW][6];                                                            \
     const u32 wave_ = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);               \
-    WWire W; W.init(s_msg[wave_], s_cnt[wave_]);                                            \
+    typename ElWire<NW == 1 ? PRF_PAIR : PRF_ALONE>::T W; W.init(s_msg[wave_], s_cnt[wave_]); \
     const int p = W.p;                                                                      \
     ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.keys = a.c.keys; T.mat = s_mat;
 
@@ -1013,7 +1013,7 @@ __global__ __launch_bounds__(64 * NW) void k_div(DivArgs a)
 //   op+2 ..:     restoring division, tau+1 steps
 //   op+tau+3:    score = quo(j=0) + quo(j=1), masked = score * gamma[r*d+k], written to `score`
 // Everything is local to the two elements of a candidate, so nothing but the masked score reaches memory
-// (five launches and six arrays before; 17 steps for up to 9,408 elements 29 us, 105 us before).
+// (five launches and six arrays before; 17 steps for up to 9,408 elements 24 us, 105 us before).
 struct ScoreArgs { KCommon c; P6 C, gamma, score; u64 n; u32 d, K, CW, nsteps; };
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void k_score(ScoreArgs a)
@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(64 * NW) void k_score(ScoreArgs a)
             // the candidate's two quotients meet in its even lane (the party's own words, no message)
             const u64 mine[2] = { quo.o, quo.n };
             u64 other[2];
-            W.template pass64<2>(mine, other, W.t & 1 ? W.m - 1 : (W.t < GT_EL ? W.m + 1 : W.m));
+            W.template pass64<2>(mine, other, W.lane_of(W.t < GT_EL ? W.t ^ 1 : W.t));
             const bool ev = act && !(W.t & 1);
             Sh sc = { quo.o + other[0], quo.n + other[1] }, g = { 0, 0 };
             if (ev) g = ld(a.gamma, p, cand);
@@ -1075,8 +1075,8 @@ __global__ __launch_bounds__(64 * NW) void k_score(ScoreArgs a)
 
 // Compare-and-select of a tile: b = [right > left]; val = left + b (right-left); idx likewise (material
 // of operation `op`, elements from e0).
-template <class TileT>
-__device__ __forceinline__ void select_el(WWire &W, TileT &T, int p, u32 op, u64 e0, u32 nel, Sh &L, Sh R, Sh &IL, Sh IR, bool act)
+template <class WireT, class TileT>
+__device__ __forceinline__ void select_el(WireT &W, TileT &T, int p, u32 op, u64 e0, u32 nel, Sh &L, Sh R, Sh &IL, Sh IR, bool act)
 {
     const u32 st4[4] = { 1, 2, 3, 4 }, w = (u32)(e0 & 7) + W.t;
     T.deal(W, op, e0, st4, nel);
@@ -1142,7 +1142,7 @@ __global__ __launch_bounds__(64 * NW) void k_argmax(ArgmaxArgs a)
     __shared__ u64 s_cnt[NW][6];
     __shared__ u64 s_buf[12][RES + RES / 2];                            // results of the even rounds, of the odd ones
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
-    WWire W; W.init(s_msg[wave], s_cnt[wave]);
+    ElWire<PRF_ALONE>::T W; W.init(s_msg[wave], s_cnt[wave]);
     const int p = W.p;
     ElTile<4> T; T.keys = a.c.keys; T.mat = s_mat[wave];
     u64 *vo = s_buf[4 * p], *vn = s_buf[4 * p + 1], *io = s_buf[4 * p + 2], *in = s_buf[4 * p + 3];
@@ -1172,7 +1172,7 @@ __global__ __launch_bounds__(64 * NW) void k_argmax(ArgmaxArgs a)
             if (NW > 1) __syncthreads(); else wave_sync();
         }
         if (a.len == 1)                                                 // one candidate: index 0
-            for (u32 j = W.t; j < nn; j += GT_TP) if (W.real && wave == 0) st(a.SD, p, r0 + j, Sh{ 0, 0 });
+            for (u32 j = W.t; j < nn; j += GT_EL) if (W.real && wave == 0) st(a.SD, p, r0 + j, Sh{ 0, 0 });
         W.drain();
     }
     W.flush(a.c.wire);

@@ -381,6 +381,12 @@ def test_train_argmax_nodes_per_wavefront(mods, seed, N, d, K, h):
     g.close()
 
 
+@pytest.mark.parametrize("N,d,K,h", [(20, 1, 2, 5), (20, 1, 2, 6), (24, 2, 2, 6)])
+def test_train_argmax_many_nodes_of_one_column(mods, seed, N, d, K, h):
+    """32 and 64 nodes per wavefront and one or two columns: more nodes than a party has lanes in a wavefront."""
+    test_train_argmax_nodes_per_wavefront(mods, seed, N, d, K, h)
+
+
 def test_train_argmax_time_follows_the_candidates(mods, seed):
     """65,536 candidates cost about the same as one node's, as 128 nodes' or as 8192 nodes': the per-node
     protocols of a level (score to update) may differ by a factor of 2.2 between the three.  Measured 1.4; with a
