@@ -1509,13 +1509,13 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // bcol0: first column (row of B) of this launch, zcol0: its column in the output
 // rt: row tiles of 32 per workgroup (4, 2 or 1); the other 4/rt wavefronts take further column tiles
 // chunkblk: sample blocks of 32 per workgroup (at most CT_CHUNK_BLOCKS; the int32 accumulators bound it by 128)
-// nns: slots per chunk (0 = none) for one more column group of at most 16 columns (first column
-// nbcol0 of B, column nzcol0 of the output), handled by the same launch with 16-wide tiles; X, Y: its
+// nns: slots per chunk (0 = none) for one more column group on 16-wide tiles, at most 16 columns unless x holds them (first
+// column nbcol0 of B, column nzcol0 of the output), handled by the same launch with 16-wide tiles; X, Y: its
 // operands (x per component, y as (own+next, own) per party), xcols: x holds the columns and y the nodes
 struct CountArgs { LimbSet A, B; LimbTri X; LimbSet Y; int xcols; u64 nblk; u32 nh, ncol; u64 bcol0; u32 zcol0; u64 *Zacc; u32 nchunk, nrowgrp, nwide, rt, chunkblk, ncoltiles;   // ncoltiles: column tiles of 32*NB in this launch; nwide: slots per chunk that they take
                    u32 nns; u64 nbcol0; u32 nzcol0; };
 
-// A remainder of at most 16 columns (the class totals): 16 rows of x per wavefront with
+// A remainder of at most 16 columns (the class totals), or all columns of few nodes: 16 rows of x per wavefront with
 // v_mfma_i32_16x16x64_i8 (lane l holds row or column l%16 and the 16 samples
 // 16*(l/16).. of a pair of sample blocks; result C[4*(l/16)+v][l%16]), for ALL THREE
 // parties at once.  With so few columns the products are limited by the rate at which L
@@ -1595,7 +1595,7 @@ __device__ __forceinline__ void count_narrow(const CountArgs &a, u64 x0, u32 nx,
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 const u64 xr = 4 * kq + v;               // row of x and of y of this sum: node and column, or the reverse
-                const u64 r = a.xcols ? brow : x0 + xr, c = a.nzcol0 + (a.xcols ? xr : brow - a.nbcol0);
+                const u64 r = a.xcols ? brow : x0 + xr, c = a.nzcol0 + (a.xcols ? x0 + xr : brow) - a.nbcol0;
                 u64 z = 0;
 #pragma unroll
                 for (int u = 0; u < 8; u++) z += (u64)(long long)acc[j][u][v] << (8 * u);
@@ -1632,11 +1632,14 @@ __global__ __launch_bounds__(256) void k_count(CountArgs a)
     const u32 rg = blockIdx.z;
     if (sl >= a.nwide) {
         // a narrow slot of this chunk: its workgroups of 4 wavefronts share out the nodes, 16 rows of x
-        // (each tile for all three parties) or, where x holds the columns, 8 rows of y per wavefront
+        // (each tile for all three parties) or, where x holds the columns, 8 rows of y and 16 columns per wavefront, the
+        // wavefronts of the same columns side by side
         const u64 wv = ((u64)(sl - a.nwide) * a.nrowgrp + rg) * 4 + wave;
         const u32 nreal = a.ncol - a.nzcol0;
         if (a.xcols) {
-            if (wv * 8 < a.nh) count_narrow(a, a.nbcol0, nreal, wv * 8, wv * 8 + 8 < a.nh ? wv * 8 + 8 : a.nh, ib0, ib1, lane);
+            const u32 ny = (a.nh + 7) / 8;
+            const u64 y0 = wv % ny * 8, c0 = wv / ny * 16;
+            if (c0 < nreal) count_narrow(a, a.nbcol0 + c0, nreal - c0 < 16 ? (u32)(nreal - c0) : 16, y0, y0 + 8 < a.nh ? y0 + 8 : a.nh, ib0, ib1, lane);
         } else if (wv * 16 < a.nh) {
             const u64 left = a.nh - wv * 16;
             count_narrow(a, wv * 16, left < 16 ? (u32)left : 16, a.nbcol0, a.nbcol0 + nreal, ib0, ib1, lane);

@@ -317,6 +317,17 @@ def test_train_column_group_remainders(mods, seed, N, d, K, H):
     run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=12)
 
 
+@pytest.mark.parametrize("N,d,K,H", [(70, 7, 2, 5), (33, 16, 3, 4), (257, 63, 2, 4), (4100, 9, 5, 5)])
+def test_train_count_few_nodes(mods, seed, N, d, K, H):
+    """Levels of up to eight nodes on the narrow tiles and of 16 on the wide ones: column counts just above one tile
+    of 16, below, and of several tiles; one sample block, an odd number of them and more than one chunk."""
+    rng = np.random.default_rng(N + d)
+    X = (rng.random((N, d)) < 0.5).astype(np.uint64)
+    y = rng.integers(0, K, N)
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=3)
+
+
 @pytest.mark.parametrize("H", [7, 8])
 @pytest.mark.parametrize("literal", [False, True])
 def test_train_operand_layouts(mods, seed, H, literal):
