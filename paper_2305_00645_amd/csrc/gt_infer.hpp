@@ -19,7 +19,7 @@ struct InferArgs {
     u32 cus;                   // compute units of the device
 };
 
-// k_infer: a workgroup is NW wavefronts (1 or 2), each with the three parties in 21 lanes (WWire).  Its 21 NW lanes per party are
+// k_infer: a workgroup is NW wavefronts (1; 2 or 4 for some tiles that the caller asks for), each with the three parties in 21 lanes (WWire).  Its 21 NW lanes per party are
 // split into noct groups of 8 instances x ncol columns: lane (o, cl) tests the 8 instances of group o against columns cl,
 // cl + ncol, ... of the current access and adds up its share of the inner products in registers; the ncol partial
 // sums meet in LDS.  The messages of the tests stay inside a wavefront; a workgroup synchronises three times per

@@ -410,9 +410,9 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
 // Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
 // replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
 // adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
-// last wave; a SIMD with one wavefront takes 0.7 of the time of one with two.  `sums`: more than one range costs the
-// launch that completes the sums (5 us and more with the rows, in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
-// in one range 11 us, in two 10 and 5.  Measured with 1, 3,
+// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  `sums`: more than one range costs the
+// launch that completes the sums (in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
+// in one range 11 us, in two 10 and 5; 50,000 rows x 5 columns 21 in one, 19 in three.  Measured with 1, 3,
 // 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
 // 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
 static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps, bool sums)
@@ -425,8 +425,8 @@ static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps, bool sums)
         const u64 len = (nsteps + n - 1) / n;
         n = (nsteps + len - 1) / len;
         const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
-        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.7 : 1.0)) * ((double)len + 2.5)
-                            + (sums && n > 1 ? 1.6 + 0.0035 * (double)ntile : 0.0);
+        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5)
+                            + (sums && n > 1 ? 1.0 + 0.002 * (double)ntile : 0.0);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
     }
     return best;
@@ -483,8 +483,9 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
         const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
-        // a wavefront that has its SIMD to itself runs the variant without issue priorities (see chacha8)
-        GTCHK(ntile * a.nkc <= c->simds ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
+        // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
+        // priorities), run the variant without issue priorities (see chacha8)
+        GTCHK(ntile * a.nkc <= c->simds || a.kchunk <= kstep ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
         if (a.dacc) {
             EqArgs eq{};
             if (rider) { eq = *rider; eq.c = kc(c, c->op); rider->n = 0; }
@@ -1200,7 +1201,7 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
 // 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
 // other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
 // depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of
-// depth 5 on 5,003 x 30: 570 and 436 us); of two wavefronts where the caller asks for tiles of 64 instances.
+// depth 5 on 5,003 x 30: 570 and 436 us); of two or four for some tiles that the caller asks for.
 // The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
 // opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its
 // SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
@@ -1228,17 +1229,24 @@ static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 
             const double chain = (0.11 + 0.093 * nq) * (2 * H + 1) + (has_thr ? 0.41 : 0.32) * steps(ncol) + (has_thr ? 0.27 * (double)(H * ((4 + ncol - 1) / ncol)) : 0.0);
             take(nq, 0, noct, 3.6 + chain * (1.0 + 1.17 * (double)(items * nq) / (double)simds));
         }
-    for (u32 nw = 2; nw >= 1; nw /= 2)
-        for (u32 noct = nw == 1 ? 1 : GT_INFER_OCT(1) + 1; noct <= GT_INFER_OCT(nw); noct++) {
-            if (!forced(noct) || (nw == 2 && !c->infer_lgi)) continue;
-            const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nw) / noct;
-            double units = 2.4 * (2 * H + 1) + steps(ncol) + (has_thr ? H * (0.4 + 0.4 * (double)((8 + ncol - 1) / ncol)) : 0.0);
-            const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
-            if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.27 * H * (double)((d + ncol - 1) / ncol);
-            const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
-            const double last = rest == 0 ? 0.0 : rest <= simds ? 0.84 : full ? 0.84 + 0.16 * (double)(rest - simds) / (double)simds : 1.0;
-            take(0, nw, noct, units * ((double)full + last));
-        }
+    // a tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
+    // unless the rows stay in the L2s (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of 64: 5.8 with two)
+    u32 nw = 1;
+    const u32 ask = c->infer_lgi ? (1u << c->infer_lgi) / 8 : 0;
+    if (ask) {
+        const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
+        while (nw < 4 && (ask > GT_INFER_OCT(nw) || (!in_l2 && (d + GT_INFER_LANES(nw) / ask - 1) / (GT_INFER_LANES(nw) / ask) > 2 * ((d + 15) / 16)))) nw *= 2;
+    }
+    for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
+        if (!forced(noct)) continue;
+        const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nw) / noct;
+        double units = 2.4 * (2 * H + 1) + steps(ncol) + (has_thr ? H * (0.4 + 0.4 * (double)((8 + ncol - 1) / ncol)) : 0.0);
+        const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
+        if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.27 * H * (double)((d + ncol - 1) / ncol);
+        const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
+        const double last = rest == 0 ? 0.0 : rest <= simds ? 0.84 : full ? 0.84 + 0.16 * (double)(rest - simds) / (double)simds : 1.0;
+        take(0, nw, noct, units * ((double)full + last));
+    }
     return best;
 }
 
@@ -1262,6 +1270,7 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     if (sh.nq == 4) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 4>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 4>, g, aq, a);
     else if (sh.nq == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 2>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 2>, g, aq, a);
     else if (sh.nq == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 1>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 1>, g, aq, a);
+    else if (sh.nw == 4) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 4, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 4, false>, g, blk, a);
     else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, false>, g, blk, a);
     else if (a.noct <= 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, true>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, true>, g, blk, a);
     else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, false>, g, blk, a);

@@ -849,6 +849,12 @@ def test_infer_small_forced_tiles(mods, seed, how, binary, NI, H, d):
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
 
 
+@pytest.mark.parametrize("how,binary,NI,H,d", [(32, True, 8300, 1, 100), (64, False, 17000, 1, 60), (64, True, 17003, 1, 40)])
+def test_infer_forced_tiles_of_wide_rows(mods, seed, how, binary, NI, H, d):
+    """Tiles asked for, more of them than compute units and rows that do not stay in the L2s: two and four wavefronts per tile."""
+    test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
+
+
 def test_forest_time_on_one_instance(mods, seed):
     """1,000 trees on one instance fit the wavefront slots at once: less than twice the time of 40 trees, which
     leave most of the chip idle.  Measured 1.2; with four wavefronts per tree 3.3, from two fillings of the slots."""
