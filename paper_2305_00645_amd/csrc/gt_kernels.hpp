@@ -425,8 +425,10 @@ __device__ __forceinline__ void y_limbs(const YLimbsArgs &a)
     }
 }
 
+__global__ __launch_bounds__(256) void k_y_limbs(YLimbsArgs a) { y_limbs(a); }
+
 // what a training starts from, one launch (blockIdx.y): M, T, C := 0; F := 0, the root a leaf (1); gamma of the
-// root := 1; 5: the class columns' limb tiles
+// root := 1; 5: the class columns' limb tiles, where they are few
 struct StartArgs { P6 M, T, F, C, gamma; u64 N, nodes, nC, d; };
 __global__ __launch_bounds__(256) void k_start(StartArgs a, YLimbsArgs yl)
 {

@@ -617,7 +617,11 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     // M = 0, T = 0, the root is a leaf with empty statistics, no candidate used yet
     StartArgs st{}; st.M = t->M.v; st.T = t->T.v; st.F = t->F.v; st.C = t->C.v; st.gamma = t->gamma.v;
     st.N = N; st.nodes = nodes; st.nC = nmax * t->CW; st.d = d;
-    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>({ N, nmax * t->CW, N8 / 8 * K })).x, 6), B256, st, yl));
+    // the class columns' tiles beside it while they are a matter of the launch (267 x 2: 9 us together, 5 + 5 apart; 100,000 x
+    // 8: 62 together, 5 + 50 apart)
+    const bool beside = N8 / 8 * K <= 32768;
+    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>(N, nmax * t->CW)).x, beside ? 6 : 5), B256, st, yl));
+    if (!beside) GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1(N8 / 8 * K), B256, yl));
     t->level = 0; t->last = 0; t->finished = false; t->fresh_import = false; t->lt_level = ~0u;
     return GT_OK;
 }
@@ -776,7 +780,9 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     // Up to eight nodes all columns run on the narrow tiles, where x holds the columns: every component of a column is then
     // fetched once for the three parties, and no row is padding but those below 8.  48,842 x 590 columns with 1, 2, 4, 8 nodes:
     // 210, 190, 192, 198 us on the wide tiles, 170, 136, 142, 162 on the narrow ones; with 16 nodes, two narrow tiles, 205 and 260.
-    const bool few = a.xcols && nh <= 8;
+    // Not with few samples and many columns, where the adds of a tile's sums count, which on the narrow tiles go to a line each:
+    // 500 samples x 4,002 columns, 4 nodes, 24 and 50 us (267 x 46 9 and 7).
+    const bool few = a.xcols && nh <= 8 && (t->nblk > 64 || ncol <= 64);
     const u32 rem = ncol % 64, nfull = few ? 0 : ncol / 64 + (rem > 32 ? 1 : 0);
     // (a remainder of at most 16 columns with no full group beside it - the class totals of the
     // label level - runs on the 16-wide tiles alone)
