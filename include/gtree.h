@@ -5,8 +5,8 @@
  *
  * All three computing parties are simulated on ONE GPU.  Each party has its own
  * share buffers and keys; a message between parties is a store into a message
- * region on the device (LDS) that the receiving party's lanes load; rounds and
- * wire bytes are counted.  Offline material (edaBits, daBits) is derived from a
+ * region on the device (LDS) that the receiving party's lanes load, or a copy from
+ * lane to lane; rounds and wire bytes are counted.  Offline material (edaBits, daBits) is derived from a
  * dealer key inside the kernels, because the paper times only the online phase
  * (Sec. VI).  This is a performance simulation, not a deployable secure system.
  *

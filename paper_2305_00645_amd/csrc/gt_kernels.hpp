@@ -668,16 +668,16 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 
 // Equality grid (first lines of the array-access protocol, Sec. V-A; per-sample leaf flags of
 // the learning protocol, Sec. V-B): see GridArgs for the modes.
-// Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, at
-// one per 4 cycles and SIMD, and takes about 4,900 cycles.  One wavefront per workgroup, two per
+// Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, and
+// takes about 3,750 cycles of a SIMD (4,900 before the PRF's additions were made to pair, see chacha8).  One wavefront per workgroup, two per
 // SIMD: the rows' public values, Boolean components and sums and the values of the next column
 // fit their 256 registers but for 8 in GM_ROWS and 4 with two sums, and two barrier-free wavefronts
 // keep the vector unit as busy as three did; three had to spill far more, and every reload waited
 // for the loads from HBM issued before it (GM_ROWS, 64 columns of 10^6 samples: 1.17 ms with three,
 // 0.88 ms with two).  Before, with one party per wavefront and ten workgroup barriers per step:
-// array access 200,003 x 100 0.40 ms, now 0.27; 10^6 samples x (64 + 128 nodes) 3.45 -> 2.67 ms, own
-// rows 2 x 64 columns 2.35 -> 1.77 ms, leaf grid of 128 + 256 nodes 6.28 -> 6.2 ms (5.52 before it also
-// wrote the sums of the level); 48,842 samples x 294 columns 0.31 -> 0.20 ms.
+// array access 200,003 x 100 0.40 ms, then 0.27, with paired additions 0.21; 10^6 samples x (64 + 128 nodes) 3.45, 2.67,
+// 2.05 ms, own rows 2 x 64 columns 2.35, 1.77, 1.48 ms, leaf grid of 128 + 256 nodes 6.28 (5.52 before it also
+// wrote the sums of the level), 6.2, 5.8 ms.
 template <int MODE, bool HAS_G, int NDOT, int ISSUE>
 __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 {
