@@ -12,9 +12,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-typedef uint64_t u64;
-typedef uint32_t u32;
+#include "gt_shape.hpp"
 
 #define GT_LANES 64
 #define GT_KEY_DEALER 3
@@ -455,7 +453,6 @@ __device__ __forceinline__ Sh not_bit(int p, Sh b) { if (p == 0) b.o ^= 1; if (p
 // that the receiving party's lane loads; LDS operations of one wavefront complete in order,
 // so no workgroup barrier is needed and the wavefronts of a compute unit run independently
 // of each other.
-#define GT_TP 21
 
 // orders this wavefront's LDS accesses for the compiler (the hardware keeps their order)
 __device__ __forceinline__ void wave_sync()

@@ -25,8 +25,6 @@ struct InferArgs {
 // sums meet in LDS.  The messages of the tests stay inside a wavefront; a workgroup synchronises three times per
 // access, where the offline and zero-sharing words of the rows, evaluated by all lanes side by side, and the sums
 // change hands.  k_infer_ahead, for few instances, is described further down.
-#define GT_INFER_LANES(NW) ((NW) * GT_TP)
-#define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup at most: 19 KB of LDS per wavefront, two per SIMD
 // words per group of 8 instances.  Material of an access: r's arithmetic and Boolean components
 // [6][8], zero-sharing words [2 streams][3 keys][8]; of a comparison: [9][8] components (r, r's bits,
 // beta), beta's bits [8], mask words [2][3][8].  Values: index, id, threshold as [party][own, next][8].
@@ -343,7 +341,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
 //   a comparison       the rows' material of the next level's access
 // Every lane of a group computes the group's results, so that a result goes into the next opening without
 // a barrier; sums are cleared in the opening that follows their last reading.
-#define GT_AHEAD_OCT(NQ) (4 * (NQ))                     // groups of a tile at most: 39 KB of LDS per NQ, 155 KB on a compute unit
 // Bound: the intervals' longer side, about 2,500 cycles of a PRF block and its handing over or of a step's rounds; on a full
 // chip the vector ALU (masks and daBits of the columns that a level does not have are evaluated all the same).  Measured, in one
 // wavefront per 21 lanes that did both, four per tile, and now: one instance of 22 features, depth 7, thresholds 127 -> 60 us;

@@ -469,7 +469,6 @@ __global__ __launch_bounds__(256) void k_l_export(LimbTri L, P6 out, u64 nh, u64
 //   GM_ROWS  : z[i] = sum_k E[k][i] * XT[k*N8+i]
 //   epilogue 0: out[i] = z;  1: out[i] = 2*prev[i] + z + 1  (index update of the
 //   partition and inference protocols).
-enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };
 struct GridArgs {
     KCommon c;
     P6 u; u64 base; u32 w; u64 N, N8;

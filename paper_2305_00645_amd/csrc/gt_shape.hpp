@@ -1,0 +1,123 @@
+// Which variant of a kernel runs and how the work is split: rules on sizes, modes and the number of SIMDs alone, in plain
+// C++, so that they can be compiled and checked without a GPU.
+#pragma once
+#include <algorithm>
+#include <stdint.h>
+
+typedef uint64_t u64;
+typedef uint32_t u32;
+
+#define GT_TP 21                             // lanes of a party in a wavefront (the wavefront model)
+#define GT_INFER_LANES(NW) ((NW) * GT_TP)
+#define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup of k_infer at most: 19 KB of LDS per wavefront, two per SIMD
+#define GT_AHEAD_OCT(NQ) (4 * (NQ))          // groups of a tile of k_infer_ahead at most: 39 KB of LDS per NQ, 155 KB on a compute unit
+enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality grid, see k_eqgrid
+
+// Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
+// replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
+// adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
+// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  `sums`: more than one range costs the
+// launch that completes the sums (in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
+// in one range 11 us, in two 10 and 5; 50,000 rows x 5 columns 21 in one, 19 in three.  Measured with 1, 3,
+// 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
+// 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
+static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, bool sums)
+{
+    const u64 half = simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
+    u64 best = 1;
+    double best_cost = 0;
+    for (u64 f : fills) {
+        u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * half / ntile));
+        const u64 len = (nsteps + n - 1) / n;
+        n = (nsteps + len - 1) / len;
+        const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
+        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5)
+                            + (sums && n > 1 ? 1.0 + 0.002 * (double)ntile : 0.0);
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
+    }
+    return best;
+}
+
+// Split of an equality grid: gpt groups of 8 samples x rps adjacent columns per step and wavefront, ntile tiles, nkc ranges of
+// kchunk columns each.  alone: the variant without issue priorities (see chacha8).
+struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; };
+static inline GridShape grid_shape(u64 simds, int mode, u32 w, u64 N8)
+{
+    GridShape s;
+    // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
+    // four groups (the 32 samples of a sample block) of five adjacent columns, eight of two (at most three
+    // columns) or twenty of one: the 32-byte pieces that it stores per limb then lie side by side.
+    s.rps = mode != GM_STORE || w == 1 ? 1 : (w <= 3 ? 2 : 5);
+    s.gpt = s.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (s.rps == 2 ? 8 : 4);
+    const u64 nsteps = ((u64)w + s.rps - 1) / s.rps;
+    s.ntile = (N8 / 8 + s.gpt - 1) / s.gpt;
+    const u64 nkc = column_ranges(simds, s.ntile, nsteps, mode != GM_STORE);
+    s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
+    s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
+    // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
+    // priorities)
+    s.alone = s.ntile * s.nkc <= simds || s.kchunk <= s.rps;
+    return s;
+}
+
+// Up to eight nodes all columns run on the narrow tiles, where x holds the columns: every component of a column is then
+// fetched once for the three parties, and no row is padding but those below 8.  48,842 x 590 columns with 1, 2, 4, 8 nodes:
+// 210, 190, 192, 198 us on the wide tiles, 170, 136, 142, 162 on the narrow ones; with 16 nodes, two narrow tiles, 205 and 260.
+// Not with few samples and many columns, where the adds of a tile's sums count, which on the narrow tiles go to a line each:
+// 500 samples x 4,002 columns, 4 nodes, 24 and 50 us (267 x 46 9 and 7).
+// xcols: x holds the columns (CountArgs); nh nodes, nblk blocks of 32 samples, ncol columns.
+static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xcols && nh <= 8 && (nblk > 64 || ncol <= 64); }
+
+// Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
+// groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
+// 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
+// other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
+// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of
+// depth 5 on 5,003 x 30: 570 and 436 us); of two or four for some tiles that the caller asks for.
+// simds: of the device; lgi: log2 of the instances per workgroup that the caller asks for, 0: none; ngrp: groups of 8 instances.
+// The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
+// opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its
+// SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
+// lines that it had before.  k_infer_ahead: 3.6 for a launch, 0.1 and 0.1 more for every 21 lanes an access (barriers), 0.32 a
+// step, 0.41 with thresholds, 0.27 for every instance of a half group that a lane compares; all but the launch times
+// 2.2 where the chip is full.  Over 53 batches and forests of 1 to 700,000 instances this picks within 2 % of the
+// best of all shapes on average, 16 % at worst.
+struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
+static inline InferShape infer_shape(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u32 H, u32 d, bool has_thr)
+{
+    InferShape best = { 0, 1, 1 };
+    double best_cost = 0;
+    const auto steps = [&](u64 ncol) {
+        u64 n = H * ((d + ncol - 1) / ncol);
+        for (u32 h = 0; h <= H; h++) n += (((u64)1 << h) + ncol - 1) / ncol;
+        return (double)n;
+    };
+    const auto forced = [&](u32 noct) { return !lgi || noct == (1u << lgi) / 8; };
+    const auto take = [&](u32 nq, u32 nw, u32 noct, double cost) { if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { nq, nw, noct }; } };
+    for (u32 nq = 4; nq >= 1; nq /= 2)
+        for (u32 noct = 1; noct <= GT_AHEAD_OCT(nq); noct++) {
+            const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nq) / noct;
+            if (!forced(noct) || items > simds / nq) continue;
+            const double chain = (0.11 + 0.093 * nq) * (2 * H + 1) + (has_thr ? 0.41 : 0.32) * steps(ncol) + (has_thr ? 0.27 * (double)(H * ((4 + ncol - 1) / ncol)) : 0.0);
+            take(nq, 0, noct, 3.6 + chain * (1.0 + 1.17 * (double)(items * nq) / (double)simds));
+        }
+    // a tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
+    // unless the rows stay in the L2s (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of 64: 5.8 with two)
+    u32 nw = 1;
+    const u32 ask = lgi ? (1u << lgi) / 8 : 0;
+    if (ask) {
+        const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
+        while (nw < 4 && (ask > GT_INFER_OCT(nw) || (!in_l2 && (d + GT_INFER_LANES(nw) / ask - 1) / (GT_INFER_LANES(nw) / ask) > 2 * ((d + 15) / 16)))) nw *= 2;
+    }
+    for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
+        if (!forced(noct)) continue;
+        const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nw) / noct;
+        double units = 2.4 * (2 * H + 1) + steps(ncol) + (has_thr ? H * (0.4 + 0.4 * (double)((8 + ncol - 1) / ncol)) : 0.0);
+        const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
+        if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.27 * H * (double)((d + ncol - 1) / ncol);
+        const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
+        const double last = rest == 0 ? 0.0 : rest <= simds ? 0.84 : full ? 0.84 + 0.16 * (double)(rest - simds) / (double)simds : 1.0;
+        take(0, nw, noct, units * ((double)full + last));
+    }
+    return best;
+}

@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in include/gtree.h: argument checks, device
 // state, the operation schedule of each protocol, message accounting, launches.
 #include "gtree.h"
+#include "gt_shape.hpp"
 #include "gt_kernels.hpp"
 #include "gt_infer.hpp"
 #include "gt_partmm.hpp"
@@ -407,30 +408,6 @@ extern "C" int gt_ge_a(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
     return T.finish(rc);
 }
 
-// Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
-// replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
-// adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
-// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  `sums`: more than one range costs the
-// launch that completes the sums (in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
-// in one range 11 us, in two 10 and 5; 50,000 rows x 5 columns 21 in one, 19 in three.  Measured with 1, 3,
-// 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
-// 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
-static u64 column_ranges(const gt_ctx *c, u64 ntile, u64 nsteps, bool sums)
-{
-    const u64 half = c->simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
-    u64 best = 1;
-    double best_cost = 0;
-    for (u64 f : fills) {
-        u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * half / ntile));
-        const u64 len = (nsteps + n - 1) / n;
-        n = (nsteps + len - 1) / len;
-        const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
-        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5)
-                            + (sums && n > 1 ? 1.0 + 0.002 * (double)ntile : 0.0);
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
-    }
-    return best;
-}
 // The context's workspace of partial inner products.  Zero once: its users (k_dot_fin, k_lit_fin) leave every
 // word that they have read at zero again.
 static int grow_dacc(gt_ctx *c, size_t need)
@@ -460,16 +437,8 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
     a.ndot = ndot;
     const u64 nel = (u64)a.w * a.N;
     if (a.N && a.w) {
-        // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
-        // four groups (the 32 samples of a sample block) of five adjacent columns, eight of two (at most three
-        // columns) or twenty of one: the 32-byte pieces that it stores per limb then lie side by side.
-        a.rps = mode != GM_STORE || a.w == 1 ? 1 : (a.w <= 3 ? 2 : 5);
-        a.gpt = a.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (a.rps == 2 ? 8 : 4);
-        const u64 kstep = a.rps, nsteps = (a.w + kstep - 1) / kstep;
-        const u64 ntile = (a.N8 / 8 + a.gpt - 1) / a.gpt;
-        const u64 nkc = column_ranges(c, ntile, nsteps, mode != GM_STORE);
-        a.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * kstep);
-        a.nkc = (a.w + a.kchunk - 1) / a.kchunk;
+        const GridShape s = grid_shape(c->simds, mode, a.w, a.N8);
+        a.rps = s.rps; a.gpt = s.gpt; a.kchunk = s.kchunk; a.nkc = s.nkc;
         u64 *const own = a.dacc;               // a training object's: zero, like the context's
         a.dacc = nullptr;
         if (mode != GM_STORE && a.nkc > 1) {
@@ -482,10 +451,8 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
             else { GTCHK(grow_dacc(c, need)); a.dacc = c->dacc; }
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
-        const dim3 g((unsigned)std::min<u64>(ntile * a.nkc, 1u << 20)), B1(GT_LANES);
-        // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
-        // priorities), run the variant without issue priorities (see chacha8)
-        GTCHK(ntile * a.nkc <= c->simds || a.kchunk <= kstep ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
+        const dim3 g((unsigned)std::min<u64>(s.ntile * a.nkc, 1u << 20)), B1(GT_LANES);
+        GTCHK(s.alone ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
         if (a.dacc) {
             EqArgs eq{};
             if (rider) { eq = *rider; eq.c = kc(c, c->op); rider->n = 0; }
@@ -777,12 +744,7 @@ static int count(gt_ctx *c, gt_train *t, u32 h, bool totals_only)
     const u32 cper = 4 / a.rt;
     // groups of 64 columns; a remainder of at most 16 columns joins their launch as a
     // narrow group, one of 17 to 32 columns runs in a launch of its own with a 32-wide tile
-    // Up to eight nodes all columns run on the narrow tiles, where x holds the columns: every component of a column is then
-    // fetched once for the three parties, and no row is padding but those below 8.  48,842 x 590 columns with 1, 2, 4, 8 nodes:
-    // 210, 190, 192, 198 us on the wide tiles, 170, 136, 142, 162 on the narrow ones; with 16 nodes, two narrow tiles, 205 and 260.
-    // Not with few samples and many columns, where the adds of a tile's sums count, which on the narrow tiles go to a line each:
-    // 500 samples x 4,002 columns, 4 nodes, 24 and 50 us (267 x 46 9 and 7).
-    const bool few = a.xcols && nh <= 8 && (t->nblk > 64 || ncol <= 64);
+    const bool few = count_few(a.xcols, nh, t->nblk, ncol);
     const u32 rem = ncol % 64, nfull = few ? 0 : ncol / 64 + (rem > 32 ? 1 : 0);
     // (a remainder of at most 16 columns with no full group beside it - the class totals of the
     // label level - runs on the 16-wide tiles alone)
@@ -1202,60 +1164,6 @@ extern "C" int gt_tree_destroy(gt_tree *tr)
     return GT_OK;
 }
 
-// Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
-// groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
-// 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
-// other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
-// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of
-// depth 5 on 5,003 x 30: 570 and 436 us); of two or four for some tiles that the caller asks for.
-// The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
-// opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its
-// SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
-// lines that it had before.  k_infer_ahead: 3.6 for a launch, 0.1 and 0.1 more for every 21 lanes an access (barriers), 0.32 a
-// step, 0.41 with thresholds, 0.27 for every instance of a half group that a lane compares; all but the launch times
-// 2.2 where the chip is full.  Over 53 batches and forests of 1 to 700,000 instances this picks within 2 % of the
-// best of all shapes on average, 16 % at worst.
-struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
-static InferShape infer_shape(const gt_ctx *c, u64 ngrp, u32 ntrees, u32 H, u32 d, bool has_thr)
-{
-    const u64 simds = c->simds;
-    InferShape best = { 0, 1, 1 };
-    double best_cost = 0;
-    const auto steps = [&](u64 ncol) {
-        u64 n = H * ((d + ncol - 1) / ncol);
-        for (u32 h = 0; h <= H; h++) n += (((u64)1 << h) + ncol - 1) / ncol;
-        return (double)n;
-    };
-    const auto forced = [&](u32 noct) { return !c->infer_lgi || noct == (1u << c->infer_lgi) / 8; };
-    const auto take = [&](u32 nq, u32 nw, u32 noct, double cost) { if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { nq, nw, noct }; } };
-    for (u32 nq = 4; nq >= 1; nq /= 2)
-        for (u32 noct = 1; noct <= GT_AHEAD_OCT(nq); noct++) {
-            const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nq) / noct;
-            if (!forced(noct) || items > simds / nq) continue;
-            const double chain = (0.11 + 0.093 * nq) * (2 * H + 1) + (has_thr ? 0.41 : 0.32) * steps(ncol) + (has_thr ? 0.27 * (double)(H * ((4 + ncol - 1) / ncol)) : 0.0);
-            take(nq, 0, noct, 3.6 + chain * (1.0 + 1.17 * (double)(items * nq) / (double)simds));
-        }
-    // a tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
-    // unless the rows stay in the L2s (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of 64: 5.8 with two)
-    u32 nw = 1;
-    const u32 ask = c->infer_lgi ? (1u << c->infer_lgi) / 8 : 0;
-    if (ask) {
-        const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
-        while (nw < 4 && (ask > GT_INFER_OCT(nw) || (!in_l2 && (d + GT_INFER_LANES(nw) / ask - 1) / (GT_INFER_LANES(nw) / ask) > 2 * ((d + 15) / 16)))) nw *= 2;
-    }
-    for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
-        if (!forced(noct)) continue;
-        const u64 items = (ngrp + noct - 1) / noct * ntrees, ncol = GT_INFER_LANES(nw) / noct;
-        double units = 2.4 * (2 * H + 1) + steps(ncol) + (has_thr ? H * (0.4 + 0.4 * (double)((8 + ncol - 1) / ncol)) : 0.0);
-        const double at_work = std::min(8.0 * noct, 4.0 * (double)(items * noct) / (double)simds);    // groups per compute unit
-        if (d > 16 && ncol < 16 && at_work > 18.0) units += 0.27 * H * (double)((d + ncol - 1) / ncol);
-        const u64 waves = items * nw, full = waves / (2 * simds), rest = waves % (2 * simds);
-        const double last = rest == 0 ? 0.0 : rest <= simds ? 0.84 : full ? 0.84 + 0.16 * (double)(rest - simds) / (double)simds : 1.0;
-        take(0, nw, noct, units * ((double)full + last));
-    }
-    return best;
-}
-
 // One launch for the whole batch (and for every tree of a forest): a workgroup carries a
 // tile of instances through all levels of one tree.
 static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u32 H, u32 ntrees,
@@ -1267,7 +1175,7 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     const u32 S = has_thr ? 3 : 2;
     c->op += ntrees * (H * S + 1);
     const u64 ngrp = N8 / 8;
-    const InferShape sh = infer_shape(c, ngrp, ntrees, H, d, has_thr);
+    const InferShape sh = infer_shape(c->simds, c->infer_lgi, ngrp, ntrees, H, d, has_thr);
     a.noct = sh.noct; a.cus = std::max(1u, c->simds / 4);
     const u64 nitem = ((ngrp + a.noct - 1) / a.noct) * ntrees;
     const dim3 g((unsigned)std::min<u64>(nitem, 1u << 20)), blk(GT_LANES * sh.nw);

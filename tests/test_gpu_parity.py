@@ -317,10 +317,16 @@ def test_train_column_group_remainders(mods, seed, N, d, K, H):
     run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=12)
 
 
-@pytest.mark.parametrize("N,d,K,H", [(70, 7, 2, 5), (33, 16, 3, 4), (257, 63, 2, 4), (4100, 9, 5, 5)])
+# (test_shapes.py checks which tiles they take)
+COUNT_FEW_NARROW = [(70, 7, 2, 5), (33, 16, 3, 4), (4100, 9, 5, 5), (2100, 37, 2, 4), (2100, 72, 4, 4)]
+COUNT_FEW_WIDE = [(257, 63, 2, 4)]
+
+
+@pytest.mark.parametrize("N,d,K,H", COUNT_FEW_NARROW + COUNT_FEW_WIDE)
 def test_train_count_few_nodes(mods, seed, N, d, K, H):
-    """Levels of up to eight nodes on the narrow tiles and of 16 on the wide ones: column counts just above one tile
-    of 16, below, and of several tiles; one sample block, an odd number of them and more than one chunk."""
+    """Levels of up to eight nodes on the narrow tiles and of 16 on the wide ones: column counts of one tile of 16 with a
+    remainder, of three and four tiles, of five (a second workgroup per chunk) and of 19 with a remainder; one sample block, an odd number of
+    them and more than one chunk.  Last: few samples and more than 64 columns, on the wide tiles at every level."""
     rng = np.random.default_rng(N + d)
     X = (rng.random((N, d)) < 0.5).astype(np.uint64)
     y = rng.integers(0, K, N)
@@ -738,10 +744,9 @@ def test_infer(mods, seed, binary, NI, H):
 @pytest.mark.parametrize("how", ["levelwise", 16, 32, 64])
 @pytest.mark.parametrize("binary,NI,H,d", [(False, 333, 5, 16), (True, 1000, 7, 16), (True, 70, 9, 3), (False, 129, 3, 37), (True, 17, 0, 5)])
 def test_infer_paths_agree(mods, seed, how, binary, NI, H, d):
-    """The level-by-level path and the one-launch path with each of its three tile shapes
-    (16, 32, 64 instances per workgroup; 42, 21, 10 columns per step, so column counts that
-    are not a multiple of the step and instance counts that leave a ragged tile) all give the
-    oracle's shares, rounds, bytes and bits."""
+    """The level-by-level path and the one-launch path with each of its three tile shapes (16, 32, 64
+    instances per workgroup; column counts that are not a multiple of a step's columns and instance counts that
+    leave a ragged tile) all give the oracle's shares, rounds, bytes and bits."""
     import plain_cart
     Oracle, gtree = mods
     from paper_2305_00645_amd import workloads as wl
@@ -767,9 +772,8 @@ def test_infer_paths_agree(mods, seed, how, binary, NI, H, d):
 
 @pytest.mark.parametrize("binary,NI,H,d", [(False, 1, 2, 90), (False, 3, 7, 84), (True, 8, 3, 85), (False, 2501, 2, 19), (True, 70001, 1, 3), (False, 40009, 2, 6)])
 def test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d):
-    """The split of a workgroup's 84 lanes per party chosen from the batch: one group of 8
-    instances with 84 columns a step (one column less, as many, one more), a few groups, and the
-    largest tile (16 groups, 5 columns) with a ragged last tile; alone on a compute unit and two."""
+    """The split of the lanes chosen from the batch: one group of 8 instances with 42 or 84 columns a step (as many columns,
+    one more, a few more), and single wavefronts with three groups and a ragged last tile."""
     Oracle, gtree = mods
     from paper_2305_00645_amd import workloads as wl
     w = wl.c4_infer(NI=NI, H=H, d=d, binary=binary, seed=5000 + NI)
@@ -785,15 +789,22 @@ def test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d):
     tree.close(); g.close()
 
 
-@pytest.mark.parametrize("binary,NI,H,d", [(False, 13001, 4, 9), (True, 20011, 1, 70), (False, 16391, 2, 33), (True, 33003, 2, 22), (False, 52005, 1, 12)])
+# (test_shapes.py checks which kernel and how many groups the cases of the following lists take)
+SINGLE_WAVEFRONT_TILES = [(True, 33003, 2, 22), (False, 52005, 1, 12), (False, 30001, 1, 150), (True, 30001, 1, 294)]
+
+
+@pytest.mark.parametrize("binary,NI,H,d", SINGLE_WAVEFRONT_TILES)
 def test_infer_single_wavefront_tiles(mods, seed, binary, NI, H, d):
-    """Batches of more tiles than compute units: workgroups of one wavefront with one to four groups of 8 instances
-    (21, 10, 7, 5 columns a step, the last lanes idle where these do not divide 21), with a ragged last tile."""
+    """Batches of more tiles than k_infer_ahead takes: workgroups of one wavefront with two to four groups of 8 instances
+    (10, 7, 5 columns a step, the last lanes idle where these do not divide 21), with a ragged last tile."""
     test_infer_tile_choice_extremes(mods, seed, binary, NI, H, d)
 
 
-@pytest.mark.parametrize("binary,NI,H,d", [(False, 1, 1, 1), (True, 4, 1, 64), (False, 5, 4, 22), (True, 2044, 8, 13), (False, 4101, 3, 43), (True, 8190, 4, 30),
-                                           (False, 10004, 2, 200)])
+AHEAD_TILES = [(False, 1, 1, 1), (True, 4, 1, 64), (False, 5, 4, 22), (True, 2044, 8, 13), (False, 4101, 3, 43), (True, 8190, 4, 30),
+               (False, 10004, 2, 200), (False, 13001, 4, 9), (True, 20011, 1, 70), (False, 16391, 2, 33), (True, 8, 9, 200), (False, 5, 5, 150)]
+
+
+@pytest.mark.parametrize("binary,NI,H,d", AHEAD_TILES)
 def test_infer_ahead_tiles(mods, seed, binary, NI, H, d):
     """Batches whose tiles are all on the chip at once: one column and more than a step has, one step and several (an odd and
     an even number, so that either buffer of the material comes first), only the first half of a group's instances
@@ -835,24 +846,59 @@ def test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d):
     forest.close(); g.close()
 
 
-# two and one wavefronts per workgroup: 1 group of 8 instances with 42 and with 21 columns a step (more and
-# fewer features), ragged tiles of 2, 3 and 4 groups
-@pytest.mark.parametrize("binary,ntrees,NI,H,d", [(False, 300, 1, 3, 16), (False, 700, 5, 2, 9), (True, 600, 9, 2, 23), (True, 300, 30, 2, 16),
-                                                  (False, 500, 20, 3, 5), (True, 900, 30, 1, 3)])
+# k_infer_ahead with 21 lanes per party: 1 group of 8 instances with 21 columns a step (more and fewer features), ragged
+# tiles of 2, 3 and 4 groups
+FOREST_FEW = [(False, 300, 1, 3, 16), (False, 700, 5, 2, 9), (True, 600, 9, 2, 23), (True, 300, 30, 2, 16), (False, 500, 20, 3, 5), (True, 900, 30, 1, 3)]
+
+
+@pytest.mark.parametrize("binary,ntrees,NI,H,d", FOREST_FEW)
 def test_forest_on_few_instances(mods, seed, binary, ntrees, NI, H, d):
     test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d)
 
 
-# forced tiles that take one wavefront (2 and 4 groups) or two (8 groups)
-@pytest.mark.parametrize("how,binary,NI,H,d", [(16, True, 9001, 2, 5), (32, False, 20003, 2, 5), (64, True, 40007, 2, 5)])
+# tiles asked for that are on the chip at once (k_infer_ahead, 21 and 42 lanes per party), and one of two wavefronts
+SMALL_FORCED_TILES = [(16, True, 9001, 2, 5), (32, False, 20003, 2, 5), (32, True, 8300, 1, 100), (64, False, 17000, 1, 60), (64, True, 17003, 1, 40),
+                      (64, True, 40007, 2, 5)]
+
+
+@pytest.mark.parametrize("how,binary,NI,H,d", SMALL_FORCED_TILES)
 def test_infer_small_forced_tiles(mods, seed, how, binary, NI, H, d):
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
 
 
-@pytest.mark.parametrize("how,binary,NI,H,d", [(32, True, 8300, 1, 100), (64, False, 17000, 1, 60), (64, True, 17003, 1, 40)])
+WIDE_FORCED_TILES = [(32, True, 33003, 1, 13), (32, False, 33010, 1, 21), (32, False, 20003, 1, 100), (64, True, 33003, 1, 13), (64, False, 33003, 1, 13),
+                     (64, False, 20003, 1, 100)]
+
+
+@pytest.mark.parametrize("how,binary,NI,H,d", WIDE_FORCED_TILES)
 def test_infer_forced_tiles_of_wide_rows(mods, seed, how, binary, NI, H, d):
-    """Tiles asked for, more of them than compute units and rows that do not stay in the L2s: two and four wavefronts per tile."""
+    """Tiles asked for, more of them than k_infer_ahead takes and rows that do not stay in the L2s: two and four wavefronts per tile."""
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
+
+
+# one or two groups per wavefront, whose sums meet through LDS: fewer tree slots and features than the columns of a step (21,
+# 10), as many, more; a last tile with one group of two, a last group with one instance
+STAGED_SUMS_FORESTS = [(False, 1100, 7, 2, 23), (True, 1100, 7, 2, 23), (False, 1100, 3, 5, 5), (True, 1100, 3, 5, 22), (False, 1100, 13, 4, 12),
+                       (True, 1100, 9, 4, 12), (False, 1100, 9, 2, 9), (True, 1100, 12, 1, 11)]
+STAGED_SUMS_TILES = [(16, False, 16401, 3, 12), (16, True, 16405, 2, 30), (16, False, 17001, 4, 9)]
+
+
+@pytest.mark.parametrize("binary,ntrees,NI,H,d", STAGED_SUMS_FORESTS)
+def test_forest_staged_sums(mods, seed, binary, ntrees, NI, H, d):
+    test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d)
+
+
+@pytest.mark.parametrize("how,binary,NI,H,d", STAGED_SUMS_TILES)
+def test_infer_staged_sums(mods, seed, how, binary, NI, H, d):
+    test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
+
+
+LEVELWISE_LARGE = (False, 30001, 6, 3)
+
+
+def test_infer_levelwise_large(mods, seed):
+    """Level by level with thresholds and two wavefronts per SIMD: the grid with two sums under issue priorities."""
+    test_infer_paths_agree(mods, seed, "levelwise", *LEVELWISE_LARGE)
 
 
 def test_forest_time_on_one_instance(mods, seed):

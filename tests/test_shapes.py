@@ -1,0 +1,59 @@
+"""Which variant the rules of the library choose: for the calls that the parity tests make of them, so that every
+variant meets the oracle and every test runs what it names."""
+import test_gpu_parity as gp
+from shapes import COMMON, ROWS, STORE, few, grid, infer
+
+ALL_INFER = {"ahead1", "ahead2", "ahead4", "infer1", "infer2", "infer4"}
+
+
+def one(cases):
+    return {(binary,) + infer(NI, H, d, not binary) for binary, NI, H, d in cases}
+
+
+def asked(cases):
+    return {(binary,) + infer(NI, H, d, not binary, tile=how) for how, binary, NI, H, d in cases}
+
+
+def forest(cases):
+    return {(binary,) + infer(NI, H, d, not binary, ntrees=nt) for binary, nt, NI, H, d in cases}
+
+
+def test_inference_cases_run_what_they_name():
+    single = one(gp.SINGLE_WAVEFRONT_TILES)
+    assert {k for _, k, _ in single} == {"infer1"} and {n for _, _, n in single} == {2, 3, 4}, single
+    ahead = one(gp.AHEAD_TILES)
+    assert {(b, k) for b, k, _ in ahead} == {(b, k) for b in (False, True) for k in ("ahead1", "ahead2", "ahead4")}, ahead
+    few_inst = forest(gp.FOREST_FEW)
+    assert {k for _, k, _ in few_inst} == {"ahead1"} and {n for _, _, n in few_inst} == {1, 2, 3, 4}, few_inst
+    small = asked(gp.SMALL_FORCED_TILES)
+    assert {k for _, k, _ in small} == {"ahead1", "ahead2", "infer2"}, small
+    wide = asked(gp.WIDE_FORCED_TILES)
+    assert {(b, k) for b, k, _ in wide} == {(b, k) for b in (False, True) for k in ("infer2", "infer4")}, wide
+    staged = forest(gp.STAGED_SUMS_FORESTS)
+    assert staged == {(b, "infer1", n) for b in (False, True) for n in (1, 2)}, staged
+    assert asked(gp.STAGED_SUMS_TILES) == {(b, "infer1", 2) for b in (False, True)}
+
+
+def test_every_inference_variant_meets_the_oracle():
+    """Both modes of every kernel; k_infer in single wavefronts with staged sums (one, two groups) and without."""
+    seen = set()
+    for b, k, n in (one(gp.SINGLE_WAVEFRONT_TILES + gp.AHEAD_TILES) | asked(gp.SMALL_FORCED_TILES + gp.WIDE_FORCED_TILES + gp.STAGED_SUMS_TILES)
+                    | forest(gp.FOREST_FEW + gp.STAGED_SUMS_FORESTS)):
+        seen.add((b, k, k == "infer1" and n <= 2))
+    assert seen == {(b, k, False) for b in (False, True) for k in ALL_INFER} | {(b, "infer1", True) for b in (False, True)}, seen
+
+
+def test_grid_variants_meet_the_oracle():
+    """The grids with issue priorities: two sums level by level, the others at the full sizes of the census table (own rows) and of
+    the level on 10^6 samples (a tree level, the leaf one-hot)."""
+    _, N, H, d = gp.LEVELWISE_LARGE
+    assert not grid(COMMON, 1 << (H - 1), N)["alone"]
+    assert not grid(ROWS, 294, 48842)["alone"]
+    assert not grid(COMMON, 64, 1000000)["alone"] and not grid(STORE, 128, 1000000)["alone"]
+
+
+def test_count_few_cases_run_what_they_name():
+    for N, d, K, H in gp.COUNT_FEW_NARROW:
+        assert all(few(1 << h, N, d * K + K) == (h <= 3) for h in range(H)), (N, d, K)
+    for N, d, K, H in gp.COUNT_FEW_WIDE:
+        assert not any(few(1 << h, N, d * K + K) for h in range(H)), (N, d, K)
