@@ -62,9 +62,10 @@ static inline GridShape grid_shape(u64 simds, int mode, u32 w, u64 N8)
 
 // Up to eight nodes all columns run on the narrow tiles, where x holds the columns: every component of a column is then
 // fetched once for the three parties, and no row is padding but those below 8.  48,842 x 590 columns with 1, 2, 4, 8 nodes:
-// 210, 190, 192, 198 us on the wide tiles, 170, 136, 142, 162 on the narrow ones; with 16 nodes, two narrow tiles, 205 and 260.
-// Not with few samples and many columns, where the adds of a tile's sums count, which on the narrow tiles go to a line each:
-// 500 samples x 4,002 columns, 4 nodes, 24 and 50 us (267 x 46 9 and 7).
+// 215, 199, 198, 204 us on the wide tiles, 172, 135, 139, 150 on the narrow ones; 50,000 x 34: 33 and 31-32; with 16 nodes, two narrow
+// tiles, 205 and 260.  Not with few samples and many columns, where the adds of a tile's sums count (a wide tile adds 64 columns
+// at a time): 8 nodes, 500 samples x 2,408 columns 15 and 18 us, x 8,002 42 and 56; 1,500 x 2,408 27 and 29; beyond the line,
+// 2,100 samples: x 2,408 36 and 37, x 8,002 121 and 115; 3,000 x 2,408 44 and 44.
 // xcols: x holds the columns (CountArgs); nh nodes, nblk blocks of 32 samples, ncol columns.
 static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xcols && nh <= 8 && (nblk > 64 || ncol <= 64); }
 
