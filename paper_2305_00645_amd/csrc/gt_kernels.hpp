@@ -743,6 +743,9 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
                 if (MODE == GM_COMMON) { Wk.o = w1o[k]; Wk.n = w1n[k]; }
                 if (MODE == GM_COMMON && NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
             });
+            // without this the compiler adds own + next of the values right behind their loads and waits for these at the start of
+            // the step (6,495 rows x 248 columns, a wavefront per SIMD: 37.4 us, 33.3 with it)
+            if (MODE == GM_ROWS && ISSUE == PRF_ALONE) __builtin_amdgcn_sched_barrier(0);
             if (MODE == GM_COMMON) {
                 // E W = f ? c - z : z with z = b W, c = (the public 1) W, a constant of the column:
                 // ((z + (m & ~c)) xor m)

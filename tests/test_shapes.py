@@ -46,6 +46,8 @@ def test_every_inference_variant_meets_the_oracle():
 def test_grid_variants_meet_the_oracle():
     """The grids with issue priorities: two sums level by level, the others at the full sizes of the census table (own rows) and of
     the level on 10^6 samples (a tree level, the leaf one-hot)."""
+    n, d = gp.OWN_ROWS_ALONE
+    assert grid(ROWS, d, n)["alone"] and grid(ROWS, d, n)["ranges"] == grid(COMMON, d, n)["ranges"]
     _, N, H, d = gp.LEVELWISE_LARGE
     assert not grid(COMMON, 1 << (H - 1), N)["alone"]
     assert not grid(ROWS, 294, 48842)["alone"]
