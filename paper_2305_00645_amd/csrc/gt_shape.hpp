@@ -16,12 +16,15 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
 // replays the row's part, which costs as much as 2.5 steps (3 PRF blocks, the opening, the atomic
 // adds).  Items that fill the two wavefronts per SIMD a whole number of times leave no nearly empty
-// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  `sums`: more than one range costs the
-// launch that completes the sums (in units of a step of two wavefronts, 3 us): 267 rows x 2 columns
-// in one range 11 us, in two 10 and 5; 50,000 rows x 5 columns 21 in one, 19 in three.  Measured with 1, 3,
+// last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  Measured with 1, 3,
 // 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
 // 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
-static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, bool sums)
+// launch: what the launch that completes the sums of more than one range costs, in units of a step of two wavefronts (3 us),
+// less what it saves at the grid's end, where a wavefront completes the sums of eight rows per lane.  Two columns in one range and in
+// two, with that launch: against a shared array 13 rows 12.2 and 12.2 us, 30,000 rows 13.2 and 14.6; own rows (which are fetched
+// meanwhile), 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9 more; two sums 13 to 20,000 rows 3 to 3.5 us less in
+// two, 30,000 0.9 less, 60,000 3.7 more.
+static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, double launch)
 {
     const u64 half = simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
     u64 best = 1;
@@ -32,7 +35,7 @@ static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, bool sums)
         n = (nsteps + len - 1) / len;
         const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
         const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5)
-                            + (sums && n > 1 ? 1.0 + 0.002 * (double)ntile : 0.0);
+                            + (n > 1 ? launch : 0.0);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
     }
     return best;
@@ -41,7 +44,7 @@ static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, bool sums)
 // Split of an equality grid: gpt groups of 8 samples x rps adjacent columns per step and wavefront, ntile tiles, nkc ranges of
 // kchunk columns each.  alone: the variant without issue priorities (see chacha8).
 struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; };
-static inline GridShape grid_shape(u64 simds, int mode, u32 w, u64 N8)
+static inline GridShape grid_shape(u64 simds, int mode, int ndot, u32 w, u64 N8)
 {
     GridShape s;
     // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
@@ -51,7 +54,8 @@ static inline GridShape grid_shape(u64 simds, int mode, u32 w, u64 N8)
     s.gpt = s.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (s.rps == 2 ? 8 : 4);
     const u64 nsteps = ((u64)w + s.rps - 1) / s.rps;
     s.ntile = (N8 / 8 + s.gpt - 1) / s.gpt;
-    const u64 nkc = column_ranges(simds, s.ntile, nsteps, mode != GM_STORE);
+    const double launch = mode == GM_STORE ? 0.0 : (ndot == 2 ? 0.2 : mode == GM_ROWS ? 0.45 : 1.0) + 0.002 * (double)s.ntile;
+    const u64 nkc = column_ranges(simds, s.ntile, nsteps, launch);
     s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
     s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
     // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with

@@ -49,7 +49,7 @@ def test_grid_variants_meet_the_oracle():
     n, d = gp.OWN_ROWS_ALONE
     assert grid(ROWS, d, n)["alone"] and grid(ROWS, d, n)["ranges"] == grid(COMMON, d, n)["ranges"]
     _, N, H, d = gp.LEVELWISE_LARGE
-    assert not grid(COMMON, 1 << (H - 1), N)["alone"]
+    assert not grid(COMMON, 1 << (H - 1), N, sums=2)["alone"]
     assert not grid(ROWS, 294, 48842)["alone"]
     assert not grid(COMMON, 64, 1000000)["alone"] and not grid(STORE, 128, 1000000)["alone"]
 
@@ -59,3 +59,14 @@ def test_count_few_cases_run_what_they_name():
         assert all(few(1 << h, N, d * K + K) == (h <= 3) for h in range(H)), (N, d, K)
     for N, d, K, H in gp.COUNT_FEW_WIDE:
         assert not any(few(1 << h, N, d * K + K) for h in range(H)), (N, d, K)
+
+
+def test_two_columns_take_the_faster_split():
+    """Two columns in one range, or in two with the launch that completes the sums: on the side that measured faster (see
+    column_ranges), for few rows and for many."""
+    for n in (13, 267, 3000, 10000):
+        assert grid(ROWS, 2, n)["ranges"] == 2 and grid(COMMON, 2, n, sums=2)["ranges"] == 2, n
+        assert grid(COMMON, 2, n)["ranges"] == 1, n
+    assert grid(ROWS, 2, 30000)["ranges"] == 1 and grid(COMMON, 2, 30000, sums=2)["ranges"] == 2
+    for n in (60000, 170000):
+        assert grid(ROWS, 2, n)["ranges"] == grid(COMMON, 2, n, sums=2)["ranges"] == grid(COMMON, 2, n)["ranges"] == 1, n
