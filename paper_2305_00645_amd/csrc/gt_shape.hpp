@@ -106,6 +106,9 @@ static inline InferShape infer_shape(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u
             const double chain = (0.11 + 0.093 * nq) * (2 * H + 1) + (has_thr ? 0.41 : 0.32) * steps(ncol) + (has_thr ? 0.27 * (double)(H * ((4 + ncol - 1) / ncol)) : 0.0);
             take(nq, 0, noct, 3.6 + chain * (1.0 + 1.17 * (double)(items * nq) / (double)simds));
         }
+    // a lone label: k_infer's start and end count beside its one access, which its cost above leaves out (137, 2,699, 12,110 instances
+    // 11.4, 12.5, 13.6 us; k_infer_ahead 8.6, 8.7, 9.6)
+    if (H == 0 && best.nq) return best;
     // a tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
     // unless the rows stay in the L2s (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of 64: 5.8 with two)
     u32 nw = 1;

@@ -823,7 +823,8 @@ def test_infer_single_wavefront_tiles(mods, seed, binary, NI, H, d):
 
 
 AHEAD_TILES = [(False, 1, 1, 1), (True, 4, 1, 64), (False, 5, 4, 22), (True, 2044, 8, 13), (False, 4101, 3, 43), (True, 8190, 4, 30),
-               (False, 10004, 2, 200), (False, 13001, 4, 9), (True, 20011, 1, 70), (False, 16391, 2, 33), (True, 8, 9, 200), (False, 5, 5, 150)]
+               (False, 10004, 2, 200), (False, 13001, 4, 9), (True, 20011, 1, 70), (False, 16391, 2, 33), (True, 8, 9, 200), (False, 5, 5, 150), (True, 2699, 0, 5),
+               (False, 133, 0, 3)]
 
 
 @pytest.mark.parametrize("binary,NI,H,d", AHEAD_TILES)

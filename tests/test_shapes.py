@@ -70,3 +70,12 @@ def test_two_columns_take_the_faster_split():
     assert grid(ROWS, 2, 30000)["ranges"] == 1 and grid(COMMON, 2, 30000, sums=2)["ranges"] == 2
     for n in (60000, 170000):
         assert grid(ROWS, 2, n)["ranges"] == grid(COMMON, 2, n, sums=2)["ranges"] == grid(COMMON, 2, n)["ranges"] == 1, n
+
+
+def test_lone_label_runs_ahead():
+    """Trees of depth 0: the kernel for few instances wherever it takes them (see infer_shape)."""
+    for n in (1, 137, 2699, 12110, 30000):
+        for thr in (False, True):
+            assert infer(n, 0, 2, thr)[0] == "ahead1", n
+    assert infer(60386, 0, 7, False)[0] == "infer1"
+    assert [infer(49, 0, 2, False, tile)[0] for tile in (16, 32, 64)] == ["ahead1", "ahead1", "ahead2"]
