@@ -19,14 +19,18 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // last wave; a SIMD with one wavefront takes 0.6 of the time of one with two.  Measured with 1, 3,
 // 5, 6 ranges for 200,003 rows x 100 columns: 446, 309, 287, 285 us; with 7, 14, 21, 28 ranges for
 // 48,842 rows x 294 columns of their own: 199, 199, 203, 221 us.
-// launch: what the launch that completes the sums of more than one range costs, in units of a step of two wavefronts (3 us),
-// less what it saves at the grid's end, where a wavefront completes the sums of eight rows per lane.  Two columns in one range and in
-// two, with that launch: against a shared array 13 rows 12.2 and 12.2 us, 30,000 rows 13.2 and 14.6; own rows (which are fetched
-// meanwhile), 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9 more; two sums 13 to 20,000 rows 3 to 3.5 us less in
-// two, 30,000 0.9 less, 60,000 3.7 more.
-static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, double launch)
+// Inner products (sums: how many, 0: none): more than one range costs the launch that completes the sums, against one range, whose
+// wavefronts, alone on a SIMD, take 0.82 of the time of two with paired additions (the sums of many short ranges meet at the same words,
+// which is why 0.6 is the better line there: 445 rows x 669 columns 29 us in 341 ranges, 51 in 683).  140,244 rows x 32 columns: 92
+// in one, 61 and 11 in two; x 8 columns 31 in one, 22 and 11 in two.  Two columns in one range and in two, with that launch: 13 rows 12.2
+// and 12.2 us, 30,000 rows 13.2 and 14.6; of their own (fetched meanwhile) 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9
+// more; two sums, 13 to 20,000 rows 3 to 3.5 us less in two (one range completes the sums of eight rows per lane), 30,000 0.9
+// less, 60,000 3.7 more.
+static inline u64 column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
 {
     const u64 half = simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
+    // in units of a step of two wavefronts, 3 us
+    const double launch = sums == 0 ? 0.0 : sums == 2 ? 0.5 + 0.006 * (double)ntile : mode == GM_ROWS ? 1.2 + 0.003 * (double)ntile : 1.6 + 0.0027 * (double)ntile;
     u64 best = 1;
     double best_cost = 0;
     for (u64 f : fills) {
@@ -34,8 +38,8 @@ static inline u64 column_ranges(u64 simds, u64 ntile, u64 nsteps, double launch)
         const u64 len = (nsteps + n - 1) / n;
         n = (nsteps + len - 1) / len;
         const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
-        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? 0.6 : 1.0)) * ((double)len + 2.5)
-                            + (n > 1 ? launch : 0.0);
+        const double alone = n == 1 && sums ? 0.82 : 0.6;
+        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? alone : 1.0)) * ((double)len + 2.5) + (n > 1 ? launch : 0.0);
         if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
     }
     return best;
@@ -54,8 +58,7 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, u32 w, u64 N8)
     s.gpt = s.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (s.rps == 2 ? 8 : 4);
     const u64 nsteps = ((u64)w + s.rps - 1) / s.rps;
     s.ntile = (N8 / 8 + s.gpt - 1) / s.gpt;
-    const double launch = mode == GM_STORE ? 0.0 : (ndot == 2 ? 0.2 : mode == GM_ROWS ? 0.45 : 1.0) + 0.002 * (double)s.ntile;
-    const u64 nkc = column_ranges(simds, s.ntile, nsteps, launch);
+    const u64 nkc = column_ranges(simds, mode, mode == GM_STORE ? 0 : ndot, s.ntile, nsteps);
     s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
     s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
     // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with

@@ -61,6 +61,15 @@ def test_count_few_cases_run_what_they_name():
         assert not any(few(1 << h, N, d * K + K) for h in range(H)), (N, d, K)
 
 
+def test_many_columns_fill_the_chip():
+    """More than half of the SIMDs' worth of tiles: one range only where the columns are few (see column_ranges)."""
+    for n in (100003, 140244, 168657):
+        assert grid(COMMON, 32, n)["ranges"] >= 2 and grid(COMMON, 3, n)["ranges"] == 1, n
+    assert grid(ROWS, 20, 140244)["ranges"] == grid(ROWS, 17, 168657)["ranges"] == 2
+    for n, w, ranges in ((445, 669, 335), (3604, 57, 29), (6495, 248, 25)):        # few rows: a wavefront per SIMD
+        assert grid(COMMON, w, n)["ranges"] == ranges and grid(COMMON, w, n)["alone"], n
+
+
 def test_two_columns_take_the_faster_split():
     """Two columns in one range, or in two with the launch that completes the sums: on the side that measured faster (see
     column_ranges), for few rows and for many."""
