@@ -46,9 +46,9 @@ static inline u64 column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 ns
 }
 
 // Split of an equality grid: gpt groups of 8 samples x rps adjacent columns per step and wavefront, ntile tiles, nkc ranges of
-// kchunk columns each.  alone: the variant without issue priorities (see chacha8).
+// kchunk columns each.  alone: the variant without issue priorities (see chacha8).  sums: GM_STORE writes the tiles of the sums, too.
 struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; };
-static inline GridShape grid_shape(u64 simds, int mode, int ndot, u32 w, u64 N8)
+static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32 w, u64 N8)
 {
     GridShape s;
     // A wavefront covers 21 groups of 8 samples of one column per step.  The leaf one-hot grid takes
@@ -62,8 +62,11 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, u32 w, u64 N8)
     s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
     s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
     // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
-    // priorities)
-    s.alone = s.ntile * s.nkc <= simds || s.kchunk <= s.rps;
+    // priorities); and the grid that writes a level's tiles and their sums for many samples: what it gains by priorities the
+    // contraction behind it loses, which reads tiles that were written in a different order.  Grid + contraction without and with them, 16, 32,
+    // 64 nodes: 60,000 samples x 122 columns 37 + 78, 54 + 78, 86 + 109 us and 32 + 78, 46 + 79, 73 + 113; 140,244: 75 + 182, 113 + 195,
+    // 190 + 273 and 73 + 195, 110 + 213, 187 + 298; 400,000: 173 + 500, 281 + 531, 493 + 659 and 161 + 519, 271 + 553, 493 + 663.
+    s.alone = s.ntile * s.nkc <= simds || s.kchunk <= s.rps || (sums && N8 > 131072);
     return s;
 }
 

@@ -437,7 +437,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
     a.ndot = ndot;
     const u64 nel = (u64)a.w * a.N;
     if (a.N && a.w) {
-        const GridShape s = grid_shape(c->simds, mode, ndot, a.w, a.N8);
+        const GridShape s = grid_shape(c->simds, mode, ndot, a.sums != 0, a.w, a.N8);
         a.rps = s.rps; a.gpt = s.gpt; a.kchunk = s.kchunk; a.nkc = s.nkc;
         u64 *const own = a.dacc;               // a training object's: zero, like the context's
         a.dacc = nullptr;

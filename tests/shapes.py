@@ -15,9 +15,9 @@ extern "C" void infer(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u32 H, u32 d, in
     const InferShape s = infer_shape(simds, lgi, ngrp, ntrees, H, d, thr != 0);
     out[0] = s.nq; out[1] = s.nw; out[2] = s.noct;
 }
-extern "C" void grid(u64 simds, int mode, int ndot, u32 w, u64 N8, u64 *out)
+extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64 *out)
 {
-    const GridShape s = grid_shape(simds, mode, ndot, w, N8);
+    const GridShape s = grid_shape(simds, mode, ndot, sums != 0, w, N8);
     out[0] = s.ntile; out[1] = s.nkc; out[2] = s.kchunk; out[3] = s.alone; out[4] = s.rps;
 }
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
@@ -35,7 +35,7 @@ def _lib():
         L = C.CDLL(so)
     u32, u64, i, vp = C.c_uint32, C.c_uint64, C.c_int, C.c_void_p
     L.infer.argtypes, L.infer.restype = [u64, u32, u64, u32, u32, u32, i, vp], None
-    L.grid.argtypes, L.grid.restype = [u64, i, i, u32, u64, vp], None
+    L.grid.argtypes, L.grid.restype = [u64, i, i, i, u32, u64, vp], None
     L.few.argtypes, L.few.restype = [i, u64, u64, u64], i
     return L
 
@@ -48,10 +48,11 @@ def infer(NI, H, d, thr, tile=0, ntrees=1):
     return ("ahead%d" % nq if nq else "infer%d" % nw), noct
 
 
-def grid(mode, w, N, sums=1):
-    """dict(tiles, ranges, columns, alone, adjacent) of an equality grid of N rows and w columns."""
+def grid(mode, w, N, sums=1, tile_sums=False):
+    """dict(tiles, ranges, columns, alone, adjacent) of an equality grid of N rows and w columns; sums: inner products;
+    tile_sums: the leaf one-hot is written with its sums."""
     out = (C.c_uint64 * 5)()
-    _lib().grid(SIMDS, mode, sums, w, (N + 7) // 8 * 8, out)
+    _lib().grid(SIMDS, mode, sums, int(tile_sums), w, (N + 7) // 8 * 8, out)
     return dict(tiles=out[0], ranges=out[1], columns=out[2], alone=bool(out[3]), adjacent=out[4])
 
 

@@ -51,7 +51,9 @@ def test_grid_variants_meet_the_oracle():
     _, N, H, d = gp.LEVELWISE_LARGE
     assert not grid(COMMON, 1 << (H - 1), N, sums=2)["alone"]
     assert not grid(ROWS, 294, 48842)["alone"]
-    assert not grid(COMMON, 64, 1000000)["alone"] and not grid(STORE, 128, 1000000)["alone"]
+    assert not grid(COMMON, 64, 1000000)["alone"]
+    assert not grid(STORE, 128, 48842, tile_sums=False)["alone"] and not grid(STORE, 64, 48842, tile_sums=True)["alone"]
+    assert grid(STORE, 128, 1000000, tile_sums=True)["alone"] and not grid(STORE, 256, 1000000)["alone"]
 
 
 def test_count_few_cases_run_what_they_name():
