@@ -62,11 +62,13 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
     s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
     s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
     // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
-    // priorities); and the grid that writes a level's tiles and their sums for many samples: what it gains by priorities the
+    // priorities); inner products over up to three columns whose last wavefronts are alone (360,000 rows, 2,143 tiles, x 2, 3, 6 columns: 31,
+    // 37, 54 us, 35, 40, 54 with them; 534,134 rows, 3,180 tiles: 40, 47, 70 and 40, 45, 60); and the grid that writes a level's tiles and their sums for many samples: what it gains by priorities the
     // contraction behind it loses, which reads tiles that were written in a different order.  Grid + contraction without and with them, 16, 32,
     // 64 nodes: 60,000 samples x 122 columns 37 + 78, 54 + 78, 86 + 109 us and 32 + 78, 46 + 79, 73 + 113; 140,244: 75 + 182, 113 + 195,
     // 190 + 273 and 73 + 195, 110 + 213, 187 + 298; 400,000: 173 + 500, 281 + 531, 493 + 659 and 161 + 519, 271 + 553, 493 + 663.
-    s.alone = s.ntile * s.nkc <= simds || s.kchunk <= s.rps || (sums && N8 > 131072);
+    const u64 items = s.ntile * s.nkc, rest = items % (2 * simds);
+    s.alone = items <= simds || s.kchunk <= s.rps || (mode != GM_STORE && s.kchunk <= 3 && items > 2 * simds && rest && rest <= simds) || (sums && N8 > 131072);
     return s;
 }
 

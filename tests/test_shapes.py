@@ -68,6 +68,7 @@ def test_many_columns_fill_the_chip():
     for n in (100003, 140244, 168657):
         assert grid(COMMON, 32, n)["ranges"] >= 2 and grid(COMMON, 3, n)["ranges"] == 1, n
     assert grid(ROWS, 20, 140244)["ranges"] == grid(ROWS, 17, 168657)["ranges"] == 2
+    assert [grid(COMMON, w, 360000)["alone"] for w in (2, 3, 6)] == [True, True, False] and not grid(COMMON, 2, 534134)["alone"]
     for n, w, ranges in ((445, 669, 335), (3604, 57, 29), (6495, 248, 25)):        # few rows: a wavefront per SIMD
         assert grid(COMMON, w, n)["ranges"] == ranges and grid(COMMON, w, n)["alone"], n
 
