@@ -91,3 +91,11 @@ def test_lone_label_runs_ahead():
             assert infer(n, 0, 2, thr)[0] == "ahead1", n
     assert infer(60386, 0, 7, False)[0] == "infer1"
     assert [infer(49, 0, 2, False, tile)[0] for tile in (16, 32, 64)] == ["ahead1", "ahead1", "ahead2"]
+
+
+def test_asked_tiles_of_wide_rows():
+    """Tiles asked for: ten columns a step up to 249, at least 21 from 250 on (see infer_shape)."""
+    for thr in (False, True):
+        assert [infer(208758, 3, d, thr, 32)[0] for d in (100, 200, 373, 600)] == ["infer2", "infer2", "infer4", "infer4"]
+        assert [infer(208758, 3, d, thr, 16)[0] for d in (100, 200, 373, 600)] == ["infer1", "infer1", "infer2", "infer2"]
+        assert [infer(208758, 3, d, thr, 64)[0] for d in (20, 100, 373)] == ["infer2", "infer4", "infer4"]
