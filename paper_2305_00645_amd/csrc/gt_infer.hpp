@@ -33,14 +33,15 @@ struct InferArgs {
 
 // Adds up what the lanes of a wavefront hold for the same group of instances (lanes t, t + noct, .. of a party; q0: number of
 // the wavefront's first lane in the workgroup's party) and adds the sums to sum[group * stride + 8 party ..]; a lane
-// that is not `active` holds nothing.  With three groups and more every lane adds its words by itself; with one or two (few),
-// where 10 to 21 lanes would meet at every word (one instance: 4,000 cycles an access), the lanes' words go
-// through `stage` (8 * GT_LANES words) and an output is one lane's work, two lanes' where there are eight outputs per
-// party only.  One instance 92 -> 74 us; 10^4 x 16 in tiles of five groups 108 us either way, 200 x 8 in tiles of four
-// 26.4 us by atomic adds, 27.5 through LDS.
-__device__ __forceinline__ void group_sums(const WWire &W, u64 *stage, const u64 (&acc)[8], bool active, u32 q0, u32 noct, bool few, u64 *sum, u32 stride)
+// that is not `active` holds nothing.  Every lane adds its words by itself; with a single group (staged), where 21 lanes would meet
+// at every word (one instance alone: 4,000 cycles an access), the lanes' words go through `stage` (8 * GT_LANES words) and
+// an output is two lanes' work.  1,847 trees of depth 5 on one instance of 15 features 111 us by atomic adds, 98 through LDS, 50,000 x 294,
+// depth 6, 1.45 and 1.43 ms.  Not with two groups (208,758 x 200, depth 3: 1.98 and 2.01 ms) or thresholds, where the registers that
+// it takes spill (148 for 101): 1.59 and 1.77 ms with one group of the 50,000 x 294, 37,015 x 47, depth 6, two groups 428 and 484 us.
+template <bool STAGED>
+__device__ __forceinline__ void group_sums(const WWire &W, u64 *stage, const u64 (&acc)[8], bool active, u32 q0, u32 noct, u64 *sum, u32 stride)
 {
-    if (!few) {
+    if (!STAGED) {
         u64 *d = sum + (q0 + W.t) % noct * stride + W.p * 8;
         if (active && W.real) {
 #pragma unroll
@@ -53,21 +54,20 @@ __device__ __forceinline__ void group_sums(const WWire &W, u64 *stage, const u64
 #pragma unroll
     for (int j = 0; j < 4; j++) out[j] = make_ulonglong2(active ? acc[2 * j] : 0, active ? acc[2 * j + 1] : 0);
     wave_sync();
-    const u32 parts = noct == 1 ? 2 : 1, step = noct * parts;
     const u64 *in = stage + W.p * GT_TP * 8;
-    const u32 t0 = W.t >> 3, s = W.t & 7;              // 16 outputs or halves of eight
+    const u32 t0 = W.t >> 3, s = W.t & 7;              // 16 halves of the eight outputs
     u64 v = 0;
-    for (u32 t = t0; t < GT_TP; t += 4 * step) {       // four loads in flight
+    for (u32 t = t0; t < GT_TP; t += 8) {              // four loads in flight
         u64 x[4];
 #pragma unroll
-        for (int j = 0; j < 4; j++) x[j] = in[(t + j * step < GT_TP ? t + j * step : t0) * 8 + s];
+        for (int j = 0; j < 4; j++) x[j] = in[(t + j * 2 < GT_TP ? t + j * 2 : t0) * 8 + s];
 #pragma unroll
-        for (int j = 0; j < 4; j++) v += t + j * step < GT_TP ? x[j] : 0;
+        for (int j = 0; j < 4; j++) v += t + j * 2 < GT_TP ? x[j] : 0;
     }
-    if (W.real && W.t < 16) atomicAdd((unsigned long long *)&sum[(q0 + t0) % noct * stride + W.p * 8 + s], (unsigned long long)v);
+    if (W.real && W.t < 16) atomicAdd((unsigned long long *)&sum[W.p * 8 + s], (unsigned long long)v);
 }
 
-template <int ISSUE, bool FEW>
+template <int ISSUE, bool STAGED>
 struct InferWg {
     EqWave E;
     u64 *sums;                   // of the workgroup's groups
@@ -188,8 +188,8 @@ struct InferWg {
                 }
             }
         }
-        group_sums(W, (u64 *)W.buf, acc, active, q0, noct, FEW, sums, 48);
-        if (NDOT == 2 && nd2) group_sums(W, (u64 *)W.buf, acc2, active, q0, noct, FEW, sums + 24, 48);
+        group_sums<STAGED>(W, (u64 *)W.buf, acc, active, q0, noct, sums, 48);
+        if (NDOT == 2 && nd2) group_sums<STAGED>(W, (u64 *)W.buf, acc2, active, q0, noct, sums + 24, 48);
         __syncthreads();
         // every lane of a group finishes the group's result
 #pragma unroll
@@ -250,11 +250,11 @@ struct InferWg {
     }
 };
 
-// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD (70 spill, 117 with thresholds and
-// the sums of one or two groups, FEW).  Measured, with one party per wavefront and a barrier per message, in
+// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD (68 spill, 101 with thresholds, 73 with
+// STAGED sums).  Measured, with one party per wavefront and a barrier per message, in
 // workgroups of four wavefronts, now: 10^6 instances x 64 features, depth 10, 46.6, 34.5, 27 ms; 16 trees of
 // depth 5 on 5,003 x 30 with thresholds 0.74, 0.58, 0.44 ms.  For NW see infer_shape.
-template <bool THR, int NW, bool FEW>
+template <bool THR, int NW, bool STAGED>
 __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
 {
     __shared__ uint4 s_msg[NW][GT_WMSG_QUADS];
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
     __shared__ u64 s_val[GT_INFER_OCT(NW)][3 * GT_INFER_VAL];
     __shared__ u64 s_sum[GT_INFER_OCT(NW)][48];
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
-    InferWg<PRF_PAIR_LOOP, FEW> X;
+    InferWg<PRF_PAIR_LOOP, STAGED> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
     WWire &W = X.E.W;
     X.p = W.p; X.pn = W.pn; X.keys = a.c.keys;

@@ -96,6 +96,8 @@ static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xc
 // 2.2 where the chip is full.  Over 53 batches and forests of 1 to 700,000 instances this picks within 2 % of the
 // best of all shapes on average, 16 % at worst.
 struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
+// whether single wavefronts of k_infer add up their sums through LDS, see group_sums
+static inline bool staged_sums(u32 noct, bool has_thr) { return noct == 1 && !has_thr; }
 static inline InferShape infer_shape(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u32 H, u32 d, bool has_thr)
 {
     InferShape best = { 0, 1, 1 };

@@ -1186,7 +1186,7 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
     else if (sh.nq == 1) rc = has_thr ? launch(c, GT_KC_INFER, k_infer_ahead<true, 1>, g, aq, a) : launch(c, GT_KC_INFER, k_infer_ahead<false, 1>, g, aq, a);
     else if (sh.nw == 4) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 4, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 4, false>, g, blk, a);
     else if (sh.nw == 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 2, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 2, false>, g, blk, a);
-    else if (a.noct <= 2) rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, true>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, true>, g, blk, a);
+    else if (staged_sums(sh.noct, has_thr)) rc = launch(c, GT_KC_INFER, k_infer<false, 1, true>, g, blk, a);
     else rc = has_thr ? launch(c, GT_KC_INFER, k_infer<true, 1, false>, g, blk, a) : launch(c, GT_KC_INFER, k_infer<false, 1, false>, g, blk, a);
     for (u32 t = 0; t < ntrees; t++) {
         for (u32 n = 0; n < H; n++) {

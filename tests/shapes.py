@@ -20,6 +20,7 @@ extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64
     const GridShape s = grid_shape(simds, mode, ndot, sums != 0, w, N8);
     out[0] = s.ntile; out[1] = s.nkc; out[2] = s.kchunk; out[3] = s.alone; out[4] = s.rps;
 }
+extern "C" int staged(u32 noct, int thr) { return staged_sums(noct, thr != 0); }
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
 """
 STORE, COMMON, ROWS = 0, 1, 2                      # modes of the equality grid
@@ -36,6 +37,7 @@ def _lib():
     u32, u64, i, vp = C.c_uint32, C.c_uint64, C.c_int, C.c_void_p
     L.infer.argtypes, L.infer.restype = [u64, u32, u64, u32, u32, u32, i, vp], None
     L.grid.argtypes, L.grid.restype = [u64, i, i, i, u32, u64, vp], None
+    L.staged.argtypes, L.staged.restype = [u32, i], i
     L.few.argtypes, L.few.restype = [i, u64, u64, u64], i
     return L
 
@@ -46,6 +48,11 @@ def infer(NI, H, d, thr, tile=0, ntrees=1):
     _lib().infer(SIMDS, tile.bit_length() - 1 if tile else 0, (NI + 7) // 8, ntrees, H, d, int(thr), out)
     nq, nw, noct = out
     return ("ahead%d" % nq if nq else "infer%d" % nw), noct
+
+
+def staged(noct, thr):
+    """Whether single wavefronts with that many groups add up their sums through LDS."""
+    return bool(_lib().staged(noct, int(thr)))
 
 
 def grid(mode, w, N, sums=1, tile_sums=False):

@@ -899,20 +899,20 @@ def test_infer_forced_tiles_of_wide_rows(mods, seed, how, binary, NI, H, d):
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
 
 
-# one or two groups per wavefront, whose sums meet through LDS: fewer tree slots and features than the columns of a step (21,
-# 10), as many, more; a last tile with one group of two, a last group with one instance
-STAGED_SUMS_FORESTS = [(False, 1100, 7, 2, 23), (True, 1100, 7, 2, 23), (False, 1100, 3, 5, 5), (True, 1100, 3, 5, 22), (False, 1100, 13, 4, 12),
+# one or two groups per wavefront (the sums of one without thresholds meet through LDS): fewer tree slots and features than the
+# columns of a step (21, 10), as many, more; a last tile with one group of two, a last group with one instance
+ONE_OR_TWO_GROUPS_FORESTS = [(False, 1100, 7, 2, 23), (True, 1100, 7, 2, 23), (False, 1100, 3, 5, 5), (True, 1100, 3, 5, 22), (False, 1100, 13, 4, 12),
                        (True, 1100, 9, 4, 12), (False, 1100, 9, 2, 9), (True, 1100, 12, 1, 11)]
-STAGED_SUMS_TILES = [(16, False, 16401, 3, 12), (16, True, 16405, 2, 30), (16, False, 17001, 4, 9)]
+ONE_OR_TWO_GROUPS_TILES = [(16, False, 16401, 3, 12), (16, True, 16405, 2, 30), (16, False, 17001, 4, 9)]
 
 
-@pytest.mark.parametrize("binary,ntrees,NI,H,d", STAGED_SUMS_FORESTS)
-def test_forest_staged_sums(mods, seed, binary, ntrees, NI, H, d):
+@pytest.mark.parametrize("binary,ntrees,NI,H,d", ONE_OR_TWO_GROUPS_FORESTS)
+def test_forest_one_or_two_groups(mods, seed, binary, ntrees, NI, H, d):
     test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d)
 
 
-@pytest.mark.parametrize("how,binary,NI,H,d", STAGED_SUMS_TILES)
-def test_infer_staged_sums(mods, seed, how, binary, NI, H, d):
+@pytest.mark.parametrize("how,binary,NI,H,d", ONE_OR_TWO_GROUPS_TILES)
+def test_infer_one_or_two_groups(mods, seed, how, binary, NI, H, d):
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
 
 

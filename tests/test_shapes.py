@@ -1,7 +1,7 @@
 """Which variant the rules of the library choose: for the calls that the parity tests make of them, so that every
 variant meets the oracle and every test runs what it names."""
 import test_gpu_parity as gp
-from shapes import COMMON, ROWS, STORE, few, grid, infer
+from shapes import COMMON, ROWS, STORE, few, grid, infer, staged
 
 ALL_INFER = {"ahead1", "ahead2", "ahead4", "infer1", "infer2", "infer4"}
 
@@ -29,18 +29,20 @@ def test_inference_cases_run_what_they_name():
     assert {k for _, k, _ in small} == {"ahead1", "ahead2", "infer2"}, small
     wide = asked(gp.WIDE_FORCED_TILES)
     assert {(b, k) for b, k, _ in wide} == {(b, k) for b in (False, True) for k in ("infer2", "infer4")}, wide
-    staged = forest(gp.STAGED_SUMS_FORESTS)
-    assert staged == {(b, "infer1", n) for b in (False, True) for n in (1, 2)}, staged
-    assert asked(gp.STAGED_SUMS_TILES) == {(b, "infer1", 2) for b in (False, True)}
+    groups = forest(gp.ONE_OR_TWO_GROUPS_FORESTS)
+    assert groups == {(b, "infer1", n) for b in (False, True) for n in (1, 2)}, groups
+    assert asked(gp.ONE_OR_TWO_GROUPS_TILES) == {(b, "infer1", 2) for b in (False, True)}
 
 
 def test_every_inference_variant_meets_the_oracle():
-    """Both modes of every kernel; k_infer in single wavefronts with staged sums (one, two groups) and without."""
+    """Both modes of every kernel; k_infer in single wavefronts with staged sums and without."""
     seen = set()
-    for b, k, n in (one(gp.SINGLE_WAVEFRONT_TILES + gp.AHEAD_TILES) | asked(gp.SMALL_FORCED_TILES + gp.WIDE_FORCED_TILES + gp.STAGED_SUMS_TILES)
-                    | forest(gp.FOREST_FEW + gp.STAGED_SUMS_FORESTS)):
-        seen.add((b, k, k == "infer1" and n <= 2))
-    assert seen == {(b, k, False) for b in (False, True) for k in ALL_INFER} | {(b, "infer1", True) for b in (False, True)}, seen
+    for b, k, n in (one(gp.SINGLE_WAVEFRONT_TILES + gp.AHEAD_TILES) | asked(gp.SMALL_FORCED_TILES + gp.WIDE_FORCED_TILES + gp.ONE_OR_TWO_GROUPS_TILES)
+                    | forest(gp.FOREST_FEW + gp.ONE_OR_TWO_GROUPS_FORESTS)):
+        seen.add((b, k, k == "infer1" and staged(n, not b)))
+    assert seen == {(b, k, False) for b in (False, True) for k in ALL_INFER} | {(True, "infer1", True)}, seen
+    # staged sums only where they measured faster (see group_sums)
+    assert [staged(n, thr) for thr in (False, True) for n in (1, 2, 3)] == [True, False, False, False, False, False]
 
 
 def test_grid_variants_meet_the_oracle():
