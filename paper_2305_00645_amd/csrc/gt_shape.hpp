@@ -119,16 +119,21 @@ static inline InferShape infer_shape(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u
     // a lone label: k_infer's start and end count beside its one access, which its cost above leaves out (137, 2,699, 12,110 instances
     // 11.4, 12.5, 13.6 us; k_infer_ahead 8.6, 8.7, 9.6)
     if (H == 0 && best.nq) return best;
-    // a tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
-    // unless the rows stay in the L2s (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of 64: 5.8 with two),
-    // and of rows of 250 columns on at least 21 a step (208,758 x 373, depth 3, tiles of 32: 4.14 ms with 10, two wavefronts, 3.79 with
-    // 21, four; of 16: 3.65 and 3.45, thresholds 4.12 and 3.64; of 200 columns 2.23 and 2.30, 1.99 and 2.02)
+    // A tile that the caller asks for: the fewest wavefronts whose steps do not fetch the rows' 128-byte lines more than twice,
+    // unless the rows stay in the L2s or are of less than 48 columns (300,000 x 150, depth 4, tiles of 32: 4.2 ms with one, 3.8 with four; tiles of
+    // 64: 5.8 with two; but 208,758 x 30, depth 3: 522 us with one, 595 with two, 1,052 with four; of depth 12, where the tree's
+    // steps divide by the wavefronts as well, 20.3 ms with one, 18.5 with two), and of rows of 250 columns on at least 21 a step once
+    // the wavefronts fill the chip (208,758 x 373, depth 3, tiles of 32: 4.14 ms with 10, two wavefronts, 3.79 with 21, four; of 16: 3.65 and 3.45,
+    // thresholds 4.12 and 3.64; of 200 columns 2.23 and 2.30, 1.99 and 2.02; 25,000 x 300, 782 tiles of 32: 468 us with 10, 484 with 21).
     u32 nw = 1;
     const u32 ask = lgi ? (1u << lgi) / 8 : 0;
     if (ask) {
         const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
-        const auto few_columns = [&](u32 ncol) { return !in_l2 && ((d + ncol - 1) / ncol > 2 * ((d + 15) / 16) || (d >= 250 && ncol < GT_TP)); };
-        while (nw < 4 && (ask > GT_INFER_OCT(nw) || few_columns(GT_INFER_LANES(nw) / ask))) nw *= 2;
+        const u64 tiles = (ngrp + ask - 1) / ask * ntrees;
+        const auto more = [&](u32 ncol) {
+            return !in_l2 && (((d >= 48 || H >= 10) && (d + ncol - 1) / ncol > 2 * ((d + 15) / 16)) || (d >= 250 && ncol < GT_TP && tiles * nw > 2 * simds));
+        };
+        while (nw < 4 && (ask > GT_INFER_OCT(nw) || more(GT_INFER_LANES(nw) / ask))) nw *= 2;
     }
     for (u32 noct = 1; noct <= GT_INFER_OCT(nw); noct++) {
         if (!forced(noct)) continue;

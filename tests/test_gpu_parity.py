@@ -879,9 +879,9 @@ def test_forest_on_few_instances(mods, seed, binary, ntrees, NI, H, d):
     test_forest_in_one_launch(mods, seed, binary, ntrees, NI, H, d)
 
 
-# tiles asked for that are on the chip at once (k_infer_ahead, 21 and 42 lanes per party), and one of two wavefronts
+# tiles asked for that are on the chip at once (k_infer_ahead, 21 and 42 lanes per party), and narrow rows on one and two wavefronts
 SMALL_FORCED_TILES = [(16, True, 9001, 2, 5), (32, False, 20003, 2, 5), (32, True, 8300, 1, 100), (64, False, 17000, 1, 60), (64, True, 17003, 1, 40),
-                      (64, True, 40007, 2, 5)]
+                      (64, True, 40007, 2, 5), (64, False, 33003, 1, 13), (32, True, 33003, 1, 13)]
 
 
 @pytest.mark.parametrize("how,binary,NI,H,d", SMALL_FORCED_TILES)
@@ -889,7 +889,7 @@ def test_infer_small_forced_tiles(mods, seed, how, binary, NI, H, d):
     test_infer_paths_agree(mods, seed, how, binary, NI, H, d)
 
 
-WIDE_FORCED_TILES = [(32, True, 33003, 1, 13), (32, False, 33010, 1, 21), (32, False, 20003, 1, 100), (64, True, 33003, 1, 13), (64, False, 33003, 1, 13),
+WIDE_FORCED_TILES = [(32, True, 33003, 1, 60), (32, False, 33010, 1, 50), (32, False, 20003, 1, 100), (64, True, 36001, 1, 50), (64, False, 33003, 1, 60),
                      (64, False, 20003, 1, 100)]
 
 

@@ -26,7 +26,7 @@ def test_inference_cases_run_what_they_name():
     few_inst = forest(gp.FOREST_FEW)
     assert {k for _, k, _ in few_inst} == {"ahead1"} and {n for _, _, n in few_inst} == {1, 2, 3, 4}, few_inst
     small = asked(gp.SMALL_FORCED_TILES)
-    assert {k for _, k, _ in small} == {"ahead1", "ahead2", "infer2"}, small
+    assert {k for _, k, _ in small} == {"ahead1", "ahead2", "infer1", "infer2"}, small
     wide = asked(gp.WIDE_FORCED_TILES)
     assert {(b, k) for b, k, _ in wide} == {(b, k) for b in (False, True) for k in ("infer2", "infer4")}, wide
     groups = forest(gp.ONE_OR_TWO_GROUPS_FORESTS)
@@ -101,3 +101,6 @@ def test_asked_tiles_of_wide_rows():
         assert [infer(208758, 3, d, thr, 32)[0] for d in (100, 200, 373, 600)] == ["infer2", "infer2", "infer4", "infer4"]
         assert [infer(208758, 3, d, thr, 16)[0] for d in (100, 200, 373, 600)] == ["infer1", "infer1", "infer2", "infer2"]
         assert [infer(208758, 3, d, thr, 64)[0] for d in (20, 100, 373)] == ["infer2", "infer4", "infer4"]
+        assert [infer(208758, 3, d, thr, 32)[0] for d in (20, 30, 47)] == ["infer1"] * 3      # narrow rows: the fewest that hold the tile
+        assert [infer(208758, 12, d, thr, 32)[0] for d in (20, 30, 64)] == ["infer1", "infer2", "infer2"]
+        assert infer(25000, 3, 300, thr, 32)[0] == "infer2" and infer(25000, 3, 300, thr, 16)[0] == "infer1"
