@@ -96,12 +96,12 @@ typedef struct {
 #define GT_FLAG_INFER_TILE(n) ((n) == 16 ? 0x100u : (n) == 32 ? 0x200u : (n) == 64 ? 0x300u : 0u)
 enum {
     GT_KC_SHARE = 0, /* share / reconstruct */
-    GT_KC_MULT = 1,  /* elementwise products with reshare */
+    GT_KC_MULT = 1,  /* elementwise products with reshare; a level's node split with the local copies that end the level */
     GT_KC_EQGRID = 2,/* equality grid with inner product against a shared array (array access over a
                         tree level or the leaf labels) */
     GT_KC_COUNT = 3, /* statistics contraction */
-    GT_KC_SMALL = 4, /* per-node protocols: division, arg-max, updates */
-    GT_KC_LOCAL = 5, /* copies, transposes, fills (no messages) */
+    GT_KC_SMALL = 4, /* per-node protocols: division, arg-max, updates; completion of split inner products, with a level's leaf flags */
+    GT_KC_LOCAL = 5, /* copies, transposes, fills, a training's start with the tiles of its class columns (no messages) */
     GT_KC_EQGRID_ROWS = 6,  /* equality grid with inner product against the sample's own row */
     GT_KC_EQGRID_STORE = 7, /* equality grid that stores the per-sample leaf one-hot */
     GT_KC_INFER = 8,        /* one-launch inference */

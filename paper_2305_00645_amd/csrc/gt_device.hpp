@@ -39,7 +39,7 @@ __device__ __forceinline__ u32 rotl32(u32 x, int r) { return __builtin_rotatelef
 // second kind) in between: whoever stands at a rotation goes first, and the two wavefronts meet again at the additions.
 // Blocks alone, cycles per instruction: with two wavefronts per SIMD 4.53 -> 2.60, with four 4.08 -> 2.62, with eight 4.09 -> 2.41.
 // Array access 200,003 x 100 269 -> 210 us, 100,003 quotients 109 -> 75 us; the same priority for additions and the rest: 225 and 87.
-// PRF_ALONE: none of this, where a SIMD has one wavefront (4.91 -> 5.00 cycles).  PRF_PAIR_LOOP: in loops that call this
+// PRF_ALONE: none of this, where a SIMD has one wavefront as a rule (4.91 -> 5.00 cycles).  PRF_PAIR_LOOP: in loops that call this
 // with one key, operation and stream three of the first round's quarter rounds are constants and leave the loop; the first
 // round goes without priorities then (10^6 instances of depth 10: 28.9 ms, 30.9 with them; the quotients 77 us without, 75 with).
 enum { PRF_ALONE = 0, PRF_PAIR = 1, PRF_PAIR_LOOP = 2 };
@@ -545,8 +545,12 @@ struct WWire {
 // The wavefront model for the per-element protocols where their chain counts and not the vector unit: a row of 16 lanes is 5
 // elements x 3 parties (lane 16 r + 5 p + j: party p of element 5 r + j; the row's last lane repeats its first and
 // neither stores nor counts), so that a message is a copy from lane to lane inside a row, two DPP moves a dword and no LDS
-// latency: about 30 cycles instead of 150.  Not where SIMDs are full: the moves take the vector unit's time.
-// Training of 267 x 22, depth 4, 473 -> 463 us; of 1,200 x 60, depth 6, 738 -> 720 us.
+// latency: about 30 cycles instead of 150.  Training of 267 x 22, depth 4, 473 -> 463 us; of 1,200 x 60, depth 6, 738 -> 720 us.
+// Chosen by kernel, not by launch: PRF_ALONE, without issue priorities, where the launches are small as a rule (the arg-max, the
+// updates, one-hots, labels, completions of sums, Boolean tests, divisions and scores with four wavefronts per tile), whatever their size.  On a
+// full chip the lane moves still cost no more than LDS does: 10,001 wavefronts of k_dot_fin 14.2 us (through LDS 14.4), 14,746 of k_count_fin
+// 22.7 (22.7), 7,374 of k_update 17.5 (19.4), 4,096 of k_argmax<1> 18.3 (18.4); through LDS with priorities 13.0, 20.0, 18.1 and 15.4, and
+// 2 to 8 % more than DPP where SIMDs have one wavefront.
 struct DWire : WWire {
     __device__ __forceinline__ void init(uint4 *region, u64 *s_cnt)
     {

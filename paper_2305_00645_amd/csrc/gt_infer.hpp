@@ -345,7 +345,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
 // chip the vector ALU (masks and daBits of the columns that a level does not have are evaluated all the same).  Measured, in one
 // wavefront per 21 lanes that did both, four per tile, and now: one instance of 22 features, depth 7, thresholds 127 -> 60 us;
 // 10^4 x 16, depth 7, thresholds 161 -> 112 us; 300 x 100, depth 5, 89 -> 48 us; 1,000 trees of depth 3 on one instance 73 -> 44 us.
-// Both sides on eight tests a lane, with two wavefronts per SIMD: 70, 104, 54 us for the first three.
+// Both sides on eight tests a lane, with two wavefronts per SIMD: 70, 104, 54 us for the first three.  The 128 registers of four
+// wavefronts per SIMD spill 31 or 32, with thresholds 42 (128 to 172 bytes a lane).
 #define GT_AHEAD_T 96                                  // words per group: material of an access to the tree, [6][8] and [2][3][8]
 #define GT_AHEAD_F 72                                  // to the features, [6][8] and [3][8]
 #define GT_AHEAD_G 128                                 // of a comparison, as in InferWg

@@ -670,7 +670,7 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 // Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, and
 // takes about 3,750 cycles of a SIMD (4,900 before the PRF's additions were made to pair, see chacha8).  One wavefront per workgroup, two per
 // SIMD: the rows' public values, Boolean components and sums and the values of the next column
-// fit their 256 registers but for 8 in GM_ROWS and 4 with two sums, and two barrier-free wavefronts
+// fit their 256 registers but for 9 in GM_ROWS and 4 with two sums (with issue priorities 6 in GM_ROWS and 5 with one sum), and two barrier-free wavefronts
 // keep the vector unit as busy as three did; three had to spill far more, and every reload waited
 // for the loads from HBM issued before it (GM_ROWS, 64 columns of 10^6 samples: 1.17 ms with three,
 // 0.88 ms with two).  Before, with one party per wavefront and ten workgroup barriers per step:
@@ -908,7 +908,8 @@ __global__ __launch_bounds__(64) void k_dot_fin(GridArgs a, u32 finblk, EqArgs e
     W.flush(a.c.wire);
 }
 
-// z = B2A([x >= y]).  300,007 elements: 54 us with a party per wavefront, 27 us now.
+// z = B2A([x >= y]).  300,007 elements: 54 us with a party per wavefront, 27 us in the wavefront model, 25 with the issue
+// priorities of PRF_PAIR.
 struct GeArgs { KCommon c; P6 x, y, z; u64 n; };
 __global__ __launch_bounds__(64) void k_ge(GeArgs a)
 {
@@ -992,8 +993,8 @@ __device__ __forceinline__ void div_steps_el(WireT &W, TileT &T, u64 *s_mat, int
     const int p = W.p;                                                                      \
     ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.keys = a.c.keys; T.mat = s_mat;
 
-// 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us now (VALU: a PRF pass and 330
-// instructions of protocol per step and 20 elements).
+// 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us in the wavefront model, 75 with the issue priorities of
+// PRF_PAIR (VALU: a PRF pass and 330 instructions of protocol per step and 20 elements).
 struct DivArgs { KCommon c; P6 S, Q, quo; u64 n; u32 nsteps; };
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void k_div(DivArgs a)

@@ -61,7 +61,7 @@ __device__ __forceinline__ void pm_prf_pass(const PartMmArgs &a, const Key &own,
 }
 
 // More than GT_PM16_NODES nodes in the level before.  Bound: vector work (the PRF, recombination, byte permutes) beside matrix-core time, one wavefront per SIMD on three of a
-// compute unit's four: 256 accumulators leave room for no second workgroup, and 47 registers spill (192 B a lane).
+// compute unit's four: 256 accumulators leave room for no second workgroup, and 45 registers spill (184 B a lane).
 __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 {
     __shared__ u64 s_wire[GT_LWIRE_WORDS];
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(192, 1) void k_part_mm(PartMmArgs a)
 // 32 columns x 16 samples: one PRF pass, 72 matrix-core instructions, two barriers.
 // Bound: the vector ALU (PRF, recombination, three-term products) and the reads of X, with three wavefronts per SIMD.
 // 19,997 samples x 101 columns, 1 to 32 nodes in the level before: 131 us a level with k_part_mm, 51 now (with two wavefronts
-// per SIMD 56, with four, which spill 100 registers, 90).
+// per SIMD 56, with four, which spill 100 registers, 90; with three 3 spill).
 #define GT_PM16_NODES 32
 #define PM16_STRIDE 80                       // bytes between the samples of a limb in the staging area (64 and a pad)
 __global__ __launch_bounds__(192, 3) void k_part_mm16(PartMmArgs a)

@@ -85,16 +85,16 @@ static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xc
 // groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
 // 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
 // other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
-// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.48 ms; 16 trees of
-// depth 5 on 5,003 x 30: 570 and 436 us); of two or four for some tiles that the caller asks for.
+// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.64 ms; 16 trees of
+// depth 5 on 5,003 x 30: 570 and 437 us); of two or four for some tiles that the caller asks for.
 // simds: of the device; lgi: log2 of the instances per workgroup that the caller asks for, 0: none; ngrp: groups of 8 instances.
 // The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
 // opening, the sums), a comparison 0.4 and 0.4 for every instance of a group that a lane takes; a wavefront alone on its
 // SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
 // lines that it had before.  k_infer_ahead: 3.6 for a launch, 0.1 and 0.1 more for every 21 lanes an access (barriers), 0.32 a
 // step, 0.41 with thresholds, 0.27 for every instance of a half group that a lane compares; all but the launch times
-// 2.2 where the chip is full.  Over 53 batches and forests of 1 to 700,000 instances this picks within 2 % of the
-// best of all shapes on average, 16 % at worst.
+// 2.2 where the chip is full.  Over the 53 batches and forests of 1 to 700,000 instances that it was
+// fitted to this picks within 2 % of the best of all shapes on average, 16 % at worst (50,000 x 294, depth 6: two groups, 1.64 ms; one 1.43).
 struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
 // whether single wavefronts of k_infer add up their sums through LDS, see group_sums
 static inline bool staged_sums(u32 noct, bool has_thr) { return noct == 1 && !has_thr; }
