@@ -921,22 +921,22 @@ OWN_ROWS_ALONE = (6495, 252)
 
 def test_own_rows_wait_for_no_load(mods, seed):
     """A wavefront per SIMD: the grid over the rows' own values, fetched a step ahead, takes as long as the one against a
-    shared array (within 6 %).  Measured 1.00; where a step waits for its fetch 1.11.  (Launches after a call's first, whose
+    shared array (within 2 %).  Measured 0.98 to 0.99; where a step waits for its fetch 1.05 to 1.06.  (Launches after a call's first, whose
     rows come from memory.)"""
     _, gtree = mods
     rng = np.random.default_rng(5)
     n, d = OWN_ROWS_ALONE
     g = gtree.GTree(seed, flags=gtree.GT_FLAG_LEVELWISE_INFER, profile=True)
-    trees = {H: g.tree_import(g.share_a(rng.integers(0, d, (1 << H) - 1).astype(np.uint64)), None, g.share_a(u64([0, 1] * (1 << H - 1))), H) for H in (1, 5)}
+    trees = {H: g.tree_import(g.share_a(rng.integers(0, d, (1 << H) - 1).astype(np.uint64)), None, g.share_a(u64([0, 1] * (1 << H - 1))), H) for H in (1, 9)}
     I = g.share_a((rng.random(n * d) < 0.5).astype(np.uint64))
     W, u = g.share_a(rng.integers(0, 9, d).astype(np.uint64)), g.share_a(rng.integers(0, d, n).astype(np.uint64))
-    rows, common = {1: 1e9, 5: 1e9}, 1e9
-    for _ in range(12):
+    rows, common = {1: 1e9, 9: 1e9}, 1e9
+    for _ in range(40):
         for H in rows:
             g.stats_reset(); g.infer_batch(trees[H], I, n, d); rows[H] = min(rows[H], g.prof()["eqgrid_rows"][0])
         g.stats_reset(); g.oaa(W, u); common = min(common, g.prof()["eqgrid"][0])
     g.close()
-    assert (rows[5] - rows[1]) / 4 < 1.06 * common, (rows, common)
+    assert (rows[9] - rows[1]) / 8 < 1.02 * common, (rows, common)
 
 
 LEVELWISE_LARGE = (False, 30001, 6, 3)
