@@ -23,14 +23,14 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // wavefronts, alone on a SIMD, take 0.82 of the time of two with paired additions (the sums of many short ranges meet at the same words,
 // which is why 0.6 is the better line there: 445 rows x 669 columns 29 us in 341 ranges, 51 in 683).  140,244 rows x 32 columns: 92
 // in one, 61 and 11 in two; x 8 columns 31 in one, 22 and 11 in two.  Two columns in one range and in two, with that launch: 13 rows 12.2
-// and 12.2 us, 30,000 rows 13.2 and 14.6; of their own (fetched meanwhile) 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9
+// and 12.2 us, 30,000 rows 13.2 and 14.6 (three columns: 15.5 either way, 45,753 rows 16.4 in one, 17.4 in three); of their own (fetched meanwhile) 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9
 // more; two sums, 13 to 20,000 rows 3 to 3.5 us less in two (one range completes the sums of eight rows per lane), 30,000 0.9
 // less, 60,000 3.7 more.
 static inline u64 column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
 {
     const u64 half = simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
     // in units of a step of two wavefronts, 3 us
-    const double launch = sums == 0 ? 0.0 : sums == 2 ? 0.5 + 0.006 * (double)ntile : mode == GM_ROWS ? 1.2 + 0.003 * (double)ntile : 1.6 + 0.0027 * (double)ntile;
+    const double launch = sums == 0 ? 0.0 : sums == 2 ? 0.5 + 0.006 * (double)ntile : (mode == GM_ROWS ? 1.2 : 1.6) + 0.003 * (double)ntile;
     u64 best = 1;
     double best_cost = 0;
     for (u64 f : fills) {

@@ -81,6 +81,7 @@ def test_two_columns_take_the_faster_split():
     for n in (13, 267, 3000, 10000):
         assert grid(ROWS, 2, n)["ranges"] == 2 and grid(COMMON, 2, n, sums=2)["ranges"] == 2, n
         assert grid(COMMON, 2, n)["ranges"] == 1, n
+    assert grid(COMMON, 3, 45753)["ranges"] == 1 and grid(COMMON, 4, 30000)["ranges"] == 4
     assert grid(ROWS, 2, 30000)["ranges"] == 1 and grid(COMMON, 2, 30000, sums=2)["ranges"] == 2
     for n in (60000, 170000):
         assert grid(ROWS, 2, n)["ranges"] == grid(COMMON, 2, n, sums=2)["ranges"] == grid(COMMON, 2, n)["ranges"] == 1, n
