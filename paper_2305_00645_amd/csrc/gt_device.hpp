@@ -461,7 +461,7 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-#define GT_WMSG_QUADS (4 * GT_LANES)                 // message region of a wavefront: 16 dwords per lane
+#define GT_WMSG_QUADS (2 * GT_LANES)                 // message region of a wavefront: 8 dwords per lane
 struct WWire {
     uint4 *buf;
     u64 *cnt;
@@ -485,7 +485,7 @@ struct WWire {
     template <int ND>
     __device__ __forceinline__ void pass(const u32 (&s)[ND], u32 (&r)[ND], u32 from)
     {
-        static_assert(ND == 1 || ND == 2 || (ND % 4 == 0 && ND <= 16), "message size");
+        static_assert(ND == 1 || ND == 2 || (ND % 4 == 0 && ND <= 8), "message size");
         wave_sync();
         // small messages use the same 16-byte slots: one address register per direction for all sizes
         if (ND == 1) buf[m].x = s[0];
@@ -508,12 +508,17 @@ struct WWire {
     template <int NW>
     __device__ __forceinline__ void pass64(const u64 (&s)[NW], u64 (&r)[NW], u32 from)
     {
-        u32 a[2 * NW], b[2 * NW];
+        constexpr int M = NW < 4 ? NW : 4;             // words at a time: the region's 8 dwords per lane
+        static_assert(NW % M == 0, "message size");
 #pragma unroll
-        for (int j = 0; j < NW; j++) { a[2 * j] = (u32)s[j]; a[2 * j + 1] = (u32)(s[j] >> 32); }
-        pass<2 * NW>(a, b, from);
+        for (int h = 0; h < NW; h += M) {
+            u32 a[2 * M], b[2 * M];
 #pragma unroll
-        for (int j = 0; j < NW; j++) r[j] = (u64)b[2 * j] | ((u64)b[2 * j + 1] << 32);
+            for (int j = 0; j < M; j++) { a[2 * j] = (u32)s[h + j]; a[2 * j + 1] = (u32)(s[h + j] >> 32); }
+            pass<2 * M>(a, b, from);
+#pragma unroll
+            for (int j = 0; j < M; j++) r[h + j] = (u64)b[2 * j] | ((u64)b[2 * j + 1] << 32);
+        }
     }
     template <int ND> __device__ __forceinline__ void reshare(const u32 (&s)[ND], u32 (&r)[ND]) { pass<ND>(s, r, nx); }
     template <int NW> __device__ __forceinline__ void reshare64(const u64 (&s)[NW], u64 (&r)[NW]) { pass64<NW>(s, r, nx); }

@@ -26,10 +26,12 @@ struct InferArgs {
 // access, where the offline and zero-sharing words of the rows, evaluated by all lanes side by side, and the sums
 // change hands.  k_infer_ahead, for few instances, is described further down.
 // words per group of 8 instances.  Material of an access: r's arithmetic and Boolean components
-// [6][8], zero-sharing words [2 streams][3 keys][8]; of a comparison: [9][8] components (r, r's bits,
-// beta), beta's bits [8], mask words [2][3][8].  Values: index, id, threshold as [party][own, next][8].
-#define GT_INFER_MAT 128
-#define GT_INFER_VAL 48
+// [6][8], zero-sharing words [2 streams, one without thresholds][3 keys][8]; of a comparison: [9][8] components (r, r's bits,
+// beta), beta's bits [8], mask words [2][3][8].  Sums: [2, 1][3][8].  Values: index, id, threshold by component, [3][8]
+// each: a component is written by the party whose own it is.
+#define GT_INFER_MAT(THR) ((THR) ? 128 : 72)
+#define GT_INFER_SUM(THR) ((THR) ? 48 : 24)
+#define GT_INFER_VAL 24
 
 // Adds up what the lanes of a wavefront hold for the same group of instances (lanes t, t + noct, .. of a party; q0: number of
 // the wavefront's first lane in the workgroup's party) and adds the sums to sum[group * stride + 8 party ..]; a lane
@@ -71,14 +73,16 @@ template <int ISSUE, bool STAGED>
 struct InferWg {
     EqWave E;
     u64 *sums;                   // of the workgroup's groups
-    u64 *mat, *val, *sum;        // of this lane's group: GT_INFER_MAT, 3 * GT_INFER_VAL, [2][3][8] words
+    u64 *opened;                 // this wavefront's copy of the group's opened values u + r - base, 8 words
+    u64 *mat, *val, *sum;        // of this lane's group: material, values, sums
     const u32 *keys;
-    u32 cl, ncol, q0, noct;      // q0: the wavefront's first lane in the workgroup's party
+    u32 cl, ncol, q0, noct, stride;      // q0: the wavefront's first lane in the workgroup's party
     u64 ngrp, grp, NI;           // groups of the batch, this lane's group
     bool active, one;            // the lane has a group / is the one that counts and stores for its group and party
     int p, pn;
 
-    __device__ __forceinline__ u64 &value(int which, int party, int comp, int s) { return val[which * GT_INFER_VAL + (party * 2 + comp) * 8 + s]; }
+    // component `comp` of a value, for both parties that hold it
+    __device__ __forceinline__ u64 &value(int which, int comp, int s) { return val[which * GT_INFER_VAL + comp * 8 + s]; }
     __device__ __forceinline__ u32 live() const { return grp < ngrp ? live8(grp * 8, NI) : 0u; }
 
     // the PRF block of role b: block `blk` of a stream under a key; which lanes evaluate it is free
@@ -125,18 +129,18 @@ struct InferWg {
         __syncthreads();
         // the one opening of the access: c = u + r - base is public afterwards; the lanes of a group
         // replay the same message, one of them counts
-        u64 cpub[8], rho_o[8], rho_n[8];
         {
             u64 snd[8], mn[8], rcv[8];
 #pragma unroll
             for (int s = 0; s < 8; s++) {
-                snd[s] = value(which, p, 0, s) + mat[p * 8 + s]; mn[s] = value(which, p, 1, s) + mat[W.pn * 8 + s];
-                rho_o[s] = mat[24 + p * 8 + s]; rho_n[s] = mat[24 + W.pn * 8 + s];
+                snd[s] = value(which, p, s) + mat[p * 8 + s]; mn[s] = value(which, pn, s) + mat[W.pn * 8 + s];
             }
             W.open64<8>(snd, rcv);
             W.nopen += one ? 64u * live() : 0u;
+            // every lane of a group has the same words; kept in LDS, like r's Boolean components, for the access's steps
 #pragma unroll
-            for (int s = 0; s < 8; s++) cpub[s] = snd[s] + mn[s] + rcv[s] - base;
+            for (int s = 0; s < 8; s++) opened[s] = snd[s] + mn[s] + rcv[s] - base;
+            wave_sync();
         }
         u64 acc[8], acc2[8], xo[8], xn[8];
 #pragma unroll
@@ -160,10 +164,12 @@ struct InferWg {
             const u32 col = k0 + cl;
             const bool act = active && col < w;
             Sh Wk = { 0, 0 }, Wk2 = { 0, 0 };
-            u64 cd[8];
+            const u32 f = E.template tests<false, ISSUE>(op, (u64)col * ngrp + grp, [&](int h, u64 (&cd)[4], u64 (&ro)[4], u64 (&rn)[4]) {
 #pragma unroll
-            for (int s = 0; s < 8; s++) cd[s] = cpub[s] - col;
-            const u32 f = E.template tests<false, ISSUE>(op, (u64)col * ngrp + grp, cd, rho_o, rho_n, 0, 0, act ? live() : 0u, [&]() {
+                for (int j = 0; j < 4; j++) {
+                    cd[j] = opened[h + j] - col; ro[j] = mat[24 + p * 8 + h + j]; rn[j] = mat[24 + W.pn * 8 + h + j];
+                }
+            }, 0, 0, act ? live() : 0u, [&]() {
                 if (!ROWS && act) { Wk.o = w1o[col]; Wk.n = w1n[col]; }
                 if (!ROWS && NDOT == 2 && act && nd2) { Wk2.o = w2o[col]; Wk2.n = w2n[col]; }
             });
@@ -188,8 +194,8 @@ struct InferWg {
                 }
             }
         }
-        group_sums<STAGED>(W, (u64 *)W.buf, acc, active, q0, noct, sums, 48);
-        if (NDOT == 2 && nd2) group_sums<STAGED>(W, (u64 *)W.buf, acc2, active, q0, noct, sums + 24, 48);
+        group_sums<STAGED>(W, E.rows, acc, active, q0, noct, sums, stride);
+        if (NDOT == 2 && nd2) group_sums<STAGED>(W, E.rows, acc2, active, q0, noct, sums + 24, stride);
         __syncthreads();
         // every lane of a group finishes the group's result
 #pragma unroll
@@ -240,29 +246,29 @@ struct InferWg {
             D.bA.o = mat[48 + p * 8 + s]; D.bA.n = mat[48 + pn * 8 + s];
             D.bBo = (u32)(mat[72 + s] >> p) & 1; D.bBn = (u32)(mat[72 + s] >> pn) & 1;
             const u64 AG = mat[80 + p * 8 + s] ^ mat[80 + pn * 8 + s], AE = mat[104 + p * 8 + s] ^ mat[104 + pn * 8 + s];
-            const Sh v = { value(2, p, 0, s) - value(1, p, 0, s), value(2, p, 1, s) - value(1, p, 1, s) };
+            const Sh v = { value(2, p, s) - value(1, p, s), value(2, pn, s) - value(1, pn, s) };
             const Sh bit = b2a(W, p, not_bit(p, ge_bit_masks(W, p, v, D, AG, AE, act)), D, act);
-            if (mine && W.real) {
-                value(0, p, 0, s) = 2 * value(0, p, 0, s) + bit.o + one1.o;
-                value(0, p, 1, s) = 2 * value(0, p, 1, s) + bit.n + one1.n;
-            }
+            if (mine && W.real) value(0, p, s) = 2 * value(0, p, s) + bit.o + one1.o;
         }
     }
 };
 
-// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD (68 spill, 101 with thresholds, 73 with
-// STAGED sums).  Measured, with one party per wavefront and a barrier per message, in
-// workgroups of four wavefronts, now: 10^6 instances x 64 features, depth 10, 46.6, 34.5, 27 ms; 16 trees of
-// depth 5 on 5,003 x 30 with thresholds 0.74, 0.58, 0.44 ms.  For NW see infer_shape.
+// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD: 9 spill, 15 with thresholds, since the rows'
+// opened values and Boolean components are read from LDS in every step (68 and 101 when the lanes held them: 16 trees of depth 5 on
+// 5,003 x 30 with thresholds 439 us, 414 now; 300,000 x 20, depth 5, 1,055 and 1,006; 10^6 x 64, depth 10, 26.9 and 26.7 ms).  Three wavefronts of
+// 168 registers spill 100 around the accesses, which only accesses of thousands of columns outweigh: 50,000 x 294, depth 6, 1.66 and 2.53 ms.
+// Before, with one party per wavefront and a barrier per message, and in workgroups of four wavefronts: 10^6 x 64 46.6 and 34.5 ms,
+// 16 trees 0.74 and 0.58 ms.  For NW see infer_shape.
 template <bool THR, int NW, bool STAGED>
 __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
 {
     __shared__ uint4 s_msg[NW][GT_WMSG_QUADS];
     __shared__ u64 s_rows[NW][GT_EQ_ROWS];
     __shared__ u64 s_cnt[NW][6];
-    __shared__ u64 s_mat[GT_INFER_OCT(NW)][GT_INFER_MAT];
-    __shared__ u64 s_val[GT_INFER_OCT(NW)][3 * GT_INFER_VAL];
-    __shared__ u64 s_sum[GT_INFER_OCT(NW)][48];
+    __shared__ u64 s_mat[GT_INFER_OCT(NW)][GT_INFER_MAT(THR)];
+    __shared__ u64 s_val[GT_INFER_OCT(NW)][(THR ? 3 : 2) * GT_INFER_VAL];
+    __shared__ u64 s_sum[GT_INFER_OCT(NW)][GT_INFER_SUM(THR)];
+    __shared__ u64 s_open[NW][GT_INFER_OCT(NW)][8];
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     InferWg<PRF_PAIR_LOOP, STAGED> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
@@ -271,8 +277,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
     X.ncol = GT_INFER_LANES(NW) / a.noct;
     const u32 q = wave * GT_TP + W.t, o = q % a.noct;
     X.cl = q / a.noct; X.active = X.cl < X.ncol; X.one = X.cl == 0 && W.real;
-    X.sums = s_sum[0]; X.q0 = wave * GT_TP; X.noct = a.noct;
-    X.mat = s_mat[o]; X.val = s_val[o]; X.sum = s_sum[o];
+    X.sums = s_sum[0]; X.stride = GT_INFER_SUM(THR); X.q0 = wave * GT_TP; X.noct = a.noct;
+    X.opened = s_open[wave][o]; X.mat = s_mat[o]; X.val = s_val[o]; X.sum = s_sum[o];
     X.ngrp = a.N8 / 8; X.NI = a.NI;
     const Sh one = pub(W.p, 1);
     const int p = W.p;
@@ -285,7 +291,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
         __syncthreads();
         if (X.one) {
 #pragma unroll
-            for (int s = 0; s < 8; s++) { X.value(0, p, 0, s) = 0; X.value(0, p, 1, s) = 0; }
+            for (int s = 0; s < 8; s++) X.value(0, p, s) = 0;
         }
         for (u32 n = 0; n <= a.H; n++) {
             // level n's ids (and thresholds) at the index; after the last level the labels
@@ -305,19 +311,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
             if (X.one) {
 #pragma unroll
                 for (int s = 0; s < 8; s++) {
-                    X.value(1, p, 0, s) = zo[s]; X.value(1, p, 1, s) = zn[s];
-                    if (THR) { X.value(2, p, 0, s) = yo[s]; X.value(2, p, 1, s) = yn[s]; }
+                    X.value(1, p, s) = zo[s];
+                    if (THR) X.value(2, p, s) = yo[s];
                 }
             }
             X.template access<true, 1>(op0 + n * S + 1, 1, 0, a.d, a.feat, a.feat, 0, false, a.I, a.d, zo, zn, yo, yn);
             if (X.one) {
 #pragma unroll
                 for (int s = 0; s < 8; s++) {
-                    if (THR) { X.value(1, p, 0, s) = zo[s]; X.value(1, p, 1, s) = zn[s]; }
-                    else {
-                        X.value(0, p, 0, s) = 2 * X.value(0, p, 0, s) + zo[s] + one.o;
-                        X.value(0, p, 1, s) = 2 * X.value(0, p, 1, s) + zn[s] + one.n;
-                    }
+                    if (THR) X.value(1, p, s) = zo[s];
+                    else X.value(0, p, s) = 2 * X.value(0, p, s) + zo[s] + one.o;
                 }
             }
             if (THR) X.greater(op0 + n * S + 2);
@@ -350,7 +353,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
 #define GT_AHEAD_T 96                                  // words per group: material of an access to the tree, [6][8] and [2][3][8]
 #define GT_AHEAD_F 72                                  // to the features, [6][8] and [3][8]
 #define GT_AHEAD_G 128                                 // of a comparison, as in InferWg
-struct AheadStep { uint4 mask[4 * GT_LANES]; u64 rows[GT_EQ_ROWS]; u32 bits[GT_LANES]; };   // a step's material of 21 lanes per party
+// daBit rows test after test here, as the wavefronts of a half take them (in the order of eq_row one instance takes 60.1 us instead of 59.5)
+#define GT_AHEAD_COMP (9 * (GT_TP + 1))
+struct AheadStep { uint4 mask[4 * GT_LANES]; u64 rows[3 * GT_AHEAD_COMP]; u32 bits[GT_LANES]; };   // a step's material of 21 lanes per party
 
 // The AND rounds of four equality tests, as EqWave::rounds for eight: [cd == 0] of tests 4h .. 4h + 3; the opened f has test j in
 // bit 8 j, and so has bw, the Boolean components of the daBits.
@@ -404,8 +409,8 @@ __global__ __launch_bounds__(256 * NQ, 4) void k_infer_ahead(InferArgs a)
     __shared__ uint4 s_msg[2 * NQ][2 * GT_LANES];
     __shared__ AheadStep s_step[2][NQ];
     __shared__ u64 s_matT[OCT][GT_AHEAD_T], s_matF[OCT][GT_AHEAD_F], s_matG[THR ? OCT : 1][GT_AHEAD_G];
-    __shared__ u64 s_val[2][OCT][GT_INFER_VAL];                // the index, of even and of odd levels
-    __shared__ u64 s_th[THR ? OCT : 1][GT_INFER_VAL];          // the threshold
+    __shared__ u64 s_val[2][OCT][2 * GT_INFER_VAL];                // the index, of even and of odd levels
+    __shared__ u64 s_th[THR ? OCT : 1][2 * GT_INFER_VAL];          // the threshold
     __shared__ u64 s_sumT[OCT][48], s_sumF[OCT][24];
     __shared__ u64 s_cnt[2 * NQ][6];
     // A workgroup's wavefronts go to the SIMDs in turn; the roles of the second, third, .. workgroup of a compute unit are
@@ -463,7 +468,7 @@ __global__ __launch_bounds__(256 * NQ, 4) void k_infer_ahead(InferArgs a)
         };
         const auto deal_bits = [&](u32 op, u32 k0, u32 at) {
             AheadStep &T = s_step[at & 1][wave];
-            T.bits[W.m] = E.template deal_bits<PRF_PAIR>(op, (u64)(k0 + cl) * ngrp + grp, T.rows + W.t);
+            T.bits[W.m] = E.template deal_bits<PRF_PAIR, GT_AHEAD_COMP, GT_TP + 1, 3 * (GT_TP + 1)>(op, (u64)(k0 + cl) * ngrp + grp, T.rows + W.t);
         };
         // the steps of an access after its first: their material, then the interval of the step before
         const auto deal_steps = [&](u32 op, u32 w) {
@@ -549,7 +554,7 @@ __global__ __launch_bounds__(256 * NQ, 4) void k_infer_ahead(InferArgs a)
         for (int s = 0; s < 4; s++) cd[s] = cpub[s] - k0;
         return eq_rounds4(W, M0, M2, A, An, bw, cd, rho_o, rho_n, act ? live : 0u);
     };
-    const auto bit = [&](int c, int s) { return s_step[turn & 1][wave].rows[(c * 9 + h4 + s) * (GT_TP + 1) + W.t]; };
+    const auto bit = [&](int c, int s) { return s_step[turn & 1][wave].rows[c * GT_AHEAD_COMP + (h4 + s) * (GT_TP + 1) + W.t]; };
     // adds up the four words of a group's lanes: every lane by itself, or with one or two groups, where 10 to 21 lanes would meet at
     // every word, through the message region (one instance: 4,000 cycles an access without that)
     const auto add_up = [&](const u64 (&x)[4], u64 *sum, u32 stride) {

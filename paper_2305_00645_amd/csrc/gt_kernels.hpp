@@ -501,7 +501,12 @@ struct GridArgs {
 // party j-1, the other holder of k_j.
 #define GT_EQ_NIB 0x11111111u
 __host__ __device__ constexpr int eq_pos(int s) { return s < 4 ? 8 * s : 8 * (s - 4) + 4; }     // bit of test s after the rounds
-#define GT_EQ_ROWS (3 * 9 * (GT_TP + 1))         // words of the daBit components: [component][test, one unused][lane]
+// Rows of the daBit components in LDS, a word per lane of a party: component c of test s at eq_row(c, s).  The three tests that the parties
+// deal together lie side by side, and a component's rows are 21 words on from the one before modulo 32, so that neither the dealing
+// lanes' stores nor the parties' loads, each of another component, meet in a bank.
+#define GT_EQ_COMP (9 * GT_TP + 24)              // 9 tests, one unused; 213 = 21 modulo 32
+#define GT_EQ_ROWS (2 * GT_EQ_COMP + 9 * GT_TP)
+__host__ __device__ constexpr int eq_row(int c, int s) { return c * GT_EQ_COMP + (s % 3 * 3 + s / 3) * GT_TP; }
 
 struct EqWave {
     WWire W;
@@ -522,23 +527,24 @@ struct EqWave {
         k2 = W.p == 2 ? 0u : 7u;
     }
     // daBit component c of this lane's test s
-    __device__ __forceinline__ u64 &row(int c, int s) { return rows[(c * 9 + s) * (GT_TP + 1) + W.t]; }
+    __device__ __forceinline__ u64 &row(int c, int s) { return rows[c * GT_EQ_COMP + eq_row(0, s) + W.t]; }
 
     // The daBits of the eight tests of block index g of operation op: this lane's block, components to the rows of `r` (row(0, 0)
-    // of a row area); returns the Boolean components of its three tests, in their positions.
-    template <int ISSUE>
+    // of a row area: COMP words from a component to the next, STEP from the lane's test to its next, PARTY from a party's first test to the
+    // next party's); returns the Boolean components of its three tests, in their positions.
+    template <int ISSUE, int COMP = GT_EQ_COMP, int STEP = 3 * GT_TP, int PARTY = GT_TP>
     __device__ __forceinline__ u32 deal_bits(u32 op, u64 g, u64 *r)
     {
         u64 D[8];
         chacha8<ISSUE>(dlr, 3 * g + (u32)W.p, op, 4, D);
         wave_sync();
         const u32 x = (u32)D[6] & 0x1ffu;
-        r += 3 * W.p * (GT_TP + 1);
+        r += W.p * PARTY;
 #pragma unroll
         for (int q = 0; q < 3; q++) {
-            u64 *rq = r + q * (GT_TP + 1);
-            rq[0] = D[2 * q]; rq[9 * (GT_TP + 1)] = D[2 * q + 1];
-            rq[18 * (GT_TP + 1)] = (u64)((x >> (3 * q)) & 1) - D[2 * q] - D[2 * q + 1];
+            u64 *rq = r + q * STEP;
+            rq[0] = D[2 * q]; rq[COMP] = D[2 * q + 1];
+            rq[2 * COMP] = (u64)((x >> (3 * q)) & 1) - D[2 * q] - D[2 * q + 1];
         }
         // per test three Boolean components in a nibble: bits 1, 2 of its field and beta xor both
         const u32 z = ((x >> 1) & 0xdbu) | ((xor3l(x, x >> 1, x >> 2) & 0x49u) << 2);
@@ -546,38 +552,45 @@ struct EqWave {
     }
 
     // [c - base - k == 0] (and the shared bit g) for the eight rows of block index g of operation
-    // op: cd = c - base - k (public), rho the Boolean components of r.  Returns the opened
-    // f = result xor beta, test s in bit eq_pos(s); beta's arithmetic components are in row(.,s).
+    // op.  state(h, cd, ro, rn) fetches what rows h .. h + 3 are tested with: cd = c - base - k (public), ro and rn the Boolean
+    // components of r.  Returns the opened f = result xor beta, test s in bit eq_pos(s); beta's arithmetic components are in row(.,s).
     // early(): the loads of what the tests' results meet, issued after the PRF blocks (their registers
     // are free again) and in flight during the rounds.
-    template <bool HAS_G, int ISSUE, class F>
-    __device__ __forceinline__ u32 tests(u32 op, u64 g, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
-                                         u32 go, u32 gn, u32 nl, F early)
+    template <bool HAS_G, int ISSUE, class S, class F>
+    __device__ __forceinline__ u32 tests(u32 op, u64 g, S state, u32 go, u32 gn, u32 nl, F early)
     {
         u32 b1[1] = { deal_bits<ISSUE>(op, g, &row(0, 0)) }, b2[1];
         W.pass<1>(b1, b2, W.nx);
         const u32 bw = b1[0] | b2[0] | W.buf[W.pv].x;
-        u64 A[8], An[8];
+        u64 A[8];
         chacha8<ISSUE>(own, g, op, 1, A);
-        W.pass64<8>(A, An, W.nx);
-        return rounds<HAS_G>(A, An, bw, cd, rho_o, rho_n, go, gn, nl, early);
+        return rounds<HAS_G>(A, bw, state, go, gn, nl, early);
     }
 
-    // The rounds of the eight tests: A, An the mask words under the party's two keys, bw the Boolean components of the daBits.
-    template <bool HAS_G, class F>
-    __device__ __forceinline__ u32 rounds(const u64 (&A)[8], const u64 (&An)[8], u32 bw, const u64 (&cd)[8], const u64 (&rho_o)[8], const u64 (&rho_n)[8],
-                                          u32 go, u32 gn, u32 nl, F early)
+    // The rounds of the eight tests: A the mask words under the party's own key (those under the other come from the next party,
+    // four tests at a time: fewer registers, half the message region), bw the Boolean components of the daBits.
+    template <bool HAS_G, class S, class F>
+    __device__ __forceinline__ u32 rounds(const u64 (&A)[8], u32 bw, S state, u32 go, u32 gn, u32 nl, F early)
     {
         u32 Ah[8], xo[8], xn[8];
         // round 0, width 32: the high word onto the low word
 #pragma unroll
-        for (int s = 0; s < 8; s++) {
-            const u32 dl = (u32)cd[s], dh = (u32)(cd[s] >> 32);
-            // t = rho with the complement of cd xored into component 0
-            const u32 tol = logic3<0xd2>((u32)rho_o[s], dl, M0), toh = logic3<0xd2>((u32)(rho_o[s] >> 32), dh, M0);
-            const u32 tnl = logic3<0xd2>((u32)rho_n[s], dl, M2), tnh = logic3<0xd2>((u32)(rho_n[s] >> 32), dh, M2);
-            xo[s] = xor3l(and3l(tol, tnl, toh, tnh), (u32)A[s], (u32)An[s]);
-            Ah[s] = (u32)(A[s] >> 32) ^ (u32)(An[s] >> 32);
+        for (int h = 0; h < 8; h += 4) {
+            const u64 A4[4] = { A[h], A[h + 1], A[h + 2], A[h + 3] };
+            u64 An[4];
+            W.pass64<4>(A4, An, W.nx);
+            u64 cd[4], ro[4], rn[4];
+            state(h, cd, ro, rn);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int s = h + j;
+                const u32 dl = (u32)cd[j], dh = (u32)(cd[j] >> 32);
+                // t = rho with the complement of cd xored into component 0
+                const u32 tol = logic3<0xd2>((u32)ro[j], dl, M0), toh = logic3<0xd2>((u32)(ro[j] >> 32), dh, M0);
+                const u32 tnl = logic3<0xd2>((u32)rn[j], dl, M2), tnh = logic3<0xd2>((u32)(rn[j] >> 32), dh, M2);
+                xo[s] = xor3l(and3l(tol, tnl, toh, tnh), (u32)A[s], (u32)An[j]);
+                Ah[s] = (u32)(A[s] >> 32) ^ (u32)(An[j] >> 32);
+            }
         }
         early();
         W.reshare<8>(xo, xn);
@@ -637,14 +650,15 @@ struct EqWave {
         for (int h = 0; h < 2; h++) {                  // arithmetic components, then the Boolean ones, through the same rows
 #pragma unroll
             for (int q = 0; q < 3; q++) {
-                const int s = W.p + 3 * q;             // s = 8 (party 2): the unused row
+                const int s = 3 * W.p + q;             // s = 8 (party 2): the unused row
+                u64 *r = rows + (3 * q + W.p) * GT_TP + W.t;           // row(0, s)
                 if (h == 0) {
                     u64 D[8];
                     chacha8<ISSUE>(dlr, i0 + (u32)s, op, 0, D);
                     wave_sync();
-                    row(0, s) = D[1]; row(1, s) = D[2]; row(2, s) = D[0] - D[1] - D[2];
+                    r[0] = D[1]; r[GT_EQ_COMP] = D[2]; r[2 * GT_EQ_COMP] = D[0] - D[1] - D[2];
                     keep[q][0] = D[3]; keep[q][1] = D[4]; keep[q][2] = D[0] ^ D[3] ^ D[4];
-                } else { row(0, s) = keep[q][0]; row(1, s) = keep[q][1]; row(2, s) = keep[q][2]; }
+                } else { r[0] = keep[q][0]; r[GT_EQ_COMP] = keep[q][1]; r[2 * GT_EQ_COMP] = keep[q][2]; }
             }
             wave_sync();
 #pragma unroll
@@ -667,22 +681,25 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 
 // Equality grid (first lines of the array-access protocol, Sec. V-A; per-sample leaf flags of
 // the learning protocol, Sec. V-B): see GridArgs for the modes.
-// Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF, and
-// takes about 3,750 cycles of a SIMD (4,900 before the PRF's additions were made to pair, see chacha8).  One wavefront per workgroup, two per
-// SIMD: the rows' public values, Boolean components and sums and the values of the next column
-// fit their 256 registers but for 9 in GM_ROWS and 4 with two sums (with issue priorities 6 in GM_ROWS and 5 with one sum), and two barrier-free wavefronts
-// keep the vector unit as busy as three did; three had to spill far more, and every reload waited
-// for the loads from HBM issued before it (GM_ROWS, 64 columns of 10^6 samples: 1.17 ms with three,
-// 0.88 ms with two).  Before, with one party per wavefront and ten workgroup barriers per step:
-// array access 200,003 x 100 0.40 ms, then 0.27, with paired additions 0.21; 10^6 samples x (64 + 128 nodes) 3.45, 2.67,
-// 2.05 ms, own rows 2 x 64 columns 2.35, 1.77, 1.48 ms, leaf grid of 128 + 256 nodes 6.28 (5.52 before it also
-// wrote the sums of the level), 6.2, 5.8 ms.
-template <int MODE, bool HAS_G, int NDOT, int ISSUE>
-__global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
+// Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF (two thirds of these can pair, see chacha8), and
+// with two wavefronts per SIMD 31 % of a wavefront's time is waiting: 19 for LDS (messages, daBits), 12 for the issue.  WAVES 3: a third one
+// fills that.  Its 168 registers hold the keys, the sums and a step's words; the rows' public values and Boolean components are
+// read from LDS in every step (12.5 KB a wavefront).  WAVES 2: they stay in registers (none spill), for launches that do not fill three,
+// and for the samples' own values (GM_ROWS), which are fetched a step ahead and take the registers of the third.  A step
+// takes 3,750 cycles of a SIMD with two and 3,400 with three: 1,000,000 x 64 583 and 528 us (x 512 11.4 and 12.9 * 10^10 tests/s),
+// array access 200,003 x 100 211 and 195 us, leaf one-hot of 48,842 x (128 + 256 nodes) 307 and 225; but own rows 100,000 x 100 135 and 145,
+// 48,842 x 64, which fills two per SIMD, 46.5 and 50.2.  Which: column_ranges.  One wavefront per workgroup.
+// Earlier: one party per wavefront and ten workgroup barriers per step, then without paired additions, then with them: array access
+// 0.40, 0.27, 0.21 ms; 10^6 samples x (64 + 128 nodes) 3.45, 2.67, 2.14 (now 1.95), own rows 2 x 64 columns 2.35, 1.77, 1.5 ms,
+// leaf grid of 128 + 256 nodes 6.3, 6.2, 5.9 (now 5.6) ms.
+template <int MODE, bool HAS_G, int NDOT, int ISSUE, int WAVES>
+__global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
 {
     __shared__ uint4 s_msg[GT_WMSG_QUADS];
     __shared__ u64 s_rows[GT_EQ_ROWS];
     __shared__ u64 s_cnt[6];
+    constexpr bool IN_LDS = WAVES > 2;                 // the rows' opened values and Boolean components
+    __shared__ ulonglong2 s_rho[IN_LDS ? 4 * GT_LANES : 1], s_open[IN_LDS ? 4 * GT_TP : 1];
     EqWave E;
     E.init(a.c.keys, s_msg, s_rows, s_cnt);
     WWire &W = E.W;
@@ -711,6 +728,15 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
             E.template open_rows<ISSUE>(op, i0, uo, un, cpub, rho_o, rho_n, kbeg == 0 && ro == 0 ? 64u * live8(i0, nvg) : 0u);
 #pragma unroll
             for (int s = 0; s < 8; s++) cpub[s] -= a.base;
+            if (IN_LDS) {
+                wave_sync();
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    s_rho[j * GT_LANES + W.m] = make_ulonglong2(rho_o[2 * j], rho_o[2 * j + 1]);
+                    s_open[j * GT_TP + W.t] = make_ulonglong2(cpub[2 * j], cpub[2 * j + 1]);
+                }
+                wave_sync();
+            }
         }
         const u64 *w1o = nullptr, *w1n = nullptr, *xto = nullptr, *xtn = nullptr;
         if (MODE == GM_COMMON) { w1o = own_of(a.W1, p) + a.w1off; w1n = nxt_of(a.W1, p) + a.w1off; }
@@ -724,7 +750,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
 #pragma unroll
             for (int j = 0; j < 4; j++) { const ulonglong2 v = qn[j]; xn[2 * j] = v.x; xn[2 * j + 1] = v.y; }
         };
-        if (MODE == GM_ROWS) fetch_x(kbeg);
+        if (MODE == GM_ROWS && !IN_LDS) fetch_x(kbeg);
         u64 acc[8], acc2[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) { acc[s] = 0; acc2[s] = 0; }
@@ -733,13 +759,22 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
             const u32 k = MODE == GM_STORE ? (act ? k0 + ro : kbeg) : k0;   // this lane's column (an existing one when idle)
             const u64 nv = act ? a.N : 0;              // samples of this lane that exist
             const u32 nl = live8(i0, nv);              // how many of the lane's eight tests exist
-            u64 cd[8];
-#pragma unroll
-            for (int s = 0; s < 8; s++) cd[s] = cpub[s] - k;
             u32 go = 0, gn = 0;
             if (HAS_G) { const Sh gk = ld(a.g, p, k); go = 0u - ((u32)gk.o & 1); gn = 0u - ((u32)gk.n & 1); }
             Sh Wk = { 0, 0 }, Wk2 = { 0, 0 };
-            const u32 f = E.template tests<HAS_G, ISSUE>(op, (u64)k * ngrp + grp, cd, rho_o, rho_n, go, gn, nl, [&]() {
+            const u32 f = E.template tests<HAS_G, ISSUE>(op, (u64)k * ngrp + grp, [&](int h, u64 (&cd)[4], u64 (&ro)[4], u64 (&rn)[4]) {
+                if (IN_LDS) {
+#pragma unroll
+                    for (int j = 0; j < 2; j++) {
+                        const ulonglong2 c = s_open[(h / 2 + j) * GT_TP + W.t], o = s_rho[(h / 2 + j) * GT_LANES + W.m], n = s_rho[(h / 2 + j) * GT_LANES + W.nx];
+                        cd[2 * j] = c.x - k; cd[2 * j + 1] = c.y - k; ro[2 * j] = o.x; ro[2 * j + 1] = o.y; rn[2 * j] = n.x; rn[2 * j + 1] = n.y;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; j++) { cd[j] = cpub[h + j] - k; ro[j] = rho_o[h + j]; rn[j] = rho_n[h + j]; }
+                }
+            }, go, gn, nl, [&]() {
+                if (MODE == GM_ROWS && IN_LDS) fetch_x(k);
                 if (MODE == GM_COMMON) { Wk.o = w1o[k]; Wk.n = w1n[k]; }
                 if (MODE == GM_COMMON && NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
             });
@@ -773,7 +808,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
                         acc[s] += prod3(e, x);
                     }
                 }
-                if (MODE == GM_ROWS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
+                if (MODE == GM_ROWS && !IN_LDS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
                 if (MODE == GM_STORE && act && W.real) {
                     store_limbs8(p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]), k, i0, Eo);
                     if (a.sums) store_limbs8(p == 0 ? a.S.m[0] : (p == 1 ? a.S.m[1] : a.S.m[2]), k, i0, Es);
@@ -786,7 +821,7 @@ __global__ __launch_bounds__(64, 2) void k_eqgrid(GridArgs a)
             // after the other every lane of an instruction touched a line of its own)
 #pragma unroll
             for (int q = 0; q < NDOT; q++) {
-                u64 *lin = (u64 *)s_msg;
+                u64 *lin = s_rows;                     // 512 words
                 wave_sync();
 #pragma unroll
                 for (int s = 0; s < 8; s++) lin[W.m * 8 + s] = q ? acc2[s] : acc[s];

@@ -26,28 +26,36 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // and 12.2 us, 30,000 rows 13.2 and 14.6 (three columns: 15.5 either way, 45,753 rows 16.4 in one, 17.4 in three); of their own (fetched meanwhile) 13 rows 1.3 us less in two, 3,000 rows 1.4, 10,000 0.7, 30,000 0.9
 // more; two sums, 13 to 20,000 rows 3 to 3.5 us less in two (one range completes the sums of eight rows per lane), 30,000 0.9
 // less, 60,000 3.7 more.
-static inline u64 column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
+// Wavefronts per SIMD: two, or three of 168 registers with the rows' opened values in LDS (shared arrays and the leaf one-hot; own rows gain
+// nothing by it).  Three take 1.37 of the time of two for a step of each, two of them 1.05, one 0.66: 1,000,000 x 64 593 us and 533;
+// 200,003 x 100 in 5 ranges 213 and 196, 48,842 x 64 in the 7 ranges that fill two per SIMD 46.5 and 50.2, in ten 62.5 and 49.3.
+struct ColumnRanges { u64 n; u32 waves; };
+static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
 {
-    const u64 half = simds, fills[] = { 0, 1, 2, 4, 6, 8 };          // in halves of the wavefront slots; 0: one range
     // in units of a step of two wavefronts, 3 us
     const double launch = sums == 0 ? 0.0 : sums == 2 ? 0.5 + 0.006 * (double)ntile : (mode == GM_ROWS ? 1.2 : 1.6) + 0.003 * (double)ntile;
-    u64 best = 1;
+    ColumnRanges best = { 1, 2 };
     double best_cost = 0;
-    for (u64 f : fills) {
-        u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * half / ntile));
-        const u64 len = (nsteps + n - 1) / n;
-        n = (nsteps + len - 1) / len;
-        const u64 items = ntile * n, full = items / (2 * half), rest = items % (2 * half);
-        const double alone = n == 1 && sums ? 0.82 : 0.6;
-        const double cost = ((double)full + (rest == 0 ? 0.0 : rest <= half ? alone : 1.0)) * ((double)len + 2.5) + (n > 1 ? launch : 0.0);
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = n; }
+    for (u32 waves = 2; waves <= (mode == GM_ROWS || sums == 2 ? 2 : 3); waves++) {
+        const u64 fills2[] = { 0, 1, 2, 4, 6, 8 }, fills3[] = { 0, 3, 6, 9, 12, 12 };   // wavefronts per SIMD; 0: one range
+        for (u64 f : waves == 2 ? fills2 : fills3) {
+            u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * simds / ntile));
+            const u64 len = (nsteps + n - 1) / n;
+            n = (nsteps + len - 1) / len;
+            const u64 items = ntile * n, full = items / (waves * simds), rest = items % (waves * simds);
+            if (waves == 3 && items <= 2 * simds) continue;
+            const double last = rest == 0 ? 0.0 : waves == 2 ? (rest > simds ? 1.0 : n == 1 && sums ? 0.82 : 0.6)
+                                : rest > 2 * simds ? 1.37 : rest > simds ? 1.05 : 0.66;
+            const double cost = ((waves == 2 ? 1.0 : 1.37) * (double)full + last) * ((double)len + 2.5) + (n > 1 ? launch : 0.0);
+            if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { n, waves }; }
+        }
     }
     return best;
 }
 
 // Split of an equality grid: gpt groups of 8 samples x rps adjacent columns per step and wavefront, ntile tiles, nkc ranges of
 // kchunk columns each.  alone: the variant without issue priorities (see chacha8).  sums: GM_STORE writes the tiles of the sums, too.
-struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; };
+struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; u32 waves; };
 static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32 w, u64 N8)
 {
     GridShape s;
@@ -58,7 +66,8 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
     s.gpt = s.rps == 1 ? (mode == GM_STORE ? 20 : GT_TP) : (s.rps == 2 ? 8 : 4);
     const u64 nsteps = ((u64)w + s.rps - 1) / s.rps;
     s.ntile = (N8 / 8 + s.gpt - 1) / s.gpt;
-    const u64 nkc = column_ranges(simds, mode, mode == GM_STORE ? 0 : ndot, s.ntile, nsteps);
+    const ColumnRanges ranges = column_ranges(simds, mode, mode == GM_STORE ? 0 : ndot, s.ntile, nsteps);
+    const u64 nkc = ranges.n;
     s.kchunk = (u32)(((nsteps + nkc - 1) / nkc) * s.rps);
     s.nkc = (u32)(((u64)w + s.kchunk - 1) / s.kchunk);
     // wavefronts that have their SIMD to themselves, or a single step per item (1.5 * 10^6 rows x 1 column: 76 us, 83 with
@@ -69,6 +78,7 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
     // 190 + 273 and 73 + 195, 110 + 213, 187 + 298; 400,000: 173 + 500, 281 + 531, 493 + 659 and 161 + 519, 271 + 553, 493 + 663.
     const u64 items = s.ntile * s.nkc, rest = items % (2 * simds);
     s.alone = items <= simds || s.kchunk <= s.rps || (mode != GM_STORE && s.kchunk <= 3 && items > 2 * simds && rest && rest <= simds) || (sums && N8 > 131072);
+    s.waves = s.alone && mode != GM_STORE ? 2 : ranges.waves;
     return s;
 }
 

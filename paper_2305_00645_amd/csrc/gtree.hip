@@ -421,13 +421,13 @@ static int grow_dacc(gt_ctx *c, size_t need)
     HIPCHK(hipMemsetAsync(c->dacc, 0, need * 8, c->stream));
     return GT_OK;
 }
-template <int ISSUE>
+template <int ISSUE, int WAVES>
 static int launch_grid(gt_ctx *c, int mode, int ndot, dim3 g, dim3 b, const GridArgs &a)
 {
-    if (mode == GM_STORE) return launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, ISSUE>, g, b, a);
-    if (mode == GM_ROWS) return launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1, ISSUE>, g, b, a);
-    if (ndot == 2) return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2, ISSUE>, g, b, a);
-    return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1, ISSUE>, g, b, a);
+    if (mode == GM_STORE) return launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, ISSUE, WAVES>, g, b, a);
+    if (mode == GM_ROWS) return launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1, ISSUE, WAVES>, g, b, a);
+    if (ndot == 2) return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2, ISSUE, WAVES>, g, b, a);
+    return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1, ISSUE, WAVES>, g, b, a);
 }
 // the equality grid with its accounting
 // rider: equality tests that may run beside the sums' completion, as the operation after this one; n = 0 afterwards: they do
@@ -452,7 +452,10 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
         const dim3 g((unsigned)std::min<u64>(s.ntile * a.nkc, 1u << 20)), B1(GT_LANES);
-        GTCHK(s.alone ? launch_grid<PRF_ALONE>(c, mode, ndot, g, B1, a) : launch_grid<PRF_PAIR_LOOP>(c, mode, ndot, g, B1, a));
+        const int rc = s.alone && s.waves == 3 ? launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, PRF_ALONE, 3>, g, B1, a)
+                     : s.alone ? launch_grid<PRF_ALONE, 2>(c, mode, ndot, g, B1, a) : s.waves == 3 ? launch_grid<PRF_PAIR_LOOP, 3>(c, mode, ndot, g, B1, a)
+                               : launch_grid<PRF_PAIR_LOOP, 2>(c, mode, ndot, g, B1, a);
+        GTCHK(rc);
         if (a.dacc) {
             EqArgs eq{};
             if (rider) { eq = *rider; eq.c = kc(c, c->op); rider->n = 0; }

@@ -18,7 +18,7 @@ extern "C" void infer(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u32 H, u32 d, in
 extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64 *out)
 {
     const GridShape s = grid_shape(simds, mode, ndot, sums != 0, w, N8);
-    out[0] = s.ntile; out[1] = s.nkc; out[2] = s.kchunk; out[3] = s.alone; out[4] = s.rps;
+    out[0] = s.ntile; out[1] = s.nkc; out[2] = s.kchunk; out[3] = s.alone; out[4] = s.rps; out[5] = s.waves;
 }
 extern "C" int staged(u32 noct, int thr) { return staged_sums(noct, thr != 0); }
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
@@ -56,11 +56,11 @@ def staged(noct, thr):
 
 
 def grid(mode, w, N, sums=1, tile_sums=False):
-    """dict(tiles, ranges, columns, alone, adjacent) of an equality grid of N rows and w columns; sums: inner products;
+    """dict(tiles, ranges, columns, alone, adjacent, waves) of an equality grid of N rows and w columns; sums: inner products;
     tile_sums: the leaf one-hot is written with its sums."""
-    out = (C.c_uint64 * 5)()
+    out = (C.c_uint64 * 6)()
     _lib().grid(SIMDS, mode, sums, int(tile_sums), w, (N + 7) // 8 * 8, out)
-    return dict(tiles=out[0], ranges=out[1], columns=out[2], alone=bool(out[3]), adjacent=out[4])
+    return dict(tiles=out[0], ranges=out[1], columns=out[2], alone=bool(out[3]), adjacent=out[4], waves=out[5])
 
 
 def few(nodes, N, ncol):

@@ -1119,3 +1119,12 @@ def test_context_on_a_side_stream(mods, seed):
         same(zg, zo, "mult on side stream")
         same(ug, uo, "oaa on side stream")
         g.close()
+
+
+OAA_THREE_WAVEFRONTS = [(30, 100003), (5, 364001), (300, 20003)]
+
+
+@pytest.mark.parametrize("w,n", OAA_THREE_WAVEFRONTS)
+def test_oaa_three_wavefronts(mods, seed, w, n):
+    """Three wavefronts per SIMD, the rows' opened values in LDS: several ranges, one range of few columns, few rows."""
+    test_oaa_at_tile_edges(mods, seed, w, n)
