@@ -14,6 +14,8 @@
  *  - Every pointer in a gt_shares is DEVICE memory, 8-byte aligned, owned by the
  *    caller, of `n` 64-bit words.  party[p].own holds component p, party[p].next
  *    component p+1 mod 3 (Sec. II-B: P_i holds (x_i, x_{i+1})).
+ *    The two copies of a component of an input are equal: where a call reads it for both of its holders (gt_mult's
+ *    factors, the instances of an inference, a training's data) it may read one copy, the own one.
  *  - `plain` buffers are device memory too.
  *  - Calls only enqueue work on the context's HIP stream and return; gt_stats_get,
  *    gt_prof_get, gt_stats_reset and the destroy calls wait for it.  Calls on one

@@ -109,15 +109,15 @@ __global__ __launch_bounds__(256) void k_copy(CopyArgs a)
 
 // dst[k][i] (row stride N8) = src[i][k] (row stride w): sample-contiguous layout.
 // 32 x 32 tiles through LDS so that both the reads and the writes are contiguous;
-// blockIdx.z selects one of the six planes, of the second pair of matrices from 6 on (a training's Y beside its X).
+// blockIdx.z selects one of the three components (the own planes), of the second pair of matrices from 3 on (a training's Y beside its X).
 __global__ __launch_bounds__(256) void k_transpose(P6 dst0, P6 src0, u32 w0, P6 dst1, P6 src1, u32 w1, u64 N, u64 N8)
 {
     __shared__ u64 tile[32][33];
-    const P6 &dst = blockIdx.z < 6 ? dst0 : dst1, &src = blockIdx.z < 6 ? src0 : src1;
-    const u32 w = blockIdx.z < 6 ? w0 : w1;
-    const int pl = blockIdx.z % 6, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
-    const u64 *in = pl < 3 ? src.o[pl] : src.n[pl - 3];
-    u64 *out = pl < 3 ? dst.o[pl] : dst.n[pl - 3];
+    const P6 &dst = blockIdx.z < 3 ? dst0 : dst1, &src = blockIdx.z < 3 ? src0 : src1;
+    const u32 w = blockIdx.z < 3 ? w0 : w1;
+    const int pl = blockIdx.z % 3, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
+    const u64 *in = src.o[pl];
+    u64 *out = dst.o[pl];
     const u64 ntx = (w + 31) / 32, nty = (N + 31) / 32;
     for (u64 t = blockIdx.x; t < ntx * nty; t += gridDim.x) {
         const u64 k0 = (t % ntx) * 32, i0 = (t / ntx) * 32;
@@ -267,8 +267,10 @@ struct LimbTri { LimbMat m[3]; };
 // MODE 2 (node split): e = r*CW + col, z = C[e] * (1 - split[r]), written to both
 //         children (2r, 2r+1) of the next level.
 // The zero-sharing words under key k_j are evaluated by party j's wavefront and also loaded by
-// party j-1, the other holder of that key.  Bound: memory (12 words read, 6 written).  2^24 products:
-// 0.92 ms with lanes on 8 consecutive elements each and both keys' blocks per party, 0.50 ms now (4.8 TB/s).
+// party j-1, the other holder of that key.  Bound: memory.  2^24 products:
+// 0.92 ms with lanes on 8 consecutive elements each and both keys' blocks per party, 0.50 ms with the six planes of each factor
+// read (12 words, 4.8 TB/s), 0.36 ms with each component of the factors read once, for both of its holders, from the plane of the party whose own
+// it is (6 words read, 6 written).  In place is safe: a barrier lies between the loads of a half tile and its stores.
 struct MultArgs { KCommon c; P6 x, y, z; u64 n; u32 CW; };   // CW: MODE 2
 
 template <int MODE>

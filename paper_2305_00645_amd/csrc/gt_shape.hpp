@@ -55,6 +55,7 @@ static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntil
 
 // Split of an equality grid: gpt groups of 8 samples x rps adjacent columns per step and wavefront, ntile tiles, nkc ranges of
 // kchunk columns each.  alone: the variant without issue priorities (see chacha8).  sums: GM_STORE writes the tiles of the sums, too.
+// waves: wavefronts per SIMD that the variant's registers are cut for.
 struct GridShape { u32 rps, gpt, kchunk, nkc; u64 ntile; bool alone; u32 waves; };
 static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32 w, u64 N8)
 {
@@ -78,7 +79,7 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
     // 190 + 273 and 73 + 195, 110 + 213, 187 + 298; 400,000: 173 + 500, 281 + 531, 493 + 659 and 161 + 519, 271 + 553, 493 + 663.
     const u64 items = s.ntile * s.nkc, rest = items % (2 * simds);
     s.alone = items <= simds || s.kchunk <= s.rps || (mode != GM_STORE && s.kchunk <= 3 && items > 2 * simds && rest && rest <= simds) || (sums && N8 > 131072);
-    s.waves = s.alone && mode != GM_STORE ? 2 : ranges.waves;
+    s.waves = s.alone ? 2 : ranges.waves;
     return s;
 }
 

@@ -106,14 +106,16 @@ struct gt_train {
 static bool select_by_rounds(const gt_ctx *c, u64 nh, u64 len);
 static size_t pad8(size_t n) { return (n + 7) & ~(size_t)7; }
 
-static int dsh_alloc(DSh &s, size_t n, hipStream_t st)
+// once: a plane per component, which both parties that hold it read (for data that only a copy of the own planes writes)
+static int dsh_alloc(DSh &s, size_t n, hipStream_t st, bool once = false)
 {
     s.n = n;
     const size_t stride = pad8(n ? n : 1);           // planes start 64-byte aligned
-    const size_t words = 6 * stride;
+    const size_t words = (once ? 3 : 6) * stride;
     if (hipMalloc(&s.base, words * 8) != hipSuccess) { s.base = nullptr; return GT_ENOMEM; }
     HIPCHK(hipMemsetAsync(s.base, 0, words * 8, st));
-    for (int p = 0; p < 3; p++) { s.v.o[p] = s.base + (size_t)(2 * p) * stride; s.v.n[p] = s.base + (size_t)(2 * p + 1) * stride; }
+    for (int p = 0; p < 3; p++) s.v.o[p] = s.base + (size_t)(once ? p : 2 * p) * stride;
+    for (int p = 0; p < 3; p++) s.v.n[p] = once ? s.v.o[(p + 1) % 3] : s.v.o[p] + stride;
     return GT_OK;
 }
 static void dsh_free(DSh &s) { if (s.base) (void)hipFree(s.base); s.base = nullptr; s.n = 0; }
@@ -130,6 +132,16 @@ static P6 to_p6(const gt_shares *s)
 {
     P6 a;
     for (int p = 0; p < 3; p++) { a.o[p] = s->party[p].own; a.n[p] = s->party[p].next; }
+    return a;
+}
+
+// the same sharing read by component: both holders of a component from the plane of the party whose own it is (the two copies are
+// equal), so that it comes from memory once.  2^24 products 0.50 and 0.36 ms; inferences whose rows exceed the L2s, where a step of few columns
+// fetches lines that it had before: 45,000 x 186, depth 5, thresholds 868 and 605 us, 200,000 x 52, depth 6, 1.81 and 1.56 ms, 50,000 x 294,
+// depth 6, 1.66 and 1.42 ms.
+static P6 once(P6 a)
+{
+    for (int p = 0; p < 3; p++) a.n[p] = a.o[(p + 1) % 3];
     return a;
 }
 
@@ -229,7 +241,7 @@ static dim3 g1(u64 n) { return dim3(blocks_for(n, 256)); }   // plain elementwis
 static const dim3 B256(256);
 static dim3 gE(u64 n) { return dim3((unsigned)std::min<u64>((n + GT_EL - 1) / GT_EL, 1u << 16)); }   // element kernels: a wavefront per GT_EL elements
 static const dim3 B64(GT_LANES);
-static dim3 gT(u64 N, u64 w) { return dim3((unsigned)std::min<u64>(((N + 31) / 32) * ((w + 31) / 32), 65535), 1, 6); }  // k_transpose
+static dim3 gT(u64 N, u64 w) { return dim3((unsigned)std::min<u64>(((N + 31) / 32) * ((w + 31) / 32), 65535), 1, 3); }  // k_transpose
 
 // ---------------------------------------------------------------------------------
 extern "C" const char *gt_strerror(int code)
@@ -373,7 +385,7 @@ extern "C" int gt_mult(gt_ctx *c, const gt_shares *x, const gt_shares *y, size_t
 {
     if (!c || !shares_ok(x, n) || !shares_ok(y, n) || !shares_ok(z, n)) return GT_EINVAL;
     Timed T(c);
-    MultArgs a{}; a.x = to_p6(x); a.y = to_p6(y); a.z = to_p6(z); a.n = n;
+    MultArgs a{}; a.x = once(to_p6(x)); a.y = once(to_p6(y)); a.z = to_p6(z); a.n = n;
     a.c = kc(c, c->op++);
     int rc = n ? launch(c, GT_KC_MULT, k_mult, dim3(tiles8(n)), GT_BLOCK, a) : GT_OK;
     acct_reshare(c, n, 1);
@@ -452,8 +464,7 @@ static int do_grid(gt_ctx *c, int mode, bool has_g, int ndot, GridArgs a, u64 *e
         }
         // more wavefronts than fit at once: the hardware balances them over the compute units
         const dim3 g((unsigned)std::min<u64>(s.ntile * a.nkc, 1u << 20)), B1(GT_LANES);
-        const int rc = s.alone && s.waves == 3 ? launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, PRF_ALONE, 3>, g, B1, a)
-                     : s.alone ? launch_grid<PRF_ALONE, 2>(c, mode, ndot, g, B1, a) : s.waves == 3 ? launch_grid<PRF_PAIR_LOOP, 3>(c, mode, ndot, g, B1, a)
+        const int rc = s.alone ? launch_grid<PRF_ALONE, 2>(c, mode, ndot, g, B1, a) : s.waves == 3 ? launch_grid<PRF_PAIR_LOOP, 3>(c, mode, ndot, g, B1, a)
                                : launch_grid<PRF_PAIR_LOOP, 2>(c, mode, ndot, g, B1, a);
         GTCHK(rc);
         if (a.dacc) {
@@ -572,8 +583,8 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
 {
     const u32 d = t->d, K = t->K;
     const size_t N = t->N, N8 = t->N8, nmax = (size_t)1 << t->H, nodes = ((size_t)2 << t->H) - 1;
-    // sample-contiguous copies of X and Y (Y goes behind the d*K product columns)
-    dim3 gXY = gT(N, d); gXY.x = std::max(gXY.x, gT(N, K).x); gXY.z = 12;
+    // sample-contiguous copies of X and Y, a plane per component (six planes: 48,842 x 294 279 us, three 140)
+    dim3 gXY = gT(N, d); gXY.x = std::max(gXY.x, gT(N, K).x); gXY.z = 6;
     GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gXY, B256, t->XT.v, to_p6(X), d, t->YT.v, to_p6(Y), K, (u64)N, (u64)N8));
     // one-time products X[i][k] * Y[i][c] and the class columns, as limb tiles
     XyArgs a{}; a.c = kc(c, c->op++); a.XT = t->XT.v; a.YT = t->YT.v; a.comps = t->comps; a.N = N; a.N8 = N8; a.K = K;
@@ -621,7 +632,7 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
         { &t->idx[0], sel }, { &t->idx[1], sel / 2 }, { &t->tval, N },
         { &t->Clast, nmax * CW }, { &t->Glast, nmax * d }, { &t->Slast, nmax * d },
     };
-    for (auto &pl : plan) { if (rc != GT_OK) break; rc = pl.n ? dsh_alloc(*pl.v, pl.n, s) : GT_OK; }
+    for (auto &pl : plan) { if (rc != GT_OK) break; rc = pl.n ? dsh_alloc(*pl.v, pl.n, s, pl.v == &t->XT || pl.v == &t->YT) : GT_OK; }
     if (rc == GT_OK) {
         t->slot = new (std::nothrow) TreeSlot();
         if (!t->slot) rc = GT_ENOMEM;
@@ -1174,7 +1185,7 @@ static int infer_one_launch(gt_ctx *c, P6 feat, P6 thr, P6 leaf, bool has_thr, u
 {
     const size_t N8 = pad8(NI);
     InferArgs a{}; a.c = kc(c, c->op); a.feat = feat; a.thr = thr; a.leaf = leaf;
-    a.I = to_p6(I); a.out = to_p6(R); a.NI = NI; a.N8 = N8; a.d = d; a.H = H; a.ntrees = ntrees;
+    a.I = once(to_p6(I)); a.out = to_p6(R); a.NI = NI; a.N8 = N8; a.d = d; a.H = H; a.ntrees = ntrees;
     const u32 S = has_thr ? 3 : 2;
     c->op += ntrees * (H * S + 1);
     const u64 ngrp = N8 / 8;
@@ -1216,7 +1227,7 @@ extern "C" int gt_infer_batch(gt_ctx *c, const gt_tree *tr, const gt_shares *I, 
     const size_t need[5] = { (size_t)d * N8, NI, NI, tr->has_thr ? NI : 0, tr->has_thr ? NI : 0 };
     int rc = GT_OK;
     for (int i = 0; i < 5 && rc == GT_OK; i++)
-        if (c->ws[i].n < need[i]) { (void)hipStreamSynchronize(c->stream); dsh_free(c->ws[i]); rc = dsh_alloc(c->ws[i], need[i], c->stream); }
+        if (c->ws[i].n < need[i]) { (void)hipStreamSynchronize(c->stream); dsh_free(c->ws[i]); rc = dsh_alloc(c->ws[i], need[i], c->stream, i == 0); }
     DSh &IT = c->ws[0], &tidx = c->ws[1], &f = c->ws[2], &th = c->ws[3], &x = c->ws[4];
     if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_fill_const, g1(NI), B256, tidx.v, (u64)0, (u64)NI, (u64)0);
     if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_transpose, gT(NI, d), B256, IT.v, to_p6(I), d, IT.v, to_p6(I), d, (u64)NI, (u64)N8);

@@ -94,6 +94,20 @@ def test_mult(mods, seed, n):
     same_stats(o, g)
 
 
+@pytest.mark.parametrize("n,onto_y", [(255, False), (512 * 5 + 37, False), (512 * 5 + 37, True)])
+def test_mult_in_place(mods, seed, n, onto_y):
+    """The product over one of its factors: a party's next component is read from the plane of the party whose own it is, which that
+    party overwrites."""
+    _, gtree = mods
+    o, g = pair(mods, seed)
+    rng = np.random.default_rng(n)
+    x, y = (rng.integers(0, M64, size=n, dtype=np.uint64) for _ in range(2))
+    xo, yo, xg, yg = o.share(x), o.share(y), g.share_a(x), g.share_a(y)
+    z = yg if onto_y else xg
+    assert g.L.gt_mult(g.ctx, gtree._ref(xg), gtree._ref(yg), n, gtree._ref(z)) == 0
+    same(z, o.mult(xo, yo), "mult in place")
+
+
 def test_eq_public_and_shared(mods, seed):
     o, g = pair(mods, seed)
     rng = np.random.default_rng(3)
