@@ -109,13 +109,11 @@ __global__ __launch_bounds__(256) void k_copy(CopyArgs a)
 
 // dst[k][i] (row stride N8) = src[i][k] (row stride w): sample-contiguous layout.
 // 32 x 32 tiles through LDS so that both the reads and the writes are contiguous;
-// blockIdx.z selects one of the three components (the own planes), of the second pair of matrices from 3 on (a training's Y beside its X).
-__global__ __launch_bounds__(256) void k_transpose(P6 dst0, P6 src0, u32 w0, P6 dst1, P6 src1, u32 w1, u64 N, u64 N8)
+// blockIdx.z selects one of the three components (the own planes).
+__global__ __launch_bounds__(256) void k_transpose(P6 dst, P6 src, u32 w, u64 N, u64 N8)
 {
     __shared__ u64 tile[32][33];
-    const P6 &dst = blockIdx.z < 3 ? dst0 : dst1, &src = blockIdx.z < 3 ? src0 : src1;
-    const u32 w = blockIdx.z < 3 ? w0 : w1;
-    const int pl = blockIdx.z % 3, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
+    const int pl = blockIdx.z, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8 threads
     const u64 *in = src.o[pl];
     u64 *out = dst.o[pl];
     const u64 ntx = (w + 31) / 32, nty = (N + 31) / 32;
@@ -148,6 +146,14 @@ __device__ __forceinline__ void ld8(const u64 *ptr, u64 i0, u64 n, u64 (&x)[8])
 #pragma unroll
         for (int j = 0; j < 8; j++) x[j] = i0 + j < n ? ptr[i0 + j] : 0;
     }
+}
+
+// the same for whole groups: 64-byte aligned, eight words that exist
+__device__ __forceinline__ void ld8_whole(const u64 *ptr, u64 (&x)[8])
+{
+    const ulonglong2 *q = (const ulonglong2 *)ptr;
+#pragma unroll
+    for (int j = 0; j < 4; j++) { const ulonglong2 v = q[j]; x[2 * j] = v.x; x[2 * j + 1] = v.y; }
 }
 
 // every element := public constant c
@@ -339,102 +345,138 @@ __global__ __launch_bounds__(192) void k_split(MultArgs m, KeepArgs k, u32 mblk)
     }
 }
 
-// One-time products of the learning protocol (Sec. V-B): column col = k*K + c,
-// element e = col*N8 + i, z = XT[k][i] * YT[c][i] for i < N, written as limb tiles
-// (own + next component into B.m[p][0], own into B.m[p][1]).  A step covers 16 groups of 8
-// samples of four adjacent columns (blockIdx.y = column quad): the four 32-byte pieces
-// that one wavefront writes per sample block and limb make up a whole 128-byte line
-// of the tile layout.
-struct XyArgs { KCommon c; P6 XT, YT; LimbSet B; LimbTri C; int comps; u64 N, N8; u32 K, ncol; };   // comps: B once per component, into C
-__global__ __launch_bounds__(192, 2) void k_xy(XyArgs a)
+// What a training computes once, one launch: the sample-contiguous copies XT[k][i] and YT[c][i] of the data (a plane per component), the one-time
+// products of the learning protocol (Sec. V-B) and the class columns, as limb tiles.  Product column col = k*K + c, element
+// e = col*N8 + i, z = X[i][k] * Y[i][c] for i < N, as rows 0 .. d*K - 1 of C (COMPS: the columns once per component) or of B (own + next
+// component into B.m[p][0], own into B.m[p][1]); class column c as row c of Yl (both forms) and, with COMPS, row d*K + c of C.
+// A workgroup takes 32 samples (a sample block) x tk features: rows of X and Y through LDS, where its four wavefronts read them: a
+// wavefront is the three parties on the block x 5 adjacent columns per step, so that the 32-byte pieces that a party's lanes write per limb
+// lie side by side.
+// Bound: memory (1.5 GB of X read, 1.5 of XT and 6.1 of tiles written at 10^6 x 64, 4 classes, in 2.49 ms: 3.7 TB/s), the vector ALU close
+// behind (the tiles' stores alone 1.6 ms, all but these 1.6).  Three workgroups per compute unit, each grid-stride over its items: a workgroup for every
+// item, whose message counters then queue at 64 lines, took 3.4 ms, with the rows' loads one after the other 3.0.  Rows of eight words from global memory by
+// the lanes that use them: 3.4 ms, each load instruction touches as many lines as it has lanes.  One wavefront per party with a barrier per message, after a
+// transposition, before class tiles of their own: 2.49 + 0.73 + 0.31 ms; 48,842 x 294, 2 classes 369 + 150 + 20 us, now 411; 19,997 x 101, 3
+// classes 118 + 25 + 10, now 83; 267 x 22 15 + 5 + 5, now 11.
+struct XyArgs { KCommon c; P6 X, Y, XT, YT; LimbSet B, Yl; LimbTri C; u64 N, N8; u32 d, K, tk; };
+#define GT_XY_COLS 5
+#define GT_XY_FEAT 32                                  // features of a workgroup at most
+#define GT_XY_ROW 34                                   // words of a row in LDS: 32 samples, 16 bytes further on in the banks
+template <bool COMPS, int KMAX>
+__global__ __launch_bounds__(256, 3) void k_xy(XyArgs a)
 {
-    __shared__ u64 s_wire[GT_LWIRE_WORDS];
-    // the zero-sharing words under key k_j are evaluated by party j's wavefront and read
-    // through LDS by party j-1, the other holder of k_j
-    __shared__ u64 s_prf[3][8 * GT_LANES];
-    __shared__ u64 s_cnt[6];
-    const int p = party_of_wave(), lane = threadIdx.x, pn = p == 2 ? 0 : p + 1;
-    LWire W; W.init(s_wire, s_cnt);
-    const PartyKeys K = load_party_keys(a.c.keys, p);
-    const u64 ngrp = a.N8 / 8, nq = (a.ncol + 3) / 4, nt = (ngrp + 15) / 16;
-    // tiles outside, column quads inside: a workgroup meets the same class columns of Y
-    // again and again for one tile of samples (cache hits) and each value of X once
-    for (u64 tile = blockIdx.x; tile < nt; tile += gridDim.x) {
-        const u64 g = tile * 16 + (lane & 15), i0 = g * 8;
-        // the lane's class column of Y stays in registers while the class does not change from one
-        // column quad to the next (never, when K divides 4 or 4 divides K)
-        u64 yo[8] = { 0, 0, 0, 0, 0, 0, 0, 0 }, yn[8] = { 0, 0, 0, 0, 0, 0, 0, 0 }, cyc = ~(u64)0;
-        for (u64 q = blockIdx.y; q < nq; q += gridDim.y) {
-            const u64 colq = q * 4 + (lane >> 4);
-            const bool act = colq < a.ncol && g < ngrp;
-            const u64 col = act ? colq : 0, kx = col / a.K, cy = col % a.K;
-            const u64 nv = act ? a.N : 0;               // rows start at multiples of 8
-            u64 ao[8], snd[8], rcv[8];
-            const u64 blk = (col * a.N8 + i0) >> 3;
-            chacha8(K.own, blk, a.c.op, 0, ao);
+    __shared__ uint4 s_msg[4][GT_WMSG_QUADS];
+    __shared__ u64 s_cnt[4][6];
+    __shared__ __align__(16) u64 s_x[3 * GT_XY_FEAT * GT_XY_ROW], s_y[3 * KMAX * GT_XY_ROW];
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES), tid = threadIdx.x;
+    WWire W; W.init(s_msg[wave], s_cnt[wave]);
+    const int p = W.p;
+    const Key own = load_lane_key(a.c.keys, p);
+    const u64 ngrp = a.N8 / 8, nt = (ngrp + 3) / 4;
+    const u32 t = W.t < 4 * GT_XY_COLS ? W.t : 4 * GT_XY_COLS - 1, ro = t / 4, gi = t % 4;
+    const LimbMat zo = COMPS ? (p == 0 ? a.C.m[0] : (p == 1 ? a.C.m[1] : a.C.m[2])) : (p == 0 ? a.B.m[0][1] : (p == 1 ? a.B.m[1][1] : a.B.m[2][1]));
+    const LimbMat zs = p == 0 ? a.B.m[0][0] : (p == 1 ? a.B.m[1][0] : a.B.m[2][0]);
+    const LimbMat lo = p == 0 ? a.Yl.m[0][1] : (p == 1 ? a.Yl.m[1][1] : a.Yl.m[2][1]), ls = p == 0 ? a.Yl.m[0][0] : (p == 1 ? a.Yl.m[1][0] : a.Yl.m[2][0]);
+    const u32 nkt = (a.d + a.tk - 1) / a.tk;
+    for (u64 item = blockIdx.x; item < nt * nkt; item += gridDim.x) {
+        const u64 tile = item / nkt, is = tile * 32;
+        const u32 k0 = (u32)(item % nkt) * a.tk, nk = k0 + a.tk < a.d ? a.tk : a.d - k0;
+        // rows of X and Y: consecutive words in consecutive threads, all loads before the first wait; samples beyond N are zero
+        {
+            constexpr int NY = (32 * KMAX + 255) / 256;
+            const u32 k = tid % GT_XY_FEAT, i = tid / GT_XY_FEAT;
+            u64 x[4][3], y[NY][3];
 #pragma unroll
-            for (int s = 0; s < 8; s++) s_prf[p][s * GT_LANES + lane] = ao[s];
-            u64 xo[8], xn[8];
-            ld8(own_of(a.XT, p) + kx * a.N8, i0, nv, xo); ld8(nxt_of(a.XT, p) + kx * a.N8, i0, nv, xn);
-            if (act && cy != cyc) {
-                ld8(own_of(a.YT, p) + cy * a.N8, i0, nv, yo); ld8(nxt_of(a.YT, p) + cy * a.N8, i0, nv, yn);
-                cyc = cy;
+            for (int r = 0; r < 4; r++) {
+                const u64 row = is + i + 8 * r;
+                const u64 at = (row < a.N ? row : a.N - 1) * a.d + k0 + (k < nk ? k : 0);
+#pragma unroll
+                for (int j = 0; j < 3; j++) x[r][j] = a.X.o[j][at];
             }
 #pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const Sh x = { xo[s], xn[s] }, y = { yo[s], yn[s] };
-                snd[s] = prod3(x, y) + ao[s];
+            for (int q = 0; q < NY; q++) {
+                const u64 at = is * a.K + tid + 256 * q, n = a.N * a.K;
+#pragma unroll
+                for (int j = 0; j < 3; j++) y[q][j] = a.Y.o[j][at < n ? at : n - 1];
             }
-            __syncthreads();
 #pragma unroll
-            for (int s = 0; s < 8; s++) snd[s] -= s_prf[pn][s * GT_LANES + lane];
-            W.reshare<8>(snd, rcv, 64u * live8(i0, nv));
-            if (act) {
+            for (int r = 0; r < 4; r++)
 #pragma unroll
-                for (int s = 0; s < 8; s++) { if (i0 + s >= a.N) { snd[s] = 0; rcv[s] = 0; } rcv[s] += snd[s]; }
-                if (a.comps) store_limbs8(p == 0 ? a.C.m[0] : (p == 1 ? a.C.m[1] : a.C.m[2]), col, i0, snd);
-                else {
-                    store_limbs8(a.B.m[p][0], col, i0, rcv);
-                    store_limbs8(a.B.m[p][1], col, i0, snd);
+                for (int j = 0; j < 3; j++) s_x[(j * GT_XY_FEAT + k) * GT_XY_ROW + i + 8 * r] = is + i + 8 * r < a.N ? x[r][j] : 0;
+#pragma unroll
+            for (int q = 0; q < NY; q++) {
+                const u32 e = tid + 256 * q, s = e / a.K, c = e - s * a.K;
+                if (e < 32 * a.K) {
+#pragma unroll
+                    for (int j = 0; j < 3; j++) s_y[(j * KMAX + c) * GT_XY_ROW + s] = is + s < a.N ? y[q][j] : 0;
                 }
             }
         }
+        __syncthreads();
+        for (u32 e = tid; e < 3 * 16 * nk; e += 256) {          // two samples each
+            const u32 i = e % 16 * 2, r = e / 16, j = r / nk, k = r - j * nk;
+            if (is + i < a.N8) *(ulonglong2 *)(a.XT.o[j] + (k0 + k) * a.N8 + is + i) = *(const ulonglong2 *)&s_x[(j * GT_XY_FEAT + k) * GT_XY_ROW + i];
+        }
+        const u64 g = tile * 4 + gi, grp = g < ngrp ? g : ngrp - 1, i0 = grp * 8;
+        const u32 off = (u32)(i0 - is);                        // the lane's first sample in the block
+        const bool actg = W.t < 4 * GT_XY_COLS && g < ngrp;    // the same in lane 63 as in lane 62
+        const auto row8 = [&](const u64 *row, u64 (&x)[8]) { ld8_whole(row + off, x); };
+        if (k0 == 0) {
+            for (u32 e = tid; e < 3 * 16 * a.K; e += 256) {
+                const u32 i = e % 16 * 2, r = e / 16, j = r / a.K, c = r - j * a.K;
+                if (is + i < a.N8) *(ulonglong2 *)(a.YT.o[j] + c * a.N8 + is + i) = *(const ulonglong2 *)&s_y[(j * KMAX + c) * GT_XY_ROW + i];
+            }
+            for (u32 c0 = wave * GT_XY_COLS; c0 < a.K; c0 += 4 * GT_XY_COLS) {
+                const u32 c = c0 + ro < a.K ? c0 + ro : a.K - 1;
+                u64 yo[8], yn[8];
+                row8(s_y + (p * KMAX + c) * GT_XY_ROW, yo); row8(s_y + (W.pn * KMAX + c) * GT_XY_ROW, yn);
+                store_limbs8(lo, c, i0, yo);
+                if (COMPS) store_limbs8(zo, (u64)a.d * a.K + c, i0, yo);
+#pragma unroll
+                for (int s = 0; s < 8; s++) yn[s] += yo[s];
+                store_limbs8(ls, c, i0, yn);
+            }
+        }
+        const bool tail = __ballot(i0 + 8 > a.N) != 0;         // uniform: a branch instead of 32 selections per step
+        const u32 kend = (k0 + nk) * a.K;
+        // lanes without an element of their own repeat another's, so that no store needs a branch
+        for (u32 kb = k0 * a.K + wave * GT_XY_COLS; kb < kend; kb += 4 * GT_XY_COLS) {
+            const u32 col = kb + ro < kend ? kb + ro : kend - 1, k = col / a.K, c = col - k * a.K;
+            u64 ao[8], an[8], snd[8], rcv[8];
+            chacha8<PRF_PAIR_LOOP>(own, (u64)col * ngrp + grp, a.c.op, 0, ao);
+            W.pass64<8>(ao, an, W.nx);                         // the words under the next key, from the other holder of that key
+            const u64 *xr = s_x + (p * GT_XY_FEAT + k - k0) * GT_XY_ROW + off, *xq = s_x + (W.pn * GT_XY_FEAT + k - k0) * GT_XY_ROW + off;
+            const u64 *yr = s_y + (p * KMAX + c) * GT_XY_ROW + off, *yq = s_y + (W.pn * KMAX + c) * GT_XY_ROW + off;
+#pragma unroll
+            for (int s = 0; s < 8; s += 2) {
+                const ulonglong2 xo = *(const ulonglong2 *)(xr + s), xn = *(const ulonglong2 *)(xq + s), yo = *(const ulonglong2 *)(yr + s), yn = *(const ulonglong2 *)(yq + s);
+                snd[s] = prod3(Sh{ xo.x, xn.x }, Sh{ yo.x, yn.x }) + (ao[s] - an[s]);
+                snd[s + 1] = prod3(Sh{ xo.y, xn.y }, Sh{ yo.y, yn.y }) + (ao[s + 1] - an[s + 1]);
+            }
+            W.reshare64<8>(snd, rcv);
+            W.nresh += actg && kb + ro < kend ? 64u * live8(i0, a.N) : 0u;
+            if (tail) {
+#pragma unroll
+                for (int s = 0; s < 8; s++) if (i0 + s >= a.N) { snd[s] = 0; rcv[s] = 0; }
+            }
+            store_limbs8(zo, col, i0, snd);
+            if (!COMPS) {
+#pragma unroll
+                for (int s = 0; s < 8; s++) rcv[s] += snd[s];
+                store_limbs8(zs, col, i0, rcv);
+            }
+        }
+        W.drain();
+        __syncthreads();                                       // the rows in LDS are overwritten next
     }
     W.flush(a.c.wire);
 }
 
-// class indicator columns into limb tiles: row c of Y (both forms) and, where the columns are
-// stored once per component (comps), row rowbase + c of C
-struct YLimbsArgs { P6 YT; LimbSet Y; LimbTri C; int comps; u64 N, N8, rowbase; u32 K; };
-__device__ __forceinline__ void y_limbs(const YLimbsArgs &a)
-{
-    const P6 &YT = a.YT;
-    const u64 N = a.N, N8 = a.N8;
-    const u64 ngrp = N8 / 8, total = ngrp * a.K;
-    for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (u64)gridDim.x * blockDim.x) {
-        const u64 c = t / ngrp, i0 = (t % ngrp) * 8;
-        for (int p = 0; p < 3; p++) {
-            u64 xo[8], xn[8];
-#pragma unroll
-            for (int s = 0; s < 8; s++) {
-                const bool live = i0 + s < N;
-                xo[s] = live ? YT.o[p][c * N8 + i0 + s] : 0; xn[s] = live ? xo[s] + YT.n[p][c * N8 + i0 + s] : 0;
-            }
-            store_limbs8(a.Y.m[p][0], c, i0, xn);
-            store_limbs8(a.Y.m[p][1], c, i0, xo);
-            if (a.comps) store_limbs8(a.C.m[p], a.rowbase + c, i0, xo);
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_y_limbs(YLimbsArgs a) { y_limbs(a); }
-
 // what a training starts from, one launch (blockIdx.y): M, T, C := 0; F := 0, the root a leaf (1); gamma of the
-// root := 1; 5: the class columns' limb tiles, where they are few
+// root := 1
 struct StartArgs { P6 M, T, F, C, gamma; u64 N, nodes, nC, d; };
-__global__ __launch_bounds__(256) void k_start(StartArgs a, YLimbsArgs yl)
+__global__ __launch_bounds__(256) void k_start(StartArgs a)
 {
-    if (blockIdx.y == 5) { y_limbs(yl); return; }
     const u32 what = blockIdx.y;
     const u64 n = what == 0 ? a.N : (what == 3 ? a.nC : (what == 4 ? a.d : a.nodes));
     const P6 &dst = what == 0 ? a.M : (what == 1 ? a.T : (what == 2 ? a.F : (what == 3 ? a.C : a.gamma)));
@@ -746,11 +788,7 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
         // GM_ROWS: the samples' own values of a column, fetched a whole step ahead (HBM latency)
         u64 xo[8], xn[8];
         const auto fetch_x = [&](u32 k) {              // whole groups: rows are padded to N8 and start at multiples of 64 bytes
-            const ulonglong2 *qo = (const ulonglong2 *)(xto + (u64)k * a.N8), *qn = (const ulonglong2 *)(xtn + (u64)k * a.N8);
-#pragma unroll
-            for (int j = 0; j < 4; j++) { const ulonglong2 v = qo[j]; xo[2 * j] = v.x; xo[2 * j + 1] = v.y; }
-#pragma unroll
-            for (int j = 0; j < 4; j++) { const ulonglong2 v = qn[j]; xn[2 * j] = v.x; xn[2 * j + 1] = v.y; }
+            ld8_whole(xto + (u64)k * a.N8, xo); ld8_whole(xtn + (u64)k * a.N8, xn);
         };
         if (MODE == GM_ROWS && !IN_LDS) fetch_x(kbeg);
         u64 acc[8], acc2[8];

@@ -583,26 +583,24 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
 {
     const u32 d = t->d, K = t->K;
     const size_t N = t->N, N8 = t->N8, nmax = (size_t)1 << t->H, nodes = ((size_t)2 << t->H) - 1;
-    // sample-contiguous copies of X and Y, a plane per component (six planes: 48,842 x 294 279 us, three 140)
-    dim3 gXY = gT(N, d); gXY.x = std::max(gXY.x, gT(N, K).x); gXY.z = 6;
-    GTCHK(launch(c, GT_KC_LOCAL, k_transpose, gXY, B256, t->XT.v, to_p6(X), d, t->YT.v, to_p6(Y), K, (u64)N, (u64)N8));
-    // one-time products X[i][k] * Y[i][c] and the class columns, as limb tiles
-    XyArgs a{}; a.c = kc(c, c->op++); a.XT = t->XT.v; a.YT = t->YT.v; a.comps = t->comps; a.N = N; a.N8 = N8; a.K = K;
+    // sample-contiguous copies of X and Y, one-time products X[i][k] * Y[i][c] and the class columns, as limb tiles
+    XyArgs a{}; a.c = kc(c, c->op++); a.X = to_p6(X); a.Y = to_p6(Y); a.XT = t->XT.v; a.YT = t->YT.v; a.N = N; a.N8 = N8; a.d = d; a.K = K;
     if (t->comps) a.C = limbs_C(t); else a.B = limbs_B(t);
-    a.ncol = d * K;
-    const unsigned gy = std::min((a.ncol + 3) / 4, 4u);
-    const unsigned gx = (unsigned)std::max<u64>(1, std::min<u64>((N8 / 8 + 15) / 16, GT_MAX_BLOCKS / gy));
-    GTCHK(launch(c, GT_KC_MULT, k_xy, dim3(gx, gy), GT_BLOCK, a));
+    a.Yl = limbs_Y(t);
+    // features in equal parts of at most 32 (whole rows of 256 bytes); fewer where the blocks are few, down to a step for each wavefront
+    // (267 x 22: 11 us in three parts, 13 in one; 10^6 x 64 in parts of 16 2.97 ms, of 32 2.49)
+    const u64 blocks = (N8 / 8 + 3) / 4, cus = std::max(1u, c->simds / 4);
+    const u32 parts = (u32)std::max<u64>((d + GT_XY_FEAT - 1) / GT_XY_FEAT, std::min<u64>(((u64)d * K + 4 * GT_XY_COLS - 1) / (4 * GT_XY_COLS), cus / blocks));
+    a.tk = (d + parts - 1) / parts;
+    const dim3 gxy((unsigned)std::min<u64>(blocks * ((d + a.tk - 1) / a.tk), 3 * cus));
+    const int rc = K <= 4 ? (t->comps ? launch(c, GT_KC_MULT, k_xy<true, 4>, gxy, B256, a) : launch(c, GT_KC_MULT, k_xy<false, 4>, gxy, B256, a))
+                          : (t->comps ? launch(c, GT_KC_MULT, k_xy<true, GT_MAX_K>, gxy, B256, a) : launch(c, GT_KC_MULT, k_xy<false, GT_MAX_K>, gxy, B256, a));
+    GTCHK(rc);
     acct_reshare(c, (u64)N * d * K, 1);
-    YLimbsArgs yl{}; yl.YT = t->YT.v; yl.Y = limbs_Y(t); if (t->comps) yl.C = limbs_C(t); yl.comps = t->comps; yl.N = N; yl.N8 = N8; yl.K = K; yl.rowbase = (u64)d * K;
     // M = 0, T = 0, the root is a leaf with empty statistics, no candidate used yet
     StartArgs st{}; st.M = t->M.v; st.T = t->T.v; st.F = t->F.v; st.C = t->C.v; st.gamma = t->gamma.v;
     st.N = N; st.nodes = nodes; st.nC = nmax * t->CW; st.d = d;
-    // the class columns' tiles beside it while they are a matter of the launch (267 x 2: 9 us together, 5 + 5 apart; 100,000 x
-    // 8: 62 together, 5 + 50 apart)
-    const bool beside = N8 / 8 * K <= 32768;
-    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>(N, nmax * t->CW)).x, beside ? 6 : 5), B256, st, yl));
-    if (!beside) GTCHK(launch(c, GT_KC_LOCAL, k_y_limbs, g1(N8 / 8 * K), B256, yl));
+    GTCHK(launch(c, GT_KC_LOCAL, k_start, dim3(g1(std::max<u64>(N, nmax * t->CW)).x, 5), B256, st));
     t->level = 0; t->last = 0; t->finished = false; t->fresh_import = false; t->lt_level = ~0u;
     return GT_OK;
 }
@@ -1230,7 +1228,7 @@ extern "C" int gt_infer_batch(gt_ctx *c, const gt_tree *tr, const gt_shares *I, 
         if (c->ws[i].n < need[i]) { (void)hipStreamSynchronize(c->stream); dsh_free(c->ws[i]); rc = dsh_alloc(c->ws[i], need[i], c->stream, i == 0); }
     DSh &IT = c->ws[0], &tidx = c->ws[1], &f = c->ws[2], &th = c->ws[3], &x = c->ws[4];
     if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_fill_const, g1(NI), B256, tidx.v, (u64)0, (u64)NI, (u64)0);
-    if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_transpose, gT(NI, d), B256, IT.v, to_p6(I), d, IT.v, to_p6(I), d, (u64)NI, (u64)N8);
+    if (rc == GT_OK) rc = launch(c, GT_KC_LOCAL, k_transpose, gT(NI, d), B256, IT.v, to_p6(I), d, (u64)NI, (u64)N8);
     for (u32 n = 0; n < H && rc == GT_OK; n++) {
         const u64 w = (u64)1 << n, base = w - 1;
         GridArgs a{}; a.u = tidx.v; a.base = base; a.w = (u32)w; a.N = NI; a.N8 = N8;

@@ -1142,3 +1142,14 @@ OAA_THREE_WAVEFRONTS = [(30, 100003), (5, 364001), (300, 20003)]
 def test_oaa_three_wavefronts(mods, seed, w, n):
     """Three wavefronts per SIMD, the rows' opened values in LDS: several ranges, one range of few columns, few rows."""
     test_oaa_at_tile_edges(mods, seed, w, n)
+
+
+# one sample, one block and one over; features of one part, two equal ones, one over; classes of both variants; more blocks than workgroups; the
+# columns kept per party (many nodes for the columns) and per component
+SETUP_SHAPES = [(1, 1, 2, 1), (31, 33, 5, 1), (32, 32, 4, 2), (33, 65, 16, 1), (64, 31, 3, 2), (24601, 3, 4, 1), (65, 2, 5, 7), (40, 3, 2, 8)]
+
+
+@pytest.mark.parametrize("N,d,K,H", SETUP_SHAPES)
+def test_train_setup_shapes(mods, seed, N, d, K, H):
+    """The launch that makes the transposed data, the products and the class columns, through whole trainings."""
+    test_train_column_group_remainders(mods, seed, N, d, K, H)
