@@ -269,11 +269,13 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
     __shared__ u64 s_val[GT_INFER_OCT(NW)][(THR ? 3 : 2) * GT_INFER_VAL];
     __shared__ u64 s_sum[GT_INFER_OCT(NW)][GT_INFER_SUM(THR)];
     __shared__ u64 s_open[NW][GT_INFER_OCT(NW)][8];
+    __shared__ __align__(16) u32 s_keys[40];               // the five keys: the blocks of the rows are evaluated with one or another by lane
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     InferWg<PRF_PAIR_LOOP, STAGED> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);
     WWire &W = X.E.W;
-    X.p = W.p; X.pn = W.pn; X.keys = a.c.keys;
+    X.p = W.p; X.pn = W.pn; X.keys = s_keys;
+    if (threadIdx.x < 40) s_keys[threadIdx.x] = a.c.keys[threadIdx.x];          // read after the first item's barrier
     X.ncol = GT_INFER_LANES(NW) / a.noct;
     const u32 q = wave * GT_TP + W.t, o = q % a.noct;
     X.cl = q / a.noct; X.active = X.cl < X.ncol; X.one = X.cl == 0 && W.real;

@@ -911,7 +911,7 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
     __shared__ u64 s_cnt[6];                                                                \
     typename ElWire<ISSUE>::T W; W.init(s_msg, s_cnt);                                      \
     const int p = W.p;                                                                      \
-    ElTile<NS, ISSUE> T; T.keys = a.c.keys; T.mat = s_mat;
+    ElTile<NS, ISSUE> T; T.init(a.c.keys, W, s_mat);
 #define GT_FOR_EL(n) for (u64 tile_ = blockIdx.x, ntiles_ = ((u64)(n) + GT_EL - 1) / GT_EL; tile_ < ntiles_; tile_ += gridDim.x)
 __device__ __forceinline__ u32 el_live(u64 e0, u64 n) { return n - e0 < GT_EL ? (u32)(n - e0) : GT_EL; }
 
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(64) void k_dot_fin(GridArgs a, u32 finblk, EqArgs e
     __shared__ u64 s_cnt[6];
     ElWire<PRF_ALONE>::T W; W.init(s_msg, s_cnt);
     const int p = W.p;
-    ElTile<2> T; T.keys = a.c.keys; T.mat = s_mat;
+    ElTile<2> T; T.init(a.c.keys, W, s_mat);
     const Sh one = pub(p, 1);
     if (blockIdx.x >= finblk) {
         for (u64 tile = blockIdx.x - finblk; tile < (eq.n + GT_EL - 1) / GT_EL; tile += gridDim.x - finblk) eq_tile<true>(eq, W, T, tile);
@@ -1066,7 +1066,7 @@ __device__ __forceinline__ void div_steps_el(WireT &W, TileT &T, u64 *s_mat, int
     const u32 wave_ = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);               \
     typename ElWire<NW == 1 ? PRF_PAIR : PRF_ALONE>::T W; W.init(s_msg[wave_], s_cnt[wave_]); \
     const int p = W.p;                                                                      \
-    ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.keys = a.c.keys; T.mat = s_mat;
+    ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.init(a.c.keys, W, s_mat);
 
 // 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us in the wavefront model, 75 with the issue priorities of
 // PRF_PAIR (VALU: a PRF pass and 330 instructions of protocol per step and 20 elements).
@@ -1224,7 +1224,7 @@ __global__ __launch_bounds__(64 * NW) void k_argmax(ArgmaxArgs a)
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     ElWire<PRF_ALONE>::T W; W.init(s_msg[wave], s_cnt[wave]);
     const int p = W.p;
-    ElTile<4> T; T.keys = a.c.keys; T.mat = s_mat[wave];
+    ElTile<4> T; T.init(a.c.keys, W, s_mat[wave]);
     u64 *vo = s_buf[4 * p], *vn = s_buf[4 * p + 1], *io = s_buf[4 * p + 2], *in = s_buf[4 * p + 3];
     const u32 per = NW == 1 ? 32 / a.len : 1;                           // nodes of a workgroup
     for (u64 r0 = (u64)blockIdx.x * per; r0 < a.nh; r0 += (u64)gridDim.x * per) {
