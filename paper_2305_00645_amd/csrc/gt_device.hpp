@@ -691,3 +691,95 @@ struct ElTile {
     __device__ __forceinline__ u64 zb(const WWire &W, int i, u32 w) const
     { const u64 *m = mat + 10 * GT_TP + i * 72 + w; return m[W.p * 24] ^ m[W.pn * 24]; }
 };
+
+// Tiles of NEL elements (a multiple of 8), two per lane of a party, for launches that fill the chip: a tile starts at a multiple of 8, so that its
+// words under the three keys are whole blocks, 3 NEL / 8 a stream, and NEL dealer blocks and these make up one pass of the block function
+// (40 elements and one stream: 55 of 63 lanes, where ElTile's 20 leave 34 idle).
+template <int NEL, int NS>
+struct ElPair {
+    static constexpr int G = NEL / 8, L = NEL / 2;      // blocks of a stream and key, lanes of a party
+    static constexpr int ROW = NEL + (L + 32 - NEL % 32) % 32;           // words of a row: L modulo 32, the parties' loads in other banks
+    static_assert(NEL + 3 * G * NS <= 3 * GT_TP && L <= GT_TP && ROW % 32 == L, "more blocks than lanes");
+    static constexpr int WORDS = (10 + 3 * NS) * ROW;   // [10] dealer components, [NS][3] words
+    const u32 *keys;
+    u64 *mat;
+    __device__ __forceinline__ void deal(const WWire &W, u32 op, u64 e0, const u32 (&st)[NS], u32 nel)
+    {
+        const u32 m = W.m, r = m - NEL, q = r / G, g = r % G;           // q = 3 i + j: stream i, key j
+        const bool dealer = m < NEL;
+        wave_sync();
+        if (dealer ? m < nel : r < 3 * G * NS) {
+            Key k;
+            const u32 *from = keys + 8 * (dealer ? GT_KEY_DEALER : q % 3);
+#pragma unroll
+            for (int i = 0; i < 8; i++) k.k[i] = from[i];
+            u32 stream = 0;
+#pragma unroll
+            for (int i = 0; i < NS; i++) stream = !dealer && q / 3 == (u32)i ? st[i] : stream;
+            u64 D[8];
+            chacha8<PRF_PAIR>(k, dealer ? e0 + m : (e0 >> 3) + g, op, stream, D);
+            if (dealer) {
+                const u64 beta = D[5] & 1;
+                const u32 b0 = (u32)(D[5] >> 1) & 1, b1 = (u32)(D[5] >> 2) & 1;
+                mat[m] = D[1]; mat[ROW + m] = D[2]; mat[2 * ROW + m] = D[0] - D[1] - D[2];
+                mat[3 * ROW + m] = D[3]; mat[4 * ROW + m] = D[4]; mat[5 * ROW + m] = D[0] ^ D[3] ^ D[4];
+                mat[6 * ROW + m] = D[6]; mat[7 * ROW + m] = D[7]; mat[8 * ROW + m] = beta - D[6] - D[7];
+                mat[9 * ROW + m] = b0 | (b1 << 1) | ((((u32)beta ^ b0 ^ b1) & 1) << 2);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; i++) mat[(10 + q) * ROW + 8 * g + i] = D[i];
+            }
+        }
+        wave_sync();
+    }
+    __device__ __forceinline__ Dealer dealer(const WWire &W, u32 e) const
+    {
+        Dealer D;
+        const u64 *m = mat + e;
+        const u32 b = (u32)m[9 * ROW];
+        D.rA.o = m[W.p * ROW]; D.rA.n = m[W.pn * ROW];
+        D.rho.o = m[(3 + W.p) * ROW]; D.rho.n = m[(3 + W.pn) * ROW];
+        D.bA.o = m[(6 + W.p) * ROW]; D.bA.n = m[(6 + W.pn) * ROW];
+        D.bBo = (b >> W.p) & 1; D.bBn = (b >> W.pn) & 1;
+        return D;
+    }
+    // the Boolean zero-sharing word of stream i
+    __device__ __forceinline__ u64 zb(const WWire &W, int i, u32 e) const { return mat[(10 + 3 * i + W.p) * ROW + e] ^ mat[(10 + 3 * i + W.pn) * ROW + e]; }
+};
+
+// [v == 0] of a lane's two elements: the rounds of eq_bit_mask, a dword for both from the second on; the result's bits 0 and 16.
+// na: how many of the two exist.
+__device__ __forceinline__ void eq_bits2(WWire &W, const Sh (&v)[2], const Dealer (&D)[2], const u64 (&A)[2], u32 na, u32 &ro, u32 &rn)
+{
+    const u32 M0 = W.p == 0 ? ~0u : 0u, M2 = W.p == 2 ? ~0u : 0u;
+    u64 snd[2], rcv[2];
+    u32 x[2], y[2], H[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) snd[h] = v[h].o + D[h].rA.o;
+    W.open64<2>(snd, rcv);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const u64 c = snd[h] + v[h].n + D[h].rA.n + rcv[h];
+        const u32 cl = (u32)c, ch = (u32)(c >> 32);
+        // t = rho with the complement of c xored into component 0
+        const u32 tol = logic3<0xd2>((u32)D[h].rho.o, cl, M0), toh = logic3<0xd2>((u32)(D[h].rho.o >> 32), ch, M0);
+        const u32 tnl = logic3<0xd2>((u32)D[h].rho.n, cl, M2), tnh = logic3<0xd2>((u32)(D[h].rho.n >> 32), ch, M2);
+        x[h] = and3l(tol, tnl, toh, tnh) ^ (u32)A[h];
+        H[h] = (u32)(A[h] >> 32);
+    }
+    W.reshare<2>(x, y);
+    const u32 LO = 0x05040100u, HI = 0x07060302u;               // halves of a pair of dwords
+    u32 P[1] = { and3l(__builtin_amdgcn_perm(x[1], x[0], LO), __builtin_amdgcn_perm(y[1], y[0], LO), __builtin_amdgcn_perm(x[1], x[0], HI), __builtin_amdgcn_perm(y[1], y[0], HI))
+                 ^ __builtin_amdgcn_perm(H[1], H[0], LO) }, Q[1];
+    u32 B = __builtin_amdgcn_perm(H[1], H[0], HI);              // bits 48-63 of the mask words
+    W.reshare<1>(P, Q);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int w = 8 >> i;
+        P[0] = logic3<0x60>(w == 8 ? 0x00ff00ffu : w == 4 ? 0x000f000fu : w == 2 ? 0x00030003u : 0x00010001u, and3l(P[0], Q[0], P[0] >> w, Q[0] >> w), B);
+        W.reshare<1>(P, Q);
+        B >>= w;
+    }
+    W.nopen += 64u * na; W.nresh += 63u * na;
+    ro = P[0]; rn = Q[0];
+}

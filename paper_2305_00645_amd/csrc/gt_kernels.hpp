@@ -941,6 +941,56 @@ __global__ __launch_bounds__(64) void k_eq(EqArgs a)
     W.flush(a.c.wire);
 }
 
+// Bits s (own ro, next rn, in bits 0 and 16) of a lane's two elements to arithmetic sharings: one message for both.
+__device__ __forceinline__ void b2a2(WWire &W, u32 ro, u32 rn, const Dealer (&D)[2], u32 na, Sh (&z)[2])
+{
+    u32 fo[1] = { ro ^ (D[0].bBo | (D[1].bBo << 16)) }, fr[1];
+    W.pass<1>(fo, fr, W.pv);
+    W.nopen += na;
+    const u32 f = fo[0] ^ rn ^ (D[0].bBn | (D[1].bBn << 16)) ^ fr[0];
+    const Sh one = pub(W.p, 1);
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const bool set = (f >> (16 * h)) & 1;
+        z[h].o = set ? one.o - D[h].bA.o : D[h].bA.o;
+        z[h].n = set ? one.n - D[h].bA.n : D[h].bA.n;
+    }
+}
+
+// k_eq<false> on tiles of 40 elements, two per lane (see ElPair), from as many on as there are SIMDs: the block function is two thirds of
+// the work, and a pass of it yields twice the elements.  60,000 elements 9.6 us in tiles of 20, 9.0 so; 300,007 21.3 and 18.3; 2,000,000 86 and 69; but
+// 30,000 8.0 and 8.1, 21,000 7.6 and 7.8.  (Order tests, 32 elements on 16 of 21 lanes a party: 300,007 24.3 and 26.4.)
+__global__ __launch_bounds__(64) void k_eq_pair(EqArgs a)
+{
+    __shared__ uint4 s_msg[GT_LANES];
+    __shared__ u64 s_mat[ElPair<40, 1>::WORDS];
+    __shared__ u64 s_cnt[6];
+    WWire W; W.init(s_msg, s_cnt);
+    const int p = W.p;
+    ElPair<40, 1> T; T.keys = a.c.keys; T.mat = s_mat;
+    for (u64 tile = blockIdx.x; tile < (a.n + 39) / 40; tile += gridDim.x) {
+        const u64 e0 = tile * 40;
+        const u32 nel = a.n - e0 < 40 ? (u32)(a.n - e0) : 40, t = W.t < 20 ? W.t : 19, e[2] = { t, t + 20 };
+        const bool act[2] = { W.t < 20 && e[0] < nel, W.t < 20 && e[1] < nel };
+        const u32 na = (u32)act[0] + (u32)act[1];
+        Sh v[2] = { { 0, 0 }, { 0, 0 } }, z[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+            if (act[h]) v[h] = ld(a.x, p, a.xoff + e0 + e[h]) - pub(p, a.ysub + (a.ypub ? a.ypub[e0 + e[h]] : 0));
+        const u32 st1[1] = { 1 };
+        T.deal(W, a.c.op, e0, st1, nel);
+        const Dealer D[2] = { T.dealer(W, e[0]), T.dealer(W, e[1]) };
+        const u64 A[2] = { T.zb(W, 0, e[0]), T.zb(W, 0, e[1]) };
+        u32 ro, rn;
+        eq_bits2(W, v, D, A, na, ro, rn);
+        b2a2(W, ro, rn, D, na, z);
+#pragma unroll
+        for (int h = 0; h < 2; h++) if (act[h] && W.real) st(a.z, p, e0 + e[h], z[h]);
+        W.drain();
+    }
+    W.flush(a.c.wire);
+}
+
 // Completion of split inner products: z_p = partial sum + alpha (stream 2, second
 // output stream 3), reshare, epilogue as in k_eqgrid.  Rows in the lanes of the element kernels:
 // consecutive rows in consecutive lanes (eight rows per lane of 64 took 11 us for 48,842 rows).  The workgroups from finblk on

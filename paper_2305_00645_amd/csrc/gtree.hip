@@ -396,7 +396,8 @@ static int do_eq(gt_ctx *c, bool bool_out, P6 x, u64 xoff, const u64 *ypub, u64 
 {
     EqArgs a{}; a.c = kc(c, c->op++); a.x = x; a.xoff = xoff; a.ypub = ypub; a.ysub = ysub; a.z = z; a.n = n;
     if (n && !launched) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, gE(n), B64, a)
-                          : launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a));
+                          : n < 40ull * c->simds ? launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a)
+                          : launch(c, GT_KC_SMALL, k_eq_pair, dim3((unsigned)std::min<u64>((n + 39) / 40, 1u << 16)), B64, a));
     acct_eq(c, n);
     if (!bool_out) acct_b2a(c, n);
     return GT_OK;

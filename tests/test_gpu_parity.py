@@ -1153,3 +1153,18 @@ SETUP_SHAPES = [(1, 1, 2, 1), (31, 33, 5, 1), (32, 32, 4, 2), (33, 65, 16, 1), (
 def test_train_setup_shapes(mods, seed, N, d, K, H):
     """The launch that makes the transposed data, the products and the class columns, through whole trainings."""
     test_train_column_group_remainders(mods, seed, N, d, K, H)
+
+
+@pytest.mark.parametrize("n", [40959, 40960, 40961, 40979, 40981, 40999, 65536 * 40 + 3])
+def test_equality_two_elements_per_lane(mods, seed, n):
+    """Tiles of 40 elements, two per lane, from 40 x 1,024 on: below, full, one element in the last tile, its lanes' second elements missing, one of
+    them, one short; more tiles than workgroups."""
+    o, g = pair(mods, seed)
+    rng = np.random.default_rng(n)
+    x = rng.integers(0, 1 << 39, size=n).astype(np.uint64)
+    y = np.where(rng.random(n) < 0.4, x, rng.integers(0, 1 << 39, size=n).astype(np.uint64))
+    xo, xg = o.share(x), g.share_a(x)
+    z = g.eq_a(xg, y)
+    same(z, o.eq_a(xo, y), "eq")
+    assert np.array_equal(g.rec(z), (x == y).astype(np.uint64))
+    same_stats(o, g)
