@@ -29,7 +29,8 @@ struct InferArgs {
 // [6][8], zero-sharing words [2 streams, one without thresholds][3 keys][8]; of a comparison: [9][8] components (r, r's bits,
 // beta), beta's bits [8], mask words [2][3][8].  Sums: [2, 1][3][8].  Values: index, id, threshold by component, [3][8]
 // each: a component is written by the party whose own it is.
-#define GT_INFER_MAT(THR) ((THR) ? 128 : 72)
+// The material's stride is 2 words modulo 32, so that the groups' and the parties' words of a step lie in different banks.
+#define GT_INFER_MAT(THR) ((THR) ? 130 : 98)           // 128 and 72 used
 #define GT_INFER_SUM(THR) ((THR) ? 48 : 24)
 #define GT_INFER_VAL 24
 
