@@ -294,6 +294,16 @@ __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blo
     const bool narrow = a.n <= 0xffffffffu;            // 32-bit division: a tenth of the instructions of the 64-bit one
     for (u64 tile = block, nt = (a.n + 511) / 512; tile < nt; tile += blocks) {
         u64 w[8];
+        // node split: a launch of few workgroups, whose loads are in flight during the block function
+        Sh px[8], py[8];
+        if (MODE == 2) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const u64 e = tile * 512 + j * GT_LANES + lane, el = e < a.n ? e : a.n - 1;
+                const u64 r = narrow ? (u64)((u32)el / a.CW) : el / a.CW;
+                px[j].o = xo[el]; px[j].n = xn[el]; py[j].o = yo[r]; py[j].n = yn[r];
+            }
+        }
         chacha8(own, tile * GT_LANES + lane, a.c.op, 0, w);
         tr_put(s_tr[p], lane, w);
         __syncthreads();
@@ -310,11 +320,10 @@ __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blo
                 at[i] = e;
                 if (e < a.n) {
                     live++;
-                    x.o = xo[e]; x.n = xn[e];
-                    if (MODE == 0) { y.o = yo[e]; y.n = yn[e]; }
+                    if (MODE == 0) { x.o = xo[e]; x.n = xn[e]; y.o = yo[e]; y.n = yn[e]; }
                     if (MODE == 2) {
                         const u64 r = narrow ? (u64)((u32)e / a.CW) : e / a.CW;
-                        y.o = one.o - yo[r]; y.n = one.n - yn[r];
+                        x = px[j]; y = one - py[j];
                         at[i] = e + r * a.CW;          // element (2r, col) of the next level
                     }
                 }
