@@ -27,8 +27,9 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // more; two sums, 13 to 20,000 rows 3 to 3.5 us less in two (one range completes the sums of eight rows per lane), 30,000 0.9
 // less, 60,000 3.7 more.
 // Wavefronts per SIMD: two, or three of 168 registers with the rows' opened values in LDS (shared arrays and the leaf one-hot; own rows gain
-// nothing by it).  Three take 1.37 of the time of two for a step of each, two of them 1.05, one 0.66: 1,000,000 x 64 593 us and 533;
-// 200,003 x 100 in 5 ranges 213 and 196, 48,842 x 64 in the 7 ranges that fill two per SIMD 46.5 and 50.2, in ten 62.5 and 49.3.
+// nothing by it).  Three take 1.37 of the time of two for a step of each, two of them 1.05, one 0.66, and the row's part 3.3 steps: 1,000,000 x 64
+// 593 us and 533; 200,003 x 100 in 5 ranges 213 and 196, 48,842 x 64 in the 7 ranges that fill two per SIMD 46.5 and 50.2, in ten 62.5 and 49.3;
+// 89,221 x 28 in 3 and 5 ranges 49.1 and 50.5.  At most 32 ranges: 8,477 x 733 in 40 and 60 ranges 72 and 77, 4,061 x 939 in 81 and 118 58 and 68.
 struct ColumnRanges { u64 n; u32 waves; };
 static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
 {
@@ -43,10 +44,10 @@ static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntil
             const u64 len = (nsteps + n - 1) / n;
             n = (nsteps + len - 1) / len;
             const u64 items = ntile * n, full = items / (waves * simds), rest = items % (waves * simds);
-            if (waves == 3 && items <= 2 * simds) continue;
+            if (waves == 3 && (items <= 2 * simds || n > 32)) continue;
             const double last = rest == 0 ? 0.0 : waves == 2 ? (rest > simds ? 1.0 : n == 1 && sums ? 0.82 : 0.6)
                                 : rest > 2 * simds ? 1.37 : rest > simds ? 1.05 : 0.66;
-            const double cost = ((waves == 2 ? 1.0 : 1.37) * (double)full + last) * ((double)len + 2.5) + (n > 1 ? launch : 0.0);
+            const double cost = ((waves == 2 ? 1.0 : 1.37) * (double)full + last) * ((double)len + (waves == 2 ? 2.5 : 3.3)) + (n > 1 ? launch : 0.0);
             if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { n, waves }; }
         }
     }

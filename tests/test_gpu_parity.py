@@ -1135,7 +1135,7 @@ def test_context_on_a_side_stream(mods, seed):
         g.close()
 
 
-OAA_THREE_WAVEFRONTS = [(30, 100003), (5, 364001), (300, 20003)]
+OAA_THREE_WAVEFRONTS = [(64, 100003), (5, 364001), (500, 20003)]
 
 
 @pytest.mark.parametrize("w,n", OAA_THREE_WAVEFRONTS)
