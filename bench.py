@@ -32,8 +32,8 @@ EQ_ALU_OPS = EQ_ALU_OPS_DEALER + EQ_ALU_OPS_ONLINE
 # (table in profiles/pmc_traffic_micro.md): inner product against a shared array, against the
 # sample's own row, leaf one-hot written as limb tiles
 # (56 for the level, whose tiles hold the sums too, and 25 for the label level, by their tests); the
-# one-launch inference reads every feature of an instance at least once per level
-EQ_HBM_BYTES = {"eqgrid": 1.7, "eqgrid_rows": 53.3, "eqgrid_store": 35.4, "infer": 18.2}
+# one-launch inference reads every feature of an instance at least once per level, much of it from the last-level cache
+EQ_HBM_BYTES = {"eqgrid": 2.2, "eqgrid_rows": 27.6, "eqgrid_store": 35.4, "infer": 5.1}
 SHADER_CLOCK_MEASURED_GHZ = 2.1  # under the equality grid's load (profiles/pmc_sq_micro.md); the peak below uses the nominal 2.4
 
 
@@ -340,7 +340,7 @@ def main():
                                "reads %.1f GHz); traffic = HBM bytes per launch = per-variant counter bytes per test "
                                "(profiles/pmc_traffic_micro.md) x this run's tests per variant; the >=50%% HBM target of the "
                                "workload description is not met and cannot be by this kernel: its messages stay in LDS and it "
-                               "is bound by the vector ALU (issue share 0.84-1.19 at 4 cycles an instruction, profiles/pmc_sq_micro.md), see eqgrid_hbm_view"
+                               "is bound by the vector ALU (issue share 0.83-1.35 at 4 cycles an instruction, profiles/pmc_sq_micro.md), see eqgrid_hbm_view"
                                % (EQ_ALU_OPS, EQ_ALU_OPS_DEALER, EQ_ALU_OPS_ONLINE,
                                   EQ_ALU_OPS_ONLINE * n_eq * k / (eq_ms / 1e3) / 1e12 / LANE_OPS_PEAK, SHADER_CLOCK_MEASURED_GHZ),
                        "avg_launch_ms": eq_ms / max(eq_l, 1), "launches_per_step": eq_l // k,
