@@ -557,7 +557,8 @@ __global__ __launch_bounds__(256 * NQ, 4) void k_infer_ahead(InferArgs a)
         for (int s = 0; s < 4; s++) cd[s] = cpub[s] - k0;
         return eq_rounds4(W, M0, M2, A, An, bw, cd, rho_o, rho_n, act ? live : 0u);
     };
-    const auto bit = [&](int c, int s) { return s_step[turn & 1][wave].rows[c * GT_AHEAD_COMP + (h4 + s) * (GT_TP + 1) + W.t]; };
+    // one product per word: with the component's stride of its own (c * 198 + ..) 10^4 x 16, depth 7, thresholds takes 114.0 us, 113.3 so
+    const auto bit = [&](int c, int s) { return s_step[turn & 1][wave].rows[(c * 9 + h4 + s) * (GT_TP + 1) + W.t]; };
     // adds up the four words of a group's lanes: every lane by itself, or with one or two groups, where 10 to 21 lanes would meet at
     // every word, through the message region (one instance: 4,000 cycles an access without that)
     const auto add_up = [&](const u64 (&x)[4], u64 *sum, u32 stride) {
