@@ -1423,17 +1423,17 @@ __global__ __launch_bounds__(64) void k_update(UpdateArgs a)
 // ---------------------------------------------------------------------------------
 // Data partition by products with the previous level's per-sample leaf one-hot (a variant
 // beyond the paper's listing: no per-sample equality tests).
-//   k_onehot  : OH[r][k] = [T[base + r] == k] as an arithmetic sharing, written as limb bytes
+//   k_onehot  : OH[r][k] = [T[base + r] == k] as an arithmetic sharing, written as limb bytes (BYTES) or as words, for k_oh_limbs
 //   k_part_mm : sel[k][i] = sum_r L[r][i] * OH[r][k], zero sharing of stream 0, word k*N8+i, and
 //               M[i] <- 2 M[i] + sum_k sel[k][i] * X[k][i] + 1, zero sharing of stream 0, word i
 //               (gt_partmm.hpp, on the matrix cores)
-// OHL[((p*2 + w)*8 + s)*dpad + k)*rpad + r] = limb s of (w ? own : own + next) of party p's OH[r][k], zero for r >= np or k >= d.  The first elblk
-// workgroups are the tests, the others zero what is padded, a row of r per thread.  (Words in memory and a launch that made the limbs: 4.9 + 5.3 us a
-// level of 19,997 x 101, 5.2 in one.)
-struct OnehotArgs { KCommon c; P6 T; unsigned char *OHL; u64 base; u32 np, d, rpad, dpad, elblk; };
+// OHL[((p*2 + w)*8 + s)*dpad + k)*rpad + r] = limb s of (w ? own : own + next) of party p's OH[r][k], zero for r >= np or k >= d.  BYTES: the first
+// elblk workgroups are the tests, the others zero what is padded, a row of r per thread; a launch less, but a line of OHL per byte.  Which: onehot_bytes.
+struct OnehotArgs { KCommon c; P6 T, OH; unsigned char *OHL; u64 base; u32 np, d, rpad, dpad, elblk; };
+template <bool BYTES>
 __global__ __launch_bounds__(64) void k_onehot(OnehotArgs a)
 {
-    if (blockIdx.x >= a.elblk) {
+    if (BYTES && blockIdx.x >= a.elblk) {
         const u64 rows = 48ull * a.dpad, step = (u64)(gridDim.x - a.elblk) * 64;
         for (u64 t = (u64)(blockIdx.x - a.elblk) * 64 + threadIdx.x; t < rows; t += step) {
             const u32 r0 = t % a.dpad < a.d ? a.np : 0;
@@ -1455,7 +1455,8 @@ __global__ __launch_bounds__(64) void k_onehot(OnehotArgs a)
         T.deal(W, a.c.op, e0, s1, el_live(e0, n));
         const Dealer D = T.dealer(W);
         const Sh oh = b2a(W, p, eq_bit_mask(W, p, v, D, T.zb(W, 0, (u32)(e0 & 7) + W.t), act), D, act);
-        if (act && W.real) {
+        if (!BYTES) { if (act && W.real) st(a.OH, p, e, oh); }
+        else if (act && W.real) {
 #pragma unroll
             for (int w = 0; w < 2; w++) {
                 const u64 y = ((w ? oh.o : oh.o + oh.n) + GT_BIAS) ^ GT_BIAS;

@@ -9,7 +9,7 @@
 // both terms), adds the zero sharing, sends its component to the predecessor through LDS
 // and accumulates the row inner product with X; sel never reaches device memory.
 //
-// Operands.  OH comes as limb bytes with the node index contiguous (k_onehot): that is the
+// Operands.  OH comes as limb bytes with the node index contiguous (k_onehot or k_oh_limbs): that is the
 // A operand as it is.  L lives in the limb tiles of the statistics contraction, where the
 // SAMPLES are contiguous ([block][limb][row r][32 samples]); the matrix core wants the
 // contraction index contiguous per lane, so every 32 x 32 byte tile is transposed through a
@@ -17,6 +17,20 @@
 // read 16 dwords of their sample's dword column and pick their byte with byte permutes.
 #pragma once
 #include "gt_kernels.hpp"
+
+// OH as limb bytes, see k_onehot
+__global__ __launch_bounds__(256) void k_oh_limbs(P6 OH, unsigned char *OHL, u32 np, u32 d, u32 rpad, u32 dpad)
+{
+    const u64 per = (u64)dpad * rpad, total = 6 * per;
+    for (u64 t = (u64)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (u64)gridDim.x * blockDim.x) {
+        const u32 pw = (u32)(t / per), k = (u32)((t % per) / rpad), r = (u32)(t % rpad), p = pw >> 1, w = pw & 1;
+        u64 x = 0;
+        if (r < np && k < d) x = OH.o[p][(u64)r * d + k] + (w ? 0 : OH.n[p][(u64)r * d + k]);
+        const u64 y = (x + GT_BIAS) ^ GT_BIAS;
+#pragma unroll
+        for (int s = 0; s < 8; s++) OHL[(((u64)pw * 8 + s) * dpad + k) * rpad + r] = (unsigned char)(y >> (8 * s));
+    }
+}
 
 #define PM_TP_STRIDE 36                      // dwords between the dword columns of the transpose area
 #define PM_TP_WORDS (8 * PM_TP_STRIDE)       // dwords per area

@@ -93,6 +93,12 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
 // xcols: x holds the columns (CountArgs); nh nodes, nblk blocks of 32 samples, ncol columns.
 static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xcols && nh <= 8 && (nblk > 64 || ncol <= 64); }
 
+// Whether a level's one-hot of split decisions (partition by products: np nodes before it, d features) is written as limb bytes by the launch
+// that tests, a line per byte, or as words that a second launch turns into limbs.  d, np*d: one launch, the two: 20, 10,240 9.0 and 9.9 us, 20,480 16.7 and
+// 10.9; 30, 15,360 10.0 and 10.4; 64, 16,384 8.4 and 10.2, 32,768 12.8 and 11.6; 300, 9,600 5.9 and 10.1, 38,400 15.2 and 11.4, 307,200 86 and 38; few
+// nodes write few bytes of a line: 2,000, 32,000 9.7 and 11.6, 64,000 14.1 and 13.3; 4,000, 32,000 10.8 and 12.6; but 10,000, 10,000 18.0 and 16.7.
+static inline bool onehot_bytes(u64 simds, u64 np, u64 d) { return np * d <= (np <= 16 ? 32 : 16) * simds && d <= 4096; }
+
 // Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
 // groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
 // 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no

@@ -81,7 +81,8 @@ struct gt_train {
     bool finished;
     bool part_matmul;                // data partition by products with the previous level's leaf one-hot
     u32 lt_level;                    // level whose leaf one-hot the limb tiles LQ hold, or ~0u
-    unsigned char *OHL;              // partition by products: limb bytes of the one-hot of the split decisions, the matrix cores' operand
+    DSh OH;                          // partition by products: one-hot of the split decisions, where a level writes it as words (onehot_bytes)
+    unsigned char *OHL;              // ... and its limb bytes, the matrix cores' operand
     bool literal;                    // learning protocol as printed (whole-tree scans, per-element SelectShare)
     DSh LB;                          // literal mode: per-sample leaf flags as Boolean bits, n_h x N8
     u64 *lit_acc;                    // literal mode: local sums, max(6*N8, 6*nmax*(1+K)*2d) words
@@ -541,7 +542,7 @@ static void train_free(gt_train *t)
     if (t->Zacc) (void)hipFree(t->Zacc);
     if (t->hcp) (void)hipFree(t->hcp);
     if (t->lit_acc) (void)hipFree(t->lit_acc);
-    dsh_free(t->LB);
+    dsh_free(t->LB); dsh_free(t->OH);
     if (t->OHL) (void)hipFree(t->OHL);
     if (t->slot) {
         if (t->slot->in_use) t->slot->orphan = true;     // the tree made from it frees it
@@ -718,8 +719,12 @@ static int partition_matmul(gt_ctx *c, gt_train *t, u32 h)
     const u64 np = (u64)1 << (h - 1), base = np - 1, d = t->d, N = t->N;
     const u32 rpad = (u32)((np + 31) / 32 * 32), dpad = (t->d + 63) / 64 * 64;
     OnehotArgs oa{}; oa.c = kc(c, c->op++); oa.T = t->T.v; oa.OHL = t->OHL; oa.base = base; oa.np = (u32)np; oa.d = t->d; oa.rpad = rpad; oa.dpad = dpad;
-    oa.elblk = gE(np * d).x;
-    GTCHK(launch(c, GT_KC_SMALL, k_onehot, dim3(oa.elblk + blocks_for(48ull * dpad, 64)), B64, oa));
+    oa.OH = t->OH.v; oa.elblk = gE(np * d).x;
+    if (t->OH.n < np * d || onehot_bytes(c->simds, np, d)) GTCHK(launch(c, GT_KC_SMALL, k_onehot<true>, dim3(oa.elblk + blocks_for(48ull * dpad, 64)), B64, oa));
+    else {
+        GTCHK(launch(c, GT_KC_SMALL, k_onehot<false>, dim3(oa.elblk), B64, oa));
+        GTCHK(launch(c, GT_KC_LOCAL, k_oh_limbs, g1(6ull * dpad * rpad), B256, t->OH.v, t->OHL, (u32)np, t->d, rpad, dpad));
+    }
     acct_eq(c, np * d); acct_b2a(c, np * d);
     PartMmArgs pa{}; pa.c = kc(c, c->op); c->op += 2;
     pa.L = limbs_L(t); pa.OHL = t->OHL; pa.XT = t->XT.v; pa.M = t->M.v; pa.N = N; pa.N8 = t->N8; pa.nblk = t->nblk;
@@ -952,6 +957,9 @@ extern "C" int gt_train_set_partition(gt_ctx *c, gt_train *t, int by_products)
     if (by_products && !t->OHL) {
         if (t->H > 13) return GT_EINVAL;               // int32 accumulators of the limb products: at most 4096 nodes in the level before
         const size_t nprev = std::max<size_t>(32, (size_t)1 << (t->H ? t->H - 1 : 0)), dpad = ((size_t)t->d + 63) / 64 * 64;
+        // words for the widest level, where any level takes them
+        const size_t words = t->H ? ((size_t)1 << (t->H - 1)) * t->d : 0;
+        if (words && !t->OH.base && !onehot_bytes(c->simds, words / t->d, t->d)) GTCHK(dsh_alloc(t->OH, words, c->stream));
         if (hipMalloc(&t->OHL, 48 * dpad * nprev) != hipSuccess) { t->OHL = nullptr; return GT_ENOMEM; }
     }
     t->part_matmul = by_products != 0;

@@ -21,6 +21,7 @@ extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64
     out[0] = s.ntile; out[1] = s.nkc; out[2] = s.kchunk; out[3] = s.alone; out[4] = s.rps; out[5] = s.waves;
 }
 extern "C" int staged(u32 noct, int thr) { return staged_sums(noct, thr != 0); }
+extern "C" int bytes(u64 simds, u64 np, u64 d) { return onehot_bytes(simds, np, d); }
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
 """
 STORE, COMMON, ROWS = 0, 1, 2                      # modes of the equality grid
@@ -38,6 +39,7 @@ def _lib():
     L.infer.argtypes, L.infer.restype = [u64, u32, u64, u32, u32, u32, i, vp], None
     L.grid.argtypes, L.grid.restype = [u64, i, i, i, u32, u64, vp], None
     L.staged.argtypes, L.staged.restype = [u32, i], i
+    L.bytes.argtypes, L.bytes.restype = [u64, u64, u64], i
     L.few.argtypes, L.few.restype = [i, u64, u64, u64], i
     return L
 
@@ -61,6 +63,11 @@ def grid(mode, w, N, sums=1, tile_sums=False):
     out = (C.c_uint64 * 6)()
     _lib().grid(SIMDS, mode, sums, int(tile_sums), w, (N + 7) // 8 * 8, out)
     return dict(tiles=out[0], ranges=out[1], columns=out[2], alone=bool(out[3]), adjacent=out[4], waves=out[5])
+
+
+def onehot_bytes(nodes, d):
+    """Whether a partition by products after a level of that many nodes writes its one-hot as bytes in the launch that tests."""
+    return bool(_lib().bytes(SIMDS, nodes, d))
 
 
 def few(nodes, N, ncol):

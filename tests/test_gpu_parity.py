@@ -737,6 +737,15 @@ def test_partition_by_products_few_nodes(mods, seed, N, d, H):
     test_partition_by_products_deep(mods, seed, N, d, H)
 
 
+PRODUCTS_WORDS = [(21, 67, 9), (19, 4097, 2)]
+
+
+@pytest.mark.parametrize("N,d,H", PRODUCTS_WORDS)
+def test_partition_by_products_words(mods, seed, N, d, H):
+    """The one-hot of the last levels as words that a second launch turns into limbs, after levels that write bytes; of all levels, where the features are many."""
+    test_partition_by_products_deep(mods, seed, N, d, H)
+
+
 def test_train_errors(mods, seed):
     Oracle, gtree = mods
     from paper_2305_00645_amd import workloads as wl

@@ -1,7 +1,7 @@
 """Which variant the rules of the library choose: for the calls that the parity tests make of them, so that every
 variant meets the oracle and every test runs what it names."""
 import test_gpu_parity as gp
-from shapes import COMMON, ROWS, STORE, few, grid, infer, staged
+from shapes import COMMON, ROWS, STORE, few, grid, infer, onehot_bytes, staged
 
 ALL_INFER = {"ahead1", "ahead2", "ahead4", "infer1", "infer2", "infer4"}
 
@@ -75,6 +75,16 @@ def test_count_few_cases_run_what_they_name():
         assert all(few(1 << h, N, d * K + K) == (h <= 3) for h in range(H)), (N, d, K)
     for N, d, K, H in gp.COUNT_FEW_WIDE:
         assert not any(few(1 << h, N, d * K + K) for h in range(H)), (N, d, K)
+
+
+def test_onehot_takes_the_faster_route():
+    """One launch or two (see onehot_bytes): on the side that measured faster, and the parity test's levels on both."""
+    for np_, d in ((64, 64), (256, 64), (512, 20), (32, 300), (16, 2000), (8, 4000), (4, 4096)):
+        assert onehot_bytes(np_, d), (np_, d)
+    for np_, d in ((1024, 20), (512, 64), (128, 300), (1024, 300), (32, 2000), (1, 10000), (32, 10000)):
+        assert not onehot_bytes(np_, d), (np_, d)
+    for N, d, H in gp.PRODUCTS_WORDS:
+        assert not onehot_bytes(1 << (H - 1), d) and (d > 4096 or onehot_bytes(1 << (H - 2), d)), (N, d, H)
 
 
 def test_many_columns_fill_the_chip():
