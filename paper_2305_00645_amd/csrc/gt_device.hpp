@@ -617,40 +617,40 @@ __device__ __forceinline__ Key load_lane_key(const u32 *keys, int p)
 template <int NS, int ISSUE = PRF_ALONE>
 struct ElTile {
     static_assert(GT_EL + 9 * NS <= 3 * GT_TP, "more blocks than lanes");
-    // The lane's block is the dealer's (m < GT_EL: element m) or, with role = 9 i + 3 j + g, stream i, key j, group g.  Its key stays in
+    // The lane's block is the dealer's (m < GT_EL: element m) or, with m - GT_EL = 9 i + 3 j + g, stream i, key j, group g.  Its key stays in
     // registers where a wavefront has its SIMD to itself (267 x 22, depth 4: 436 us, 430 so); with several per SIMD the registers are worth
     // more (100,003 quotients 75 us, 83 so) and it is fetched for every block.
     static constexpr bool HELD = ISSUE == PRF_ALONE;
     Key held;
-    const u32 *from;             // where the lane's key lies
-    u32 role;
+    const u32 *keys;
+    u32 role;                    // m - GT_EL
     u64 *mat;                    // GT_EL_WORDS(NS) words: [10][21] dealer components, [NS][3][24] words
-    __device__ __forceinline__ Key fetch() const
+    __device__ __forceinline__ Key fetch(int key) const
     {
         Key k;
 #pragma unroll
-        for (int q = 0; q < 8; q++) k.k[q] = from[q];
+        for (int q = 0; q < 8; q++) k.k[q] = keys[key * 8 + q];
         return k;
     }
-    __device__ __forceinline__ void init(const u32 *keys, const WWire &W, u64 *mat_)
+    __device__ __forceinline__ void init(const u32 *keys_, const WWire &W, u64 *mat_)
     {
-        mat = mat_;
+        keys = keys_; mat = mat_;
         role = W.m - GT_EL;
-        from = keys + 8 * (W.m < GT_EL ? GT_KEY_DEALER : (role % 9) / 3);
-        if (HELD) held = fetch();
+        if (HELD) held = fetch(W.m < GT_EL ? GT_KEY_DEALER : (int)((role % 9) / 3));
     }
     // nel_d: elements of the tile that need the dealer's words (0: none)
     __device__ __forceinline__ void deal(const WWire &W, u32 op, u64 e0, const u32 (&st)[NS], u32 nel_d)
     {
-        const u32 m = W.m, g = role % 3;
+        const u32 m = W.m, r = HELD ? role : m - GT_EL, i = r / 9, j = (r % 9) / 3, g = r % 3;
         const bool dealer = m < GT_EL;
         wave_sync();
-        if (dealer ? m < nel_d : role < 9 * NS) {
+        if (dealer ? m < nel_d : r < 9 * NS) {
+            const Key kv = HELD ? held : fetch(dealer ? GT_KEY_DEALER : (int)j);
             u32 stream = 0;
 #pragma unroll
-            for (int q = 0; q < NS; q++) stream = !dealer && role / 9 == (u32)q ? st[q] : stream;
+            for (int q = 0; q < NS; q++) stream = !dealer && i == (u32)q ? st[q] : stream;
             u64 D[8];
-            chacha8<ISSUE>(HELD ? held : fetch(), dealer ? e0 + m : (e0 >> 3) + g, op, stream, D);
+            chacha8<ISSUE>(kv, dealer ? e0 + m : (e0 >> 3) + g, op, stream, D);
             if (dealer) {
                 const u64 beta = D[5] & 1;
                 const u32 b0 = (u32)(D[5] >> 1) & 1, b1 = (u32)(D[5] >> 2) & 1;
@@ -660,7 +660,7 @@ struct ElTile {
                 mat[9 * GT_TP + m] = b0 | (b1 << 1) | ((((u32)beta ^ b0 ^ b1) & 1) << 2);
             } else {
 #pragma unroll
-                for (int q = 0; q < 8; q++) mat[10 * GT_TP + role * 8 + q] = D[q];     // (3 i + j) * 24 + 8 g
+                for (int q = 0; q < 8; q++) mat[10 * GT_TP + (HELD ? r * 8 : (i * 3 + j) * 24 + g * 8) + q] = D[q];
             }
         }
         wave_sync();

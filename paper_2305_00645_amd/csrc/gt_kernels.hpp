@@ -1087,20 +1087,23 @@ __global__ __launch_bounds__(192) void k_cmp_step(CmpArgs a)
 
 // Restoring division, all steps of an element in one launch (the steps of different
 // elements do not interact): step t uses operation id op + t; b = [r >= Q]; r <- r - b Q;
-// quo <- 2 quo + b; r starts as S and is doubled between steps.  T: the step's material.
-struct DivWords { Dealer D; u64 g, e, a; };            // a lane's words of a step
+// quo <- 2 quo + b; r starts as S and is doubled between steps.  T: the step's material, a tile or a lane's words of it.
+struct DivWords {                                      // a lane's words of a step, loaded
+    Dealer D;
+    u64 g, e, a;
+    template <class TileT> __device__ __forceinline__ void load(const WWire &W, const TileT &T, u32 w)
+    { D = T.dealer(W); g = T.zb(W, 0, w); e = T.zb(W, 1, w); a = T.za(W, 2, w); }
+    __device__ __forceinline__ const Dealer &dealer(const WWire &) const { return D; }
+    __device__ __forceinline__ u64 zb(const WWire &, int i, u32) const { return i == 0 ? g : e; }
+    __device__ __forceinline__ u64 za(const WWire &, int, u32) const { return a; }
+};
 template <class WireT, class TileT>
-__device__ __forceinline__ DivWords div_words(const WireT &W, const TileT &T, u32 w)
-{
-    const DivWords m = { T.dealer(W), T.zb(W, 0, w), T.zb(W, 1, w), T.za(W, 2, w) };
-    return m;
-}
-template <class WireT>
-__device__ __forceinline__ void div_step(WireT &W, const DivWords &m, int p, bool first, Sh Q, Sh &r, Sh &quo, bool act)
+__device__ __forceinline__ void div_step(WireT &W, const TileT &T, int p, u32 w, bool first, Sh Q, Sh &r, Sh &quo, bool act)
 {
     if (!first) r = scale(r, 2);
-    const Sh b = b2a(W, p, ge_bit_masks(W, p, r - Q, m.D, m.g, m.e, act), m.D, act);
-    const Sh bq = mult_sh(W, b, Q, m.a, act);
+    const Dealer D = T.dealer(W);
+    const Sh b = b2a(W, p, ge_bit_masks(W, p, r - Q, D, T.zb(W, 0, w), T.zb(W, 1, w), act), D, act);
+    const Sh bq = mult_sh(W, b, Q, T.za(W, 2, w), act);
     r = r - bq;
     quo = scale(quo, 2) + b;
 }
@@ -1118,17 +1121,18 @@ __device__ __forceinline__ void div_steps_el(WireT &W, TileT &T, u64 *s_mat, int
     if (NW == 1)
         for (u32 t = 0; t < nsteps; t++) {
             T.deal(W, op + t, e0, st3, nel);
-            div_step(W, div_words(W, T, w), p, t == 0, Q, r, quo, act);
+            div_step(W, T, p, w, t == 0, Q, r, quo, act);
         }
     else if (threadIdx.x < GT_LANES) {
         // a chain: the next step's words are loaded during a step (scores of 267 x 22 24.5 us a level, 23.5 so)
         T.mat = s_mat;
-        DivWords next = div_words(W, T, w);
+        DivWords next;
+        next.load(W, T, w);
         for (u32 t = 0; t < nsteps; t++) {
             const DivWords m = next;
             T.mat = s_mat + (t + 1 < nsteps ? t + 1 : t) * GT_EL_WORDS(3);
-            next = div_words(W, T, w);
-            div_step(W, m, p, t == 0, Q, r, quo, act);
+            next.load(W, T, w);
+            div_step(W, m, p, w, t == 0, Q, r, quo, act);
         }
     }
     if (NW > 1) __syncthreads();                       // the material is dealt anew for the next tile
