@@ -279,7 +279,7 @@ struct LimbTri { LimbMat m[3]; };
 // it is (6 words read, 6 written).  In place is safe: a barrier lies between the loads of a half tile and its stores.
 struct MultArgs { KCommon c; P6 x, y, z; u64 n; u32 CW; };   // CW: MODE 2
 
-template <int MODE>
+template <int MODE, bool EARLY = false>
 __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blocks)
 {
     const int p = party_of_wave(), lane = threadIdx.x, pn = p == 2 ? 0 : p + 1;
@@ -294,9 +294,8 @@ __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blo
     const bool narrow = a.n <= 0xffffffffu;            // 32-bit division: a tenth of the instructions of the 64-bit one
     for (u64 tile = block, nt = (a.n + 511) / 512; tile < nt; tile += blocks) {
         u64 w[8];
-        // node split: a launch of few workgroups, whose loads are in flight during the block function
         Sh px[8], py[8];
-        if (MODE == 2) {
+        if (EARLY) {                                   // in flight during the block function
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 const u64 e = tile * 512 + j * GT_LANES + lane, el = e < a.n ? e : a.n - 1;
@@ -323,7 +322,8 @@ __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blo
                     if (MODE == 0) { x.o = xo[e]; x.n = xn[e]; y.o = yo[e]; y.n = yn[e]; }
                     if (MODE == 2) {
                         const u64 r = narrow ? (u64)((u32)e / a.CW) : e / a.CW;
-                        x = px[j]; y = one - py[j];
+                        if (EARLY) { x = px[j]; y = one - py[j]; }
+                        else { x.o = xo[e]; x.n = xn[e]; y.o = one.o - yo[r]; y.n = one.n - yn[r]; }
                         at[i] = e + r * a.CW;          // element (2r, col) of the next level
                     }
                 }
@@ -344,10 +344,11 @@ __device__ __forceinline__ void mult_tiles(const MultArgs &a, u32 block, u32 blo
 }
 __global__ __launch_bounds__(192) void k_mult(MultArgs a) { mult_tiles<0>(a, blockIdx.x, gridDim.x); }
 // End of a level in one launch: the first mblk workgroups the children's statistics, the others (in fours) the local copies.
-// (Two launches, each a few microseconds at small levels: training of 267 x 22, depth 4.)
+// (Two launches, each a few microseconds at small levels: training of 267 x 22, depth 4.)  EARLY: 145 registers, 3 wavefronts per SIMD (102, 4): see split_early
+template <bool EARLY>
 __global__ __launch_bounds__(192) void k_split(MultArgs m, KeepArgs k, u32 mblk)
 {
-    if (blockIdx.x < mblk) mult_tiles<2>(m, blockIdx.x, mblk);
+    if (blockIdx.x < mblk) mult_tiles<2, EARLY>(m, blockIdx.x, mblk);
     else {
         const u32 b = blockIdx.x - mblk, nb = (gridDim.x - mblk) / 4;
         keep_part(k, b & 3, (u64)(b >> 2) * 192 + threadIdx.y * GT_LANES + threadIdx.x, (u64)nb * 192);

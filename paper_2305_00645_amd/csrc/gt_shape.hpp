@@ -99,6 +99,12 @@ static inline bool count_few(bool xcols, u64 nh, u64 nblk, u64 ncol) { return xc
 // nodes write few bytes of a line: 2,000, 32,000 9.7 and 11.6, 64,000 14.1 and 13.3; 4,000, 32,000 10.8 and 12.6; but 10,000, 10,000 18.0 and 16.7.
 static inline bool onehot_bytes(u64 simds, u64 np, u64 d) { return np * d <= (np <= 16 ? 32 : 16) * simds && d <= 4096; }
 
+// Whether a level's node split (n words) loads its words before the block function instead of after it.  On a full chip the registers
+// count more: 249,856 words 18.7 us with the loads after it, 20.0 before, 604,160 46.4 and 55.1, but 156,672 14.4 and 13.3.  So do the copies that the
+// same launch makes of the same words, where the columns' tiles that the level has read (tile_bytes) leave nothing of them in the 256 MB of the last-level
+// cache: 48,842 samples x 306 columns (450 MB), 612 to 78,336 words 11.4 to 13.2 and 12.3 to 14.1; 5,000 samples (46 MB) 10.3 to 12.2 and 10.1 to 11.8.
+static inline bool split_early(u64 n, u64 tile_bytes) { return n <= 163840 && tile_bytes <= (u64)256 << 20; }
+
 // Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
 // groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
 // 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no

@@ -898,7 +898,8 @@ static int node_split(gt_ctx *c, gt_train *t, u32 h)
     MultArgs m{}; m.x = t->C.v; m.y = t->split.v; m.z = t->Cn.v; m.n = nh * CW; m.CW = t->CW;
     m.c = kc(c, c->op++);
     const unsigned mblk = tiles8(m.n), kblk = 4 * blocks_for(nh * CW, 192);
-    GTCHK(launch(c, GT_KC_MULT, k_split, dim3(mblk + kblk), GT_BLOCK, m, k, mblk));
+    const bool early = split_early(m.n, (t->comps ? 3 : 6) * t->Brows * t->nblk * 256);
+    GTCHK(early ? launch(c, GT_KC_MULT, k_split<true>, dim3(mblk + kblk), GT_BLOCK, m, k, mblk) : launch(c, GT_KC_MULT, k_split<false>, dim3(mblk + kblk), GT_BLOCK, m, k, mblk));
     acct_reshare(c, nh * CW, 1);
     std::swap(t->C, t->Cn);
     if (dup) std::swap(t->gamma, t->Gn);

@@ -22,6 +22,7 @@ extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64
 }
 extern "C" int staged(u32 noct, int thr) { return staged_sums(noct, thr != 0); }
 extern "C" int bytes(u64 simds, u64 np, u64 d) { return onehot_bytes(simds, np, d); }
+extern "C" int early(u64 n, u64 tile_bytes) { return split_early(n, tile_bytes); }
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
 """
 STORE, COMMON, ROWS = 0, 1, 2                      # modes of the equality grid
@@ -40,6 +41,7 @@ def _lib():
     L.grid.argtypes, L.grid.restype = [u64, i, i, i, u32, u64, vp], None
     L.staged.argtypes, L.staged.restype = [u32, i], i
     L.bytes.argtypes, L.bytes.restype = [u64, u64, u64], i
+    L.early.argtypes, L.early.restype = [u64, u64], i
     L.few.argtypes, L.few.restype = [i, u64, u64, u64], i
     return L
 
@@ -68,6 +70,11 @@ def grid(mode, w, N, sums=1, tile_sums=False):
 def onehot_bytes(nodes, d):
     """Whether a partition by products after a level of that many nodes writes its one-hot as bytes in the launch that tests."""
     return bool(_lib().bytes(SIMDS, nodes, d))
+
+
+def split_early(nodes, N, ncol, planes=3):
+    """Whether a level's node split loads its words before the block function; planes: of the columns' tiles, 6 where they are kept per party."""
+    return bool(_lib().early(nodes * ncol, planes * ((ncol + 63) // 64 * 64 + 64) * ((N + 31) // 32) * 256))
 
 
 def few(nodes, N, ncol):

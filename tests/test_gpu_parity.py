@@ -331,6 +331,15 @@ def test_train_column_group_remainders(mods, seed, N, d, K, H):
     run_train_pair(mods, seed, dict(X=X, Y=Y, y=y, N=N, d=d, K=K, H=H), tau=12)
 
 
+SPLIT_LATE = [(20, 5000, 16, 3)]
+
+
+@pytest.mark.parametrize("N,d,K,H", SPLIT_LATE)
+def test_train_split_of_many_words(mods, seed, N, d, K, H):
+    """The last level's node split loads its words after the block function, those before it ahead of it."""
+    test_train_column_group_remainders(mods, seed, N, d, K, H)
+
+
 # (test_shapes.py checks which tiles they take)
 COUNT_FEW_NARROW = [(70, 7, 2, 5), (33, 16, 3, 4), (4100, 9, 5, 5), (2100, 37, 2, 4), (2100, 72, 4, 4)]
 COUNT_FEW_WIDE = [(257, 63, 2, 4)]

@@ -1,7 +1,7 @@
 """Which variant the rules of the library choose: for the calls that the parity tests make of them, so that every
 variant meets the oracle and every test runs what it names."""
 import test_gpu_parity as gp
-from shapes import COMMON, ROWS, STORE, few, grid, infer, onehot_bytes, staged
+from shapes import COMMON, ROWS, STORE, few, grid, infer, onehot_bytes, split_early, staged
 
 ALL_INFER = {"ahead1", "ahead2", "ahead4", "infer1", "infer2", "infer4"}
 
@@ -85,6 +85,16 @@ def test_onehot_takes_the_faster_route():
         assert not onehot_bytes(np_, d), (np_, d)
     for N, d, H in gp.PRODUCTS_WORDS:
         assert not onehot_bytes(1 << (H - 1), d) and (d > 4096 or onehot_bytes(1 << (H - 2), d)), (N, d, H)
+
+
+def test_node_split_loads_on_the_faster_side():
+    """Before the block function or after it (see split_early): on the side that measured faster; both variants meet the oracle."""
+    for nodes, N, ncol in ((1, 267, 46), (16, 267, 46), (512, 5000, 244), (256, 5000, 590), (16, 20000, 130)):
+        assert split_early(nodes, N, ncol), (nodes, N, ncol)
+    for nodes, N, ncol in ((1, 48842, 306), (64, 48842, 590), (4096, 3000, 123), (2048, 20000, 130)):
+        assert not split_early(nodes, N, ncol), (nodes, N, ncol)
+    for N, d, K, H in gp.SPLIT_LATE:
+        assert not split_early(1 << (H - 1), N, d * K + K, 6) and split_early(1 << (H - 2), N, d * K + K, 6), (N, d, K, H)
 
 
 def test_many_columns_fill_the_chip():
