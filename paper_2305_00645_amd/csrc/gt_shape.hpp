@@ -29,7 +29,11 @@ enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality
 // Wavefronts per SIMD: two, or three of 168 registers with the rows' opened values in LDS (shared arrays and the leaf one-hot; own rows gain
 // nothing by it).  Three take 1.37 of the time of two for a step of each, two of them 1.05, one 0.66, and the row's part 3.3 steps: 1,000,000 x 64
 // 593 us and 533; 200,003 x 100 in 5 ranges 213 and 196, 48,842 x 64 in the 7 ranges that fill two per SIMD 46.5 and 50.2, in ten 62.5 and 49.3;
-// 89,221 x 28 in 3 and 5 ranges 49.1 and 50.5.  At most 32 ranges: 8,477 x 733 in 40 and 60 ranges 72 and 77, 4,061 x 939 in 81 and 118 58 and 68.
+// 89,221 x 28 in 3 and 5 ranges 49.1 and 50.5.  Half a step more whatever the length, which decides where little else differs: 49,820 x 49, 6 and 10
+// ranges 41.2 and 43.5, 100,666 x 25, 3 and 5 43.7 and 46.4, 127,049 x 18, 2 and 4 45.7 and 47.7, but 25,221 x 390, 13 and 20 101.5 and 98.6.  More than 32 ranges only of
+// 22 columns on, where the sums' atomic adds count less: 8,477 x 733 in 40 and 60 ranges 72 and 77, 4,061 x 939 in 81 and 118 58 and 68, 9,027 x 1,044, 36 and 55
+// (of 19) 99 and 103, 9,993 x 1,159, 34 and 51 (of 23) 116 and 112, 12,735 x 1,463, 26 and 40 180 and 166, 5,980 x 2,920, 56 and 84 168 and 159; and at most
+// 100: 3,152 x 3,492, 106 and 159 (of 22) 113 either way.
 struct ColumnRanges { u64 n; u32 waves; };
 static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntile, u64 nsteps)
 {
@@ -38,16 +42,17 @@ static inline ColumnRanges column_ranges(u64 simds, int mode, int sums, u64 ntil
     ColumnRanges best = { 1, 2 };
     double best_cost = 0;
     for (u32 waves = 2; waves <= (mode == GM_ROWS || sums == 2 ? 2 : 3); waves++) {
-        const u64 fills2[] = { 0, 1, 2, 4, 6, 8 }, fills3[] = { 0, 3, 6, 9, 12, 12 };   // wavefronts per SIMD; 0: one range
-        for (u64 f : waves == 2 ? fills2 : fills3) {
+        const u64 fills2[] = { 0, 1, 2, 4, 6, 8 }, fills3[] = { 0, 3, 6, 9, 12 };   // wavefronts per SIMD; 0: one range
+        for (u32 i = 0; i < (waves == 2 ? 6u : 5u); i++) {
+            const u64 f = waves == 2 ? fills2[i] : fills3[i];
             u64 n = std::min<u64>(nsteps, std::max<u64>(1, f * simds / ntile));
             const u64 len = (nsteps + n - 1) / n;
             n = (nsteps + len - 1) / len;
             const u64 items = ntile * n, full = items / (waves * simds), rest = items % (waves * simds);
-            if (waves == 3 && (items <= 2 * simds || n > 32)) continue;
+            if (waves == 3 && (items <= 2 * simds || (n > 32 && (len < 22 || n > 100)))) continue;
             const double last = rest == 0 ? 0.0 : waves == 2 ? (rest > simds ? 1.0 : n == 1 && sums ? 0.82 : 0.6)
                                 : rest > 2 * simds ? 1.37 : rest > simds ? 1.05 : 0.66;
-            const double cost = ((waves == 2 ? 1.0 : 1.37) * (double)full + last) * ((double)len + (waves == 2 ? 2.5 : 3.3)) + (n > 1 ? launch : 0.0);
+            const double cost = ((waves == 2 ? 1.0 : 1.37) * (double)full + last) * ((double)len + (waves == 2 ? 2.5 : 3.3)) + (n > 1 ? launch : 0.0) + (waves == 2 ? 0.0 : 0.5);
             if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = { n, waves }; }
         }
     }

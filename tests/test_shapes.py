@@ -68,6 +68,8 @@ def test_grids_of_three_wavefronts_meet_the_oracle():
     for w, n in ((5, 30), (64, 48842), (300, 200003)):
         assert grid(ROWS, w, n)["waves"] == grid(COMMON, w, n, sums=2)["waves"] == 2, (w, n)
     assert [grid(COMMON, w, n)["waves"] for w, n in ((64, 48842), (28, 89221), (733, 8477), (939, 4061))] == [2] * 4     # measured faster
+    assert [grid(COMMON, w, n)["waves"] for w, n in ((49, 49820), (25, 100666), (18, 127049), (70, 50207), (1044, 9027), (3492, 3152))] == [2] * 6
+    assert [grid(COMMON, w, n)["waves"] for w, n in ((390, 25221), (30, 121599), (54, 73408), (1463, 12735), (2480, 15069), (2920, 5980))] == [3] * 6
 
 
 def test_count_few_cases_run_what_they_name():
