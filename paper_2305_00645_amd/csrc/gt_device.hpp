@@ -229,8 +229,7 @@ __device__ __forceinline__ int party_of_wave() { return __builtin_amdgcn_readfir
 // The message region is GT_LWIRE_WORDS words of LDS that the workgroup owns: two
 // alternating slots for messages of up to four words per lane, so that one barrier per
 // message suffices (a slot is rewritten only after the barrier of the message that
-// followed it); a message of more than four words takes the whole region and is
-// followed by a second barrier, after which the region may be written again.
+// followed it).
 #define GT_WIRE_SLOTS 64
 #define GT_LWIRE_SLOT (3 * 4 * GT_LANES)
 #define GT_LWIRE_WORDS (2 * GT_LWIRE_SLOT)
@@ -255,17 +254,14 @@ struct LWire {
     template <int NW>
     __device__ __forceinline__ void exchange(const u64 (&snd)[NW], u64 (&rcv)[NW], int from)
     {
-        static_assert(NW <= 8, "message too wide");
-        constexpr int XW = NW <= 4 ? 4 : 8;
-        u64 *buf = NW <= 4 ? base + slot * GT_LWIRE_SLOT : base;
-        if (NW <= 4) slot ^= 1;
-        else __syncthreads();    // a wide message overwrites both slots: the last slot message must have been read
+        static_assert(NW <= 4, "message too wide");
+        u64 *buf = base + slot * GT_LWIRE_SLOT;
+        slot ^= 1;
 #pragma unroll
-        for (int j = 0; j < NW; j++) buf[(p * XW + j) * GT_LANES + lane] = snd[j];
+        for (int j = 0; j < NW; j++) buf[(p * 4 + j) * GT_LANES + lane] = snd[j];
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < NW; j++) rcv[j] = buf[(from * XW + j) * GT_LANES + lane];
-        if (NW > 4) __syncthreads();
+        for (int j = 0; j < NW; j++) rcv[j] = buf[(from * 4 + j) * GT_LANES + lane];
     }
     template <int NW>
     __device__ __forceinline__ void reshare(const u64 (&snd)[NW], u64 (&rcv)[NW], u32 bits) { nresh += bits; exchange<NW>(snd, rcv, p == 2 ? 0 : p + 1); }

@@ -752,6 +752,7 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
     __shared__ uint4 s_msg[GT_WMSG_QUADS];
     __shared__ u64 s_rows[GT_EQ_ROWS];
     __shared__ u64 s_cnt[6];
+    static_assert(WAVES == 2 || (MODE != GM_ROWS && NDOT == 1), "own rows and two sums take two wavefronts per SIMD");
     constexpr bool IN_LDS = WAVES > 2;                 // the rows' opened values and Boolean components
     __shared__ ulonglong2 s_rho[IN_LDS ? 4 * GT_LANES : 1], s_open[IN_LDS ? 4 * GT_TP : 1];
     EqWave E;
@@ -800,7 +801,7 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
         const auto fetch_x = [&](u32 k) {              // whole groups: rows are padded to N8 and start at multiples of 64 bytes
             ld8_whole(xto + (u64)k * a.N8, xo); ld8_whole(xtn + (u64)k * a.N8, xn);
         };
-        if (MODE == GM_ROWS && !IN_LDS) fetch_x(kbeg);
+        if (MODE == GM_ROWS) fetch_x(kbeg);
         u64 acc[8], acc2[8];
 #pragma unroll
         for (int s = 0; s < 8; s++) { acc[s] = 0; acc2[s] = 0; }
@@ -824,7 +825,6 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
                     for (int j = 0; j < 4; j++) { cd[j] = cpub[h + j] - k; ro[j] = rho_o[h + j]; rn[j] = rho_n[h + j]; }
                 }
             }, go, gn, nl, [&]() {
-                if (MODE == GM_ROWS && IN_LDS) fetch_x(k);
                 if (MODE == GM_COMMON) { Wk.o = w1o[k]; Wk.n = w1n[k]; }
                 if (MODE == GM_COMMON && NDOT == 2) Wk2 = ld(a.W2, p, a.w2off + k);
             });
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(64, WAVES) void k_eqgrid(GridArgs a)
                         acc[s] += prod3(e, x);
                     }
                 }
-                if (MODE == GM_ROWS && !IN_LDS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
+                if (MODE == GM_ROWS) fetch_x(k0 + 1 < kend ? k0 + 1 : k0);
                 if (MODE == GM_STORE && act && W.real) {
                     store_limbs8(p == 0 ? a.L.m[0] : (p == 1 ? a.L.m[1] : a.L.m[2]), k, i0, Eo);
                     if (a.sums) store_limbs8(p == 0 ? a.S.m[0] : (p == 1 ? a.S.m[1] : a.S.m[2]), k, i0, Es);

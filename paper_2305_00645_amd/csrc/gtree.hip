@@ -438,10 +438,10 @@ template <int ISSUE, int WAVES>
 static int launch_grid(gt_ctx *c, int mode, int ndot, dim3 g, dim3 b, const GridArgs &a)
 {
     if (mode == GM_STORE) return launch(c, GT_KC_EQGRID_STORE, k_eqgrid<GM_STORE, true, 1, ISSUE, WAVES>, g, b, a);
-    if constexpr (WAVES == 2) {                        // own rows and two sums never take three, see column_ranges
+    if constexpr (WAVES == 2) {
         if (mode == GM_ROWS) return launch(c, GT_KC_EQGRID_ROWS, k_eqgrid<GM_ROWS, false, 1, ISSUE, 2>, g, b, a);
         if (ndot == 2) return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 2, ISSUE, 2>, g, b, a);
-    }
+    } else if (mode == GM_ROWS || ndot == 2) return GT_EINVAL;          // no such kernel; column_ranges never asks for it
     return launch(c, GT_KC_EQGRID, k_eqgrid<GM_COMMON, false, 1, ISSUE, WAVES>, g, b, a);
 }
 // the equality grid with its accounting
