@@ -8,7 +8,11 @@
 // party p (threadIdx.y = p), lane l of each works on the same element(s).  Either way a
 // party's lane holds its own two components, a protocol message is a store into a message
 // region in LDS that the receiving party's lane loads (after a workgroup barrier in the second
-// model), and a party's lanes never read another party's shares, only the words sent to it.
+// model), and a party's lanes use no component that the party does not hold and nothing of another
+// party's but the words sent to it.  Where a component is stored once for both of its holders (a
+// training's data and tiles, the values of an inference) or read once for both (products' factors,
+// instances, a training's input), party p takes its next component from the place of party p + 1's own,
+// which equals its own copy: less to read where the three parties share a GPU's memory, and only there.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -614,8 +618,9 @@ template <int NS, int ISSUE = PRF_ALONE>
 struct ElTile {
     static_assert(GT_EL + 9 * NS <= 3 * GT_TP, "more blocks than lanes");
     // The lane's block is the dealer's (m < GT_EL: element m) or, with m - GT_EL = 9 i + 3 j + g, stream i, key j, group g.  Its key stays in
-    // registers where a wavefront has its SIMD to itself (267 x 22, depth 4: 436 us, 430 so); with several per SIMD the registers are worth
-    // more (100,003 quotients 75 us, 83 so) and it is fetched for every block.
+    // registers in the kernels without issue priorities (267 x 22, depth 4: 436 us, 430 so; 267 tiles of scores 24.3 and 23.2; on a full chip, too:
+    // 2,456 tiles of k_dot_fin 8.4 and 8.2, 15,104 of k_count_fin 27.0 and 26.3, 7,553 of k_update 22.8 and 22.3, 4,096 nodes of k_argmax<1> 47 and 41);
+    // in the others the registers are worth more (100,003 quotients 75 us, 83 so) and it is fetched for every block.
     static constexpr bool HELD = ISSUE == PRF_ALONE;
     Key held;
     const u32 *keys;

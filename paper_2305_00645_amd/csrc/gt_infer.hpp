@@ -39,8 +39,9 @@ struct InferArgs {
 // that is not `active` holds nothing.  Every lane adds its words by itself; with a single group (staged), where 21 lanes would meet
 // at every word (one instance alone: 4,000 cycles an access), the lanes' words go through `stage` (8 * GT_LANES words) and
 // an output is two lanes' work.  1,847 trees of depth 5 on one instance of 15 features 111 us by atomic adds, 98 through LDS, 50,000 x 294,
-// depth 6, 1.45 and 1.43 ms.  Not with two groups (208,758 x 200, depth 3: 1.98 and 2.01 ms) or thresholds, where the registers that
-// it takes spill (148 for 101): 1.59 and 1.77 ms with one group of the 50,000 x 294, 37,015 x 47, depth 6, two groups 428 and 484 us.
+// depth 6, 1.45 and 1.43 ms.  Not with two groups (208,758 x 200, depth 3: 1.98 and 2.01 ms) or thresholds: while the lanes held the rows'
+// opened values, 148 registers spilled for 101 (1.59 and 1.77 ms with one group of the 50,000 x 294, 37,015 x 47, depth 6, two groups 428 and 484 us); now
+// 52 would for 17, and 1,847 trees on one instance with thresholds would take 106 us for 129.
 template <bool STAGED>
 __device__ __forceinline__ void group_sums(const WWire &W, u64 *stage, const u64 (&acc)[8], bool active, u32 q0, u32 noct, u64 *sum, u32 stride)
 {
@@ -254,7 +255,7 @@ struct InferWg {
     }
 };
 
-// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD: 9 spill, 15 with thresholds, since the rows'
+// Bound: the vector ALU (see k_eqgrid).  The registers are cut for two wavefronts per SIMD: 9 to 13 spill, 14 to 17 with thresholds, since the rows'
 // opened values and Boolean components are read from LDS in every step (68 and 101 when the lanes held them: 16 trees of depth 5 on
 // 5,003 x 30 with thresholds 439 us, 414 now; 300,000 x 20, depth 5, 1,055 and 1,006; 10^6 x 64, depth 10, 26.9 and 26.7 ms).  Three wavefronts of
 // 168 registers spill 100 around the accesses, which only accesses of thousands of columns outweigh: 50,000 x 294, depth 6, 1.66 and 2.53 ms.
@@ -271,6 +272,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_infer(InferArgs a)
     __shared__ u64 s_sum[GT_INFER_OCT(NW)][GT_INFER_SUM(THR)];
     __shared__ u64 s_open[NW][GT_INFER_OCT(NW)][8];
     __shared__ __align__(16) u32 s_keys[40];               // the five keys: the blocks of the rows are evaluated with one or another by lane
+    static_assert(sizeof s_msg + sizeof s_rows + sizeof s_cnt + sizeof s_mat + sizeof s_val + sizeof s_sum + sizeof s_open + sizeof s_keys <= NW * 20480,
+                  "eight wavefronts on a compute unit's 160 KB");
     const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x / GT_LANES);
     InferWg<PRF_PAIR_LOOP, STAGED> X;
     X.E.init(a.c.keys, s_msg[wave], s_rows[wave], s_cnt[wave]);

@@ -148,7 +148,7 @@ __device__ __forceinline__ void ld8(const u64 *ptr, u64 i0, u64 n, u64 (&x)[8])
     }
 }
 
-// the same for whole groups: 64-byte aligned, eight words that exist
+// the same for eight words that exist, 16-byte aligned (whole groups of a plane; rows in LDS)
 __device__ __forceinline__ void ld8_whole(const u64 *ptr, u64 (&x)[8])
 {
     const ulonglong2 *q = (const ulonglong2 *)ptr;
@@ -362,12 +362,12 @@ __global__ __launch_bounds__(192) void k_split(MultArgs m, KeepArgs k, u32 mblk)
 // A workgroup takes 32 samples (a sample block) x tk features: rows of X and Y through LDS, where its four wavefronts read them: a
 // wavefront is the three parties on the block x 5 adjacent columns per step, so that the 32-byte pieces that a party's lanes write per limb
 // lie side by side.
-// Bound: memory (1.5 GB of X read, 1.5 of XT and 6.1 of tiles written at 10^6 x 64, 4 classes, in 2.49 ms: 3.7 TB/s), the vector ALU close
+// Bound: memory (1.5 GB of X read, 1.5 of XT and 6.1 of tiles written at 10^6 x 64, 4 classes, in 2.44 ms: 3.7 TB/s), the vector ALU close
 // behind (the tiles' stores alone 1.6 ms, all but these 1.6).  Three workgroups per compute unit, each grid-stride over its items: a workgroup for every
 // item, whose message counters then queue at 64 lines, took 3.4 ms, with the rows' loads one after the other 3.0.  Rows of eight words from global memory by
 // the lanes that use them: 3.4 ms, each load instruction touches as many lines as it has lanes.  One wavefront per party with a barrier per message, after a
-// transposition, before class tiles of their own: 2.49 + 0.73 + 0.31 ms; 48,842 x 294, 2 classes 369 + 150 + 20 us, now 411; 19,997 x 101, 3
-// classes 118 + 25 + 10, now 83; 267 x 22 15 + 5 + 5, now 11.
+// transposition, before class tiles of their own: 2.49 + 0.73 + 0.31 ms; 48,842 x 294, 2 classes 369 + 150 + 20 us, now 357; 19,997 x 101, 3
+// classes 118 + 25 + 10, now 74; 267 x 22 15 + 5 + 5, now 8.  The 168 registers of three wavefronts per SIMD spill 9 and, without COMPS, 21 (11 and 23 with 16 classes).
 struct XyArgs { KCommon c; P6 X, Y, XT, YT; LimbSet B, Yl; LimbTri C; u64 N, N8; u32 d, K, tk; };
 #define GT_XY_COLS 5
 #define GT_XY_FEAT 32                                  // features of a workgroup at most
@@ -737,8 +737,8 @@ __device__ __forceinline__ u64 eq_select(u64 b, u32 m, u32 k1) { return (b ^ ((u
 // the learning protocol, Sec. V-B): see GridArgs for the modes.
 // Bound: vector ALU.  A step (168 tests) executes 1,070 vector instructions, 700 of them PRF (two thirds of these can pair, see chacha8), and
 // with two wavefronts per SIMD 31 % of a wavefront's time is waiting: 19 for LDS (messages, daBits), 12 for the issue.  WAVES 3: a third one
-// fills that.  Its 168 registers hold the keys, the sums and a step's words; the rows' public values and Boolean components are
-// read from LDS in every step (12.5 KB a wavefront).  WAVES 2: they stay in registers (none spill), for launches that do not fill three,
+// fills that.  Its 168 registers hold the keys, the sums and a step's words but for 19 (leaf one-hot) and 22 (80 and 92 bytes a lane in scratch, which
+// shows in the bytes written); the rows' public values and Boolean components are read from LDS in every step (12.5 KB a wavefront).  WAVES 2: they stay in registers (none spill), for launches that do not fill three,
 // and for the samples' own values (GM_ROWS), which are fetched a step ahead and take the registers of the third.  A step
 // takes 3,750 cycles of a SIMD with two and 3,400 with three: 1,000,000 x 64 583 and 528 us (x 512 11.4 and 12.9 * 10^10 tests/s),
 // array access 200,003 x 100 211 and 195 us, leaf one-hot of 48,842 x (128 + 256 nodes) 307 and 225; but own rows 100,000 x 100 135 and 145,
@@ -1149,7 +1149,7 @@ __device__ __forceinline__ void div_steps_el(WireT &W, TileT &T, u64 *s_mat, int
     ElTile<3, NW == 1 ? PRF_PAIR : PRF_ALONE> T; T.init(a.c.keys, W, s_mat);
 
 // 100,003 quotients, 17 steps: 304 us with a party per wavefront, 109 us in the wavefront model, 75 with the issue priorities of
-// PRF_PAIR (VALU: a PRF pass and 330 instructions of protocol per step and 20 elements).
+// PRF_PAIR (VALU: a PRF pass and 240 instructions of protocol per step and 20 elements).
 struct DivArgs { KCommon c; P6 S, Q, quo; u64 n; u32 nsteps; };
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void k_div(DivArgs a)

@@ -9,7 +9,7 @@ typedef uint32_t u32;
 
 #define GT_TP 21                             // lanes of a party in a wavefront (the wavefront model)
 #define GT_INFER_LANES(NW) ((NW) * GT_TP)
-#define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup of k_infer at most: 19 KB of LDS per wavefront, two per SIMD
+#define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup of k_infer at most: 13 KB of LDS per wavefront, 16 with thresholds, two per SIMD (at most 20)
 #define GT_AHEAD_OCT(NQ) (4 * (NQ))          // groups of a tile of k_infer_ahead at most: 39 KB of LDS per NQ, 155 KB on a compute unit
 enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality grid, see k_eqgrid
 
@@ -83,6 +83,8 @@ static inline GridShape grid_shape(u64 simds, int mode, int ndot, bool sums, u32
     // contraction behind it loses, which reads tiles that were written in a different order.  Grid + contraction without and with them, 16, 32,
     // 64 nodes: 60,000 samples x 122 columns 37 + 78, 54 + 78, 86 + 109 us and 32 + 78, 46 + 79, 73 + 113; 140,244: 75 + 182, 113 + 195,
     // 190 + 273 and 73 + 195, 110 + 213, 187 + 298; 400,000: 173 + 500, 281 + 531, 493 + 659 and 161 + 519, 271 + 553, 493 + 663.
+    // These run with two wavefronts per SIMD, whichever the ranges were priced for: without priorities three gain nothing (the level's grid of 10^6 samples x 64
+    // nodes 2.45 ms with two, 2.50 with three).  Their ranges stay as priced: 135,000 samples x 128 and 256 nodes 284 and 543 us in one, 218 and 406 in two.
     const u64 items = s.ntile * s.nkc, rest = items % (2 * simds);
     s.alone = items <= simds || s.kchunk <= s.rps || (mode != GM_STORE && s.kchunk <= 3 && items > 2 * simds && rest && rest <= simds) || (sums && N8 > 131072);
     s.waves = s.alone ? 2 : ranges.waves;
@@ -114,7 +116,7 @@ static inline bool split_early(u64 n, u64 tile_bytes) { return n <= 163840 && ti
 // groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or
 // 21 lanes per party.  Otherwise k_infer in workgroups of one wavefront with at most four groups: a wavefront waits for no
 // other one, and its loads touch the lines of at most 32 rows of instances at a time (50,000 instances of 20 features,
-// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.64 ms; 16 trees of
+// depth 6, thresholds: 405 us in workgroups of four, 308 in single ones; 50,000 x 294, depth 6: 2.74 and 1.64 ms (1.42 since a component is read once); 16 trees of
 // depth 5 on 5,003 x 30: 570 and 437 us); of two or four for some tiles that the caller asks for.
 // simds: of the device; lgi: log2 of the instances per workgroup that the caller asks for, 0: none; ngrp: groups of 8 instances.
 // The cost, in steps of k_infer on a full SIMD.  k_infer: an access costs 2.4 beside its steps (PRF blocks of its own, the
@@ -122,8 +124,8 @@ static inline bool split_early(u64 n, u64 tile_bytes) { return n <= 163840 && ti
 // SIMD takes 0.84 of the time of two; and where the rows of all groups at work exceed the L2s, a step of few columns waits for
 // lines that it had before.  k_infer_ahead: 3.6 for a launch, 0.1 and 0.1 more for every 21 lanes an access (barriers), 0.32 a
 // step, 0.41 with thresholds, 0.27 for every instance of a half group that a lane compares; all but the launch times
-// 2.2 where the chip is full.  Over the 53 batches and forests of 1 to 700,000 instances that it was
-// fitted to this picks within 2 % of the best of all shapes on average, 16 % at worst (50,000 x 294, depth 6: two groups, 1.64 ms; one 1.43).
+// 2.2 where the chip is full.  Fitted to 53 batches and forests of 1 to 700,000 instances while k_infer read six planes and held the rows' opened
+// values; of 22 batches of k_infer as it is, this picks within 1 % of the best of all shapes on average, 7 % at worst (300,000 x 8, depth 12: 4 groups are faster).
 struct InferShape { u32 nq, nw, noct; };                // nq: k_infer_ahead<., nq>; else nw wavefronts of k_infer
 // whether single wavefronts of k_infer add up their sums through LDS, see group_sums
 static inline bool staged_sums(u32 noct, bool has_thr) { return noct == 1 && !has_thr; }
@@ -157,7 +159,7 @@ static inline InferShape infer_shape(u64 simds, u32 lgi, u64 ngrp, u32 ntrees, u
     u32 nw = 1;
     const u32 ask = lgi ? (1u << lgi) / 8 : 0;
     if (ask) {
-        const bool in_l2 = ngrp * 8 * d * 48 <= (u64)16 << 20;
+        const bool in_l2 = ngrp * 8 * d * 24 <= (u64)8 << 20;          // three planes are read; up to 16 MB 40 batches took the same time either way
         const u64 tiles = (ngrp + ask - 1) / ask * ntrees;
         const auto more = [&](u32 ncol) {
             return !in_l2 && (((d >= 48 || H >= 10) && (d + ncol - 1) / ncol > 2 * ((d + 15) / 16)) || (d >= 250 && ncol < GT_TP && tiles * nw > 2 * simds));
