@@ -369,8 +369,6 @@ __global__ __launch_bounds__(192) void k_split(MultArgs m, KeepArgs k, u32 mblk)
 // transposition, before class tiles of their own: 2.49 + 0.73 + 0.31 ms; 48,842 x 294, 2 classes 369 + 150 + 20 us, now 357; 19,997 x 101, 3
 // classes 118 + 25 + 10, now 74; 267 x 22 15 + 5 + 5, now 8.  The 168 registers of three wavefronts per SIMD spill 9 and, without COMPS, 21 (11 and 23 with 16 classes).
 struct XyArgs { KCommon c; P6 X, Y, XT, YT; LimbSet B, Yl; LimbTri C; u64 N, N8; u32 d, K, tk; };
-#define GT_XY_COLS 5
-#define GT_XY_FEAT 32                                  // features of a workgroup at most
 #define GT_XY_ROW 34                                   // words of a row in LDS: 32 samples, 16 bytes further on in the banks
 template <bool COMPS, int KMAX>
 __global__ __launch_bounds__(256, 3) void k_xy(XyArgs a)

@@ -11,6 +11,9 @@ typedef uint32_t u32;
 #define GT_INFER_LANES(NW) ((NW) * GT_TP)
 #define GT_INFER_OCT(NW) (4 * (NW))          // groups of a workgroup of k_infer at most: 13 KB of LDS per wavefront, 16 with thresholds, two per SIMD (at most 20)
 #define GT_AHEAD_OCT(NQ) (4 * (NQ))          // groups of a tile of k_infer_ahead at most: 39 KB of LDS per NQ, 155 KB on a compute unit
+#define GT_XY_COLS 5                         // adjacent product columns of a wavefront's step of k_xy
+#define GT_XY_FEAT 32                        // features of a workgroup of k_xy at most
+#define GT_YROWS 16                          // rows of the class columns' tiles where they have their own: GT_MAX_K
 enum { GM_STORE = 0, GM_COMMON = 1, GM_ROWS = 2 };      // modes of the equality grid, see k_eqgrid
 
 // Column ranges per tile of an equality grid.  A wavefront per item (tile, range); every range
@@ -111,6 +114,35 @@ static inline bool onehot_bytes(u64 simds, u64 np, u64 d) { return np * d <= (np
 // same launch makes of the same words, where the columns' tiles that the level has read (tile_bytes) leave nothing of them in the 256 MB of the last-level
 // cache: 48,842 samples x 306 columns (450 MB), 612 to 78,336 words 11.4 to 13.2 and 12.3 to 14.1; 5,000 samples (46 MB) 10.3 to 12.2 and 10.1 to 11.8.
 static inline bool split_early(u64 n, u64 tile_bytes) { return n <= 163840 && tile_bytes <= (u64)256 << 20; }
+
+// Whether equality tests of n elements take tiles of 40, see k_eq_pair: from as many of these on as there are SIMDs (both sides there).
+static inline bool eq_pairs(u64 simds, u64 n) { return n >= 40 * simds; }
+
+// Rows of a training's tiles (nodes of the level before the last, columns, a multiple of 32 and of 64) and whether the columns are kept once per component, with the
+// sums own + next on the nodes: whichever way needs less memory, and with it traffic.
+struct TileRows { u64 nodes, cols; bool comps; };
+static inline TileRows tile_rows(u32 H, u64 ncol)
+{
+    TileRows r;
+    r.cols = (ncol + 63) / 64 * 64 + 64;
+    r.nodes = H ? std::max<u64>(32, (((u64)1 << H) / 2 + 31) / 32 * 32) : 0;
+    r.comps = 3 * r.nodes + 3 * r.cols + 6 * GT_YROWS <= 6 * r.cols;
+    return r;
+}
+
+// k_xy: features in equal parts of at most 32 (whole rows of 256 bytes), tk each; more parts where the blocks of 32 samples are few, down to a step for each wavefront
+// (267 x 22: 11 us in three parts, 13 in one; 10^6 x 64 in parts of 16 2.97 ms, of 32 2.49).  items: a block x a part, groups: workgroups.
+struct XySplit { u32 tk; u64 items, groups; };
+static inline XySplit xy_split(u64 simds, u64 N8, u32 d, u32 K)
+{
+    XySplit s;
+    const u64 blocks = (N8 / 8 + 3) / 4, cus = std::max<u64>(1, simds / 4);
+    const u32 parts = (u32)std::max<u64>((d + GT_XY_FEAT - 1) / GT_XY_FEAT, std::min<u64>(((u64)d * K + 4 * GT_XY_COLS - 1) / (4 * GT_XY_COLS), cus / blocks));
+    s.tk = (d + parts - 1) / parts;
+    s.items = blocks * ((d + s.tk - 1) / s.tk);
+    s.groups = std::min<u64>(s.items, 3 * cus);
+    return s;
+}
 
 // Kernel and tile of an inference: the 21 lanes of a party per wavefront (pair of wavefronts, k_infer_ahead) are split into noct
 // groups of 8 instances x ncol columns per step.  Where all tiles are on the chip at once: k_infer_ahead with 84, 42 or

@@ -396,7 +396,7 @@ static int do_eq(gt_ctx *c, bool bool_out, P6 x, u64 xoff, const u64 *ypub, u64 
 {
     EqArgs a{}; a.c = kc(c, c->op++); a.x = x; a.xoff = xoff; a.ypub = ypub; a.ysub = ysub; a.z = z; a.n = n;
     if (n && !launched) GTCHK(bool_out ? launch(c, GT_KC_SMALL, k_eq<true>, gE(n), B64, a)
-                          : n < 40ull * c->simds ? launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a)
+                          : !eq_pairs(c->simds, n) ? launch(c, GT_KC_SMALL, k_eq<false>, gE(n), B64, a)
                           : launch(c, GT_KC_SMALL, k_eq_pair, dim3((unsigned)std::min<u64>((n + 39) / 40, 1u << 16)), B64, a));
     acct_eq(c, n);
     if (!bool_out) acct_b2a(c, n);
@@ -565,7 +565,6 @@ static LimbTri tri_of(unsigned char *base, size_t nblk, size_t rows)
     for (int j = 0; j < 3; j++) { L.m[j].base = base + (size_t)j * per; L.m[j].rows = rows; }
     return L;
 }
-#define GT_YROWS 16              // rows of YQ: GT_MAX_K
 static LimbTri limbs_L(const gt_train *t) { return tri_of(t->LQ, t->nblk, t->Lrows); }
 static LimbTri limbs_S(const gt_train *t) { return tri_of(t->SQ, t->nblk, t->Srows); }
 static LimbSet limbs_B(const gt_train *t) { return limbs_of(t->BQ, t->nblk, t->Brows); }
@@ -590,12 +589,9 @@ static int train_start(gt_ctx *c, gt_train *t, const gt_shares *X, const gt_shar
     XyArgs a{}; a.c = kc(c, c->op++); a.X = to_p6(X); a.Y = to_p6(Y); a.XT = t->XT.v; a.YT = t->YT.v; a.N = N; a.N8 = N8; a.d = d; a.K = K;
     if (t->comps) a.C = limbs_C(t); else a.B = limbs_B(t);
     a.Yl = limbs_Y(t);
-    // features in equal parts of at most 32 (whole rows of 256 bytes); fewer where the blocks are few, down to a step for each wavefront
-    // (267 x 22: 11 us in three parts, 13 in one; 10^6 x 64 in parts of 16 2.97 ms, of 32 2.49)
-    const u64 blocks = (N8 / 8 + 3) / 4, cus = std::max(1u, c->simds / 4);
-    const u32 parts = (u32)std::max<u64>((d + GT_XY_FEAT - 1) / GT_XY_FEAT, std::min<u64>(((u64)d * K + 4 * GT_XY_COLS - 1) / (4 * GT_XY_COLS), cus / blocks));
-    a.tk = (d + parts - 1) / parts;
-    const dim3 gxy((unsigned)std::min<u64>(blocks * ((d + a.tk - 1) / a.tk), 3 * cus));
+    const XySplit s = xy_split(c->simds, N8, d, K);
+    a.tk = s.tk;
+    const dim3 gxy((unsigned)s.groups);
     const int rc = K <= 4 ? (t->comps ? launch(c, GT_KC_MULT, k_xy<true, 4>, gxy, B256, a) : launch(c, GT_KC_MULT, k_xy<false, 4>, gxy, B256, a))
                           : (t->comps ? launch(c, GT_KC_MULT, k_xy<true, GT_MAX_K>, gxy, B256, a) : launch(c, GT_KC_MULT, k_xy<false, GT_MAX_K>, gxy, B256, a));
     GTCHK(rc);
@@ -648,10 +644,8 @@ extern "C" int gt_train_create(gt_ctx *c, const gt_shares *X, const gt_shares *Y
     if (rc == GT_OK && hipMemsetAsync(t->Zacc, 0, (zacc + 6 * N8) * 8, s) != hipSuccess) rc = GT_EHIP;
     t->nblk = (N + 31) / 32;
     t->Lrows = std::max<size_t>(32, (nmax + 31) / 32 * 32);
-    t->Brows = (CW + 63) / 64 * 64 + 64;
-    // the sums go to the operand with fewer rows: whichever way needs less memory, and with it traffic
-    t->Srows = H ? std::max<size_t>(32, (nmax / 2 + 31) / 32 * 32) : 0;
-    t->comps = 3 * t->Srows + 3 * t->Brows + 6 * GT_YROWS <= 6 * t->Brows;
+    const TileRows rows = tile_rows(H, CW);
+    t->Brows = rows.cols; t->Srows = rows.nodes; t->comps = rows.comps;
     const size_t rowb = t->nblk * 8 * 32;
     // two allocations, the nodes' tiles and the columns'; planes are multiples of 256 bytes
     const size_t lq = 3 * t->Lrows * rowb, bq = (t->comps ? 3 : 6) * t->Brows * rowb, sq = t->comps ? 3 * t->Srows * rowb : 0, yq = t->comps ? 6 * GT_YROWS * rowb : 0;

@@ -23,6 +23,13 @@ extern "C" void grid(u64 simds, int mode, int ndot, int sums, u32 w, u64 N8, u64
 extern "C" int staged(u32 noct, int thr) { return staged_sums(noct, thr != 0); }
 extern "C" int bytes(u64 simds, u64 np, u64 d) { return onehot_bytes(simds, np, d); }
 extern "C" int early(u64 n, u64 tile_bytes) { return split_early(n, tile_bytes); }
+extern "C" int pairs(u64 simds, u64 n) { return eq_pairs(simds, n); }
+extern "C" int comps(u32 H, u64 ncol) { return tile_rows(H, ncol).comps; }
+extern "C" void xy(u64 simds, u64 N8, u32 d, u32 K, u64 *out)
+{
+    const XySplit s = xy_split(simds, N8, d, K);
+    out[0] = s.tk; out[1] = s.items; out[2] = s.groups;
+}
 extern "C" int few(int xcols, u64 nh, u64 nblk, u64 ncol) { return count_few(xcols != 0, nh, nblk, ncol); }
 """
 STORE, COMMON, ROWS = 0, 1, 2                      # modes of the equality grid
@@ -42,6 +49,9 @@ def _lib():
     L.staged.argtypes, L.staged.restype = [u32, i], i
     L.bytes.argtypes, L.bytes.restype = [u64, u64, u64], i
     L.early.argtypes, L.early.restype = [u64, u64], i
+    L.pairs.argtypes, L.pairs.restype = [u64, u64], i
+    L.comps.argtypes, L.comps.restype = [u32, u64], i
+    L.xy.argtypes, L.xy.restype = [u64, u64, u32, u32, vp], None
     L.few.argtypes, L.few.restype = [i, u64, u64, u64], i
     return L
 
@@ -75,6 +85,19 @@ def onehot_bytes(nodes, d):
 def split_early(nodes, N, ncol, planes=3):
     """Whether a level's node split loads its words before the block function; planes: of the columns' tiles, 6 where they are kept per party."""
     return bool(_lib().early(nodes * ncol, planes * ((ncol + 63) // 64 * 64 + 64) * ((N + 31) // 32) * 256))
+
+
+def eq_pairs(n):
+    """Whether equality tests of n elements take tiles of 40, two per lane."""
+    return bool(_lib().pairs(SIMDS, n))
+
+
+def setup(N, d, K, H):
+    """dict(comps, features, items, groups) of a training's set-up: the columns kept once per component, features of a workgroup's part, blocks x
+    parts, workgroups."""
+    out = (C.c_uint64 * 3)()
+    _lib().xy(SIMDS, (N + 7) // 8 * 8, d, K, out)
+    return dict(comps=bool(_lib().comps(H, d * K + K)), features=out[0], items=out[1], groups=out[2])
 
 
 def few(nodes, N, ncol):

@@ -1162,7 +1162,7 @@ def test_oaa_three_wavefronts(mods, seed, w, n):
     test_oaa_at_tile_edges(mods, seed, w, n)
 
 
-# one sample, one block and one over; features of one part, two equal ones, one over; classes of both variants; more blocks than workgroups; the
+# one sample, one block and one over; few blocks, whose features go in parts of one to seven; classes of both variants; more blocks than workgroups; the
 # columns kept per party (many nodes for the columns) and per component
 SETUP_SHAPES = [(1, 1, 2, 1), (31, 33, 5, 1), (32, 32, 4, 2), (33, 65, 16, 1), (64, 31, 3, 2), (24601, 3, 4, 1), (65, 2, 5, 7), (40, 3, 2, 8)]
 
@@ -1173,7 +1173,38 @@ def test_train_setup_shapes(mods, seed, N, d, K, H):
     test_train_column_group_remainders(mods, seed, N, d, K, H)
 
 
-@pytest.mark.parametrize("n", [40959, 40960, 40961, 40979, 40981, 40999, 65536 * 40 + 3])
+# one part of 32 features, two of 17 and 16, two of 32, three; the same with the columns kept per party; two items of a workgroup, in two parts
+# (test_shapes.py checks it)
+SETUP_SPLITS = [(4129, 32, 2, 2), (4129, 33, 4, 2), (4129, 64, 5, 2), (4129, 65, 1, 9), (4129, 32, 5, 9), (13001, 64, 2, 2), (12500, 64, 5, 10)]
+
+
+@pytest.mark.parametrize("N,d,K,H", SETUP_SPLITS)
+def test_train_setup_splits(mods, seed, N, d, K, H):
+    """The same launch where samples are many: the sums of all its columns at the root, and the samples' nodes and the sums at the level after it."""
+    from oracle import X_M, X_C
+    rng = np.random.default_rng(N + d)
+    X = (rng.random((N, d)) < 0.45).astype(np.uint64)
+    y = rng.integers(0, K, N)
+    Y = np.zeros((N, K), dtype=np.uint64); Y[np.arange(N), y] = 1
+    o, g = pair(mods, seed, tau=4, K=K)
+    o.train_create(o.share(X.reshape(-1)), o.share(Y.reshape(-1)), N, d, H)
+    g.train_create(g.share_a(X.reshape(-1)), g.share_a(Y.reshape(-1)), N, d, H)
+    for h in range(2):
+        o.train_level(h); g.train_level(h)
+        for what in (X_M, X_C):
+            same(g.train_export(what), o.train_export(what), "level %d, export %d" % (h, what))
+        if h == 0:
+            C = g.rec(g.train_export(X_C)).astype(np.int64)
+            assert np.array_equal(C[:d * K].reshape(d, K), X.T.astype(np.int64) @ Y.astype(np.int64))
+    same_stats(o, g)
+    g.close()
+
+
+# (test_shapes.py checks which kernel they take)
+EQUALITY_PAIRS = [40959, 40960, 40961, 40979, 40981, 40999, 65536 * 40 + 3]
+
+
+@pytest.mark.parametrize("n", EQUALITY_PAIRS)
 def test_equality_two_elements_per_lane(mods, seed, n):
     """Tiles of 40 elements, two per lane, from 40 x 1,024 on: below, full, one element in the last tile, its lanes' second elements missing, one of
     them, one short; more tiles than workgroups."""

@@ -1,7 +1,7 @@
 """Which variant the rules of the library choose: for the calls that the parity tests make of them, so that every
 variant meets the oracle and every test runs what it names."""
 import test_gpu_parity as gp
-from shapes import COMMON, ROWS, STORE, few, grid, infer, onehot_bytes, split_early, staged
+from shapes import COMMON, ROWS, STORE, eq_pairs, few, grid, infer, onehot_bytes, setup, split_early, staged
 
 ALL_INFER = {"ahead1", "ahead2", "ahead4", "infer1", "infer2", "infer4"}
 
@@ -97,6 +97,21 @@ def test_node_split_loads_on_the_faster_side():
         assert not split_early(nodes, N, ncol), (nodes, N, ncol)
     for N, d, K, H in gp.SPLIT_LATE:
         assert not split_early(1 << (H - 1), N, d * K + K, 6) and split_early(1 << (H - 2), N, d * K + K, 6), (N, d, K, H)
+
+
+def test_equality_sizes_lie_on_both_sides():
+    assert [eq_pairs(n) for n in gp.EQUALITY_PAIRS] == [False] + [True] * (len(gp.EQUALITY_PAIRS) - 1)
+    n0 = next(n for n in gp.EQUALITY_PAIRS if eq_pairs(n))
+    assert not eq_pairs(n0 - 1) and gp.EQUALITY_PAIRS[0] == n0 - 1
+    assert {n % 40 for n in gp.EQUALITY_PAIRS[1:]} >= {0, 1, 19, 21, 39}
+
+
+def test_setup_shapes_run_what_they_name():
+    """Both storage forms x both class variants with parts of several features; parts of 32; workgroups with a second item in both forms."""
+    seen = [(setup(*s), s[1], s[2]) for s in gp.SETUP_SPLITS]
+    assert {(s["comps"], K > 4) for s, d, K in seen if s["features"] >= 17} == {(c, k) for c in (False, True) for k in (False, True)}
+    assert [(s["features"], d) for s, d, K in seen] == [(32, 32), (17, 33), (32, 64), (22, 65), (32, 32), (32, 64), (32, 64)]
+    assert {(s["comps"], K > 4) for s, d, K in seen if s["items"] > s["groups"] and d > s["features"]} == {(True, False), (False, True)}
 
 
 def test_many_columns_fill_the_chip():
